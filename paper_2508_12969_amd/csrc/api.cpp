@@ -259,6 +259,12 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
   a.tile_class = t.tile_class;
   a.class_mask = t.class_mask;
   a.class_perm = t.class_perm;
+  a.num_classes = (int32_t)L->class_mask.size();
+  for (size_t c = 0; c < L->class_mask.size() && c < 8; ++c) {
+    uint64_t tokens = 0;
+    for (uint32_t w : L->class_mask[c].w) tokens += (uint64_t)__builtin_popcount(w);
+    a.class_valid |= tokens << (8 * c);
+  }
   a.batch = L->prob.batch;
   a.num_heads = L->prob.num_heads;
   a.n = L->n;

@@ -41,6 +41,8 @@ struct AttnArgs {
   const int32_t* tile_class;   // device [n]
   const SlotMask* class_mask;  // device
   const uint8_t* class_perm;   // device [num_classes * 128]; per class: valid slots ascending, then padding slots ascending
+  int32_t num_classes;
+  uint64_t class_valid;        // byte c: tokens of a tile of padding class c (the first eight classes)
   int32_t batch, num_heads;
   int64_t n;                   // tiles
   int32_t B, D;
