@@ -1,8 +1,9 @@
 // Block-sparse attention forward in full fp32 on the f32 matrix instructions of gfx950 (Appendix D's
 // block loop with online softmax), for fp32 problems of any tile size up to 128 tokens.
 //
-// What bounds it: v_mfma_f32_16x16x4_f32 (a multiply-add in full fp32; the card reaches about
-// 150 TFLOP/s with it, against half of that on the vector ALU).  Per 16 keys and 16 queries a wave
+// What bounds it: v_mfma_f32_16x16x4_f32 (a multiply-add in full fp32; a large fp32 matrix product
+// reaches 152 TFLOP/s on this card).  8 heads of 7K tokens, head dim 128, 0.094 TFLOP on real tokens:
+// 1.20 ms, 21.4 ms with one thread per query; 2 heads of 256 tokens: 8 us, 222 us.  Per 16 keys and 16 queries a wave
 // issues D / 2 of them, 32 cycles each, beside D / 8 16-byte LDS reads and four exponentials, so
 // everything else fits beside the matrix pipe.
 //
@@ -32,8 +33,6 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
-
-constexpr int64_t kF32MinWorkgroups = 2048;
 
 template <int D_, int QW_>
 struct F32Shape {
@@ -106,6 +105,13 @@ void attn_f32_kernel(AttnArgs a, int parts, int64_t workgroups) {
   const bool wave_active = q_first < q_valid;
   const char* tile_q = static_cast<const char*>(a.q) + plane + q_tile * tile_bytes;
   char* tile_o = static_cast<char*>(a.out) + plane + q_tile * tile_bytes;
+  if (part * QW * 16 >= q_valid) {  // padding slots only: zero rows
+    for (int e = threadIdx.x; e < QW * 16 * S::kChunks; e += 256) {
+      const int pos = part * QW * 16 + e / S::kChunks;
+      if (pos < a.B) *reinterpret_cast<f32x4*>(tile_o + (int64_t)a.class_perm[q_cls * 128 + pos] * S::kRowBytes + e % S::kChunks * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    return;
+  }
   f32x4 qf[D / 16];
 #pragma unroll
   for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const f32x4*>(tile_q + (int64_t)q_slot * S::kRowBytes + (16 * s + 4 * g) * 4);
@@ -328,10 +334,17 @@ void attn_f32_kernel(AttnArgs a, int parts, int64_t workgroups) {
 
 template <int D>
 hipError_t launch(const AttnArgs& a, hipStream_t stream) {
+  // As many query groups side by side as the tile has, because they share the staged keys; fewer, with
+  // the keys of a query split over the waves instead, while the launch has less than five workgroups
+  // per CU.  Measured: 1128 rows of 64 tokens at D = 128, QW 4 / 2: 1.27 / 1.20 ms; 732 rows of 60 at
+  // D = 32, QW 4 / 2 / 1: 0.63 / 0.65 / 0.69 ms.  At D = 128, QW = 1 fills the LDS of a CU with one
+  // workgroup and waits for copies (240 rows of 128 tokens, QW 2 / 1: 0.31 / 0.37 ms): small tiles only.
+  constexpr int64_t kMinWorkgroups = 1280;
+  constexpr int kFewest = D == 128 ? 2 : 1;
   const int64_t rows = (int64_t)a.batch * a.num_heads * a.n;
   auto parts_of = [&](int qw) { return (a.B + 16 * qw - 1) / (16 * qw); };
   int qw = a.B <= 16 ? 1 : a.B <= 32 ? 2 : 4;
-  while (qw > 1 && rows * parts_of(qw) < kF32MinWorkgroups) qw /= 2;
+  while (qw > kFewest && rows * parts_of(qw) < kMinWorkgroups) qw /= 2;
   const int parts = parts_of(qw);
   const int64_t workgroups = rows * parts, width = std::min(workgroups, (int64_t)1 << 23);  // a grid dimension holds fewer than 2^32 threads
   if (workgroups > (int64_t)1 << 38) return hipErrorInvalidValue;

@@ -905,3 +905,34 @@ def test_layout_on_device_matches_oracle_after_upload():
     for h in range(wl.num_heads):
         rp, ci = ca.compact_attn_layout_csr(lay, h)
         assert np.array_equal(rp, want[h][0]) and np.array_equal(ci, want[h][1])
+
+
+# ---------------------------------------------------------------- fp32: every split of a tile over waves
+
+@pytest.mark.parametrize("D,grid,tile,text_tiles,num_heads", [
+    (64, (2, 3, 5), (1, 1, 1), 1, 2),         # one-token tiles: every block of 16 keys holds one
+    (32, (5, 7, 9), (1, 3, 7), 1, 3),         # 21 slots: two query groups, the second with five
+    (64, (2, 9, 11), (1, 6, 10), 1, 3),       # 60 slots, padded along H and W
+    (128, (3, 17, 20), (2, 6, 8), 0, 2),      # 96 slots, padded along all axes
+    (128, (3, 9, 9), (2, 8, 8), 1, 2),        # 128 slots, tiles down to one token, parts without any
+    (32, (2, 32, 29), (1, 8, 8), 0, 20),      # 640 rows of 64: two groups side by side
+    (64, (2, 32, 29), (1, 8, 8), 0, 40),      # 1280 rows of 64: four
+])
+def test_fp32_splits_of_a_tile(D, grid, tile, text_tiles, num_heads):
+    """The fp32 kernel at the edges of its query groups and key blocks; what the padding slots of K and V hold does not matter."""
+    _say("fp32 split", D, grid, tile, num_heads)
+    B = tile[0] * tile[1] * tile[2]
+    heads = (_EDGE_HEADS[:3] * num_heads)[:num_heads]
+    wl = make_workload("f32-split", *grid, tile, text_tiles * B, num_heads, D, "f32", heads)
+    g = geometry_of(wl)
+    lay = build_layout(ca, wl)
+    q, k, v = make_qkv(wl, DEV, q_gain=2.0)
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    held = ca.compact_attn_permute(torch.ones_like(q), lay) != 0
+    kp[~held] = float("nan")
+    vp[~held] = float("nan")
+    out = ca.compact_attn_forward(qp, kp, vp, lay, out=torch.full_like(qp, float("nan")))
+    assert torch.all(out[~held] == 0)
+    got = ca.compact_attn_permute(out, lay, inverse=True)
+    want = OA.masked_attention(g, heads, to_f64(q[0]), to_f64(k[0]), to_f64(v[0]))
+    _say(compare(to_f64(got[0]), want, *tolerances("f32"), what="fp32 split"))
