@@ -147,9 +147,9 @@ int ensure_uploaded(ca_layout* L, hipStream_t stream) {
   return CA_OK;
 }
 
-// The tile-mass kernel is launched with as many workgroups as the device holds at a time (two waves
-// per SIMD), each of which takes rows by ticket and keeps two floats per (query, key tile) of the row
-// it is working on.  The workspace for that and the ticket counter are allocated at the first call
+// The tile-mass kernel is launched with as many workgroups as the device holds at a time, each of which
+// takes groups of 128 queries by ticket and keeps two floats per (query, key tile) of the group it is
+// working on.  The workspace for that and the ticket counter are allocated at the first call
 // for the layout (not under capture, like the tables) and freed with it.
 int ensure_mass_workspace(ca_layout* L, hipStream_t stream) {
   std::lock_guard<std::mutex> lock(L->upload_mutex);
@@ -169,14 +169,17 @@ int ensure_mass_workspace(ca_layout* L, hipStream_t stream) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
   if (cus < 1) cus = 1;
-  const int64_t rows_total = (int64_t)L->prob.batch * L->prob.num_heads * L->n;
-  const int64_t resident = (int64_t)cus * (8 / (L->B / 32));  // eight waves per CU, B / 32 waves per workgroup
-  const int64_t rows = std::max<int64_t>(1, std::min(rows_total, resident));
-  const size_t bytes = (size_t)rows * (size_t)L->N_pad * 2 * sizeof(float);
+  const int64_t rows_total = (int64_t)L->prob.batch * L->prob.num_heads * ca::mass_row_groups(L->n, L->B);
+  const int64_t resident = (int64_t)cus * ca::mass_workgroups_per_cu(L->B, L->prob.head_dim);
+  int64_t rows = std::max<int64_t>(1, std::min(rows_total, resident));
+  size_t bytes = 0;
   void* p = nullptr;
-  e = hipMalloc(&p, bytes + 256);  // the ticket counter follows the workspace
-  if (e != hipSuccess) {
+  for (;; rows = (rows + 1) / 2) {  // any number of workgroups will do: on a card that is nearly full, fewer
+    bytes = (size_t)rows * (size_t)L->n * 128 * 2 * sizeof(float);
+    e = hipMalloc(&p, bytes + 256);  // the ticket counter follows the workspace
+    if (e == hipSuccess) break;
     (void)hipGetLastError();
+    if (rows > 1) continue;
     set_error("hipMalloc of the tile-mass workspace (%zu bytes): %s", bytes, hipGetErrorString(e));
     return CA_ERR_ALLOC;
   }
@@ -676,11 +679,6 @@ int compact_attn_tile_mass(const void* q, const void* k, ca_layout* L, float* ma
   a.partial = L->dev.mass_partial;
   a.partial_rows = L->dev.mass_partial_rows;
   a.counter = L->dev.mass_counter;
-  // 128-token tiles: one launch, every workgroup goes from row to row.  64-token tiles: one launch per
-  // set of resident workgroups, so that all of them start a row together and walk the key tiles in
-  // step: their steps are short, and once the workgroups of an XCD have drifted apart the tile copies
-  // miss its L2 (measured at the 75K-token layout: 94.7 ms in one launch against 84.6 ms).
-  a.rows_per_launch = L->B >= 128 ? (int64_t)p.batch * p.num_heads * L->n : L->dev.mass_partial_rows;
   a.dense_meta = L->dev.dense_meta;
   a.tile_class = L->dev.tile_class;
   a.class_mask = L->dev.class_mask;

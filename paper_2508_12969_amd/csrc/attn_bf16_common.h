@@ -77,12 +77,12 @@ struct Shape {
   static constexpr int kTileBytes = B * D * 2;
   static constexpr int kLoadsPerThread = kTileBytes / (kThreads * 16);
   static constexpr int kRowsPerLoad = 1024 / kRowBytes;  // rows covered by one wave-wide 16-byte load
-  // 64-token tiles, head dim 128: a product phase has 16 matrix instructions, and the compiler's order
-  // leaves many of them waiting for their LDS reads.  With the reads three (K) and two (V) products ahead
-  // the paired kernel takes 35.7 instead of 36.7 ms at the 75K-token layout and the tile-mass kernel 17.0
-  // instead of 17.3 ms (six and four ahead: half of that).  128-token tiles (61.27 against 61.24 ms) and
-  // head dim 64 (4.63 against 4.57 ms) gain nothing.
-  static constexpr bool kShortPhases = B == 64 && D == 128;
+  // How many products ahead the LDS reads of a phase are kept (reads_ahead), 0 = the compiler's order.
+  // 64-token tiles, head dim 128: a phase has 16 matrix instructions, and the compiler's order leaves
+  // many of them waiting for their reads.  With three (K) and two (V) ahead the paired kernel takes 35.7
+  // instead of 36.7 ms at the 75K-token layout; six and four: half of that.  128-token tiles (61.27
+  // against 61.24 ms) and head dim 64 (4.63 against 4.57 ms) gain nothing.
+  static constexpr int kLeadK = B == 64 && D == 128 ? 3 : 0, kLeadV = B == 64 && D == 128 ? 2 : 0;
   static_assert(kLoadsPerThread * kThreads * 16 == kTileBytes, "tile must split evenly");
 };
 
@@ -293,14 +293,14 @@ __device__ __forceinline__ QuerySlot query_slot(const Args& a, int64_t q_tile, i
 // of them is issued, and stay that far ahead.
 template <int kProducts, int kReads, int kLead>
 __device__ __forceinline__ void reads_ahead() {
-  static_assert(kLead <= kProducts, "no more reads than products");
-  __builtin_amdgcn_sched_group_barrier(0x100, kLead * kReads, 0);
+  constexpr int lead = kLead < kProducts ? kLead : kProducts;
+  __builtin_amdgcn_sched_group_barrier(0x100, lead * kReads, 0);
 #pragma unroll
-  for (int i = 0; i < kProducts - kLead; ++i) {
+  for (int i = 0; i < kProducts - lead; ++i) {
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
   }
-  __builtin_amdgcn_sched_group_barrier(0x008, kLead, 0);
+  __builtin_amdgcn_sched_group_barrier(0x008, lead, 0);
 }
 
 // One wave's 32 queries: operand fragments, accumulators and softmax state, and the tile step.
@@ -379,7 +379,7 @@ struct QueryWave {
         acc_s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], s == 0 ? neg_m : acc_s[kb], 0, 0, 0);
       }
     }
-    if constexpr (S::kShortPhases && kKb1 > kKb0) reads_ahead<(kKb1 - kKb0) * S::kQkSteps, 1, 3>();
+    if constexpr (S::kLeadK > 0 && kKb1 > kKb0) reads_ahead<(kKb1 - kKb0) * S::kQkSteps, 1, S::kLeadK>();
   }
 
   // S^T of one tile.  `upper_keys` false: the upper half of the key slots is padding only (a tile on
@@ -497,7 +497,7 @@ struct QueryWave {
 #pragma unroll
         for (int db = 0; db < S::kDBlocks; ++db)
           acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v(lds_v, kb, t, db), pf[kb][t], acc_o[db], 0, 0, 0);
-    if constexpr (S::kShortPhases && kKb1 > kKb0) reads_ahead<(kKb1 - kKb0) * 2 * S::kDBlocks, 2, 2>();
+    if constexpr (S::kLeadV > 0 && kKb1 > kKb0) reads_ahead<(kKb1 - kKb0) * 2 * S::kDBlocks, 2, S::kLeadV>();
   }
 
   // O^T += V^T P^T of one tile; the upper key blocks are skipped with their scores (see qk_tile):

@@ -936,3 +936,32 @@ def test_fp32_splits_of_a_tile(D, grid, tile, text_tiles, num_heads):
     got = ca.compact_attn_permute(out, lay, inverse=True)
     want = OA.masked_attention(g, heads, to_f64(q[0]), to_f64(k[0]), to_f64(v[0]))
     _say(compare(to_f64(got[0]), want, *tolerances("f32"), what="fp32 split"))
+
+
+# ---------------------------------------------------------------- tile mass: row groups and steps
+
+@pytest.mark.parametrize("D,grid,tile,text_tiles", [
+    (64, (1, 8, 8), (1, 8, 8), 0),            # one tile: half a row group, half a step of two key tiles
+    (64, (1, 7, 15), (1, 8, 8), 0),           # two tiles, the second with 49 slots of 64
+    (64, (1, 16, 20), (1, 8, 8), 1),          # seven tiles: the last group has one row, the last step one tile
+    (128, (1, 8, 8), (1, 8, 8), 0),           # 64-token tiles, head dim 128: one key tile a step
+    (128, (3, 8, 5), (1, 8, 8), 0),
+    (64, (1, 8, 8), (2, 8, 8), 0),            # 128-token tile with an empty upper half
+    (128, (3, 8, 9), (2, 8, 8), 1),
+])
+def test_tile_mass_short_walks(D, grid, tile, text_tiles):
+    """Layouts of a few tiles: row groups and steps that are not full, with quiet and with peaked rows."""
+    from oracle import search as OS
+    _say("tile mass, short", D, grid, tile)
+    B = tile[0] * tile[1] * tile[2]
+    wl = make_workload("mass-short", *grid, tile, text_tiles * B, 3, D, "bf16", [[]] * 3)
+    g = geometry_of(wl)
+    lay = build_layout(ca, wl)
+    for gain in (1.0, 8.0):
+        q, k, _ = make_qkv(wl, DEV, q_gain=gain)
+        mass = torch.full((1, 3, g.n, g.n), float("nan"), device=DEV)
+        ca.compact_attn_tile_mass(ca.compact_attn_permute(q, lay), ca.compact_attn_permute(k, lay), lay, out=mass)
+        got = mass[0].double().cpu().numpy()
+        for h in range(3):
+            err = np.abs(got[h] - OS.tile_mass(g, to_f64(q[0, h]), to_f64(k[0, h])))
+            assert err.max() <= MASS_ABS, (h, gain, err.max())
