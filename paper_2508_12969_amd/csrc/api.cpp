@@ -283,7 +283,8 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
   a.n_vid = L->n_vid;
   a.N_real = L->N_real;
   const bool bf16 = L->prob.dtype == CA_BF16;
-  // Which kernel serves which rows.  64-token tiles with head dim 128: the paired kernel, all rows.
+  // Which kernel serves which rows.  Launches that choose_ways (layout.cpp) sends there: the kernels of
+  // attn_bf16_ways.hip, all rows.  Else: 64-token tiles with head dim 128: the paired kernel, all rows.
   // 128-token tiles with head dim 128 on a padded grid: one launch of the one-tile-per-workgroup
   // kernel whose order (launch_rows) also holds the workgroups of packed query tiles.  Everything
   // else: that kernel on `order`.
@@ -309,11 +310,15 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
     }
   };
   hipError_t e = hipSuccess;
-  if (!all_paired && a.entries > 0) {
+  a.ways = dense ? L->ways_dense : L->ways;
+  if (a.ways != ca::kWaysNone) {
+    a.order = dense ? nullptr : t.order;
+    e = ca::launch_attn_bf16(a, (hipStream_t)stream);
+  } else if (!all_paired && a.entries > 0) {
     set_split(a.entries, dense ? L->split_rows_dense : L->split_rows);
     e = bf16 ? ca::launch_attn_bf16(a, (hipStream_t)stream) : ca::launch_attn_f32(a, (hipStream_t)stream);
   }
-  if (e == hipSuccess && all_paired) {
+  if (a.ways == ca::kWaysNone && e == hipSuccess && all_paired) {
     set_split(t.num_pairs, dense ? L->split_pairs_dense : L->split_pairs);
     e = ca::launch_attn_bf16_pair(a, (hipStream_t)stream);
   }

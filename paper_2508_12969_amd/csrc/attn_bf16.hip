@@ -162,6 +162,7 @@ hipError_t launch(const AttnArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream) {
+  if (a.ways != kWaysNone) return launch_attn_bf16_ways(a, stream);
   const int64_t items = (int64_t)a.batch * a.entries;
   if (items == 0) return hipSuccess;
   if (a.static_items + a.pool_wgs > 0x7fffffff || a.static_items + a.pool_items != items) return hipErrorInvalidValue;

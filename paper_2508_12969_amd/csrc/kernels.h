@@ -30,6 +30,7 @@ struct AttnArgs {
   const int32_t* col_meta;     // device; per kept tile: tile id | padding class << 24; readable two words past the end
   const int32_t* order;        // device [entries]; the launch order: row ids; null = identity
   int64_t entries;             // launch-order entries per batch entry (num_heads * n rows, or fewer entries when query tiles are packed)
+  Ways ways;                   // bf16 kernels: which of the kernels of attn_bf16_ways.hip, on `order` as rows, or kWaysNone = the others
   int32_t packed;              // 1: `order` also holds workgroups of two packed query tiles, as the complement of their index in the pair tables
   const int32_t* pair_rows;    // device [2*num_pairs]; row ids of the two query tiles of a workgroup (-1: none), paired kernel only
   int64_t num_pairs;
@@ -63,6 +64,8 @@ struct AttnArgs {
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream);
 // bf16 problems, (B, D) in {64,128} x {64,128}
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream);
+// the part of it with a.ways != kWaysNone
+hipError_t launch_attn_bf16_ways(const AttnArgs& a, hipStream_t stream);
 // bf16 problems with D = 128: workgroups that serve two query tiles (B = 64: every pair of neighbours; B = 128: the
 // packed tiles of the grid's padded faces)
 hipError_t launch_attn_bf16_pair(const AttnArgs& a, hipStream_t stream);

@@ -404,6 +404,92 @@ void build_launch_splits(ca_layout& L) {
 }
 }  // namespace
 
+namespace {
+
+// Predicted time of a launch in us: its workgroups' steps spread over the CUs, or its longest walk, whichever
+// is longer.  A step is 128 keys.
+struct LaunchCost {
+  double start;  // launch, first copies, epilogue
+  double step;   // per workgroup and step, as time of a whole CU that is full
+  double walk;   // per step of the longest walk, on a CU with little else to do
+  double group;  // per workgroup, as time of a whole CU
+  double of(double steps, double longest, double groups) const {
+    constexpr double kCus = 256;
+    return start + std::max((step * steps + group * groups) / kCus, walk * longest);
+  }
+};
+struct WayCost {
+  Ways ways;
+  int stage_keys, part_queries;
+  LaunchCost cost;
+};
+
+// Which kernel serves the sparse (or the dense) walk: the one with the shortest predicted time, the
+// one-tile and paired kernels unless another is at least 5 % better.  The constants are a least-squares
+// fit of log time over 82 launches (heads 1-40, 1-64 x 8-60 x 8-104 grids, 128 and 64 tokens per tile, 8-500 us
+// a launch for the most part, masks from 5 % to dense), per tile size and head dim; residual 3-14 %.  Over these
+// and 28 more the choice made launches 1.26 (head dim 64), 1.11 and 1.19 times faster (head dim 128, 64- and
+// 128-token tiles; geometric means), the best choice in hindsight 1.27, 1.12 and 1.21.
+Ways choose_ways(const ca_layout& L, bool dense) {
+  const ca_problem& p = L.prob;
+  if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
+  // 32-bit lane offsets inside a tile of the natural order; a grid dimension of fewer than 2^32 threads
+  if ((int64_t)p.tt * p.H * p.W * p.head_dim * 2 >= (int64_t)1 << 31) return kWaysNone;
+  if ((int64_t)p.batch * p.num_heads * L.n * 2 * 512 >= (int64_t)1 << 32) return kWaysNone;
+  static const LaunchCost kPlain[2][2] = {{{0.8, 0.61, 2.09, 0.89}, {1.1, 1.17, 2.09, 2.48}}, {{7.7, 0.93, 2.35, 8.2}, {6.0, 1.82, 2.31, 1.0}}};
+  static const WayCost k64x64[] = {{kWays8x2, 128, 64, {4.3, 0.91, 1.53, 1.1}}};
+  static const WayCost k64x128[] = {{kWays4x4, 64, 128, {2.5, 1.22, 2.70, 5.6}}, {kWays8x2, 128, 64, {6.9, 0.93, 1.19, 9.4}}};
+  static const WayCost k128x64[] = {{kWays8x2, 128, 64, {9.9, 2.05, 1.79, 7.4}}};
+  static const WayCost k128x128[] = {
+      {kWays4x4, 64, 128, {8.9, 2.37, 2.94, 3.0}}, {kWays8x4, 128, 128, {10.3, 2.97, 2.36, 1.0}}, {kWays8x2, 128, 64, {7.6, 2.24, 2.09, 13.7}}};
+  const bool big_d = p.head_dim == 128, big_b = L.B == 128;
+  const WayCost* options = big_d ? (big_b ? k128x128 : k128x64) : (big_b ? k64x128 : k64x64);
+  const int count = big_b ? (big_d ? 3 : 2) : 1;
+
+  // walks in 128-key steps of the plain kernels and in 16-token granules; a large layout is sampled
+  std::vector<int> tokens(L.class_mask.size()), granules(L.class_mask.size());
+  for (size_t c = 0; c < tokens.size(); ++c) {
+    for (uint32_t w : L.class_mask[c].w) tokens[c] += __builtin_popcount(w);
+    granules[c] = (tokens[c] + 15) / 16;
+  }
+  const int64_t rows = (int64_t)p.num_heads * L.n;
+  const int64_t stride = dense ? 1 : 1 + (int64_t)L.col_idx.size() / 2000000;
+  int64_t all = 0;  // granules of a row that keeps every tile
+  for (int64_t t = 0; t < L.n; ++t) all += granules[L.tile_class[t]];
+  double plain_steps = 0, plain_longest = 0, steps[3] = {}, longest[3] = {}, groups[3] = {};
+  for (int64_t r = 0; r < rows; r += stride) {
+    int64_t tiles = L.n, kept = all;
+    if (!dense) {
+      const int32_t *t = L.col_idx.data() + L.row_ptr[r], *end = L.col_idx.data() + L.row_ptr[r + 1];
+      tiles = end - t;
+      kept = 0;
+      if (tokens.size() == 1) kept = tiles * granules[0];
+      else for (; t < end; ++t) kept += granules[L.tile_class[*t]];
+    }
+    const double plain = (double)(tiles * L.B) / 128;
+    plain_steps += plain;
+    plain_longest = std::max(plain_longest, plain);
+    for (int i = 0; i < count; ++i) {
+      const WayCost& w = options[i];
+      const int64_t parts = (tokens[L.tile_class[r % L.n]] + w.part_queries - 1) / w.part_queries;  // those with a token
+      const double walk = (double)((kept * 16 + w.stage_keys - 1) / w.stage_keys * w.stage_keys) / 128;
+      steps[i] += walk * parts;
+      longest[i] = std::max(longest[i], walk);
+      groups[i] += (double)parts;
+    }
+  }
+  const double scale = (double)stride * p.batch;
+  double best = 0.95 * kPlain[big_d][big_b].of(plain_steps * scale, plain_longest, (double)rows * p.batch);
+  Ways ways = kWaysNone;
+  for (int i = 0; i < count; ++i) {
+    const double t = options[i].cost.of(steps[i] * scale, longest[i], groups[i] * scale);
+    if (t < best) best = t, ways = options[i].ways;
+  }
+  return ways;
+}
+
+}  // namespace
+
 void finish_host_tables(ca_layout& L) {
   const int32_t Hd = L.prob.num_heads;
   // per-head relative offsets for the C-ABI view
@@ -424,6 +510,8 @@ void finish_host_tables(ca_layout& L) {
   if (L.prob.dtype == CA_BF16 && L.B == 64 && L.prob.head_dim == 128) build_pair_table(L);
   if (L.prob.dtype == CA_BF16 && L.B == 128 && L.prob.head_dim == 128) build_packed_faces(L);
   build_launch_splits(L);
+  L.ways = choose_ways(L, false);
+  L.ways_dense = choose_ways(L, true);
 }
 
 int import_host_tables(ca_layout& L, const int64_t* const* row_ptr, const int32_t* const* col_idx) {

@@ -40,6 +40,9 @@ constexpr int64_t kPoolMinItems = 4096; // smaller launches are dealt statically
 // `work[i]`: cost of launch-order entry i (tile steps); returns the split of one batch entry's launch.
 LaunchSplit split_launch(const int64_t* work, int64_t entries);
 
+// The kernels of attn_bf16_ways.hip: waves of a workgroup x 32-query waves side by side.
+enum Ways : int32_t { kWaysNone = 0, kWays4x4, kWays8x4, kWays8x2 };
+
 // Device-resident tables.  All pointers are device memory owned by the layout.
 struct DeviceTables {
   int64_t* row_ptr = nullptr;    // [num_heads*n + 1] offsets into col_idx (global over heads)
@@ -95,6 +98,7 @@ struct ca_layout {
   // leaves the cheapest entries at the end of the launch order to be drawn by whichever XCD gets there
   // first: rows / pairs of the sparse and of the dense walk.
   ca::LaunchSplit split_rows, split_rows_dense, split_pairs, split_pairs_dense;
+  ca::Ways ways = ca::kWaysNone, ways_dense = ca::kWaysNone;  // kernel of the sparse and of the dense walk, natural order included
   mutable std::atomic<uint32_t> launch_seq{0};  // picks the pool counter of a launch
 
   // device tables, created once

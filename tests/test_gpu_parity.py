@@ -965,3 +965,49 @@ def test_tile_mass_short_walks(D, grid, tile, text_tiles):
         for h in range(3):
             err = np.abs(got[h] - OS.tile_mass(g, to_f64(q[0, h]), to_f64(k[0, h])))
             assert err.max() <= MASS_ABS, (h, gain, err.max())
+
+
+# ---------------------------------------------------------------- every bf16 kernel at small sizes
+
+@pytest.mark.parametrize("D,grid,tile,text_tiles,copies,batch", [
+    # keys split over four ways, 64 queries to a workgroup: padded along all axes, empty rows, tiles of a few tokens
+    (128, (5, 13, 20), (2, 8, 8), 0, 1, 2),       # (its dense walk: two ways, 128 queries)
+    (64, (5, 13, 20), (2, 8, 8), 0, 1, 2),
+    (128, (3, 13, 20), (1, 8, 8), 1, 1, 1),
+    (64, (3, 13, 20), (1, 8, 8), 1, 1, 1),
+    (128, (1, 9, 17), (2, 8, 8), 1, 1, 1),
+    (64, (5, 9, 9), (4, 4, 8), 0, 1, 1),
+    # one way, 128 queries, tiles closed up
+    (128, (7, 17, 17), (2, 8, 8), 0, 12, 1),
+    (64, (7, 17, 17), (2, 8, 8), 0, 12, 1),
+    (128, (9, 16, 17), (2, 8, 8), 1, 3, 1),
+    # many short rows: one query tile per workgroup (packed faces at head dim 128), paired 64-token tiles
+    (128, (5, 13, 20), (2, 8, 8), 1, 40, 2),      # (its dense walk: one way, tiles closed up)
+    (64, (4, 16, 24), (2, 8, 8), 0, 60, 2),
+    (128, (3, 13, 20), (1, 8, 8), 1, 16, 2),
+    (64, (3, 13, 20), (1, 8, 8), 1, 40, 2),
+])
+def test_bf16_kernels_by_launch_size(D, grid, tile, text_tiles, copies, batch):
+    """The same four heads in launches small and large enough for every kernel of the bf16 dispatch: sparse and
+    dense walk against the oracle with peaked rows, natural order and the static entry point bit for bit."""
+    import dataclasses
+    _say("bf16 by launch size", D, grid, tile, copies, batch)
+    B = tile[0] * tile[1] * tile[2]
+    heads = list(_EDGE_HEADS) * copies
+    wl = dataclasses.replace(make_workload("by-size", *grid, tile, text_tiles * B, len(heads), D, "bf16", heads), batch=batch)
+    g = geometry_of(wl)
+    lay = build_layout(ca, wl)
+    q, k, v = make_qkv(wl, DEV, q_gain=3.0)
+    out, out_tiled = gpu_attention(ca, wl, lay, q, k, v)
+    dense, _ = gpu_attention(ca, wl, lay, q, k, v, dense=True)
+    assert torch.equal(ca.compact_attn_forward_natural(q, k, v, lay, out=torch.full_like(q, float("nan"))), out)
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    assert torch.equal(ca.compact_attn_forward_static(qp, kp, vp, lay, out=torch.full_like(qp, float("nan"))), out_tiled)
+    held = ca.compact_attn_permute(torch.ones_like(q), lay) != 0
+    assert torch.all(out_tiled[~held] == 0)
+    full = [[(g.nT - 1, (g.nH - 1, g.nW - 1), ABSENT)]]
+    h0 = len(heads) - 4                                     # the last four heads of the last batch entry
+    for h in range(4):
+        qkv = [to_f64(x[batch - 1, h0 + h])[None] for x in (q, k, v)]
+        _say(h, compare(to_f64(out[batch - 1, h0 + h])[None], OA.masked_attention(g, [heads[h]], *qkv), *tolerances("bf16"), what="sparse"))
+        _say(h, compare(to_f64(dense[batch - 1, h0 + h])[None], OA.masked_attention(g, full, *qkv), *tolerances("bf16"), what="dense"))
