@@ -311,6 +311,7 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
   };
   hipError_t e = hipSuccess;
   a.ways = dense ? L->ways_dense : L->ways;
+  a.simd_waves = dense ? L->simd_waves_dense : L->simd_waves;
   if (a.ways != ca::kWaysNone) {
     a.order = dense ? nullptr : t.order;
     e = ca::launch_attn_bf16(a, (hipStream_t)stream);

@@ -125,8 +125,8 @@ __device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, in
 }
 
 // kPacked: the launch order may hold workgroups of two packed query tiles (entries below zero)
-template <int B, int D, bool kNat, bool kPacked>
-__global__ __attribute__((amdgpu_flat_work_group_size(B * 2, B * 2), amdgpu_waves_per_eu(2, 2)))
+template <int B, int D, bool kNat, bool kPacked, int kSimdWaves = 2>
+__global__ __attribute__((amdgpu_flat_work_group_size(B * 2, B * 2), amdgpu_waves_per_eu(kSimdWaves, kSimdWaves)))
 void attn_bf16_kernel(AttnArgs a) {
   using S = Shape<B, D>;
   __shared__ __attribute__((aligned(1024))) char lds_k[S::kTileBytes];
@@ -147,14 +147,14 @@ void attn_bf16_kernel(AttnArgs a) {
   attn_row_body<B, D, kNat>(a, entry, batch, lds_k, lds_v);
 }
 
-template <int B, int D>
+template <int B, int D, int kSimdWaves>
 hipError_t launch(const AttnArgs& a, hipStream_t stream) {
   const int64_t items = a.static_items + a.pool_wgs;
   if (a.natural) {
     if (a.tw % Shape<B, D>::kRowsPerLoad != 0) return hipErrorInvalidValue;  // a KiB block must stay inside one run
-    hipLaunchKernelGGL((attn_bf16_kernel<B, D, true, false>), dim3((unsigned)items), dim3(B * 2), 0, stream, a);
+    hipLaunchKernelGGL((attn_bf16_kernel<B, D, true, false, kSimdWaves>), dim3((unsigned)items), dim3(B * 2), 0, stream, a);
   } else {
-    hipLaunchKernelGGL((attn_bf16_kernel<B, D, false, false>), dim3((unsigned)items), dim3(B * 2), 0, stream, a);
+    hipLaunchKernelGGL((attn_bf16_kernel<B, D, false, false, kSimdWaves>), dim3((unsigned)items), dim3(B * 2), 0, stream, a);
   }
   return hipGetLastError();
 }
@@ -177,8 +177,8 @@ hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream) {
     else hipLaunchKernelGGL((attn_bf16_kernel<128, 128, false, true>), grid, block, 0, stream, a);
     return hipGetLastError();
   }
-  if (a.B == 128 && a.D == 64) return launch<128, 64>(a, stream);
-  if (a.B == 64 && a.D == 64) return launch<64, 64>(a, stream);
+  if (a.B == 128 && a.D == 64) return launch<128, 64, 2>(a, stream);
+  if (a.B == 64 && a.D == 64) return a.simd_waves == 3 ? launch<64, 64, 3>(a, stream) : launch<64, 64, 2>(a, stream);
   return hipErrorInvalidValue;
 }
 

@@ -30,6 +30,7 @@ struct AttnArgs {
   const int32_t* col_meta;     // device; per kept tile: tile id | padding class << 24; readable two words past the end
   const int32_t* order;        // device [entries]; the launch order: row ids; null = identity
   int64_t entries;             // launch-order entries per batch entry (num_heads * n rows, or fewer entries when query tiles are packed)
+  int32_t simd_waves;          // one-tile kernel, 64-token tiles of head dim 64: waves per SIMD, 2 or 3
   Ways ways;                   // bf16 kernels: which of the kernels of attn_bf16_ways.hip, on `order` as rows, or kWaysNone = the others
   int32_t packed;              // 1: `order` also holds workgroups of two packed query tiles, as the complement of their index in the pair tables
   const int32_t* pair_rows;    // device [2*num_pairs]; row ids of the two query tiles of a workgroup (-1: none), paired kernel only

@@ -98,6 +98,7 @@ struct ca_layout {
   // leaves the cheapest entries at the end of the launch order to be drawn by whichever XCD gets there
   // first: rows / pairs of the sparse and of the dense walk.
   ca::LaunchSplit split_rows, split_rows_dense, split_pairs, split_pairs_dense;
+  int32_t simd_waves = 2, simd_waves_dense = 2;               // waves per SIMD of the one-tile kernel (choose_simd_waves)
   ca::Ways ways = ca::kWaysNone, ways_dense = ca::kWaysNone;  // kernel of the sparse and of the dense walk, natural order included
   mutable std::atomic<uint32_t> launch_seq{0};  // picks the pool counter of a launch
 
