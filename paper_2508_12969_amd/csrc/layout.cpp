@@ -409,7 +409,7 @@ void build_launch_splits(ca_layout& L) {
 namespace {
 
 // Predicted time of a launch in us: its workgroups' steps spread over the CUs, or its longest walk, whichever
-// is longer.  A step is 128 keys.
+// is longer.  A step is 128 keys, or one tile of the paired kernel's walk.
 struct LaunchCost {
   double start;  // launch, first copies, epilogue
   double step;   // per workgroup and step, as time of a whole CU that is full
@@ -427,28 +427,41 @@ struct WayCost {
 };
 
 // Which kernel serves the sparse (or the dense) walk: the one with the shortest predicted time, the
-// one-tile and paired kernels unless another is at least 5 % better.  The constants are a least-squares
-// fit of log time over 82 launches (heads 1-40, 1-64 x 8-60 x 8-104 grids, 128 and 64 tokens per tile, 8-500 us
-// a launch for the most part, masks from 5 % to dense), per tile size and head dim; residual 3-14 %.  Over these
-// and 28 more the choice made launches 1.26 (head dim 64), 1.11 and 1.19 times faster (head dim 128, 64- and
-// 128-token tiles; geometric means), the best choice in hindsight 1.27, 1.12 and 1.21.
+// one-tile and paired kernels unless another is at least 10 % better.  The constants are a least-squares
+// fit of log time over 240 launches of under 3 TFLOP (1-40 heads, grids of 1-64 x 8-60 x 8-104, masks from 5 % to
+// dense, all entry points), per tile size and head dim; residual 9-14 %.  The choice made these launches
+// 1.11 and 1.30 (head dim 64, tiles of 64 and 128 tokens), 1.14 and 1.21 times faster (head dim 128; geometric
+// means), five of them 4-15 % slower; the best choice in hindsight gives 1.11, 1.32, 1.15 and 1.24.
 Ways choose_ways(const ca_layout& L, bool dense) {
   const ca_problem& p = L.prob;
   if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
   // 32-bit lane offsets inside a tile of the natural order; a grid dimension of fewer than 2^32 threads
   if ((int64_t)p.tt * p.H * p.W * p.head_dim * 2 >= (int64_t)1 << 31) return kWaysNone;
   if ((int64_t)p.batch * p.num_heads * L.n * 2 * 512 >= (int64_t)1 << 32) return kWaysNone;
-  static const LaunchCost kPlain[2][2] = {{{0.8, 0.61, 2.09, 0.89}, {1.1, 1.17, 2.09, 2.48}}, {{7.7, 0.93, 2.35, 8.2}, {6.0, 1.82, 2.31, 1.0}}};
-  static const WayCost k64x64[] = {{kWays8x2, 128, 64, {4.3, 0.91, 1.53, 1.1}}};
-  static const WayCost k64x128[] = {{kWays4x4, 64, 128, {2.5, 1.22, 2.70, 5.6}}, {kWays8x2, 128, 64, {6.9, 0.93, 1.19, 9.4}}};
-  static const WayCost k128x64[] = {{kWays8x2, 128, 64, {9.9, 2.05, 1.79, 7.4}}};
+  static const LaunchCost kPlain[2][2] = {{{2.2, 0.68, 2.20, 0.5}, {4.6, 1.08, 1.62, 10.7}}, {{6.1, 0.95, 1.28, 12.9}, {5.9, 1.99, 2.29, 7.9}}};
+  static const WayCost k64x64[] = {{kWays8x2, 128, 64, {5.9, 0.95, 1.57, 4.6}}};
+  static const WayCost k64x128[] = {{kWays4x4, 64, 128, {6.3, 1.17, 2.43, 3.4}}, {kWays8x2, 128, 64, {7.6, 0.95, 1.20, 8.3}}};
+  static const WayCost k128x64[] = {{kWays8x2, 128, 64, {8.7, 2.23, 1.95, 6.4}}};
   static const WayCost k128x128[] = {
-      {kWays4x4, 64, 128, {8.9, 2.37, 2.94, 3.0}}, {kWays8x4, 128, 128, {10.3, 2.97, 2.36, 1.0}}, {kWays8x2, 128, 64, {7.6, 2.24, 2.09, 13.7}}};
+      {kWays4x4, 64, 128, {6.6, 2.36, 3.15, 6.2}}, {kWays8x4, 128, 128, {7.2, 2.95, 2.55, 9.3}}, {kWays8x2, 128, 64, {7.5, 2.35, 1.99, 14.7}}};
   const bool big_d = p.head_dim == 128, big_b = L.B == 128;
   const WayCost* options = big_d ? (big_b ? k128x128 : k128x64) : (big_b ? k64x128 : k64x64);
   const int count = big_b ? (big_d ? 3 : 2) : 1;
 
-  // walks in 128-key steps of the plain kernels and in 16-token granules; a large layout is sampled
+  // the workgroups of the one-tile and paired kernels
+  const std::vector<int32_t>& launched = L.packed_faces ? L.launch_rows : L.order;
+  const bool paired = !L.pair_rows.empty() && !L.packed_faces;
+  const int64_t plain_groups = paired ? (int64_t)L.pair_rows.size() / 2 : (int64_t)launched.size();
+  double plain_steps = 0, plain_longest = 0;
+  for (int64_t i = 0; i < plain_groups; ++i) {
+    const int64_t e = paired ? ~i : launched[i];
+    const int64_t tiles = dense ? L.n : e < 0 ? L.pair_walk_ptr[~e + 1] - L.pair_walk_ptr[~e] : L.row_ptr[e + 1] - L.row_ptr[e];
+    const double walk = paired ? (double)tiles : (double)(tiles * L.B) / 128;
+    plain_steps += walk;
+    plain_longest = std::max(plain_longest, walk);
+  }
+
+  // walks in 16-token granules; a large layout is sampled
   std::vector<int> tokens(L.class_mask.size()), granules(L.class_mask.size());
   for (size_t c = 0; c < tokens.size(); ++c) {
     for (uint32_t w : L.class_mask[c].w) tokens[c] += __builtin_popcount(w);
@@ -458,7 +471,7 @@ Ways choose_ways(const ca_layout& L, bool dense) {
   const int64_t stride = dense ? 1 : 1 + (int64_t)L.col_idx.size() / 2000000;
   int64_t all = 0;  // granules of a row that keeps every tile
   for (int64_t t = 0; t < L.n; ++t) all += granules[L.tile_class[t]];
-  double plain_steps = 0, plain_longest = 0, steps[3] = {}, longest[3] = {}, groups[3] = {};
+  double steps[3] = {}, longest[3] = {}, groups[3] = {};
   for (int64_t r = 0; r < rows; r += stride) {
     int64_t tiles = L.n, kept = all;
     if (!dense) {
@@ -468,9 +481,6 @@ Ways choose_ways(const ca_layout& L, bool dense) {
       if (tokens.size() == 1) kept = tiles * granules[0];
       else for (; t < end; ++t) kept += granules[L.tile_class[*t]];
     }
-    const double plain = (double)(tiles * L.B) / 128;
-    plain_steps += plain;
-    plain_longest = std::max(plain_longest, plain);
     for (int i = 0; i < count; ++i) {
       const WayCost& w = options[i];
       const int64_t parts = (tokens[L.tile_class[r % L.n]] + w.part_queries - 1) / w.part_queries;  // those with a token
@@ -481,7 +491,7 @@ Ways choose_ways(const ca_layout& L, bool dense) {
     }
   }
   const double scale = (double)stride * p.batch;
-  double best = 0.95 * kPlain[big_d][big_b].of(plain_steps * scale, plain_longest, (double)rows * p.batch);
+  double best = 0.9 * kPlain[big_d][big_b].of(plain_steps * p.batch, plain_longest, (double)plain_groups * p.batch);
   Ways ways = kWaysNone;
   for (int i = 0; i < count; ++i) {
     const double t = options[i].cost.of(steps[i] * scale, longest[i], groups[i] * scale);

@@ -980,12 +980,14 @@ def test_tile_mass_short_walks(D, grid, tile, text_tiles):
     # one way, 128 queries, tiles closed up
     (128, (7, 17, 17), (2, 8, 8), 0, 12, 1),
     (64, (7, 17, 17), (2, 8, 8), 0, 12, 1),
-    (128, (9, 16, 17), (2, 8, 8), 1, 3, 1),
-    # many short rows: one query tile per workgroup (packed faces at head dim 128), paired 64-token tiles
-    (128, (5, 13, 20), (2, 8, 8), 1, 40, 2),      # (its dense walk: one way, tiles closed up)
+    (128, (7, 17, 17), (2, 8, 8), 1, 3, 2),
     (64, (4, 16, 24), (2, 8, 8), 0, 60, 2),
+    (128, (5, 13, 20), (2, 8, 8), 1, 40, 2),
+    # rows enough for one query tile per workgroup (packed faces at head dim 128), paired 64-token tiles
+    (128, (9, 20, 20), (2, 8, 8), 1, 8, 1),
+    (64, (5, 13, 20), (2, 8, 8), 1, 4, 1),        # (its dense walk: one way, tiles closed up)
     (128, (3, 13, 20), (1, 8, 8), 1, 16, 2),
-    (64, (3, 13, 20), (1, 8, 8), 1, 40, 2),
+    (64, (3, 13, 20), (1, 8, 8), 1, 40, 2),       # three waves per SIMD
 ])
 def test_bf16_kernels_by_launch_size(D, grid, tile, text_tiles, copies, batch):
     """The same four heads in launches small and large enough for every kernel of the bf16 dispatch: sparse and
