@@ -212,7 +212,7 @@ int compact_attn_permute(const void* src, void* dst, ca_layout* layout, int32_t 
  * the kept key tiles.  A row whose kept set holds no real key yields zeros.
  * bf16 problems run on the MFMA kernel: bf16 operands, fp32 accumulation and softmax state,
  * probabilities rounded to bf16 before the PV product; supported (B, D): (64,64), (64,128),
- * (128,128) and (128,64).  f32 problems run on a plain fp32 kernel for B <= 128, D in {32,64,128}.
+ * (128,128) and (128,64).  f32 problems run on an fp32 kernel for B <= 128, D in {32,64,128}.
  * Anything else: CA_ERR_UNSUPPORTED. */
 int compact_attn_forward(const void* q, const void* k, const void* v, ca_layout* layout, void* out,
                          void* stream);
@@ -263,10 +263,12 @@ int compact_attn_dense(const void* q, const void* k, const void* v, ca_layout* l
  * Row a of mass sums to the number of real tokens of tile a.  One Q K^T product per tile pair: half
  * the FLOPs of one dense pass.
  *   Workspace: the kernel keeps two floats per (query token, key tile) of the rows in flight.  The
- *   first call for a layout allocates min(batch * heads * n, W) * N_pad * 8 bytes of device memory,
- *   W = the workgroups the device holds at a time (two per compute unit for 128-token tiles, four
- *   for 64-token tiles: 0.54 GB for 130K tokens on 256 compute units), (synchronously; refused with CA_ERR_INVALID_ARG on a stream under capture: call once
- *   before capturing), which the layout owns until compact_attn_free_layout.  Calls on the same
+ *   first call for a layout allocates min(batch * heads * ceil(n * B / 128), W) * n * 1024 bytes of
+ *   device memory, W = the workgroups the device holds at a time (three per compute unit; two for
+ *   128-token tiles of head dim 128: 0.54 GB for 130K tokens on 256 compute units; fewer workgroups
+ *   run where the device has no room for that), synchronously (refused with CA_ERR_INVALID_ARG on a
+ *   stream under capture: call once before capturing), which the layout owns until
+ *   compact_attn_free_layout.  Calls on the same
  *   layout that overlap in time (different streams) would share that workspace and race: give
  *   concurrent calls a layout each.  CA_ERR_ALLOC if the allocation fails.
  * Supported: bf16 with (B, D) in {64,128} x {64,128}; otherwise CA_ERR_UNSUPPORTED. */
