@@ -145,6 +145,9 @@ class Layout:
         _check(load_library().compact_attn_layout_info(handle, n, B, n_real, n_pad, nnz))
         self.n_tiles, self.tokens_per_tile = n.value, B.value
         self.n_tokens_real, self.n_tokens_padded, self.nnz_total = n_real.value, n_pad.value, nnz.value
+        # tensor shapes, natural and padded: every call compares them
+        self._shapes = tuple((problem.batch, problem.num_heads, tokens, problem.head_dim) for tokens in (n_real.value, n_pad.value))
+        self._is_bf16 = problem.dtype == CA_BF16
 
     def free(self):
         if self.handle is not None:
@@ -158,8 +161,7 @@ class Layout:
             pass
 
     def shape(self, padded):
-        p = self.problem
-        return (p.batch, p.num_heads, self.n_tokens_padded if padded else self.n_tokens_real, p.head_dim)
+        return self._shapes[bool(padded)]
 
 
 def compact_attn_build_layout(T, H, W, tile, n_text, batch, num_heads, head_dim, dtype, heads, scale=0.0, clamp_centre=False):
@@ -277,14 +279,15 @@ def compact_attn_free_layout(layout):
 
 def _torch_dtype(layout):
     import torch
-    return torch.bfloat16 if layout.problem.dtype == CA_BF16 else torch.float32
+    return torch.bfloat16 if layout._is_bf16 else torch.float32
 
 
 def _stream_ptr(stream):
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    # the handle of torch.cuda.current_stream() without the Python object around it (2 us a call)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check_tensor(t, layout, padded, name):
@@ -294,31 +297,30 @@ def _check_tensor(t, layout, padded, name):
         raise ValueError(f"{name} must be contiguous")
     if t.dtype != _torch_dtype(layout):
         raise ValueError(f"{name} has dtype {t.dtype}, layout expects {_torch_dtype(layout)}")
-    if tuple(t.shape) != layout.shape(padded):
+    if t.shape != layout.shape(padded):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {layout.shape(padded)}")
 
 
 def compact_attn_permute(src, layout, inverse=False, out=None, stream=None):
     """natural order -> tile order (inverse=False) or back (inverse=True)."""
-    import torch
-    _check_tensor(src, layout, padded=bool(inverse), name="src")
+    inverse = bool(inverse)
+    _check_tensor(src, layout, inverse, "src")
     if out is None:
-        out = torch.empty(layout.shape(padded=not inverse), dtype=src.dtype, device=src.device)
-    _check_tensor(out, layout, padded=not inverse, name="out")
-    _check(load_library().compact_attn_permute(ctypes.c_void_p(src.data_ptr()), ctypes.c_void_p(out.data_ptr()),
-                                               layout.handle, int(bool(inverse)), _stream_ptr(stream)))
+        out = src.new_empty(layout.shape(not inverse))
+    else:
+        _check_tensor(out, layout, not inverse, "out")
+    _check(load_library().compact_attn_permute(src.data_ptr(), out.data_ptr(), layout.handle, int(inverse), _stream_ptr(stream)))
     return out
 
 
 def _attention(fn, q, k, v, layout, out, stream, padded=True):
-    import torch
     for name, t in (("q", q), ("k", k), ("v", v)):
         _check_tensor(t, layout, padded, name)
     if out is None:
-        out = torch.empty_like(q)
-    _check_tensor(out, layout, padded, "out")
-    _check(fn(ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k.data_ptr()), ctypes.c_void_p(v.data_ptr()),
-              layout.handle, ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)))
+        out = q.new_empty(q.shape)
+    else:
+        _check_tensor(out, layout, padded, "out")
+    _check(fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), layout.handle, out.data_ptr(), _stream_ptr(stream)))
     return out
 
 
