@@ -468,29 +468,32 @@ Ways choose_ways(const ca_layout& L, bool dense) {
     granules[c] = (tokens[c] + 15) / 16;
   }
   const int64_t rows = (int64_t)p.num_heads * L.n;
-  const int64_t stride = dense ? 1 : 1 + (int64_t)L.col_idx.size() / 2000000;
+  const int64_t stride = dense ? 1 : 1 + (int64_t)L.col_idx.size() / 500000;
   int64_t all = 0;  // granules of a row that keeps every tile
-  for (int64_t t = 0; t < L.n; ++t) all += granules[L.tile_class[t]];
+  std::vector<uint8_t> tile_granules(L.n);
+  for (int64_t t = 0; t < L.n; ++t) all += tile_granules[t] = (uint8_t)granules[L.tile_class[t]];
   double steps[3] = {}, longest[3] = {}, groups[3] = {};
-  for (int64_t r = 0; r < rows; r += stride) {
+  const int64_t looked_at = dense ? L.n : rows;  // every head's dense walk is the same
+  for (int64_t r = 0; r < looked_at; r += stride) {
     int64_t tiles = L.n, kept = all;
     if (!dense) {
       const int32_t *t = L.col_idx.data() + L.row_ptr[r], *end = L.col_idx.data() + L.row_ptr[r + 1];
       tiles = end - t;
       kept = 0;
       if (tokens.size() == 1) kept = tiles * granules[0];
-      else for (; t < end; ++t) kept += granules[L.tile_class[*t]];
+      else for (; t < end; ++t) kept += tile_granules[*t];
     }
     for (int i = 0; i < count; ++i) {
       const WayCost& w = options[i];
       const int64_t parts = (tokens[L.tile_class[r % L.n]] + w.part_queries - 1) / w.part_queries;  // those with a token
-      const double walk = (double)((kept * 16 + w.stage_keys - 1) / w.stage_keys * w.stage_keys) / 128;
+      const uint32_t stage = (uint32_t)w.stage_keys / 16;  // in granules
+      const double walk = (double)(((uint32_t)kept + stage - 1) / stage * stage) / 8;
       steps[i] += walk * parts;
       longest[i] = std::max(longest[i], walk);
       groups[i] += (double)parts;
     }
   }
-  const double scale = (double)stride * p.batch;
+  const double scale = (double)stride * p.batch * (dense ? p.num_heads : 1);
   double best = 0.9 * kPlain[big_d][big_b].of(plain_steps * p.batch, plain_longest, (double)plain_groups * p.batch);
   Ways ways = kWaysNone;
   for (int i = 0; i < count; ++i) {
@@ -511,11 +514,12 @@ int choose_simd_waves(const ca_layout& L, bool dense) {
   const int64_t rows = (int64_t)L.order.size(), items = rows * L.prob.batch;
   if (items > 4096) return 3;
   auto makespan = [&](size_t slots) {
+    if (dense) return (double)((items + (int64_t)slots - 1) / (int64_t)slots * L.n);  // all walks are equal
     std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> free_at;
     int64_t end = 0;
     for (int64_t i = 0; i < items; ++i) {  // in launch order: batch entry after batch entry
       const int64_t r = L.order[i % rows];
-      int64_t t = dense ? L.n : L.row_ptr[r + 1] - L.row_ptr[r];
+      int64_t t = L.row_ptr[r + 1] - L.row_ptr[r];
       if (free_at.size() >= slots) {
         t += free_at.top();
         free_at.pop();
