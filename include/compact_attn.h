@@ -187,6 +187,20 @@ int compact_attn_layout_pairs(const ca_layout* layout, const int32_t** pairs, in
 int compact_attn_layout_packing(const ca_layout* layout, const int32_t** desc, const int32_t** launch_rows,
                                 int64_t* num_launch_rows);
 
+/* Name of the kernel that serves the layout's attention calls: the sparse walk (dense = 0; forward,
+ * forward_natural and forward_static alike) or the dense one (dense = 1).  *name receives a string
+ * with static storage, one of
+ *   "f32"
+ *   "one-tile"        a query tile per workgroup, two waves per SIMD
+ *   "one-tile-3"      the same with three waves per SIMD (64-token tiles of head dim 64)
+ *   "packed-faces"    the same with partly filled query tiles packed (compact_attn_layout_packing)
+ *   "paired"          two query tiles per workgroup (compact_attn_layout_pairs)
+ *   "ways-4x4", "ways-8x4", "ways-8x2"   keys in stages of tokens, split over waves: waves of a
+ *                     workgroup x 32-query waves side by side
+ * The choice follows a cost model and is no part of the interface; this is for tests and profiles.
+ * Errors: CA_ERR_INVALID_ARG, CA_ERR_UNSUPPORTED (no kernel takes this layout). */
+int compact_attn_layout_kernel(const ca_layout* layout, int32_t dense, const char** name);
+
 /* Copy the layout's device-side tables (CSR, order, padding masks) to the current HIP device.
  * Synchronous; idempotent.  The compute calls below do it on first use if it was not called
  * (not possible while their stream is being captured).

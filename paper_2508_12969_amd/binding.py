@@ -32,6 +32,7 @@ EXPORTED = (
     "compact_attn_layout_order",
     "compact_attn_layout_pairs",
     "compact_attn_layout_packing",
+    "compact_attn_layout_kernel",
     "compact_attn_layout_upload",
     "compact_attn_free_layout",
     "compact_attn_permute",
@@ -105,6 +106,7 @@ def load_library():
                                               ctypes.POINTER(ctypes.POINTER(ctypes.c_int32))]
     lib.compact_attn_layout_packing.argtypes = [vp, ctypes.POINTER(ctypes.POINTER(ctypes.c_int32)),
                                                 ctypes.POINTER(ctypes.POINTER(ctypes.c_int32)), i64p]
+    lib.compact_attn_layout_kernel.argtypes = [vp, i32, ctypes.POINTER(ctypes.c_char_p)]
     lib.compact_attn_layout_upload.argtypes = [vp]
     lib.compact_attn_free_layout.argtypes = [vp]
     lib.compact_attn_free_layout.restype = None
@@ -267,6 +269,13 @@ def compact_attn_layout_packing(layout):
     desc = np.ctypeslib.as_array(d, shape=(num_pairs,)).copy().view(np.uint32) if num_pairs else np.zeros(0, dtype=np.uint32)
     rows = np.ctypeslib.as_array(r, shape=(count.value,)).copy() if count.value else np.zeros(0, dtype=np.int32)
     return desc, rows
+
+
+def compact_attn_layout_kernel(layout, dense=False):
+    """Name of the kernel that serves the layout's sparse (or dense) attention calls."""
+    name = ctypes.c_char_p()
+    _check(load_library().compact_attn_layout_kernel(layout.handle, int(bool(dense)), ctypes.byref(name)))
+    return name.value.decode()
 
 
 def compact_attn_layout_upload(layout):

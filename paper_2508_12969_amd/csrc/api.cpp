@@ -537,6 +537,21 @@ int compact_attn_layout_packing(const ca_layout* L, const int32_t** desc, const 
   return CA_OK;
 }
 
+int compact_attn_layout_kernel(const ca_layout* L, int32_t dense, const char** name) {
+  ca::clear_error();
+  if (!L || !name) return fail(CA_ERR_INVALID_ARG, "null argument");
+  if (dense != 0 && dense != 1) return fail(CA_ERR_INVALID_ARG, "dense must be 0 or 1");
+  const int st = check_attn_support(L);
+  if (st != CA_OK) return st;
+  const ca::Ways ways = dense ? L->ways_dense : L->ways;  // the order of the tests is that of launch_attention
+  if (ways != ca::kWaysNone) *name = ways == ca::kWays4x4 ? "ways-4x4" : ways == ca::kWays8x4 ? "ways-8x4" : "ways-8x2";
+  else if (L->prob.dtype != CA_BF16) *name = "f32";
+  else if (L->B == 64 && L->prob.head_dim == 128) *name = "paired";
+  else if (L->packed_faces) *name = "packed-faces";
+  else *name = (dense ? L->simd_waves_dense : L->simd_waves) == 3 ? "one-tile-3" : "one-tile";
+  return CA_OK;
+}
+
 int compact_attn_layout_upload(ca_layout* L) {
   ca::clear_error();
   if (!L) return fail(CA_ERR_INVALID_ARG, "null layout");

@@ -500,3 +500,17 @@ def test_pair_table_of_config3_heads_and_absent_elsewhere():
         lay = build_layout(ca, get_workload(name))
         assert ca.compact_attn_layout_pairs(lay)[0].shape == (0, 2)
         lay.free()
+
+
+def test_layout_kernel_names():
+    """The kernel of a layout's attention calls is reported, and a layout that no kernel takes is refused."""
+    heads = [[(9, (9, 9), (-1, -1))]] * 24
+    name = lambda D, dtype, tile, grid, **kw: ca.compact_attn_layout_kernel(
+        ca.compact_attn_build_layout(*grid, tile, 0, 1, len(heads), D, dtype, heads), **kw)
+    assert name(64, "f32", (1, 8, 8), (4, 16, 16)) == name(64, "f32", (1, 8, 8), (4, 16, 16), dense=True) == "f32"
+    assert name(128, "bf16", (1, 8, 8), (8, 32, 32)) == "paired"
+    assert name(128, "bf16", (2, 8, 8), (15, 40, 40), dense=True) == "packed-faces"
+    with pytest.raises(ca.CompactAttnError):
+        name(96, "bf16", (1, 8, 8), (2, 8, 8))
+    with pytest.raises(ca.CompactAttnError):
+        name(128, "bf16", (1, 4, 4), (2, 8, 8))
