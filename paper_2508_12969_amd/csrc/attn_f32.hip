@@ -22,8 +22,9 @@
 //
 // Keys are staged by LDS DMA, two buffers, one barrier per stage.  Only tokens are staged: the slots of
 // a padded tile are taken token-holding slots first (class_perm), in blocks of 16, and a stage is filled
-// from as many consecutive kept tiles as it takes.  A block's rows past its last token repeat that token
-// and are masked by count, so a padding slot is never read.
+// from as many consecutive kept tiles as it takes.  A block's rows past its last token are masked by count:
+// K repeats that token there, and V is zero, because a weight of zero does not cancel an infinity.  A
+// padding slot is never read.
 #include <algorithm>
 
 #include "attn_bf16_common.h"
@@ -170,11 +171,19 @@ void attn_f32_kernel(AttnArgs a, int parts, int64_t workgroups) {
       asm volatile(
           "s_mov_b32 m0, %[mk]\n\ts_nop 0\n\t"
           "global_load_lds_dwordx4 %[ko], %[kb]\n\t"
-          "s_mov_b32 m0, %[mv]\n\ts_nop 0\n\t"
-          "global_load_lds_dwordx4 %[vo], %[vb]\n\t"
           :
-          : [mk] "s"(k_lds), [mv] "s"(k_lds + (uint32_t)S::kStageBytes), [ko] "v"(k_off), [vo] "v"(v_off), [kb] "s"(kb), [vb] "s"(vb)
+          : [mk] "s"(k_lds), [ko] "v"(k_off), [kb] "s"(kb)
           : "memory");
+      if ((r & 15) < keys) {
+        asm volatile(
+            "s_mov_b32 m0, %[mv]\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %[vo], %[vb]\n\t"
+            :
+            : [mv] "s"(k_lds + (uint32_t)S::kStageBytes), [vo] "v"(v_off), [vb] "s"(vb)
+            : "memory");
+      } else {
+        *reinterpret_cast<f32x4*>(lds + (buf * 2 + 1) * S::kStageBytes + row0 * S::kRowBytes + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
     }
   };
 

@@ -938,6 +938,37 @@ def test_fp32_splits_of_a_tile(D, grid, tile, text_tiles, num_heads):
     _say(compare(to_f64(got[0]), want, *tolerances("f32"), what="fp32 split"))
 
 
+# ---------------------------------------------------------------- infinite values
+
+@pytest.mark.parametrize("dtype,D,grid,tile,text_tiles,num_heads,batch,kernel", [
+    ("f32", 128, (3, 13, 21), (2, 8, 8), 0, 2, 1, "f32"),
+    ("f32", 64, (3, 13, 21), (1, 6, 10), 1, 2, 1, "f32"),
+    ("f32", 32, (3, 13, 21), (1, 3, 7), 1, 2, 1, "f32"),
+])
+def test_infinite_value_in_the_last_token_of_a_tile(dtype, D, grid, tile, text_tiles, num_heads, batch, kernel):
+    """Every query keeps every key, so an infinite channel of one V token makes that channel infinite in every row
+    and leaves the others alone, also when the token is the last of a tile whose other slots are padding, or the last
+    of the walk."""
+    import dataclasses
+    _say("infinite V", dtype, D, grid, tile, num_heads, batch)
+    (T, H, W), B = grid, tile[0] * tile[1] * tile[2]
+    heads = [[(T, (H, W), ABSENT)]] * num_heads
+    wl = dataclasses.replace(make_workload("infinite", T, H, W, tile, text_tiles * B, num_heads, D, dtype, heads), batch=batch)
+    lay = build_layout(ca, wl)
+    assert ca.compact_attn_layout_kernel(lay) == kernel
+    q, k, v = make_qkv(wl, DEV)
+    v_inf = v.clone()
+    corner = T * H * W - 1
+    channels = {3: corner, 5: corner - (W - 1) % tile[2] - 1, 9: v.shape[2] - 1, 11: tile[2] - 1}  # the last video token, the last of the tile before it, ...
+    for channel, token in channels.items():
+        v_inf[:, :, token, channel] = float("inf")
+    for dense in (False, True):
+        want, _ = gpu_attention(ca, wl, lay, q, k, v, dense=dense)
+        want[..., list(channels)] = float("inf")
+        got, _ = gpu_attention(ca, wl, lay, q, k, v_inf, dense=dense)
+        assert torch.equal(got, want), (dense, torch.isnan(got).sum().item())
+
+
 # ---------------------------------------------------------------- tile mass: row groups and steps
 
 @pytest.mark.parametrize("D,grid,tile,text_tiles", [
