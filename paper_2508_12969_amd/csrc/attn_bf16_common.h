@@ -201,6 +201,14 @@ __device__ __forceinline__ float sum_with_partner(float x) {
 
 typedef __attribute__((address_space(3))) const char* LdsTile;
 
+// 16 zero bytes into LDS.  The zero is made here on purpose: the compiler would keep the four registers
+// across the loop, and the kernels that use this have none to spare.
+__device__ __forceinline__ void zero_lds16(char* lds) {
+  float zero;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+  *reinterpret_cast<float4*>(lds) = float4{zero, zero, zero, zero};
+}
+
 // Where a wave's share of a key tile comes from.  Tile order: the tile is one contiguous block.
 // Natural order (kNat): a KiB block of a tile (kRowsPerLoad consecutive slots, inside one run of tw
 // tokens) is contiguous there too, at row tile_origin[tile] + (dt*H + dy)*W + dx of the plane; a

@@ -19,8 +19,8 @@
 // Stages, not tiles.  Keys are staged by LDS DMA in granules of 16 tokens, one per wave and stage, two
 // stages in LDS, one barrier per stage.  Only tokens are staged: the slots of a padded tile are taken
 // token-holding slots first (class_perm), and a stage is filled from as many consecutive kept tiles as it
-// takes.  A granule's rows past its tile's last token repeat that token and are masked by count, so what
-// a padding slot holds is never read.  (Three or four stages in LDS, copies issued after the first
+// takes.  A granule's rows past its tile's last token are masked by count: K repeats that token there, and V is
+// zero, because a weight of zero does not cancel an infinity.  What a padding slot holds is never read.  (Three or four stages in LDS, copies issued after the first
 // product phase, and the list's words in a vector register instead of scalar loads all measured the same
 // or slower.)
 #include "attn_bf16_common.h"
@@ -159,7 +159,7 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
       word1 = meta[j + 1];
       left = padded ? (tokens_of(word) + 15) >> 4 : tile_granules;
     }
-    if (granules >= left) {  // past the end: the last granule is staged again, none of it counts
+    if (granules >= left) {  // past the end: nothing is copied
       granules = left - 1;
       j = count;
     }
@@ -177,6 +177,14 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
   auto issue = [&](int buf) {
     const int tile = __builtin_amdgcn_readfirstlane(word) & 0xffffff, cls = (word >> 24) & 7;
     const int last = tokens_of(word) - 1;
+    const int tokens = j < count ? min(16, last + 1 - first) : 0;  // of the granule
+    char* const v_lds = lds + (buf * 2 + 1) * S::kStageBytes + wave * 16 * S::kRowBytes + lane * 16;
+    if (padded && lane == 0) lds_keys[buf][wave] = (uint8_t)tokens;
+    if (tokens == 0) {  // past the end
+#pragma unroll
+      for (int i = 0; i < S::kLoads; ++i) zero_lds16(v_lds + i * 1024);
+      return;
+    }
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr + (uint32_t)(buf * 2 * S::kStageBytes));
     int64_t row0;  // of the tile's slot 0
     bool text = false;
@@ -204,10 +212,10 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
       for (int i = 0; i < S::kLoads; ++i) {  // k_lane counts my_row from the load's first row: here the slot takes its place
         const uint32_t row_off = (uint32_t)((slot[i] - my_row) * S::kRowBytes);
         copy_rows(m0 + (uint32_t)(i * 1024), kb, row_off + k_lane[i]);
-        copy_rows(m0 + (uint32_t)(S::kStageBytes + i * 1024), vb, row_off + v_lane[i]);
+        if (i * S::kRowsPerLoad + my_row < tokens) copy_rows(m0 + (uint32_t)(S::kStageBytes + i * 1024), vb, row_off + v_lane[i]);
+        else zero_lds16(v_lds + i * 1024);
       }
     }
-    if (padded && lane == 0) lds_keys[buf][wave] = (uint8_t)(j < count ? min(16, last + 1 - first) : 0);
   };
 
   bool seen = false;  // this wave has multiplied a key (wave-uniform)

@@ -182,7 +182,7 @@ void attn_f32_kernel(AttnArgs a, int parts, int64_t workgroups) {
             : [mv] "s"(k_lds + (uint32_t)S::kStageBytes), [vo] "v"(v_off), [vb] "s"(vb)
             : "memory");
       } else {
-        *reinterpret_cast<f32x4*>(lds + (buf * 2 + 1) * S::kStageBytes + row0 * S::kRowBytes + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+        zero_lds16(lds + (buf * 2 + 1) * S::kStageBytes + row0 * S::kRowBytes + lane * 16);
       }
     }
   };

@@ -1,4 +1,6 @@
 """Shared plumbing for the tests: build the same problem on both sides, move data, compare."""
+import dataclasses
+
 import numpy as np
 
 from oracle.geometry import Geometry
@@ -21,6 +23,19 @@ def build_layout(ca, wl, scale=0.0):
 def make_workload(name, T, H, W, tile, n_text, num_heads, head_dim, dtype, heads, cfg=9):
     from workloads.configs import Workload
     return Workload(name, cfg, T, H, W, tuple(tile), n_text, num_heads, head_dim, dtype, tuple(heads), None)
+
+
+def workload_for_kernel(ca, kernel, grid, tile, n_text, head_dim, dtype, heads, batch=1, dense=False):
+    """(workload, layout) with as many copies of `heads` as it takes for the layout's sparse (or dense) calls to be
+    served by the named kernel: which one that is depends on the size of the launch."""
+    for copies in (1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 96, 160):
+        wl = make_workload(kernel, *grid, tile, n_text, copies * len(heads), head_dim, dtype, list(heads) * copies)
+        wl = dataclasses.replace(wl, batch=batch)
+        layout = build_layout(ca, wl)
+        if ca.compact_attn_layout_kernel(layout, dense=dense) == kernel:
+            return wl, layout
+        layout.free()
+    raise AssertionError(f"no launch size of {grid} in tiles of {tile} takes the {kernel} kernel")
 
 
 def gpu_attention(ca, wl, layout, q, k, v, dense=False):

@@ -14,7 +14,7 @@ from oracle import permute as OP
 from workloads import get_workload, make_qkv
 
 from helpers import (build_layout, compare, geometry_of, gpu_attention, make_workload, sample_query_tiles, to_f64,
-                     tolerances)
+                     tolerances, workload_for_kernel)
 
 pytestmark = pytest.mark.gpu
 ABSENT = (-1, -1)
@@ -940,33 +940,37 @@ def test_fp32_splits_of_a_tile(D, grid, tile, text_tiles, num_heads):
 
 # ---------------------------------------------------------------- infinite values
 
-@pytest.mark.parametrize("dtype,D,grid,tile,text_tiles,num_heads,batch,kernel", [
-    ("f32", 128, (3, 13, 21), (2, 8, 8), 0, 2, 1, "f32"),
-    ("f32", 64, (3, 13, 21), (1, 6, 10), 1, 2, 1, "f32"),
-    ("f32", 32, (3, 13, 21), (1, 3, 7), 1, 2, 1, "f32"),
-])
-def test_infinite_value_in_the_last_token_of_a_tile(dtype, D, grid, tile, text_tiles, num_heads, batch, kernel):
+# kernel, head dim and tile, and video grids on which the kernel serves some launch size
+_EVERY_BF16_KERNEL = [("ways-8x2", 128, (2, 8, 8)), ("ways-8x2", 64, (2, 8, 8)), ("ways-8x2", 128, (1, 8, 8)), ("ways-8x2", 64, (1, 8, 8)),
+                      ("ways-8x4", 128, (2, 8, 8)), ("ways-4x4", 128, (2, 8, 8)), ("ways-4x4", 64, (2, 8, 8)),
+                      ("packed-faces", 128, (2, 8, 8)), ("paired", 128, (1, 8, 8)), ("one-tile", 64, (2, 8, 8)),
+                      ("one-tile", 64, (1, 8, 8)), ("one-tile-3", 64, (1, 8, 8))]
+
+
+@pytest.mark.parametrize("kernel,D,tile", [("f32", 128, (2, 8, 8)), ("f32", 64, (1, 6, 10)), ("f32", 32, (1, 3, 7)), *_EVERY_BF16_KERNEL])
+def test_infinite_value_in_the_last_token_of_a_tile(kernel, D, tile):
     """Every query keeps every key, so an infinite channel of one V token makes that channel infinite in every row
     and leaves the others alone, also when the token is the last of a tile whose other slots are padding, or the last
     of the walk."""
-    import dataclasses
-    _say("infinite V", dtype, D, grid, tile, num_heads, batch)
-    (T, H, W), B = grid, tile[0] * tile[1] * tile[2]
-    heads = [[(T, (H, W), ABSENT)]] * num_heads
-    wl = dataclasses.replace(make_workload("infinite", T, H, W, tile, text_tiles * B, num_heads, D, dtype, heads), batch=batch)
-    lay = build_layout(ca, wl)
-    assert ca.compact_attn_layout_kernel(lay) == kernel
-    q, k, v = make_qkv(wl, DEV)
-    v_inf = v.clone()
-    corner = T * H * W - 1
-    channels = {3: corner, 5: corner - (W - 1) % tile[2] - 1, 9: v.shape[2] - 1, 11: tile[2] - 1}  # the last video token, the last of the tile before it, ...
-    for channel, token in channels.items():
-        v_inf[:, :, token, channel] = float("inf")
-    for dense in (False, True):
-        want, _ = gpu_attention(ca, wl, lay, q, k, v, dense=dense)
-        want[..., list(channels)] = float("inf")
-        got, _ = gpu_attention(ca, wl, lay, q, k, v_inf, dense=dense)
-        assert torch.equal(got, want), (dense, torch.isnan(got).sum().item())
+    T, H, W = grid = (3, 13, 21)
+    dtype = "f32" if kernel == "f32" else "bf16"
+    for text_tiles in (0, 1):
+        _say("infinite V", kernel, D, tile, text_tiles)
+        wl, lay = workload_for_kernel(ca, kernel, grid, tile, text_tiles * tile[0] * tile[1] * tile[2], D, dtype, [[(T, (H, W), ABSENT)]])
+        q, k, v = make_qkv(wl, DEV)
+        corner = T * H * W - 1                             # of the last video tile
+        tokens = {3: corner, 5: corner - (W - 1) % tile[2] - 1, 9: v.shape[2] - 1, 11: tile[2] - 1}   # by channel
+        v_inf = v.clone()
+        for channel, token in tokens.items():
+            v_inf[:, :, token, channel] = float("inf")
+        for dense in (False, True):
+            want, _ = gpu_attention(ca, wl, lay, q, k, v, dense=dense)
+            want[..., list(tokens)] = float("inf")
+            got, _ = gpu_attention(ca, wl, lay, q, k, v_inf, dense=dense)
+            assert torch.equal(got, want), (dense, torch.isnan(got).sum().item())
+        if kernel.startswith("ways"):                      # the others copy whole tiles, and in natural order rows of neighbouring tiles
+            got = ca.compact_attn_forward_natural(q, k, v_inf, lay)
+            assert torch.equal(got, want)
 
 
 # ---------------------------------------------------------------- tile mass: row groups and steps
