@@ -201,6 +201,16 @@ __device__ __forceinline__ float sum_with_partner(float x) {
 
 typedef __attribute__((address_space(3))) const char* LdsTile;
 
+// One load with a row of its own for every lane group.
+__device__ __forceinline__ void copy_rows(uint32_t m0, const char* base, uint32_t lane_off) {
+  asm volatile(
+      "s_mov_b32 m0, %[m0]\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %[v], %[sb] offset:0\n\t"
+      :
+      : [m0] "s"(m0), [v] "v"(lane_off), [sb] "s"(base)
+      : "memory");
+}
+
 // 16 zero bytes into LDS.  The zero is made here on purpose: the compiler would keep the four registers
 // across the loop, and the kernels that use this have none to spare.
 __device__ __forceinline__ void zero_lds16(char* lds) {

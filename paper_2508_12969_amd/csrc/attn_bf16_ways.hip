@@ -67,16 +67,6 @@ __device__ __forceinline__ void copy_granule(uint32_t m0, const char* base, cons
   }
 }
 
-// One load with a row of its own for every lane group.
-__device__ __forceinline__ void copy_rows(uint32_t m0, const char* base, uint32_t lane_off) {
-  asm volatile(
-      "s_mov_b32 m0, %[m0]\n\ts_nop 0\n\t"
-      "global_load_lds_dwordx4 %[v], %[sb] offset:0\n\t"
-      :
-      : [m0] "s"(m0), [v] "v"(lane_off), [sb] "s"(base)
-      : "memory");
-}
-
 // Masks the keys of a 32-key block past the c0 tokens of its first granule and the c1 of its second: the
 // lane mask of each score register is built on the scalar unit (lanes 0-31 hold key 8*(r/4) + r%4 of the
 // block, lanes 32-63 that key + 4).

@@ -26,6 +26,7 @@
 // K repeats that token there, and V is zero, because a weight of zero does not cancel an infinity.  A
 // padding slot is never read.
 #include <algorithm>
+#include <type_traits>
 
 #include "attn_bf16_common.h"
 
@@ -58,6 +59,21 @@ struct F32Shape {
 template <int D>
 __device__ __forceinline__ int f32_k_swizzle(int row) {
   return D >= 64 ? (row & 15) : ((row >> 1) & 7);
+}
+
+// One load with an address of its own for every lane; lanes without a token take zeros instead.  Measured against
+// V repeating the last token (and an infinity there giving NaN): 7K tokens, head dim 128, 1.175 / 1.180 ms; grids whose
+// tiles are padded on many sides 0-5 % slower.  Lanes without a token that leave the copy out and write zeros
+// to LDS: 1.227 ms and 3-8 %.
+static __device__ const __attribute__((aligned(16))) uint32_t kZeros[4] = {0, 0, 0, 0};
+__device__ __forceinline__ void copy_rows_or_zeros(uint32_t m0, const char* base, uint32_t lane_off, bool token) {
+  const char* src = token ? base + lane_off : reinterpret_cast<const char*>(kZeros);
+  asm volatile(
+      "s_mov_b32 m0, %[m0]\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %[v], off\n\t"
+      :
+      : [m0] "s"(m0), [v] "v"(src)
+      : "memory");
 }
 
 // The 16-key blocks of one stage (wave-uniform): tile, first position in the tile's token order, tokens.
@@ -158,33 +174,34 @@ void attn_f32_kernel(AttnArgs a, int parts, int64_t workgroups) {
     if (keys == 0) return;
     const char* kb = Kp + tile * tile_bytes;
     const char* vb = Vp + tile * tile_bytes;
+    auto copy = [&](auto full) {  // full: sixteen tokens, which the rows of most blocks are
 #pragma unroll
-    for (int i = 0; i < S::kLoads; ++i) {
-      const int row0 = wave * S::kWaveRows + i * S::kRowsPerLoad;  // of the stage
-      const int r = row0 + lane / S::kChunks;
-      int slot = min(pos0 + (r & 15), valid - 1);
-      if (cls != 0) slot = lds_perm[cls * 128 + slot];
-      const int phys = lane % S::kChunks;
-      const uint32_t k_off = (uint32_t)(slot * S::kRowBytes + (phys ^ f32_k_swizzle<D>(r)) * 16);
-      const uint32_t v_off = (uint32_t)(slot * S::kRowBytes + phys * 16);
-      const uint32_t k_lds = lds_addr + (uint32_t)(buf * 2 * S::kStageBytes + row0 * S::kRowBytes);
-      asm volatile(
-          "s_mov_b32 m0, %[mk]\n\ts_nop 0\n\t"
-          "global_load_lds_dwordx4 %[ko], %[kb]\n\t"
-          :
-          : [mk] "s"(k_lds), [ko] "v"(k_off), [kb] "s"(kb)
-          : "memory");
-      if ((r & 15) < keys) {
-        asm volatile(
-            "s_mov_b32 m0, %[mv]\n\ts_nop 0\n\t"
-            "global_load_lds_dwordx4 %[vo], %[vb]\n\t"
-            :
-            : [mv] "s"(k_lds + (uint32_t)S::kStageBytes), [vo] "v"(v_off), [vb] "s"(vb)
-            : "memory");
-      } else {
-        zero_lds16(lds + (buf * 2 + 1) * S::kStageBytes + row0 * S::kRowBytes + lane * 16);
+      for (int i = 0; i < S::kLoads; ++i) {
+        const int row0 = wave * S::kWaveRows + i * S::kRowsPerLoad;  // of the stage
+        const int r = row0 + lane / S::kChunks;
+        int slot = full() ? pos0 + (r & 15) : min(pos0 + (r & 15), valid - 1);
+        if (cls != 0) slot = lds_perm[cls * 128 + slot];
+        const int phys = lane % S::kChunks;
+        const uint32_t k_off = (uint32_t)(slot * S::kRowBytes + (phys ^ f32_k_swizzle<D>(r)) * 16);
+        const uint32_t v_off = (uint32_t)(slot * S::kRowBytes + phys * 16);
+        const uint32_t k_lds = lds_addr + (uint32_t)(buf * 2 * S::kStageBytes + row0 * S::kRowBytes);
+        if constexpr (full()) {
+          asm volatile(
+              "s_mov_b32 m0, %[mk]\n\ts_nop 0\n\t"
+              "global_load_lds_dwordx4 %[ko], %[kb]\n\t"
+              "s_mov_b32 m0, %[mv]\n\ts_nop 0\n\t"
+              "global_load_lds_dwordx4 %[vo], %[vb]\n\t"
+              :
+              : [mk] "s"(k_lds), [mv] "s"(k_lds + (uint32_t)S::kStageBytes), [ko] "v"(k_off), [vo] "v"(v_off), [kb] "s"(kb), [vb] "s"(vb)
+              : "memory");
+        } else {
+          copy_rows(k_lds, kb, k_off);
+          copy_rows_or_zeros(k_lds + (uint32_t)S::kStageBytes, vb, v_off, (r & 15) < keys);
+        }
       }
-    }
+    };
+    if (keys == 16) copy(std::true_type{});
+    else copy(std::false_type{});
   };
 
   StageBlocks<S::kBlocks> cur, nxt;
