@@ -205,7 +205,8 @@ void tile_mass_kernel(MassArgs a) {
             float delta = move ? mx : 0.f;
             if (delta == kMinusInf) delta = 0.f;  // a row that has seen no real key yet keeps its reference
             w.m_run += delta;
-            l_row *= __builtin_amdgcn_exp2f(-delta * w.c2);
+            // nothing is summed yet on the first tile, and far below zero the factor overflows
+            if (j + t > 0) l_row *= __builtin_amdgcn_exp2f(-delta * w.c2);
 #pragma unroll
             for (int kb = 0; kb < S::kKeyBlocks; ++kb)
 #pragma unroll

@@ -516,6 +516,26 @@ def test_tile_mass_with_a_moving_exponent_reference(shape):
             assert err.max() <= MASS_ABS
 
 
+@pytest.mark.parametrize("D,tile", [(128, (2, 8, 8)), (64, (2, 8, 8)), (128, (1, 8, 8)), (64, (1, 8, 8))])
+def test_tile_mass_of_scores_far_below_zero(D, tile):
+    """A constant added to all scores of a query changes no mass: with every score near -150 (scaled) the masses are
+    those of the definition, as they are near zero.  The products carry the rounding of sums of that size, 2^11 in raw
+    units: D / 16 roundings to 2^-13 at most, below 1e-3 in raw units, 1e-4 relative in a probability."""
+    from oracle import search as OS
+    _say("far below zero", D, tile)
+    B = tile[0] * tile[1] * tile[2]
+    wl = make_workload("mass-low", 3, 13, 20, tile, B, 2, D, "bf16", [[]] * 2)
+    g = geometry_of(wl)
+    lay = build_layout(ca, wl)
+    q, k, _ = make_qkv(wl, DEV)
+    q[..., 0] = 32.0
+    k[..., 0] = -150.0 * D ** 0.5 / 32.0
+    mass = ca.compact_attn_tile_mass(ca.compact_attn_permute(q, lay), ca.compact_attn_permute(k, lay), lay)
+    for h in range(2):
+        want = OS.tile_mass(g, to_f64(q[0, h]), to_f64(k[0, h]))
+        assert np.abs(mass[0, h].double().cpu().numpy() - want).max() <= MASS_ABS + 1e-4 * want.max()
+
+
 def test_tile_mass_with_more_rows_than_workgroups():
     """More (batch, head, query tile) rows than the launch has workgroups (the device holds 1024 of
     this shape at a time), so workgroups take a second row by ticket and reuse their block of the
