@@ -126,12 +126,14 @@ inline void for_each_run(const ca_layout& L, const HeadPlan& plan, int32_t qt, i
 }
 
 void build_slot_masks(ca_layout& L) {
-  // A tile's padding pattern depends only on whether it is the last tile along each axis.
+  // A tile's padding pattern depends only on whether it is the last tile along each axis.  A mask holds the
+  // first 128 slots; no kernel that reads masks takes larger tiles.
   const ca_problem& p = L.prob;
   const int32_t rem_t = p.T - (L.nT - 1) * p.tt, rem_h = p.H - (L.nH - 1) * p.th, rem_w = p.W - (L.nW - 1) * p.tw;
   L.class_mask.clear();
   SlotMask full{};
-  for (int64_t s = 0; s < L.B; ++s) full.w[s >> 5] |= 1u << (s & 31);
+  constexpr int64_t kMaskSlots = 8 * (int64_t)sizeof(SlotMask);
+  for (int64_t s = 0; s < std::min(L.B, kMaskSlots); ++s) full.w[s >> 5] |= 1u << (s & 31);
   L.class_mask.push_back(full);
   int class_of_edge[8];
   for (int e = 0; e < 8; ++e) {
@@ -142,7 +144,7 @@ void build_slot_masks(ca_layout& L) {
       for (int32_t dy = 0; dy < lim_h; ++dy)
         for (int32_t dx = 0; dx < lim_w; ++dx) {
           const int32_t s = (dt * p.th + dy) * p.tw + dx;
-          m.w[s >> 5] |= 1u << (s & 31);
+          if (s < kMaskSlots) m.w[s >> 5] |= 1u << (s & 31);
         }
     class_of_edge[e] = (int)L.class_mask.size();
     L.class_mask.push_back(m);
@@ -710,7 +712,7 @@ int pack_device_tables(const ca_layout& layout, bool forward_only, PackedTables&
   }
   try {
     std::vector<uint32_t> class_word(L->class_mask.size());
-    const int words = (int)((L->B + 31) / 32);
+    const int words = L->B <= 128 ? (int)((L->B + 31) / 32) : 0;  // a mask holds no more
     for (size_t c = 0; c < class_word.size(); ++c) {
       bool upper_empty = words >= 2;
       for (int w = words / 2; w < words; ++w) upper_empty = upper_empty && L->class_mask[c].w[w] == 0;

@@ -373,6 +373,8 @@ int main() {
       {9, 33, 35, 2, 8, 8, 256, 1, 6, 128, CA_BF16, 0.f},
       {8, 64, 64, 1, 8, 8, 0, 1, 8, 64, CA_BF16, 0.f},       // 4096 rows: the tail of the launch is drawn dynamically
       {6, 64, 64, 1, 8, 8, 64, 1, 24, 128, CA_BF16, 0.f},    // the same for query-tile pairs
+      {3, 11, 33, 2, 10, 16, 320, 1, 3, 64, CA_BF16, 0.f},   // 320-token tiles: laid out and permuted, no attention kernel
+      {1, 1000, 1030, 1, 1024, 1024, 0, 1, 1, 64, CA_F32, 0.f},  // the largest tile there is
   };
   for (const ca_problem& p : cases)
     for (int rep = 0; rep < 3; ++rep) run_case(rng, p);
