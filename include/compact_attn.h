@@ -278,11 +278,12 @@ int compact_attn_dense(const void* q, const void* k, const void* v, ca_layout* l
  * the FLOPs of one dense pass.
  *   Workspace: the kernel keeps two floats per (query token, key tile) of the rows in flight.  The
  *   first call for a layout allocates min(batch * heads * ceil(n * B / 128), W) * n * 1024 bytes of
- *   device memory, W = the workgroups the device holds at a time (three per compute unit; two for
- *   128-token tiles of head dim 128: 0.54 GB for 130K tokens on 256 compute units; fewer workgroups
- *   run where the device has no room for that), synchronously (refused with CA_ERR_INVALID_ARG on a
- *   stream under capture: call once before capturing), which the layout owns until
- *   compact_attn_free_layout.  Calls on the same
+ *   device memory, W = the workgroups the device holds at a time: two per compute unit for 128-token
+ *   tiles of head dim 128 (0.54 GB for 130K tokens on 256 compute units), else three (0.99 GB for 75.6K
+ *   tokens in 64-token tiles), or two where the device has no room for three (the calls of that layout
+ *   then run with two workgroups per compute unit).  It does so synchronously (refused with
+ *   CA_ERR_INVALID_ARG on a stream under capture: call once before capturing), and the layout owns the
+ *   workspace until compact_attn_free_layout.  Calls on the same
  *   layout that overlap in time (different streams) would share that workspace and race: give
  *   concurrent calls a layout each.  CA_ERR_ALLOC if the allocation fails.
  * Supported: bf16 with (B, D) in {64,128} x {64,128}; otherwise CA_ERR_UNSUPPORTED. */

@@ -170,16 +170,18 @@ int ensure_mass_workspace(ca_layout* L, hipStream_t stream) {
   if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
   if (cus < 1) cus = 1;
   const int64_t rows_total = (int64_t)L->prob.batch * L->prob.num_heads * ca::mass_row_groups(L->n, L->B);
-  const int64_t resident = (int64_t)cus * ca::mass_workgroups_per_cu(L->B, L->prob.head_dim);
-  int64_t rows = std::max<int64_t>(1, std::min(rows_total, resident));
+  int64_t rows = 0;
   size_t bytes = 0;
   void* p = nullptr;
-  for (;; rows = (rows + 1) / 2) {  // any number of workgroups will do: on a card that is nearly full, fewer
-    bytes = (size_t)rows * (size_t)L->n * 128 * 2 * sizeof(float);
+  // If memory is short, blocks for two workgroups per CU: any number will do, but the layout keeps what it
+  // gets here, and fewer would slow down every later call.
+  for (int per_cu = ca::mass_workgroups_per_cu(L->B, L->prob.head_dim);; --per_cu) {
+    rows = std::max<int64_t>(1, std::min(rows_total, (int64_t)cus * per_cu));
+    bytes = (size_t)rows * (size_t)L->n * ca::kMassQueries * 2 * sizeof(float);
     e = hipMalloc(&p, bytes + 256);  // the ticket counter follows the workspace
     if (e == hipSuccess) break;
     (void)hipGetLastError();
-    if (rows > 1) continue;
+    if (e == hipErrorOutOfMemory && per_cu > 2) continue;
     set_error("hipMalloc of the tile-mass workspace (%zu bytes): %s", bytes, hipGetErrorString(e));
     return CA_ERR_ALLOC;
   }

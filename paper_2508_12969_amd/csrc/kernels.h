@@ -71,8 +71,9 @@ hipError_t launch_attn_bf16_ways(const AttnArgs& a, hipStream_t stream);
 // packed tiles of the grid's padded faces)
 hipError_t launch_attn_bf16_pair(const AttnArgs& a, hipStream_t stream);
 
-// The tile-mass kernel works on 128 queries at a time: one query tile of 128 tokens, or two neighbours of 64.
-inline int64_t mass_row_groups(int64_t n, int64_t B) { return (n * B + 127) / 128; }
+// The tile-mass kernel works on kMassQueries queries at a time: one query tile of 128 tokens, or two neighbours of 64.
+constexpr int kMassQueries = 128;
+inline int64_t mass_row_groups(int64_t n, int64_t B) { return (n * B + kMassQueries - 1) / kMassQueries; }
 // Workgroups of four waves that a CU holds: the kernel is bound by the vector ALU (an exponential per
 // score), and a third wave per SIMD fills what two leave; 128-token tiles of head dim 128 take too much LDS.
 constexpr int mass_workgroups_per_cu(int64_t B, int D) { return B == 128 && D == 128 ? 2 : 3; }
@@ -81,7 +82,7 @@ struct MassArgs {
   const void* q;               // [batch, heads, N_pad, D] tile order, bf16
   const void* k;
   float* mass;                 // [batch, heads, n, n]
-  float* partial;              // device workspace, partial_rows * n * 128 * 2 floats: per query and key tile (sum, reference) of the row group a workgroup is working on
+  float* partial;              // device workspace, partial_rows * n * kMassQueries * 2 floats: per query and key tile (sum, reference) of the row group a workgroup is working on
   int64_t partial_rows;        // blocks of the workspace = most workgroups a launch may have
   int32_t* counter;            // device; the ticket counter, zero before and after every launch
   const int32_t* dense_meta;   // device [n + 2]; per key tile: tile id | padding class << 24 | bit 31: upper key blocks empty

@@ -40,7 +40,7 @@ constexpr float kSumLimit = 0x1p40f;  // a tile's row sum beyond this moves the 
 // 256-key steps at head dim 64 with two workgroups: 685 us and 11.1 ms; four workgroups: 625 us, 10.2 ms.
 template <int B, int D>
 struct MassShape {
-  static constexpr int kQueries = 128, kRowTiles = kQueries / B;
+  static constexpr int kQueries = kMassQueries, kRowTiles = kQueries / B;
   static constexpr int kStepKeys = B == 64 && D == 128 ? 64 : 128, kStepTiles = kStepKeys / B;
   struct Tile : Shape<B, D, 4> {        // what a wave multiplies at a time
     // without it the reads of a whole tile are requested at once (212 instead of 186 registers), and the

@@ -1,12 +1,13 @@
 // Host-side exercise of the C ABI for a build with AddressSanitizer and UndefinedBehaviorSanitizer
 // (host code only; no kernel is launched and no GPU is needed).  It walks the pointer-heavy host
 // paths: the layout builder, CSR import with malformed input, union, similarity, query-tile pairs,
-// the window search, and the packing of the device tables including the two padding words the
+// the window search, the size of the tile-mass workspace, and the packing of the device tables including the two padding words the
 // kernels are allowed to read past the end of every list.  Any sanitizer report aborts the run;
 // a wrong result prints a message and exits with status 1.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <random>
 #include <vector>
 
@@ -20,8 +21,49 @@ hipError_t launch_permute(const PermuteArgs&, hipStream_t) { return hipErrorInva
 hipError_t launch_attn_f32(const AttnArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_attn_bf16(const AttnArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_attn_bf16_pair(const AttnArgs&, hipStream_t) { return hipErrorInvalidValue; }
-hipError_t launch_tile_mass(const MassArgs&, hipStream_t) { return hipErrorInvalidValue; }
+int64_t g_mass_rows = 0;  // workgroups that the last tile-mass launch was given
+hipError_t launch_tile_mass(const MassArgs& a, hipStream_t) {
+  g_mass_rows = a.partial_rows;
+  return hipSuccess;
+}
 }  // namespace ca
+
+// The few runtime calls of the layout upload and the tile-mass workspace, on host memory: a device of 256
+// compute units that refuses single allocations of g_alloc_limit bytes or more with g_alloc_error.
+static size_t g_alloc_limit = SIZE_MAX;
+static int g_refused = 0;
+static hipError_t g_alloc_error = hipErrorOutOfMemory;
+extern "C" {
+hipError_t hipGetDevice(int* device) {
+  *device = 0;
+  return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t, int) {
+  *value = 256;
+  return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t bytes) {
+  if (bytes >= g_alloc_limit) {
+    ++g_refused;
+    return g_alloc_error;
+  }
+  *p = std::malloc(bytes);
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void* dst, const void* src, size_t bytes, hipMemcpyKind) {
+  std::memcpy(dst, src, bytes);
+  return hipSuccess;
+}
+hipError_t hipMemset(void* dst, int value, size_t bytes) {
+  std::memset(dst, value, bytes);
+  return hipSuccess;
+}
+}
 
 namespace {
 
@@ -358,6 +400,49 @@ void run_case(std::mt19937& rng, ca_problem p) {
   compact_attn_free_layout(L);
 }
 
+// The tile-mass workspace: blocks for every workgroup the device holds, for two per compute unit if memory is
+// short, and a refusal below that, after which the layout is as it was.
+void check_mass_workspace() {
+  const struct {
+    int tt, D;
+    int64_t per_cu;
+  } shapes[] = {{1, 64, 3}, {1, 128, 3}, {2, 64, 3}, {2, 128, 2}};
+  for (const auto& sh : shapes) {
+    const ca_problem p{8 * sh.tt, 64, 64, sh.tt, 8, 8, 0, 2, 4, sh.D, CA_BF16, 0.f};  // 512 tiles, 4096 rows
+    const ca_head all{0, 0, nullptr};
+    const std::vector<ca_head> heads(p.num_heads, all);
+    const size_t block = 512 * 128 * 2 * sizeof(float);
+    const void *q = (const void*)(1ull << 40), *k = (const void*)(2ull << 40);
+    float* mass = (float*)(3ull << 40);
+    auto call = [&](ca_layout* L, size_t limit, hipError_t error) {
+      g_alloc_limit = limit;
+      g_alloc_error = error;
+      g_refused = 0;
+      ca::g_mass_rows = 0;
+      const int st = compact_attn_tile_mass(q, k, L, mass, nullptr);
+      g_alloc_limit = SIZE_MAX;
+      return st;
+    };
+    for (int shortage = 0; shortage < 4; ++shortage) {
+      ca_layout* L = nullptr;
+      CHECK(compact_attn_build_layout(&p, heads.data(), &L) == CA_OK);
+      if (!L) return;
+      CHECK(compact_attn_layout_upload(L) == CA_OK);
+      if (shortage == 0) {
+        CHECK(call(L, SIZE_MAX, hipErrorOutOfMemory) == CA_OK && ca::g_mass_rows == 256 * sh.per_cu && g_refused == 0);
+      } else if (shortage == 1 && sh.per_cu > 2) {
+        CHECK(call(L, 256 * 2 * block + 512, hipErrorOutOfMemory) == CA_OK && ca::g_mass_rows == 512 && g_refused == 1);
+      } else if (shortage == 2) {  // less than that is refused, and a later call finds the memory there is then
+        CHECK(call(L, 256 * 2 * block, hipErrorOutOfMemory) == CA_ERR_ALLOC && ca::g_mass_rows == 0);
+        CHECK(call(L, SIZE_MAX, hipErrorOutOfMemory) == CA_OK && ca::g_mass_rows == 256 * sh.per_cu);
+      } else if (shortage == 3) {  // another error is no shortage
+        CHECK(call(L, 256 * 2 * block, hipErrorInvalidValue) == CA_ERR_ALLOC && g_refused == 1);
+      }
+      compact_attn_free_layout(L);
+    }
+  }
+}
+
 }  // namespace
 
 int main() {
@@ -379,6 +464,7 @@ int main() {
   for (const ca_problem& p : cases)
     for (int rep = 0; rep < 3; ++rep) run_case(rng, p);
   check_split_function();
+  check_mass_workspace();
 
   // malformed problems and heads
   ca_layout* L = nullptr;
