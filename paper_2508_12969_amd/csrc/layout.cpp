@@ -7,6 +7,7 @@
 // walks frames and tile rows in ascending order and emits those intervals, which yields the
 // ascending tile ids directly.  No HIP call is made here.
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstdarg>
 #include <cstdio>
@@ -428,13 +429,50 @@ struct WayCost {
   LaunchCost cost;
 };
 
+}  // namespace
+
+// 16-token granules of an average kept tile (first) and the part of them that lies in padded tiles (second).  Rows
+// are sampled where they keep more than `max_words` tiles: every `stride`-th, and a stride without a common factor
+// with the tiles of a head or of an axis, so that all columns and faces of the grid have their turn.
+std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int64_t max_words) {
+  const int64_t rows = (int64_t)L.prob.num_heads * L.n;
+  std::vector<int> granules(L.class_mask.size());
+  for (size_t c = 0; c < granules.size(); ++c) {
+    int tokens = 0;
+    for (uint32_t w : L.class_mask[c].w) tokens += __builtin_popcount(w);
+    granules[c] = (tokens + 15) / 16;
+  }
+  int64_t tiles = 0, all = 0, padded = 0;
+  auto add = [&](int64_t tile) {
+    const int32_t c = L.tile_class[tile];
+    ++tiles;
+    all += granules[c];
+    if (c != 0) padded += granules[c];
+  };
+  if (dense) {
+    for (int64_t t = 0; t < L.n; ++t) add(t);
+  } else if (granules.size() == 1) {
+    return {(double)granules[0], 0.0};
+  } else {
+    auto gcd = [](int64_t a, int64_t b) {
+      while (b) std::swap(a %= b, b);
+      return a;
+    };
+    int64_t stride = 1 + (int64_t)L.col_idx.size() / max_words;
+    while (stride > 1 && (gcd(stride, L.n) > 1 || gcd(stride, L.nW) > 1 || gcd(stride, L.nH) > 1)) ++stride;
+    for (int64_t r = 0; r < rows; r += stride)
+      for (int64_t i = L.row_ptr[r]; i < L.row_ptr[r + 1]; ++i) add(L.col_idx[i]);
+  }
+  return {tiles ? (double)all / (double)tiles : 0.0, all ? (double)padded / (double)all : 0.0};
+}
+
 // Which kernel serves the sparse (or the dense) walk: the one with the shortest predicted time, the
 // one-tile and paired kernels unless another is at least 10 % better.  The constants are a least-squares
 // fit of log time over 240 launches of under 3 TFLOP (1-40 heads, grids of 1-64 x 8-60 x 8-104, masks from 5 % to
 // dense, all entry points), per tile size and head dim; residual 9-14 %.  The choice made these launches
 // 1.11 and 1.30 (head dim 64, tiles of 64 and 128 tokens), 1.14 and 1.21 times faster (head dim 128; geometric
 // means), five of them 4-15 % slower; the best choice in hindsight gives 1.11, 1.32, 1.15 and 1.24.
-Ways choose_ways(const ca_layout& L, bool dense) {
+Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words) {
   const ca_problem& p = L.prob;
   if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
   // 32-bit lane offsets inside a tile of the natural order; a grid dimension of fewer than 2^32 threads
@@ -463,39 +501,25 @@ Ways choose_ways(const ca_layout& L, bool dense) {
     plain_longest = std::max(plain_longest, walk);
   }
 
-  // walks in 16-token granules; a large layout is sampled
-  std::vector<int> tokens(L.class_mask.size()), granules(L.class_mask.size());
-  for (size_t c = 0; c < tokens.size(); ++c) {
+  std::vector<int> tokens(L.class_mask.size());
+  for (size_t c = 0; c < tokens.size(); ++c)
     for (uint32_t w : L.class_mask[c].w) tokens[c] += __builtin_popcount(w);
-    granules[c] = (tokens[c] + 15) / 16;
-  }
-  const int64_t rows = (int64_t)p.num_heads * L.n;
-  const int64_t stride = dense ? 1 : 1 + (int64_t)L.col_idx.size() / 500000;
-  int64_t all = 0;  // granules of a row that keeps every tile
-  std::vector<uint8_t> tile_granules(L.n);
-  for (int64_t t = 0; t < L.n; ++t) all += tile_granules[t] = (uint8_t)granules[L.tile_class[t]];
+  const double per_tile = granules_per_tile(L, dense, max_words).first;
   double steps[3] = {}, longest[3] = {}, groups[3] = {};
-  const int64_t looked_at = dense ? L.n : rows;  // every head's dense walk is the same
-  for (int64_t r = 0; r < looked_at; r += stride) {
-    int64_t tiles = L.n, kept = all;
-    if (!dense) {
-      const int32_t *t = L.col_idx.data() + L.row_ptr[r], *end = L.col_idx.data() + L.row_ptr[r + 1];
-      tiles = end - t;
-      kept = 0;
-      if (tokens.size() == 1) kept = tiles * granules[0];
-      else for (; t < end; ++t) kept += tile_granules[*t];
-    }
+  const int64_t looked_at = dense ? L.n : (int64_t)p.num_heads * L.n;  // every head's dense walk is the same
+  for (int64_t r = 0; r < looked_at; ++r) {
+    const double kept = (double)(dense ? L.n : L.row_ptr[r + 1] - L.row_ptr[r]) * per_tile;
     for (int i = 0; i < count; ++i) {
       const WayCost& w = options[i];
       const int64_t parts = (tokens[L.tile_class[r % L.n]] + w.part_queries - 1) / w.part_queries;  // those with a token
-      const uint32_t stage = (uint32_t)w.stage_keys / 16;  // in granules
-      const double walk = (double)(((uint32_t)kept + stage - 1) / stage * stage) / 8;
-      steps[i] += walk * parts;
+      const double stage = w.stage_keys / 16;  // in granules
+      const double walk = std::ceil(kept / stage) * stage / 8;
+      steps[i] += walk * (double)parts;
       longest[i] = std::max(longest[i], walk);
       groups[i] += (double)parts;
     }
   }
-  const double scale = (double)stride * p.batch * (dense ? p.num_heads : 1);
+  const double scale = (double)p.batch * (dense ? p.num_heads : 1);
   double best = 0.9 * kPlain[big_d][big_b].of(plain_steps * p.batch, plain_longest, (double)plain_groups * p.batch);
   Ways ways = kWaysNone;
   for (int i = 0; i < count; ++i) {
@@ -504,6 +528,8 @@ Ways choose_ways(const ca_layout& L, bool dense) {
   }
   return ways;
 }
+
+namespace {
 
 // Waves per SIMD of the one-tile kernel for 64-token tiles of head dim 64: 2, or 3.  The third makes a full card
 // 1.07 times faster, but a workgroup then has a third of its SIMDs, so a launch that ends with its longest
@@ -559,8 +585,8 @@ void finish_host_tables(ca_layout& L) {
   build_launch_splits(L);
   L.simd_waves = choose_simd_waves(L, false);
   L.simd_waves_dense = choose_simd_waves(L, true);
-  L.ways = choose_ways(L, false);
-  L.ways_dense = choose_ways(L, true);
+  L.ways = choose_ways(L, false, kSampledWords);
+  L.ways_dense = choose_ways(L, true, kSampledWords);
 }
 
 int import_host_tables(ca_layout& L, const int64_t* const* row_ptr, const int32_t* const* col_idx) {

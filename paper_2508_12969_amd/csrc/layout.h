@@ -5,6 +5,7 @@
 #include <atomic>
 #include <cstdint>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "compact_attn.h"
@@ -142,6 +143,11 @@ struct PackedTables {
 };
 // `forward_only` leaves out what only the dense and the natural-order walks read.  Returns a ca_status.
 int pack_device_tables(const ca_layout& layout, bool forward_only, PackedTables& t);
+// Kernel of the sparse or the dense walk, and the figures of the tiles it goes by; at most about `max_words` kept
+// tiles are looked at.
+constexpr int64_t kSampledWords = 500000;
+Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words);
+std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int64_t max_words);
 // Derived tables (per-head views, launch order, padding classes) once row_ptr / col_idx are set.
 void finish_host_tables(ca_layout& L);
 

@@ -4,6 +4,7 @@
 // the window search, the size of the tile-mass workspace, and the packing of the device tables including the two padding words the
 // kernels are allowed to read past the end of every list.  Any sanitizer report aborts the run;
 // a wrong result prints a message and exits with status 1.
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -443,6 +444,46 @@ void check_mass_workspace() {
   }
 }
 
+// What the choice of kernel knows of a large layout comes from a sample of its rows; grids whose extents share factors
+// with the sample's stride must not be seen from one side only.
+void check_sampling() {
+  struct {
+    ca_problem p;
+    int64_t words;
+  } cases[] = {
+      {{44, 17, 73, 1, 8, 16, 0, 1, 10, 128, CA_BF16, 0.f}, 500000},   // nW 5, nH 3, n 660
+      {{21, 45, 76, 1, 8, 8, 64, 1, 12, 64, CA_BF16, 0.f}, 100000},    // nW 10, nH 6, n 1261
+      {{30, 20, 60, 2, 8, 8, 0, 1, 8, 64, CA_BF16, 0.f}, 20000},       // nW 8, nH 3
+  };
+  for (auto& c : cases) {
+    const int nW = (c.p.W + c.p.tw - 1) / c.p.tw, nH = (c.p.H + c.p.th - 1) / c.p.th, nT = (c.p.T + c.p.tt - 1) / c.p.tt;
+    ca_group groups[2] = {{nT / 2, {nH, 1}, {-1, -1}}, {nT, {1, nW}, {nH, 0}}};
+    std::vector<ca_head> heads;
+    for (int h = 0; h < c.p.num_heads; ++h) heads.push_back(ca_head{1 + h % 2, 0, groups});
+    ca_layout* L = nullptr;
+    CHECK(compact_attn_build_layout(&c.p, heads.data(), &L) == CA_OK);
+    if (!L) return;
+    const auto all = ca::granules_per_tile(*L, false, INT64_MAX);
+    int64_t granules = 0, padded = 0;
+    std::vector<int64_t> of_tile(L->n);
+    for (int64_t t = 0; t < L->n; ++t) {
+      int tokens = 0;
+      for (uint32_t w : L->class_mask[L->tile_class[t]].w) tokens += __builtin_popcount(w);
+      of_tile[t] = (tokens + 15) / 16;
+    }
+    for (int32_t t : L->col_idx) granules += of_tile[t], padded += L->tile_class[t] ? of_tile[t] : 0;
+    CHECK(std::fabs(all.first * (double)L->col_idx.size() - (double)granules) < 1e-6 * (double)granules);
+    CHECK(std::fabs(all.second - (double)padded / (double)granules) < 1e-9);
+    // strides the kept tiles would give by themselves, and all their neighbours
+    for (int64_t words = c.words / 4; words <= c.words; words += c.words / 16) {
+      const auto some = ca::granules_per_tile(*L, false, words);
+      CHECK(std::fabs(some.first / all.first - 1) < 0.02 && std::fabs(some.second - all.second) < 0.03);
+      CHECK(ca::choose_ways(*L, false, words) == ca::choose_ways(*L, false, INT64_MAX));
+    }
+    compact_attn_free_layout(L);
+  }
+}
+
 }  // namespace
 
 int main() {
@@ -465,6 +506,7 @@ int main() {
     for (int rep = 0; rep < 3; ++rep) run_case(rng, p);
   check_split_function();
   check_mass_workspace();
+  check_sampling();
 
   // malformed problems and heads
   ca_layout* L = nullptr;
