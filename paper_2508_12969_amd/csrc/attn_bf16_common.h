@@ -24,24 +24,6 @@ typedef __attribute__((ext_vector_type(4))) short shortx4;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kMinusInf = -__builtin_inff();
 constexpr float kLazyLog2 = 8.0f;          // the exponent reference may lag the row max by 2^8
-constexpr int kXcdChunk = 64;              // consecutive launch-order entries handed to one XCD
-
-// Launch-order entry of a workgroup id.  Workgroup ids are dealt round-robin to the 8 XCDs, each
-// with an L2 of its own; they are remapped so that the workgroups resident on one XCD at a time
-// (64: two per CU) are kXcdChunk consecutive entries of the launch order (same head, neighbouring
-// query tiles, equal list lengths) instead of every eighth entry: their key-tile lists overlap, so
-// more of the K/V tile copies hit that L2.  The order is sorted by descending list length, so in a
-// round of 8 chunks the first chunk is the longest; rounds are therefore dealt to the XCDs in
-// alternating direction, which evens out the work per XCD (measured at the 130K-token layouts:
-// 1.4 % faster at 65 % sparsity, 2.3 % at 80 %, against chunks of 32 always dealt in the same
-// direction).  Ids past the last full round keep their place.
-__device__ __forceinline__ int64_t xcd_launch_order(int64_t id, int64_t total) {
-  const int64_t span = 8 * (int64_t)kXcdChunk;
-  if (id >= total / span * span) return id;
-  const int64_t xcd = id & 7, seq = id >> 3, round = seq / kXcdChunk;
-  return round * span + ((round & 1) ? 7 - xcd : xcd) * kXcdChunk + seq % kXcdChunk;
-}
-
 // Launch-order entry of this workgroup, or -1 if it has none.  Workgroup ids below a.static_items are
 // bound to entries through xcd_launch_order.  The XCDs of a card differ in speed by a few per cent,
 // and ids are bound to XCDs, so the cheapest entries at the end of the order are left unbound: each

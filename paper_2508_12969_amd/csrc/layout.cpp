@@ -411,18 +411,55 @@ void build_launch_splits(ca_layout& L) {
 
 namespace {
 
-// Predicted time of a launch in us: its workgroups' steps spread over the CUs, or its longest walk, whichever
-// is longer.  A step is 128 keys, or one tile of the paired kernel's walk.
+// Predicted time of a launch in us.  Its workgroups are dealt to the XCDs by id and to the free places of their
+// XCD in order, which decides it for launches of a few rounds: one workgroup more than the card holds, or the
+// long rows on the XCD that has the first of them, are worth up to half of the time.  A step is 128 keys, or one
+// tile of the paired kernel's walk.
 struct LaunchCost {
+  int per_cu;    // workgroups a CU holds
   double start;  // launch, first copies, epilogue
   double step;   // per workgroup and step, as time of a whole CU that is full
-  double walk;   // per step of the longest walk, on a CU with little else to do
-  double group;  // per workgroup, as time of a whole CU
-  double of(double steps, double longest, double groups) const {
-    constexpr double kCus = 256;
-    return start + std::max((step * steps + group * groups) / kCus, walk * longest);
-  }
+  double walk;   // per step of a workgroup alone on its CU
+  double group;  // per workgroup
+  double gather; // share by which all granules taken from padded tiles lengthen everything
 };
+
+// `walks`: steps of the workgroups of one batch entry in launch order, below zero: no token, returns at once.
+double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t batch, double gathered) {
+  constexpr int64_t kXcds = 8, kXcdCus = 32;
+  constexpr int64_t kExact = 6000;  // workgroups; beyond, rounds and XCDs even out
+  const int64_t entries = (int64_t)walks.size(), total = entries * batch;
+  double sum = 0, active = 0;
+  for (float w : walks) {
+    if (w < 0) continue;
+    sum += w;
+    active += 1;
+  }
+  if (active == 0) return c.start;
+  const double share = std::min((double)c.per_cu, std::max(1.0, active * (double)batch / (kXcds * kXcdCus)));  // of them on a CU
+  const double slot = c.per_cu == 1 ? c.walk : c.walk + (std::max(c.step * c.per_cu, c.walk) - c.walk) * (share - 1) / (c.per_cu - 1);
+  const double longer = 1 + c.gather * gathered;
+  if (total > kExact) {
+    const double mean = (slot * sum + c.group * active) * (double)batch / (double)(kXcds * kXcdCus * c.per_cu);
+    return c.start + longer * (mean + 0.3 * slot * sum / active);
+  }
+  double end = 0;
+  for (int64_t xcd = 0; xcd < kXcds; ++xcd) {
+    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    for (int64_t id = xcd; id < total; id += kXcds) {
+      const float w = walks[(size_t)(xcd_launch_order(id, total) % entries)];
+      double t = w < 0 ? 0.1 * slot : slot * w + c.group;
+      if ((int64_t)free_at.size() >= kXcdCus * c.per_cu) {
+        t += free_at.top();
+        free_at.pop();
+      }
+      free_at.push(t);
+      end = std::max(end, t);
+    }
+  }
+  return c.start + longer * end;
+}
+
 struct WayCost {
   Ways ways;
   int stage_keys, part_queries;
@@ -467,23 +504,28 @@ std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int6
 }
 
 // Which kernel serves the sparse (or the dense) walk: the one with the shortest predicted time, the
-// one-tile and paired kernels unless another is at least 10 % better.  The constants are a least-squares
-// fit of log time over 240 launches of under 3 TFLOP (1-40 heads, grids of 1-64 x 8-60 x 8-104, masks from 5 % to
-// dense, all entry points), per tile size and head dim; residual 9-14 %.  The choice made these launches
-// 1.11 and 1.30 (head dim 64, tiles of 64 and 128 tokens), 1.14 and 1.21 times faster (head dim 128; geometric
-// means), five of them 4-15 % slower; the best choice in hindsight gives 1.11, 1.32, 1.15 and 1.24.
+// one-tile and paired kernels unless another is at least 13 % better.
+// The constants are a fit of log time over 480 launches of under 3 TFLOP (1-40 heads, grids of 1-64 x 8-60 x 8-104,
+// masks from 5 % to dense, all entry points), per kernel, tile size and head dim; residual 5-11 %, 14-16 % for
+// kWays8x2 on 128-token tiles.  On 160 other launches of that kind the choice is 1.19 times faster than the one-tile and
+// paired kernels (geometric mean; 1.22 is the best choice in hindsight), on 100 of 3 to 40 TFLOP 1.04 (1.04), and
+// none of these is slower; of the 480 one is, by 3 %.  A model of the sums and the longest walk alone (residual
+// 10-18 %), from a predicted 10 % on, made twelve of the 480 slower by up to 25 %, eleven of them launches of one to
+// three rounds of workgroups.
 Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words) {
   const ca_problem& p = L.prob;
   if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
   // 32-bit lane offsets inside a tile of the natural order; a grid dimension of fewer than 2^32 threads
   if ((int64_t)p.tt * p.H * p.W * p.head_dim * 2 >= (int64_t)1 << 31) return kWaysNone;
   if ((int64_t)p.batch * p.num_heads * L.n * 2 * 512 >= (int64_t)1 << 32) return kWaysNone;
-  static const LaunchCost kPlain[2][2] = {{{2.2, 0.68, 2.20, 0.5}, {4.6, 1.08, 1.62, 10.7}}, {{6.1, 0.95, 1.28, 12.9}, {5.9, 1.99, 2.29, 7.9}}};
-  static const WayCost k64x64[] = {{kWays8x2, 128, 64, {5.9, 0.95, 1.57, 4.6}}};
-  static const WayCost k64x128[] = {{kWays4x4, 64, 128, {6.3, 1.17, 2.43, 3.4}}, {kWays8x2, 128, 64, {7.6, 0.95, 1.20, 8.3}}};
-  static const WayCost k128x64[] = {{kWays8x2, 128, 64, {8.7, 2.23, 1.95, 6.4}}};
-  static const WayCost k128x128[] = {
-      {kWays4x4, 64, 128, {6.6, 2.36, 3.15, 6.2}}, {kWays8x4, 128, 128, {7.2, 2.95, 2.55, 9.3}}, {kWays8x2, 128, 64, {7.5, 2.35, 1.99, 14.7}}};
+  static const LaunchCost kPlain[2][2] = {{{4, 2.99, 0.57, 1.89, 0.65, 0}, {2, 2.35, 0.93, 1.54, 3.25, 0}},
+                                          {{2, 0.0, 0.76, 1.27, 5.74, 0}, {2, 0.0, 1.39, 2.17, 6.5, 0}}};
+  static const WayCost k64x64[] = {{kWays8x2, 128, 64, {2, 2.15, 0.84, 1.37, 4.47, 0.09}}};
+  static const WayCost k64x128[] = {{kWays4x4, 64, 128, {4, 0.0, 0.87, 2.27, 7.13, 0.03}}, {kWays8x2, 128, 64, {2, 0.0, 0.8, 1.28, 6.65, 0.1}}};
+  static const WayCost k128x64[] = {{kWays8x2, 128, 64, {1, 1.76, 1.43, 1.79, 6.68, 0.14}}};
+  static const WayCost k128x128[] = {{kWays4x4, 64, 128, {2, 0.0, 1.62, 2.81, 6.9, 0.15}},
+                                     {kWays8x4, 128, 128, {1, 0.28, 1.35, 2.0, 8.95, 0.08}},
+                                     {kWays8x2, 128, 64, {1, 0.0, 1.35, 1.79, 7.9, 0.18}}};
   const bool big_d = p.head_dim == 128, big_b = L.B == 128;
   const WayCost* options = big_d ? (big_b ? k128x128 : k128x64) : (big_b ? k64x128 : k64x64);
   const int count = big_b ? (big_d ? 3 : 2) : 1;
@@ -492,39 +534,35 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words) {
   const std::vector<int32_t>& launched = L.packed_faces ? L.launch_rows : L.order;
   const bool paired = !L.pair_rows.empty() && !L.packed_faces;
   const int64_t plain_groups = paired ? (int64_t)L.pair_rows.size() / 2 : (int64_t)launched.size();
-  double plain_steps = 0, plain_longest = 0;
+  std::vector<float> walks;
+  walks.reserve((size_t)std::max(plain_groups, (int64_t)L.order.size() * 2));
   for (int64_t i = 0; i < plain_groups; ++i) {
     const int64_t e = paired ? ~i : launched[i];
     const int64_t tiles = dense ? L.n : e < 0 ? L.pair_walk_ptr[~e + 1] - L.pair_walk_ptr[~e] : L.row_ptr[e + 1] - L.row_ptr[e];
-    const double walk = paired ? (double)tiles : (double)(tiles * L.B) / 128;
-    plain_steps += walk;
-    plain_longest = std::max(plain_longest, walk);
+    walks.push_back(paired ? (float)tiles : (float)(tiles * L.B) / 128);
   }
+  double best = 0.87 * launch_time(kPlain[big_d][big_b], walks, p.batch, 0);
+  Ways ways = kWaysNone;
 
+  // the workgroups of the others: every part of every row
   std::vector<int> tokens(L.class_mask.size());
   for (size_t c = 0; c < tokens.size(); ++c)
     for (uint32_t w : L.class_mask[c].w) tokens[c] += __builtin_popcount(w);
-  const double per_tile = granules_per_tile(L, dense, max_words).first;
-  double steps[3] = {}, longest[3] = {}, groups[3] = {};
-  const int64_t looked_at = dense ? L.n : (int64_t)p.num_heads * L.n;  // every head's dense walk is the same
-  for (int64_t r = 0; r < looked_at; ++r) {
-    const double kept = (double)(dense ? L.n : L.row_ptr[r + 1] - L.row_ptr[r]) * per_tile;
-    for (int i = 0; i < count; ++i) {
-      const WayCost& w = options[i];
-      const int64_t parts = (tokens[L.tile_class[r % L.n]] + w.part_queries - 1) / w.part_queries;  // those with a token
-      const double stage = w.stage_keys / 16;  // in granules
-      const double walk = std::ceil(kept / stage) * stage / 8;
-      steps[i] += walk * (double)parts;
-      longest[i] = std::max(longest[i], walk);
-      groups[i] += (double)parts;
-    }
-  }
-  const double scale = (double)p.batch * (dense ? p.num_heads : 1);
-  double best = 0.9 * kPlain[big_d][big_b].of(plain_steps * p.batch, plain_longest, (double)plain_groups * p.batch);
-  Ways ways = kWaysNone;
+  const auto [per_tile, padded] = granules_per_tile(L, dense, max_words);
   for (int i = 0; i < count; ++i) {
-    const double t = options[i].cost.of(steps[i] * scale, longest[i], groups[i] * scale);
-    if (t < best) best = t, ways = options[i].ways;
+    const WayCost& w = options[i];
+    const int parts = (int)L.B / w.part_queries;
+    const double stage = w.stage_keys / 16;  // in granules
+    walks.clear();
+    for (int64_t j = 0; j < (int64_t)L.order.size(); ++j) {
+      const int64_t r = dense ? j : L.order[j];
+      const int64_t tiles = dense ? L.n : L.row_ptr[r + 1] - L.row_ptr[r];
+      const float steps = (float)(std::ceil((double)tiles * per_tile / stage) * stage / 8);
+      const int held = (tokens[L.tile_class[r % L.n]] + w.part_queries - 1) / w.part_queries;  // parts with a token
+      for (int part = 0; part < parts; ++part) walks.push_back(part < held ? steps : -1.f);
+    }
+    const double t = launch_time(w.cost, walks, p.batch, padded);
+    if (t < best) best = t, ways = w.ways;
   }
   return ways;
 }

@@ -41,6 +41,24 @@ constexpr int64_t kPoolMinItems = 4096; // smaller launches are dealt statically
 // `work[i]`: cost of launch-order entry i (tile steps); returns the split of one batch entry's launch.
 LaunchSplit split_launch(const int64_t* work, int64_t entries);
 
+constexpr int kXcdChunk = 64;           // consecutive launch-order entries handed to one XCD
+
+// Launch-order entry of a workgroup id.  Workgroup ids are dealt round-robin to the 8 XCDs, each
+// with an L2 of its own; they are remapped so that the workgroups resident on one XCD at a time
+// (64: two per CU) are kXcdChunk consecutive entries of the launch order (same head, neighbouring
+// query tiles, equal list lengths) instead of every eighth entry: their key-tile lists overlap, so
+// more of the K/V tile copies hit that L2.  The order is sorted by descending list length, so in a
+// round of 8 chunks the first chunk is the longest; rounds are therefore dealt to the XCDs in
+// alternating direction, which evens out the work per XCD (measured at the 130K-token layouts:
+// 1.4 % faster at 65 % sparsity, 2.3 % at 80 %, against chunks of 32 always dealt in the same
+// direction).  Ids past the last full round keep their place.
+constexpr int64_t xcd_launch_order(int64_t id, int64_t total) {
+  const int64_t span = 8 * (int64_t)kXcdChunk;
+  if (id >= total / span * span) return id;
+  const int64_t xcd = id & 7, seq = id >> 3, round = seq / kXcdChunk;
+  return round * span + ((round & 1) ? 7 - xcd : xcd) * kXcdChunk + seq % kXcdChunk;
+}
+
 // The kernels of attn_bf16_ways.hip: waves of a workgroup x 32-query waves side by side.
 enum Ways : int32_t { kWaysNone = 0, kWays4x4, kWays8x4, kWays8x2 };
 

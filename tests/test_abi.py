@@ -514,3 +514,20 @@ def test_layout_kernel_names():
         name(96, "bf16", (1, 8, 8), (2, 8, 8))
     with pytest.raises(ca.CompactAttnError):
         name(128, "bf16", (1, 4, 4), (2, 8, 8))
+
+
+@pytest.mark.parametrize("grid,tile,text_tiles,heads,batch,D,dense,slower", [
+    # us of the one-tile or paired kernel against those of the kernel in the last column: launches of a little more than
+    # one, two or three rounds of workgroups, or whose workgroups with tokens all have even ids
+    ((52, 38, 10), (4, 4, 8), 0, [[(12, (0, 1), (9, 0))], [(12, (9, 1), (-1, -1))]], 1, 128, False, "ways-4x4"),               # 648, 864
+    ((10, 32, 22), (4, 4, 8), 1, [[(1, (7, 2), (-1, -1))]], 2, 128, True, "ways-8x2"),                                         # 161, 202
+    ((3, 39, 62), (2, 4, 8), 0, [[(0, (0, 7), (9, 0))], [(1, (3, 3), (-1, -1))]], 2, 128, False, "ways-8x2"),                  # 127, 146
+    ((2, 32, 60), (4, 4, 8), 2, [[(0, (3, 3), (-1, -1))], [(0, (1, 7), (7, 1))], [(0, (0, 7), (7, 0))], [(0, (7, 7), (-1, -1))]],
+     2, 128, False, "ways-4x4"),                                                                                               # 136, 151
+    ((48, 11, 21), (2, 8, 8), 0, [[(10, (0, 2), (1, 0)), (12, (1, 1), (-1, -1))], [(11, (0, 2), (1, 0))], [(23, (1, 2), (-1, -1))],
+                                  [(6, (1, 2), (1, 1))]], 1, 128, False, "ways-4x4"),                                          # 411, 457
+])
+def test_kernel_choice_where_it_is_slower(grid, tile, text_tiles, heads, batch, D, dense, slower):
+    """Launches that a kernel with more workgroups or shorter walks would serve more slowly do not go to it."""
+    lay = ca.compact_attn_build_layout(*grid, tile, text_tiles * tile[0] * tile[1] * tile[2], batch, len(heads), D, "bf16", heads)
+    assert ca.compact_attn_layout_kernel(lay, dense=dense) != slower
