@@ -25,17 +25,26 @@ def make_workload(name, T, H, W, tile, n_text, num_heads, head_dim, dtype, heads
     return Workload(name, cfg, T, H, W, tuple(tile), n_text, num_heads, head_dim, dtype, tuple(heads), None)
 
 
-def workload_for_kernel(ca, kernel, grid, tile, n_text, head_dim, dtype, heads, batch=1, dense=False):
-    """(workload, layout) with as many copies of `heads` as it takes for the layout's sparse (or dense) calls to be
-    served by the named kernel: which one that is depends on the size of the launch."""
-    for copies in (1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 96, 160):
-        wl = make_workload(kernel, *grid, tile, n_text, copies * len(heads), head_dim, dtype, list(heads) * copies)
-        wl = dataclasses.replace(wl, batch=batch)
-        layout = build_layout(ca, wl)
+def layout_for_kernel(ca, kernel, build, dense=False):
+    """(copies, build(copies)) with the first number of copies of a head list for which the layout's sparse (or dense)
+    calls are served by the named kernel (which one that is depends on the size of the launch), or None."""
+    for copies in (*range(1, 33), 40, 48, 64, 80, 96, 128, 160, 200, 240):
+        layout = build(copies)
         if ca.compact_attn_layout_kernel(layout, dense=dense) == kernel:
-            return wl, layout
+            return copies, layout
         layout.free()
-    raise AssertionError(f"no launch size of {grid} in tiles of {tile} takes the {kernel} kernel")
+    return None
+
+
+def workload_for_kernel(ca, kernel, grid, tile, n_text, head_dim, dtype, heads, batch=1):
+    """(workload, layout) with as many copies of `heads` as it takes to reach the named kernel."""
+    def workload(copies):
+        wl = make_workload(kernel, *grid, tile, n_text, copies * len(heads), head_dim, dtype, list(heads) * copies)
+        return dataclasses.replace(wl, batch=batch)
+
+    found = layout_for_kernel(ca, kernel, lambda copies: build_layout(ca, workload(copies)))
+    assert found, f"no launch size of {grid} in tiles of {tile} takes the {kernel} kernel"
+    return workload(found[0]), found[1]
 
 
 def gpu_attention(ca, wl, layout, q, k, v, dense=False):

@@ -13,8 +13,8 @@ from oracle import layout as OL
 from oracle import permute as OP
 from workloads import get_workload, make_qkv
 
-from helpers import (build_layout, compare, geometry_of, gpu_attention, make_workload, sample_query_tiles, to_f64,
-                     tolerances, workload_for_kernel)
+from helpers import (build_layout, compare, geometry_of, gpu_attention, layout_for_kernel, make_workload,
+                     sample_query_tiles, to_f64, tolerances, workload_for_kernel)
 
 pytestmark = pytest.mark.gpu
 ABSENT = (-1, -1)
@@ -536,25 +536,30 @@ def test_tile_mass_of_scores_far_below_zero(D, tile):
         assert np.abs(mass[0, h].double().cpu().numpy() - want).max() <= MASS_ABS + 1e-4 * want.max()
 
 
-def test_tile_mass_with_more_rows_than_workgroups():
-    """More (batch, head, query tile) rows than the launch has workgroups (the device holds 1024 of
-    this shape at a time), so workgroups take a second row by ticket and reuse their block of the
-    workspace: rows of both batch entries are compared with the definition, all rows with their
-    closed-form sums."""
+@pytest.mark.parametrize("D,tile", [(64, (1, 8, 8)), (128, (1, 8, 8)), (64, (2, 8, 8)), (128, (2, 8, 8))])
+def test_tile_mass_with_more_rows_than_workgroups(D, tile):
+    """More groups of 128 queries than the launch has workgroups (two or three per compute unit), so
+    workgroups take a second group by ticket and reuse their block of the workspace and their tables in
+    LDS: heads of both batch entries are compared with the definition, among them one that only second
+    and later tickets can reach, and all rows with their closed-form sums."""
     import dataclasses
     from oracle import search as OS
-    _say("tile mass, more rows than workgroups")
-    T, H, W, tile, D, Hd, batch = 6, 32, 32, (1, 8, 8), 64, 6, 2
+    _say("tile mass, more rows than workgroups", D, tile)
+    T, H, W, Hd, batch = 6, 32, 32, 12, 2
+    B = tile[0] * tile[1] * tile[2]
     wl = dataclasses.replace(make_workload("masslaunch", T, H, W, tile, 0, Hd, D, "bf16", [[]] * Hd), batch=batch)
     g = geometry_of(wl)
-    assert batch * Hd * g.n == 1152
+    groups = -(-g.n * B // 128)                                        # per head
+    workgroups = torch.cuda.get_device_properties(0).multi_processor_count * (2 if (B, D) == (128, 128) else 3)
+    late = -(-workgroups // groups)                                    # (batch, head) whose groups all come after the first round
+    assert late + 1 < batch * Hd
     lay = build_layout(ca, wl)
     q, k, _ = make_qkv(wl, DEV, q_gain=2.0)
     mass = ca.compact_attn_tile_mass(ca.compact_attn_permute(q, lay), ca.compact_attn_permute(k, lay), lay)
     torch.cuda.synchronize()
     got = mass.double().cpu().numpy()
-    assert np.allclose(got.sum(axis=3), 64.0, atol=1e-2)            # every tile holds 64 tokens
-    for b, h in ((0, 0), (1, 4), (1, 5)):                             # row 1024 is batch 1, head 4, tile 64
+    assert np.allclose(got.sum(axis=3), float(B), atol=1e-2)           # every slot holds a token
+    for b, h in ((0, 0), divmod(late, Hd), (batch - 1, Hd - 1)):
         want = OS.tile_mass(g, to_f64(q[b, h]), to_f64(k[b, h]))
         err = np.abs(got[b, h] - want)
         _say("batch", b, "head", h, "max err", err.max())
@@ -972,7 +977,7 @@ def test_infinite_value_in_the_last_token_of_a_tile(kernel, D, tile):
     """Every query keeps every key, so an infinite channel of one V token makes that channel infinite in every row
     and leaves the others alone, also when the token is the last of a tile whose other slots are padding, or the last
     of the walk."""
-    T, H, W = grid = (3, 13, 21)
+    T, H, W = grid = (5, 13, 21)
     dtype = "f32" if kernel == "f32" else "bf16"
     for text_tiles in (0, 1):
         _say("infinite V", kernel, D, tile, text_tiles)
@@ -1025,28 +1030,27 @@ def test_tile_mass_short_walks(D, grid, tile, text_tiles):
 # ---------------------------------------------------------------- every bf16 kernel at small sizes
 
 @pytest.mark.parametrize("D,grid,tile,text_tiles,copies,batch", [
-    # keys split over four ways, 64 queries to a workgroup: padded along all axes, empty rows, tiles of a few tokens
-    (128, (5, 13, 20), (2, 8, 8), 0, 1, 2),       # (its dense walk: two ways, 128 queries)
+    # padded along all axes, empty rows, tiles of a few tokens
+    (128, (5, 13, 20), (2, 8, 8), 0, 1, 2),
     (64, (5, 13, 20), (2, 8, 8), 0, 1, 2),
     (128, (3, 13, 20), (1, 8, 8), 1, 1, 1),
     (64, (3, 13, 20), (1, 8, 8), 1, 1, 1),
     (128, (1, 9, 17), (2, 8, 8), 1, 1, 1),
     (64, (5, 9, 9), (4, 4, 8), 0, 1, 1),
-    # one way, 128 queries, tiles closed up
+    # rows enough to fill the card
     (128, (7, 17, 17), (2, 8, 8), 0, 12, 1),
     (64, (7, 17, 17), (2, 8, 8), 0, 12, 1),
     (128, (7, 17, 17), (2, 8, 8), 1, 3, 2),
     (64, (4, 16, 24), (2, 8, 8), 0, 60, 2),
     (128, (5, 13, 20), (2, 8, 8), 1, 40, 2),
-    # rows enough for one query tile per workgroup (packed faces at head dim 128), paired 64-token tiles
     (128, (9, 20, 20), (2, 8, 8), 1, 8, 1),
-    (64, (5, 13, 20), (2, 8, 8), 1, 4, 1),        # (its dense walk: one way, tiles closed up)
+    (64, (5, 13, 20), (2, 8, 8), 1, 4, 1),
     (128, (3, 13, 20), (1, 8, 8), 1, 16, 2),
-    (64, (3, 13, 20), (1, 8, 8), 1, 40, 2),       # three waves per SIMD
+    (64, (3, 13, 20), (1, 8, 8), 1, 40, 2),
 ])
 def test_bf16_kernels_by_launch_size(D, grid, tile, text_tiles, copies, batch):
-    """The same four heads in launches small and large enough for every kernel of the bf16 dispatch: sparse and
-    dense walk against the oracle with peaked rows, natural order and the static entry point bit for bit."""
+    """The same four heads in launches of many sizes, tiles and grids, whichever kernel they take: sparse and dense
+    walk against the oracle with peaked rows, natural order and the static entry point bit for bit."""
     import dataclasses
     _say("bf16 by launch size", D, grid, tile, copies, batch)
     B = tile[0] * tile[1] * tile[2]
@@ -1068,3 +1072,128 @@ def test_bf16_kernels_by_launch_size(D, grid, tile, text_tiles, copies, batch):
         qkv = [to_f64(x[batch - 1, h0 + h])[None] for x in (q, k, v)]
         _say(h, compare(to_f64(out[batch - 1, h0 + h])[None], OA.masked_attention(g, [heads[h]], *qkv), *tolerances("bf16"), what="sparse"))
         _say(h, compare(to_f64(dense[batch - 1, h0 + h])[None], OA.masked_attention(g, full, *qkv), *tolerances("bf16"), what="dense"))
+
+
+@pytest.mark.parametrize("kernel,D,tile", _EVERY_BF16_KERNEL)
+def test_every_bf16_kernel(kernel, D, tile):
+    """The sparse walk of every kernel of the bf16 dispatch against the oracle, with peaked rows on a grid padded along
+    all axes; natural order, the static entry point and a replayed graph bit for bit; the padding slots of K and V are
+    not read by the kernels that say so."""
+    _say("every kernel", kernel, D, tile)
+    wl, lay = workload_for_kernel(ca, kernel, (5, 13, 20), tile, tile[0] * tile[1] * tile[2], D, "bf16", _EDGE_HEADS, batch=2)
+    g = geometry_of(wl)
+    q, k, v = make_qkv(wl, DEV, q_gain=3.0)
+    out, out_tiled = gpu_attention(ca, wl, lay, q, k, v)
+    for h in range(wl.num_heads - 4, wl.num_heads):
+        qkv = [to_f64(x[1, h])[None] for x in (q, k, v)]
+        _say(h, compare(to_f64(out[1, h])[None], OA.masked_attention(g, [wl.heads[h]], *qkv), *tolerances("bf16"), what=kernel))
+    assert torch.equal(ca.compact_attn_forward_natural(q, k, v, lay, out=torch.full_like(q, float("nan"))), out)
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    again = torch.full_like(qp, float("nan"))
+    assert torch.equal(ca.compact_attn_forward_static(qp, kp, vp, lay, out=again), out_tiled)
+    held = ca.compact_attn_permute(torch.ones_like(q), lay) != 0
+    assert torch.all(out_tiled[~held] == 0)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        ca.compact_attn_forward(qp, kp, vp, lay, out=again)
+    for rep in range(3):
+        again.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(again, out_tiled), f"replay {rep}"
+        assert torch.equal(ca.compact_attn_forward(qp, kp, vp, lay), out_tiled)   # an eager launch between replays
+    if kernel.startswith("ways"):
+        kp[~held] = float("nan")
+        vp[~held] = float("nan")
+        assert torch.equal(ca.compact_attn_forward(qp, kp, vp, lay), out_tiled)
+
+
+@pytest.mark.parametrize("kernel,D,tile", _EVERY_BF16_KERNEL)
+def test_rising_and_huge_scores_on_every_bf16_kernel(kernel, D, tile):
+    """As test_rising_and_huge_scores: the exponent reference of every way moves along the walk, and the ways of a query
+    end with references far apart."""
+    T, H, W = grid = (5, 14, 18)
+    _say("rising scores", kernel, D, tile)
+    heads = [[(T, (1, 1), ABSENT)], [(T, (9, 9), ABSENT)]]
+    wl, lay = workload_for_kernel(ca, kernel, grid, tile, tile[0] * tile[1] * tile[2], D, "bf16", heads)
+    g = geometry_of(wl)
+    q, k, v = make_qkv(wl, DEV)
+    tok_tile, _ = g.token_tile_and_slot()
+    ramp = torch.tensor(np.asarray(tok_tile), device=DEV, dtype=torch.float32) / g.n
+    last = slice(wl.num_heads - 2, wl.num_heads)
+    for gain, q_gain in ((1.0, 2.0), (40.0, 6.0)):
+        kk = (k.float() * (1.0 + 3.0 * gain * ramp[None, None, :, None])).to(k.dtype)
+        qq = (q.float() * q_gain).to(q.dtype)
+        out, _ = gpu_attention(ca, wl, lay, qq, kk, v)
+        want = OA.masked_attention(g, heads, *(to_f64(x[0, last]) for x in (qq, kk, v)))
+        _say(gain, compare(to_f64(out[0, last]), want, *tolerances("bf16"), what=f"gain {gain}"))
+
+
+@pytest.mark.parametrize("kernel,D,tile", [*_EVERY_BF16_KERNEL, ("one-tile", 128, (2, 8, 8))])
+def test_imported_random_mask_on_every_bf16_kernel(kernel, D, tile):
+    """Arbitrary tile masks given as CSR (an empty row, a full one, whole runs of empty rows) on every kernel, and their
+    union with a second set."""
+    T, H, W = 5, 13, 20
+    B = tile[0] * tile[1] * tile[2]
+    _say("imported masks", kernel, D, tile)
+    g = geometry_of(make_workload("import", T, H, W, tile, B, 3, D, "bf16", [[]] * 3))
+    rng = np.random.default_rng(5)
+    masks = rng.random((3, g.n, g.n)) < 0.25
+    masks[0, 3] = False
+    masks[1, :, g.n - 1] = True
+    masks[2, :6] = False
+    masks[2, 7] = True
+    if kernel == "packed-faces":                           # worth it where neighbours along w share their lists
+        masks[:, :g.n_vid] = masks[:, np.arange(g.n_vid) // g.nW * g.nW]
+    other = rng.random((3, g.n, g.n)) < 0.1
+
+    def layout(ms, copies):
+        return ca.compact_attn_layout_from_csr(T, H, W, tile, B, 1, 3 * copies, D, "bf16", [OL.csr_of_mask(m) for m in ms] * copies)
+
+    copies, lay = layout_for_kernel(ca, kernel, lambda n: layout(masks, n))
+    wl = make_workload("import", T, H, W, tile, B, 3 * copies, D, "bf16", [[]] * 3 * copies)
+    q, k, v = make_qkv(wl, DEV)
+    last = slice(3 * copies - 3, 3 * copies)
+    for lay, ms in ((lay, masks), (ca.compact_attn_layout_union(lay, layout(other, copies)), OL.union_masks(masks, other))):
+        out, _ = gpu_attention(ca, wl, lay, q, k, v)
+        want = OA.tile_mask_attention(g, ms, *(to_f64(x[0, last]) for x in (q, k, v)))
+        _say(ca.compact_attn_layout_kernel(lay), compare(to_f64(out[0, last]), want, *tolerances("bf16"), what="imported masks"))
+
+
+@pytest.mark.parametrize("kernel,D,B", [("ways-8x2", 128, 128), ("ways-8x2", 64, 64), ("ways-8x4", 128, 128), ("ways-4x4", 128, 128), ("ways-4x4", 64, 128),
+                                        ("packed-faces", 128, 128), ("paired", 128, 64), ("one-tile", 64, 128), ("one-tile-3", 64, 64)])
+def test_random_problems_on_every_bf16_kernel(kernel, D, B):
+    """Four seeded random problems (tile shapes, ragged grids, text tiles, windows, batch) per kernel, with as many copies
+    of their heads as it takes to reach it: sparse walk of the last heads against the oracle, natural order and the
+    static entry point bit for bit."""
+    import dataclasses
+    done = 0
+    for seed in range(100, 220):
+        seed_B, seed_D, tile, (T, H, W), n_text, batch, heads, clamp, gain = _random_problem(seed)
+        if (seed_B, seed_D) != (B, D) or T * H * W > 5000:
+            continue
+        found = layout_for_kernel(ca, kernel, lambda n: ca.compact_attn_build_layout(T, H, W, tile, n_text, batch, n * len(heads), D, "bf16",
+                                                                                     heads * n, clamp_centre=clamp * n))
+        if not found:
+            continue
+        copies, lay = found
+        Hd = copies * len(heads)
+        _say("random problem", seed, kernel, B, D, tile, (T, H, W), n_text, batch, Hd)
+        wl = dataclasses.replace(make_workload("random", T, H, W, tile, n_text, Hd, D, "bf16", heads * copies), batch=batch)
+        g = geometry_of(wl)
+        q, k, v = make_qkv(wl, DEV, q_gain=gain)
+        out, out_tiled = gpu_attention(ca, wl, lay, q, k, v)
+        if tile[2] % (4 if D == 128 else 8) == 0:
+            assert torch.equal(ca.compact_attn_forward_natural(q, k, v, lay), out)
+        qp, kp, vp = (ca.compact_attn_permute(t, lay) for t in (q, k, v))
+        assert torch.equal(ca.compact_attn_forward_static(qp, kp, vp, lay), out_tiled)
+        last = slice(Hd - len(heads), Hd)
+        want = OA.masked_attention(g, [OL.ClampedHead(h) if c else h for h, c in zip(heads, clamp)], *(to_f64(x[batch - 1, last]) for x in (q, k, v)))
+        compare(to_f64(out[batch - 1, last]), want, *tolerances("bf16"), what=f"seed {seed}")
+        lay.free()
+        done += 1
+        if done == 4:
+            return
+    assert False, f"only {done} random problems reach the {kernel} kernel"
