@@ -424,13 +424,16 @@ struct LaunchCost {
   double gather; // share by which all granules taken from padded tiles lengthen everything
 };
 
-// `walks`: steps of the workgroups of one batch entry in launch order, below zero: no token, returns at once.
-double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t batch, double gathered) {
+// `walks`: steps of the workgroups of one batch entry in launch order, below zero: no token, returns at once.  A launch that
+// cannot take less than `limit` is not followed to its end.
+double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t batch, double gathered, double limit) {
   constexpr int64_t kXcds = 8, kXcdCus = 32;
   constexpr int64_t kExact = 6000;  // workgroups; beyond, rounds and XCDs even out
   const int64_t entries = (int64_t)walks.size(), total = entries * batch;
   double sum = 0, active = 0;
+  bool uniform = true;
   for (float w : walks) {
+    uniform = uniform && w == walks[0];
     if (w < 0) continue;
     sum += w;
     active += 1;
@@ -439,21 +442,37 @@ double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t
   const double share = std::min((double)c.per_cu, std::max(1.0, active * (double)batch / (kXcds * kXcdCus)));  // of them on a CU
   const double slot = c.per_cu == 1 ? c.walk : c.walk + (std::max(c.step * c.per_cu, c.walk) - c.walk) * (share - 1) / (c.per_cu - 1);
   const double longer = 1 + c.gather * gathered;
-  if (total > kExact) {
-    const double mean = (slot * sum + c.group * active) * (double)batch / (double)(kXcds * kXcdCus * c.per_cu);
-    return c.start + longer * (mean + 0.3 * slot * sum / active);
+  const double mean = (slot * sum + c.group * active) * (double)batch / (double)(kXcds * kXcdCus * c.per_cu);
+  if (total > kExact) return c.start + longer * (mean + 0.3 * slot * sum / active);
+  if (c.start + longer * mean >= limit) return limit;
+  if (uniform) {
+    const int64_t deepest = (total + kXcds - 1) / kXcds, rounds = (deepest + kXcdCus * c.per_cu - 1) / (kXcdCus * c.per_cu);
+    return c.start + longer * (double)rounds * (slot * walks[0] + c.group);
   }
   double end = 0;
+  std::vector<double> free_at;  // of the places taken so far; a heap, earliest first, once all are
+  const size_t places = (size_t)(kXcdCus * c.per_cu);
   for (int64_t xcd = 0; xcd < kXcds; ++xcd) {
-    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    free_at.clear();
     for (int64_t id = xcd; id < total; id += kXcds) {
-      const float w = walks[(size_t)(xcd_launch_order(id, total) % entries)];
+      int64_t entry = xcd_launch_order(id, total);
+      while (entry >= entries) entry -= entries;
+      const float w = walks[(size_t)entry];
       double t = w < 0 ? 0.1 * slot : slot * w + c.group;
-      if ((int64_t)free_at.size() >= kXcdCus * c.per_cu) {
-        t += free_at.top();
-        free_at.pop();
+      if (free_at.size() < places) {
+        free_at.push_back(t);
+        if (free_at.size() == places) std::make_heap(free_at.begin(), free_at.end(), std::greater<double>());
+      } else {
+        t += free_at[0];
+        size_t at = 0;
+        for (size_t child = 1; child < places; child = 2 * at + 1) {
+          if (child + 1 < places && free_at[child + 1] < free_at[child]) ++child;
+          if (free_at[child] >= t) break;
+          free_at[at] = free_at[child];
+          at = child;
+        }
+        free_at[at] = t;
       }
-      free_at.push(t);
       end = std::max(end, t);
     }
   }
@@ -541,7 +560,7 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words) {
     const int64_t tiles = dense ? L.n : e < 0 ? L.pair_walk_ptr[~e + 1] - L.pair_walk_ptr[~e] : L.row_ptr[e + 1] - L.row_ptr[e];
     walks.push_back(paired ? (float)tiles : (float)(tiles * L.B) / 128);
   }
-  double best = 0.87 * launch_time(kPlain[big_d][big_b], walks, p.batch, 0);
+  double best = 0.87 * launch_time(kPlain[big_d][big_b], walks, p.batch, 0, HUGE_VAL);
   Ways ways = kWaysNone;
 
   // the workgroups of the others: every part of every row
@@ -561,7 +580,7 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words) {
       const int held = (tokens[L.tile_class[r % L.n]] + w.part_queries - 1) / w.part_queries;  // parts with a token
       for (int part = 0; part < parts; ++part) walks.push_back(part < held ? steps : -1.f);
     }
-    const double t = launch_time(w.cost, walks, p.batch, padded);
+    const double t = launch_time(w.cost, walks, p.batch, padded, best);
     if (t < best) best = t, ways = w.ways;
   }
   return ways;
