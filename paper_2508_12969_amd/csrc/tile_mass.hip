@@ -205,8 +205,9 @@ void tile_mass_kernel(MassArgs a) {
             float delta = move ? mx : 0.f;
             if (delta == kMinusInf) delta = 0.f;  // a row that has seen no real key yet keeps its reference
             w.m_run += delta;
-            // nothing is summed yet on the first tile, and far below zero the factor overflows
-            if (j + t > 0) l_row *= __builtin_amdgcn_exp2f(-delta * w.c2);
+            // the reference only rises after the first tile; there nothing is summed yet, and a first maximum
+            // far below zero must not make the factor infinite
+            l_row *= __builtin_amdgcn_exp2f(fminf(-delta * w.c2, 0.f));
 #pragma unroll
             for (int kb = 0; kb < S::kKeyBlocks; ++kb)
 #pragma unroll
