@@ -3,7 +3,7 @@
 //
 // What bounds it: v_mfma_f32_16x16x4_f32 (a multiply-add in full fp32; a large fp32 matrix product
 // reaches 152 TFLOP/s on this card).  8 heads of 7K tokens, head dim 128, 0.094 TFLOP on real tokens:
-// 1.20 ms, 21.4 ms with one thread per query; 2 heads of 256 tokens: 8 us, 222 us.  Per 16 keys and 16 queries a wave
+// 1.18 ms, 21.4 ms with one thread per query; 2 heads of 256 tokens: 11 us, 222 us.  Per 16 keys and 16 queries a wave
 // issues D / 2 of them, 32 cycles each, beside D / 8 16-byte LDS reads and four exponentials, so
 // everything else fits beside the matrix pipe.
 //
@@ -363,7 +363,7 @@ hipError_t launch(const AttnArgs& a, hipStream_t stream) {
   // As many query groups side by side as the tile has, because they share the staged keys; fewer, with
   // the keys of a query split over the waves instead, while the launch has less than five workgroups
   // per CU.  Measured: 1128 rows of 64 tokens at D = 128, QW 4 / 2: 1.27 / 1.20 ms; 732 rows of 60 at
-  // D = 32, QW 4 / 2 / 1: 0.63 / 0.65 / 0.69 ms.  At D = 128, QW = 1 fills the LDS of a CU with one
+  // D = 32, QW 4 / 2 / 1: 0.63 / 0.65 / 0.69 ms, where the one line for all head dims takes 2 and is 3 % off.  At D = 128, QW = 1 fills the LDS of a CU with one
   // workgroup and waits for copies (240 rows of 128 tokens, QW 2 / 1: 0.31 / 0.37 ms): small tiles only.
   constexpr int64_t kMinWorkgroups = 1280;
   constexpr int kFewest = D == 128 ? 2 : 1;

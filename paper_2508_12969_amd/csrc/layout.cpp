@@ -452,12 +452,10 @@ double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t
   double end = 0;
   std::vector<double> free_at;  // of the places taken so far; a heap, earliest first, once all are
   const size_t places = (size_t)(kXcdCus * c.per_cu);
-  for (int64_t xcd = 0; xcd < kXcds; ++xcd) {
+  for (int64_t xcd : {0, 7}) {  // the ends of a round of chunks, and even and odd ids; all eight give the same choices
     free_at.clear();
     for (int64_t id = xcd; id < total; id += kXcds) {
-      int64_t entry = xcd_launch_order(id, total);
-      while (entry >= entries) entry -= entries;
-      const float w = walks[(size_t)entry];
+      const float w = walks[(size_t)(xcd_launch_order(id, total) % entries)];
       double t = w < 0 ? 0.1 * slot : slot * w + c.group;
       if (free_at.size() < places) {
         free_at.push_back(t);
