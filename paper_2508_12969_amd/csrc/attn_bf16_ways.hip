@@ -12,9 +12,10 @@
 // the products, the exponentials (two issue slots each) and the waits of 64 keys.  Splitting the keys of a
 // stage over four ways and a 128-token tile over two workgroups (NW 8, NQ 2) makes the longest walk about
 // twice as short and a full card 1.7 times slower.  Measured, one-tile kernel / NW 4, NQ 4 / NW 8, NQ 4 /
-// NW 8, NQ 2: 86 rows of 43 tiles, head dim 128, 92 / 47 / 42 / 35 us; 100 rows of 50 tiles, head dim 64,
-// 79 / 62 / 47 / 37 us; 1107 rows of 128 tokens on a 46 x 59 x 10 grid 880 / 652 / 757 / 1026 us; 12K rows
-// on an unpadded grid, head dim 128, 15.4 / 18.4 / 20.5 / 27 ms.
+// NW 8, NQ 2: 86 rows of 43 tiles, head dim 128, 92 / 47 / 38 / 33 us; 100 rows of 50 tiles, head dim 64,
+// 79 / 64 / - / 38 us; 1107 rows of 128 tokens on a 46 x 59 x 10 grid 883 / 649 / 547 / 797 us; 7680 rows
+// on an unpadded grid, head dim 128, 15.9 / 18.0 / 18.9 / 27.8 ms.  (Granules past the end of a walk are not copied;
+// copying the last one again took 757 us instead of 547.)
 //
 // Stages, not tiles.  Keys are staged by LDS DMA in granules of 16 tokens, one per wave and stage, two
 // stages in LDS, one barrier per stage.  Only tokens are staged: the slots of a padded tile are taken

@@ -63,7 +63,7 @@ __device__ __forceinline__ int f32_k_swizzle(int row) {
 
 // One load with an address of its own for every lane; lanes without a token take zeros instead.  Measured against
 // V repeating the last token (and an infinity there giving NaN): 7K tokens, head dim 128, 1.175 / 1.180 ms; grids whose
-// tiles are padded on many sides 0-5 % slower.  Lanes without a token that leave the copy out and write zeros
+// tiles are padded on many sides 0-7 % slower.  Lanes without a token that leave the copy out and write zeros
 // to LDS: 1.227 ms and 3-8 %.
 static __device__ const __attribute__((aligned(16))) uint32_t kZeros[4] = {0, 0, 0, 0};
 __device__ __forceinline__ void copy_rows_or_zeros(uint32_t m0, const char* base, uint32_t lane_off, bool token) {
