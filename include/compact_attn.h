@@ -233,10 +233,11 @@ int compact_attn_forward(const void* q, const void* k, const void* v, ca_layout*
 
 /* compact_attn_forward for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and the same
- * result, bit for bit, but the layout's tables (row offsets, packed tile words, launch order, padding
+ * result, bit for bit (that of compact_attn_forward_with_workspace where rows are split along the keys), but the layout's tables (row offsets, packed tile words, launch order, padding
  * masks, pair walks) are read from a fixed 8 MiB device array inside the library instead of from
  * memory allocated at compact_attn_layout_upload; the call makes no hipMalloc / hipFree and needs no
- * prior upload.  Every GPU the library runs on holds one such array until the process ends.
+ * prior upload.  Every GPU the library runs on holds one such array until the process ends, and one of 64 MiB for the
+ * partial sums of split rows.
  *   - A layout whose tables exceed the array (about 1.9 million kept tile pairs) is rejected with
  *     CA_ERR_UNSUPPORTED and a message that states both sizes; nothing is enqueued.
  *   - The array keeps the tables of the layout the previous call on this GPU used.  A call with the
@@ -266,6 +267,22 @@ int compact_attn_forward_natural(const void* q, const void* k, const void* v, ca
  * Sec. 4.2 and the baseline of Sec. 5.1); the per-head windows of the layout are ignored. */
 int compact_attn_dense(const void* q, const void* k, const void* v, ca_layout* layout, void* out,
                        void* stream);
+
+/* The three calls above for callers that can lend device memory.  Launches too small to fill the device, or
+ * that would end with a few long rows, are split along the keys: several workgroups share a row, leave their partial
+ * sums in the workspace, and a second kernel adds them up (always in the same order, so results are
+ * run-to-run identical; compact_attn_forward_static does the same with a fixed device array).
+ *   compact_attn_layout_split: *workspace_bytes = what such a call needs, at most 64 MiB, 0 where rows are not split;
+ *   sparse walk (dense = 0: forward and natural) or dense walk (dense = 1).  kernel may be NULL; *kernel receives the
+ *   name (see compact_attn_layout_kernel) of the kernel that serves the split launch, NULL where there is none.
+ *   workspace: device memory of at least that size, 16-byte aligned, not overlapping the tensors; its contents
+ *   before and after the call mean nothing.  It must not be used by anything else until the call's work on `stream` has
+ *   run.  Ignored (and may be NULL) where *workspace_bytes is 0.
+ * Errors as for the three calls; CA_ERR_INVALID_ARG for a missing, short, misaligned or overlapping workspace. */
+typedef enum { CA_CALL_FORWARD = 0, CA_CALL_NATURAL = 1, CA_CALL_DENSE = 2 } ca_call;
+int compact_attn_layout_split(const ca_layout* layout, int32_t dense, int64_t* workspace_bytes, const char** kernel);
+int compact_attn_forward_with_workspace(const void* q, const void* k, const void* v, ca_layout* layout, void* out, int32_t call,
+                                        void* workspace, int64_t workspace_bytes, void* stream);
 
 /* Attention mass per tile pair (Sec. 4.2: masks are searched by the recall they keep, the share of
  * the full attention's probability mass that falls on kept tile pairs).

@@ -21,6 +21,7 @@ from .binding import (  # noqa: F401
     compact_attn_layout_pairs,
     compact_attn_layout_packing,
     compact_attn_layout_similarity,
+    compact_attn_layout_split,
     compact_attn_layout_union,
     compact_attn_layout_upload,
     compact_attn_permute,

@@ -20,6 +20,7 @@ CA_ERR_ALLOC = -3
 CA_ERR_HIP = -4
 CA_F32 = 0
 CA_BF16 = 1
+CA_CALL_FORWARD, CA_CALL_NATURAL, CA_CALL_DENSE = 0, 1, 2
 CA_MAX_GROUPS = 8
 
 EXPORTED = (
@@ -40,6 +41,8 @@ EXPORTED = (
     "compact_attn_forward_static",
     "compact_attn_forward_natural",
     "compact_attn_dense",
+    "compact_attn_layout_split",
+    "compact_attn_forward_with_workspace",
     "compact_attn_tile_mass",
     "compact_attn_search_head",
     "compact_attn_last_error",
@@ -115,6 +118,8 @@ def load_library():
     lib.compact_attn_forward_natural.argtypes = [vp, vp, vp, vp, vp, vp]
     lib.compact_attn_forward_static.argtypes = [vp, vp, vp, vp, vp, vp]
     lib.compact_attn_dense.argtypes = [vp, vp, vp, vp, vp, vp]
+    lib.compact_attn_layout_split.argtypes = [vp, i32, i64p, ctypes.POINTER(ctypes.c_char_p)]
+    lib.compact_attn_forward_with_workspace.argtypes = [vp, vp, vp, vp, vp, i32, vp, ctypes.c_int64, vp]
     lib.compact_attn_tile_mass.argtypes = [vp, vp, vp, vp, vp]
     lib.compact_attn_search_head.argtypes = [vp, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(i32), i32, ctypes.c_double,
                                              ctypes.c_double, i32, ctypes.POINTER(ca_group), ctypes.POINTER(ctypes.c_double),
@@ -137,6 +142,12 @@ def _check(status):
         raise CompactAttnError(status, compact_attn_last_error())
 
 
+def _layout_split(handle, dense):
+    nbytes, name = ctypes.c_int64(), ctypes.c_char_p()
+    _check(load_library().compact_attn_layout_split(handle, dense, nbytes, name))
+    return nbytes.value, name.value.decode() if name.value else None
+
+
 class Layout:
     """Owner of a ca_layout*; keeps the problem description for shape checks."""
 
@@ -150,6 +161,8 @@ class Layout:
         # tensor shapes, natural and padded: every call compares them
         self._shapes = tuple((problem.batch, problem.num_heads, tokens, problem.head_dim) for tokens in (n_real.value, n_pad.value))
         self._is_bf16 = problem.dtype == CA_BF16
+        # bytes a call lends the library: the sparse walk, the dense one
+        self._workspace = tuple(_layout_split(handle, dense)[0] for dense in (0, 1))
 
     def free(self):
         if self.handle is not None:
@@ -278,6 +291,12 @@ def compact_attn_layout_kernel(layout, dense=False):
     return name.value.decode()
 
 
+def compact_attn_layout_split(layout, dense=False):
+    """(bytes, kernel): workspace of the layout's sparse (or dense) calls, which the binding allocates, and the name of the
+    kernel that splits their rows along the keys; (0, None) if rows are not split."""
+    return _layout_split(layout.handle, int(bool(dense)))
+
+
 def compact_attn_layout_upload(layout):
     _check(load_library().compact_attn_layout_upload(layout.handle))
 
@@ -322,31 +341,42 @@ def compact_attn_permute(src, layout, inverse=False, out=None, stream=None):
     return out
 
 
-def _attention(fn, q, k, v, layout, out, stream, padded=True):
+def _attention(fn, call, q, k, v, layout, out, stream, padded=True):
     for name, t in (("q", q), ("k", k), ("v", v)):
         _check_tensor(t, layout, padded, name)
     if out is None:
         out = q.new_empty(q.shape)
     else:
         _check_tensor(out, layout, padded, "out")
+    need = 0 if call is None else layout._workspace[call == CA_CALL_DENSE]
+    if need:
+        if stream is None:
+            workspace = q.new_empty(need // q.element_size())
+        else:  # from that stream's memory: what is free there has no work pending on another
+            import torch
+            with torch.cuda.stream(stream):
+                workspace = q.new_empty(need // q.element_size())
+        _check(load_library().compact_attn_forward_with_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), layout.handle, out.data_ptr(), call,
+                                                                  workspace.data_ptr(), need, _stream_ptr(stream)))
+        return out
     _check(fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), layout.handle, out.data_ptr(), _stream_ptr(stream)))
     return out
 
 
 def compact_attn_forward(q, k, v, layout, out=None, stream=None):
     """Sparse attention over tile-ordered, padded q/k/v [batch, heads, N_pad, D]."""
-    return _attention(load_library().compact_attn_forward, q, k, v, layout, out, stream)
+    return _attention(load_library().compact_attn_forward, CA_CALL_FORWARD, q, k, v, layout, out, stream)
 
 
 def compact_attn_forward_static(q, k, v, layout, out=None, stream=None):
     """compact_attn_forward with the layout tables in the library's fixed device array (no allocation
     inside the call; pass `out`, or the binding allocates it before the call)."""
-    return _attention(load_library().compact_attn_forward_static, q, k, v, layout, out, stream)
+    return _attention(load_library().compact_attn_forward_static, None, q, k, v, layout, out, stream)
 
 
 def compact_attn_forward_natural(q, k, v, layout, out=None, stream=None):
     """Sparse attention over natural-order q/k/v [batch, heads, N_real, D]; the result is in natural order too."""
-    return _attention(load_library().compact_attn_forward_natural, q, k, v, layout, out, stream, padded=False)
+    return _attention(load_library().compact_attn_forward_natural, CA_CALL_NATURAL, q, k, v, layout, out, stream, padded=False)
 
 
 def compact_attn_tile_mass(q, k, layout, out=None, stream=None):
@@ -387,4 +417,4 @@ def compact_attn_search_head(layout, mass, group_max_dt, tau, lam, pattern="dual
 
 def compact_attn_dense(q, k, v, layout, out=None, stream=None):
     """Same kernel with every query tile keeping all tiles."""
-    return _attention(load_library().compact_attn_dense, q, k, v, layout, out, stream)
+    return _attention(load_library().compact_attn_dense, CA_CALL_DENSE, q, k, v, layout, out, stream)

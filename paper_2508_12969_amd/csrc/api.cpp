@@ -20,12 +20,17 @@ namespace {
 // instead of in allocated memory.  Every GPU the library runs on holds its own copy of the array
 // until the process ends.  In host code the name below is only a handle for hipGetSymbolAddress;
 // the address kernels and copies use is the per-device pointer kept in g_scratch.
+// `scratch_shares` is the workspace of launches that split rows along the keys (SplitPlan in layout.h); its tables lie past
+// the first kScratchBytes, so that the layouts that fit do not depend on the split.
 constexpr size_t kScratchBytes = (size_t)8 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchSplitBytes = ca::kMaxSplitItems * (sizeof(ca::WorkItem) + sizeof(ca::MergeItem)) + 512;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSplitBytes];
+static __device__ __align__(256) unsigned char scratch_shares[ca::kMaxShareBytes];
 
 constexpr int kMaxDevices = 64;
 struct ScratchState {
   unsigned char* ptr = nullptr;  // device address of `scratch` on this device
+  unsigned char* workspace = nullptr;  // and of `scratch_shares`
   uint64_t owner = 0;            // serial of the layout whose tables the last call enqueued there
 };
 ScratchState g_scratch[kMaxDevices];
@@ -48,40 +53,56 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 int elem_size(int32_t dtype) { return dtype == CA_BF16 ? 2 : 4; }
 
+// A table of a layout and where its device address goes.
+struct Table {
+  const void* host;
+  size_t bytes;
+  void** dev;
+};
 template <class T>
-int upload_vec(const T* host, size_t count, T** dev) {
-  *dev = nullptr;
-  const size_t bytes = (count ? count : 1) * sizeof(T);
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(dev), bytes);
+Table table(const std::vector<T>& host, T** dev) {
+  return {host.data(), host.size() * sizeof(T), reinterpret_cast<void**>(dev)};
+}
+
+// All tables of a layout in one allocation, 256-byte aligned.  The small ones go through one buffer and one copy: at 20 us
+// for an allocation and a copy, a table at a time took 0.3 ms of the 0.7 ms that a small layout takes to make and upload.
+int upload_tables(std::vector<Table>& tables, unsigned char** block) {
+  constexpr size_t kSmall = (size_t)256 << 10;
+  auto aligned = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  std::stable_sort(tables.begin(), tables.end(), [&](const Table& x, const Table& y) { return (x.bytes <= kSmall) > (y.bytes <= kSmall); });
+  size_t total = 0, staged = 0;
+  for (const Table& t : tables) {
+    if (t.bytes <= kSmall) staged = total + aligned(t.bytes);
+    total += aligned(t.bytes);
+  }
+  std::vector<unsigned char> image(staged, 0);
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(block), total ? total : 256);
   if (e != hipSuccess) {
-    set_error("hipMalloc of %zu bytes for a layout table failed: %s", bytes, hipGetErrorString(e));
+    *block = nullptr;
+    set_error("hipMalloc of %zu bytes for the layout tables failed: %s", total, hipGetErrorString(e));
     (void)hipGetLastError();
     return CA_ERR_ALLOC;
   }
-  if (count) {
-    e = hipMemcpy(*dev, host, count * sizeof(T), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpy of a layout table");
+  size_t at = 0;
+  for (const Table& t : tables) {
+    *t.dev = *block + at;
+    if (t.bytes && t.bytes <= kSmall) std::memcpy(image.data() + at, t.host, t.bytes);
+    if (t.bytes > kSmall) {
+      e = hipMemcpy(*t.dev, t.host, t.bytes, hipMemcpyHostToDevice);
+      if (e != hipSuccess) return hip_fail(e, "hipMemcpy of a layout table");
+    }
+    at += aligned(t.bytes);
+  }
+  if (staged) {
+    e = hipMemcpy(*block, image.data(), staged, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy of the layout tables");
   }
   return CA_OK;
 }
 
 void free_device_tables(ca::DeviceTables& d) {
-  if (d.row_ptr) (void)hipFree(d.row_ptr);
-  if (d.col_meta) (void)hipFree(d.col_meta);
-  if (d.dense_meta) (void)hipFree(d.dense_meta);
-  if (d.order) (void)hipFree(d.order);
-  if (d.pair_rows) (void)hipFree(d.pair_rows);
-  if (d.pair_desc) (void)hipFree(d.pair_desc);
-  if (d.launch_rows) (void)hipFree(d.launch_rows);
-  if (d.pair_walk_ptr) (void)hipFree(d.pair_walk_ptr);
-  if (d.pair_walk) (void)hipFree(d.pair_walk);
-  if (d.dense_pair_walk) (void)hipFree(d.dense_pair_walk);
-  if (d.tile_class) (void)hipFree(d.tile_class);
-  if (d.class_mask) (void)hipFree(d.class_mask);
-  if (d.class_perm) (void)hipFree(d.class_perm);
-  if (d.tile_origin) (void)hipFree(d.tile_origin);
+  if (d.block) (void)hipFree(d.block);
   if (d.mass_partial) (void)hipFree(d.mass_partial);
-  if (d.pool_counters) (void)hipFree(d.pool_counters);
   d = ca::DeviceTables{};
 }
 
@@ -114,28 +135,26 @@ int ensure_uploaded(ca_layout* L, hipStream_t stream) {
   int st = ca::pack_device_tables(*L, false, t);
   if (st != CA_OK) return st;
   ca::DeviceTables d;
-  st = upload_vec(L->row_ptr.data(), L->row_ptr.size(), &d.row_ptr);
-  if (st == CA_OK) st = upload_vec(t.col_meta.data(), t.col_meta.size(), &d.col_meta);
-  if (st == CA_OK) st = upload_vec(t.dense_meta.data(), t.dense_meta.size(), &d.dense_meta);
-  if (st == CA_OK) st = upload_vec(L->order.data(), L->order.size(), &d.order);
-  if (st == CA_OK) st = upload_vec(L->pair_rows.data(), L->pair_rows.size(), &d.pair_rows);
-  d.num_pairs = (int64_t)L->pair_rows.size() / 2;
-  if (st == CA_OK && d.num_pairs) st = upload_vec(L->pair_desc.data(), L->pair_desc.size(), &d.pair_desc);
-  if (st == CA_OK && L->packed_faces) {
-    st = upload_vec(L->launch_rows.data(), L->launch_rows.size(), &d.launch_rows);
-    d.num_launch_rows = (int64_t)L->launch_rows.size();
-  }
-  if (st == CA_OK && d.num_pairs) st = upload_vec(L->pair_walk_ptr.data(), L->pair_walk_ptr.size(), &d.pair_walk_ptr);
-  if (st == CA_OK && d.num_pairs) st = upload_vec(t.pair_walk.data(), t.pair_walk.size(), &d.pair_walk);
-  if (st == CA_OK && d.num_pairs) st = upload_vec(t.dense_pair_walk.data(), t.dense_pair_walk.size(), &d.dense_pair_walk);
-  if (st == CA_OK) st = upload_vec(L->tile_class.data(), L->tile_class.size(), &d.tile_class);
-  if (st == CA_OK) st = upload_vec(L->class_mask.data(), L->class_mask.size(), &d.class_mask);
-  if (st == CA_OK) st = upload_vec(t.class_perm.data(), t.class_perm.size(), &d.class_perm);
-  if (st == CA_OK && !t.tile_origin.empty()) st = upload_vec(t.tile_origin.data(), t.tile_origin.size(), &d.tile_origin);
-  if (st == CA_OK) {
-    const int32_t zeros[ca::kPoolSlots] = {};
-    st = upload_vec(zeros, (size_t)ca::kPoolSlots, &d.pool_counters);
+  try {
+    const std::vector<int32_t> pool_counters(ca::kPoolSlots, 0);
+    d.num_pairs = (int64_t)L->pair_rows.size() / 2;
+    d.num_launch_rows = L->packed_faces ? (int64_t)L->launch_rows.size() : 0;
     d.pool_slots = ca::kPoolSlots;
+    std::vector<Table> tables = {table(L->row_ptr, &d.row_ptr),       table(t.col_meta, &d.col_meta),     table(t.dense_meta, &d.dense_meta),
+                                 table(L->order, &d.order),           table(L->tile_class, &d.tile_class), table(L->class_mask, &d.class_mask),
+                                 table(t.class_perm, &d.class_perm),  table(pool_counters, &d.pool_counters)};
+    if (d.num_pairs)
+      for (const Table& x : {table(L->pair_rows, &d.pair_rows), table(L->pair_desc, &d.pair_desc), table(L->pair_walk_ptr, &d.pair_walk_ptr),
+                             table(t.pair_walk, &d.pair_walk), table(t.dense_pair_walk, &d.dense_pair_walk)})
+        tables.push_back(x);
+    if (L->packed_faces) tables.push_back(table(L->launch_rows, &d.launch_rows));
+    if (!t.tile_origin.empty()) tables.push_back(table(t.tile_origin, &d.tile_origin));
+    if (L->split.shares) tables.push_back(table(L->split.items, &d.split_items)), tables.push_back(table(L->split.merges, &d.split_merges));
+    if (L->split_dense.shares) tables.push_back(table(L->split_dense.items, &d.split_items_dense)), tables.push_back(table(L->split_dense.merges, &d.split_merges_dense));
+    st = upload_tables(tables, &d.block);
+  } catch (const std::bad_alloc&) {
+    set_error("out of host memory while packing the device tables");
+    st = CA_ERR_ALLOC;
   }
   if (st != CA_OK) {
     free_device_tables(d);
@@ -248,7 +267,7 @@ int check_attention_args(const void* q, const void* k, const void* v, const ca_l
 
 // Fills the kernel arguments from the problem and a set of device tables, and launches.
 int launch_attention(const void* q, const void* k, const void* v, const ca_layout* L, const ca::DeviceTables& t, void* out,
-                     void* stream, bool dense, bool natural) {
+                     void* stream, bool dense, bool natural, void* workspace) {
   ca::AttnArgs a{};
   a.q = q;
   a.k = k;
@@ -314,29 +333,40 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
   hipError_t e = hipSuccess;
   a.ways = dense ? L->ways_dense : L->ways;
   a.simd_waves = dense ? L->simd_waves_dense : L->simd_waves;
+  const ca::SplitPlan& plan = dense ? L->split_dense : L->split;
+  if (workspace && plan.shares > 0) {
+    a.ways = plan.ways;
+    a.items = dense ? t.split_items_dense : t.split_items;
+    a.merges = dense ? t.split_merges_dense : t.split_merges;
+    a.num_items = (int64_t)plan.items.size();
+    a.num_merges = (int64_t)plan.merges.size();
+    a.shares = plan.shares;
+    a.share_waves = plan.waves;
+    a.share_stats = workspace;
+    a.share_o = static_cast<char*>(workspace) + a.batch * a.shares * ca::share_stats_bytes(32 * plan.waves);
+  }
   if (a.ways != ca::kWaysNone) {
     a.order = dense ? nullptr : t.order;
     e = ca::launch_attn_bf16(a, (hipStream_t)stream);
-  } else if (!all_paired && a.entries > 0) {
-    set_split(a.entries, dense ? L->split_rows_dense : L->split_rows);
-    e = bf16 ? ca::launch_attn_bf16(a, (hipStream_t)stream) : ca::launch_attn_f32(a, (hipStream_t)stream);
-  }
-  if (a.ways == ca::kWaysNone && e == hipSuccess && all_paired) {
+  } else if (all_paired) {
     set_split(t.num_pairs, dense ? L->split_pairs_dense : L->split_pairs);
     e = ca::launch_attn_bf16_pair(a, (hipStream_t)stream);
+  } else if (a.entries > 0) {
+    set_split(a.entries, dense ? L->split_rows_dense : L->split_rows);
+    e = bf16 ? ca::launch_attn_bf16(a, (hipStream_t)stream) : ca::launch_attn_f32(a, (hipStream_t)stream);
   }
   if (e != hipSuccess) return hip_fail(e, dense ? "dense attention launch" : "sparse attention launch");
   return CA_OK;
 }
 
 int run_attention(const void* q, const void* k, const void* v, ca_layout* L, void* out, void* stream, bool dense,
-                  bool natural = false) {
+                  bool natural = false, void* workspace = nullptr) {
   ca::clear_error();
   int st = check_attention_args(q, k, v, L, out, natural);
   if (st != CA_OK) return st;
   st = ensure_uploaded(L, (hipStream_t)stream);
   if (st != CA_OK) return st;
-  return launch_attention(q, k, v, L, L->dev, out, stream, dense, natural);
+  return launch_attention(q, k, v, L, L->dev, out, stream, dense, natural, workspace);
 }
 
 // Packs the sparse forward's tables into L->static_image (once per layout).  Caller holds g_scratch_mutex.
@@ -366,6 +396,9 @@ int build_static_image(ca_layout* L) {
       {nullptr, 2 * 256, &o.pool_counter},  // two ticket counters, 256 bytes apart; they stay zero: the kernels put them back after every launch
       {L->pair_desc.data(), paired ? L->pair_desc.size() * sizeof(int32_t) : 0, &o.pair_desc},
       {L->launch_rows.data(), L->packed_faces ? L->launch_rows.size() * sizeof(int32_t) : 0, &o.launch_rows},
+      // these two last: the size limit counts what lies before them
+      {L->split.items.data(), L->split.items.size() * sizeof(ca::WorkItem), &o.split_items},
+      {L->split.merges.data(), L->split.merges.size() * sizeof(ca::MergeItem), &o.split_merges},
   };
   size_t total = 0;
   for (const Part& p : parts) {
@@ -382,6 +415,15 @@ int build_static_image(ca_layout* L) {
   for (const Part& p : parts)
     if (p.bytes && p.src) std::memcpy(L->static_image.data() + *p.off, p.src, p.bytes);
   return CA_OK;
+}
+
+// The kernel of a layout's attention calls; the order of the tests is that of launch_attention.
+const char* kernel_name(const ca_layout* L, ca::Ways ways, bool dense) {
+  if (ways != ca::kWaysNone) return ways == ca::kWays4x4 ? "ways-4x4" : ways == ca::kWays8x4 ? "ways-8x4" : "ways-8x2";
+  if (L->prob.dtype != CA_BF16) return "f32";
+  if (L->B == 64 && L->prob.head_dim == 128) return "paired";
+  if (L->packed_faces) return "packed-faces";
+  return (dense ? L->simd_waves_dense : L->simd_waves) == 3 ? "one-tile-3" : "one-tile";
 }
 
 // Checks a problem description and allocates a layout with its geometry filled in (no tables yet).
@@ -545,12 +587,7 @@ int compact_attn_layout_kernel(const ca_layout* L, int32_t dense, const char** n
   if (dense != 0 && dense != 1) return fail(CA_ERR_INVALID_ARG, "dense must be 0 or 1");
   const int st = check_attn_support(L);
   if (st != CA_OK) return st;
-  const ca::Ways ways = dense ? L->ways_dense : L->ways;  // the order of the tests is that of launch_attention
-  if (ways != ca::kWaysNone) *name = ways == ca::kWays4x4 ? "ways-4x4" : ways == ca::kWays8x4 ? "ways-8x4" : "ways-8x2";
-  else if (L->prob.dtype != CA_BF16) *name = "f32";
-  else if (L->B == 64 && L->prob.head_dim == 128) *name = "paired";
-  else if (L->packed_faces) *name = "packed-faces";
-  else *name = (dense ? L->simd_waves_dense : L->simd_waves) == 3 ? "one-tile-3" : "one-tile";
+  *name = kernel_name(L, dense ? L->ways_dense : L->ways, dense != 0);
   return CA_OK;
 }
 
@@ -615,13 +652,18 @@ int compact_attn_forward_static(const void* q, const void* k, const void* v, ca_
     void* p = nullptr;
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e != hipSuccess || !p) return hip_fail(e, "hipGetSymbolAddress of the static table array");
+    void* w = nullptr;
+    e = hipGetSymbolAddress(&w, HIP_SYMBOL(scratch_shares));
+    if (e != hipSuccess || !w) return hip_fail(e, "hipGetSymbolAddress of the static workspace");
     sc.ptr = static_cast<unsigned char*>(p);
+    sc.workspace = static_cast<unsigned char*>(w);
   }
   st = build_static_image(L);
   if (st != CA_OK) return st;
-  if (L->static_image.size() > kScratchBytes) {
-    set_error("the layout's tables take %zu bytes, the static device array holds %zu: use compact_attn_forward",
-              L->static_image.size(), kScratchBytes);
+  const size_t table_bytes = L->split.shares > 0 ? L->static_off.split_items : L->static_image.size();
+  if (table_bytes > kScratchBytes) {
+    set_error("the layout's tables take %zu bytes, the static device array holds %zu: use compact_attn_forward", table_bytes,
+              kScratchBytes);
     return CA_ERR_UNSUPPORTED;
   }
   if (sc.owner != L->serial) {
@@ -664,7 +706,13 @@ int compact_attn_forward_static(const void* q, const void* k, const void* v, ca_
     t.launch_rows = reinterpret_cast<int32_t*>(sc.ptr + o.launch_rows);
     t.num_launch_rows = (int64_t)L->launch_rows.size();
   }
-  st = launch_attention(q, k, v, L, t, out, stream, false, false);
+  void* workspace = nullptr;
+  if (L->split.shares > 0) {
+    t.split_items = reinterpret_cast<ca::WorkItem*>(sc.ptr + o.split_items);
+    t.split_merges = reinterpret_cast<ca::MergeItem*>(sc.ptr + o.split_merges);
+    workspace = sc.workspace;
+  }
+  st = launch_attention(q, k, v, L, t, out, stream, false, false, workspace);
   if (st != CA_OK) sc.owner = 0;
   return st;
 }
@@ -675,6 +723,40 @@ int compact_attn_forward_natural(const void* q, const void* k, const void* v, ca
 
 int compact_attn_dense(const void* q, const void* k, const void* v, ca_layout* L, void* out, void* stream) {
   return run_attention(q, k, v, L, out, stream, true);
+}
+
+int compact_attn_layout_split(const ca_layout* L, int32_t dense, int64_t* workspace_bytes, const char** kernel) {
+  ca::clear_error();
+  if (!L || !workspace_bytes) return fail(CA_ERR_INVALID_ARG, "null argument");
+  if (dense != 0 && dense != 1) return fail(CA_ERR_INVALID_ARG, "dense must be 0 or 1");
+  const ca::SplitPlan& plan = dense ? L->split_dense : L->split;
+  *workspace_bytes = ca::workspace_bytes(plan, L->prob.batch, L->prob.head_dim);
+  if (kernel) *kernel = plan.shares == 0 ? nullptr : kernel_name(L, plan.ways, dense != 0);
+  return CA_OK;
+}
+
+int compact_attn_forward_with_workspace(const void* q, const void* k, const void* v, ca_layout* L, void* out, int32_t call,
+                                        void* workspace, int64_t workspace_bytes, void* stream) {
+  ca::clear_error();
+  if (call != CA_CALL_FORWARD && call != CA_CALL_NATURAL && call != CA_CALL_DENSE) return fail(CA_ERR_INVALID_ARG, "unknown call");
+  const bool dense = call == CA_CALL_DENSE, natural = call == CA_CALL_NATURAL;
+  if (L) {
+    const ca_problem& p = L->prob;
+    const int64_t need = ca::workspace_bytes(dense ? L->split_dense : L->split, p.batch, p.head_dim);
+    if (need == 0) {
+      workspace = nullptr;
+    } else {
+      if (!workspace || workspace_bytes < need) {
+        set_error("the call needs a workspace of %lld bytes", (long long)need);
+        return CA_ERR_INVALID_ARG;
+      }
+      if (!aligned16(workspace)) return fail(CA_ERR_INVALID_ARG, "the workspace must be 16-byte aligned");
+      const int64_t bytes = (int64_t)p.batch * p.num_heads * (natural ? L->N_real : L->N_pad) * p.head_dim * elem_size(p.dtype);
+      for (const void* t : {q, k, v, static_cast<const void*>(out)})
+        if (ranges_overlap(workspace, need, t, bytes)) return fail(CA_ERR_INVALID_ARG, "the workspace must not overlap q, k, v or out");
+    }
+  }
+  return run_attention(q, k, v, L, out, stream, dense, natural, workspace);
 }
 
 int compact_attn_tile_mass(const void* q, const void* k, ca_layout* L, float* mass, void* stream) {

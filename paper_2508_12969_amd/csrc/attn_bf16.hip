@@ -29,8 +29,9 @@ namespace {
 // kNat: q, k, v and out are in natural token order ([batch, heads, N_real, D]); the gather of the
 // tiles and the scatter of the output happen in the copies of this kernel instead of in separate
 // permutation passes.
-template <int B, int D, bool kNat>
-__device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, int64_t batch, char* lds_k, char* lds_v) {
+// it: the part of the row's list to walk (kSplit).
+template <int B, int D, bool kNat, bool kSplit = false>
+__device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, int64_t batch, char* lds_k, char* lds_v, const LaunchItem& it = LaunchItem()) {
   using S = Shape<B, D>;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -41,8 +42,8 @@ __device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, in
   const auto tile_origin = CONST_PTR(int32_t, a.tile_origin);
   const TileSource<S, kNat> src(a, wave, lane);
 
-  const int64_t begin = a.row_ptr ? a.row_ptr[row] : 0;
-  const int count = (int)(a.row_ptr ? a.row_ptr[row + 1] - begin : a.n);
+  const int64_t begin = (a.row_ptr ? a.row_ptr[row] : 0) + (kSplit ? it.first : 0);
+  const int count = kSplit ? it.count : (int)(a.row_ptr ? a.row_ptr[row + 1] - begin : a.n);
   // one packed word per kept tile: tile id | padding class << 24 (a slice of the packed CSR, or the
   // shared 0..n-1 list of the dense walk)
   const auto meta = CONST_PTR(int32_t, a.col_meta + begin);
@@ -52,7 +53,7 @@ __device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, in
   QueryWave<S> w(lane, a.scale);
   const QuerySlot qs = query_slot<B>(a, q_tile, wave * 32, w.qi);
   const bool wave_active = qs.wave_active;
-  const int64_t q_row = kNat ? src.query_row(a, q_tile, qs.slot) : q_tile * B + qs.slot;
+  const int64_t q_row = kNat ? natural_query_row(a, q_tile, qs.slot) : q_tile * B + qs.slot;
   w.load_q(static_cast<const char*>(a.q) + plane + q_row * S::kRowBytes);
 
   const TileLoader<S, false> k_loader(wave, lane);
@@ -121,17 +122,34 @@ __device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, in
     word1 = word2;
   }
 
+  if constexpr (kSplit) {
+    if (it.share >= 0) {
+      if (wave_active) w.store_share(a, it.share * (B / 32) + wave, lane, count > 0);
+      return;
+    }
+  }
   w.store(static_cast<char*>(a.out) + plane + q_row * S::kRowBytes, qs.real, !kNat || qs.real);
 }
 
 // kPacked: the launch order may hold workgroups of two packed query tiles (entries below zero)
-template <int B, int D, bool kNat, bool kPacked, int kSimdWaves = 2>
+template <int B, int D, bool kNat, bool kPacked, int kSimdWaves = 2, bool kSplit = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(B * 2, B * 2), amdgpu_waves_per_eu(kSimdWaves, kSimdWaves)))
 void attn_bf16_kernel(AttnArgs a) {
   using S = Shape<B, D>;
   __shared__ __attribute__((aligned(1024))) char lds_k[S::kTileBytes];
   __shared__ __attribute__((aligned(1024))) char lds_v[S::kTileBytes];
   __shared__ int pool_ticket;
+  if constexpr (kSplit) {
+    const LaunchItem it = split_item(a);
+    if constexpr (kPacked) {
+      if (it.entry < 0) {
+        attn_pair_body<128, kNat, true>(a, ~it.entry, it.batch, lds_k, lds_v, it);
+        return;
+      }
+    }
+    attn_row_body<B, D, kNat, true>(a, it.entry, it.batch, lds_k, lds_v, it);
+    return;
+  }
   const int64_t linear = launch_entry(a, &pool_ticket);
   if (linear < 0) return;  // a surplus pool workgroup (all of its threads)
   const int64_t item = linear % a.entries;
@@ -147,39 +165,39 @@ void attn_bf16_kernel(AttnArgs a) {
   attn_row_body<B, D, kNat>(a, entry, batch, lds_k, lds_v);
 }
 
-template <int B, int D, int kSimdWaves>
+template <int B, int D, bool kPacked, int kSimdWaves>
 hipError_t launch(const AttnArgs& a, hipStream_t stream) {
-  const int64_t items = a.static_items + a.pool_wgs;
-  if (a.natural) {
-    if (a.tw % Shape<B, D>::kRowsPerLoad != 0) return hipErrorInvalidValue;  // a KiB block must stay inside one run
-    hipLaunchKernelGGL((attn_bf16_kernel<B, D, true, false, kSimdWaves>), dim3((unsigned)items), dim3(B * 2), 0, stream, a);
-  } else {
-    hipLaunchKernelGGL((attn_bf16_kernel<B, D, false, false, kSimdWaves>), dim3((unsigned)items), dim3(B * 2), 0, stream, a);
-  }
+  if (a.natural && a.tw % Shape<B, D>::kRowsPerLoad != 0) return hipErrorInvalidValue;  // a KiB block must stay inside one run
+  const int64_t workgroups = a.items ? a.batch * a.num_items : a.static_items + a.pool_wgs;
+  if (workgroups < 1 || workgroups > 0x7fffffff) return hipErrorInvalidValue;
+  const auto kernel =
+      a.items ? (a.natural ? attn_bf16_kernel<B, D, true, kPacked, kSimdWaves, true> : attn_bf16_kernel<B, D, false, kPacked, kSimdWaves, true>)
+              : (a.natural ? attn_bf16_kernel<B, D, true, kPacked, kSimdWaves> : attn_bf16_kernel<B, D, false, kPacked, kSimdWaves>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)workgroups), dim3(B * 2), 0, stream, a);
   return hipGetLastError();
+}
+
+hipError_t launch_rows(const AttnArgs& a, hipStream_t stream) {
+  const int64_t items = (int64_t)a.batch * a.entries;
+  if (items == 0) return hipSuccess;
+  if (!a.items && a.static_items + a.pool_items != items) return hipErrorInvalidValue;
+  if (a.B == 128 && a.D == 128) {
+    // One instantiation serves grids with and without packed query tiles (without, no entry of the
+    // launch order is below zero).  Measured on an unpadded 32 x 48 x 80 grid: 56.9 ms against 57.4 ms
+    // for an instantiation without the pair body: the row body happens to come out better in this one.
+    if (a.packed && ((!a.order && !a.items) || !a.pair_rows || !a.pair_desc)) return hipErrorInvalidValue;
+    return launch<128, 128, true, 2>(a, stream);
+  }
+  if (a.B == 128 && a.D == 64) return launch<128, 64, false, 2>(a, stream);
+  if (a.B == 64 && a.D == 64) return a.simd_waves == 3 ? launch<64, 64, false, 3>(a, stream) : launch<64, 64, false, 2>(a, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
 
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream) {
-  if (a.ways != kWaysNone) return launch_attn_bf16_ways(a, stream);
-  const int64_t items = (int64_t)a.batch * a.entries;
-  if (items == 0) return hipSuccess;
-  if (a.static_items + a.pool_wgs > 0x7fffffff || a.static_items + a.pool_items != items) return hipErrorInvalidValue;
-  if (a.B == 128 && a.D == 128) {
-    // One instantiation serves grids with and without packed query tiles (without, no entry of the
-    // launch order is below zero).  Measured on an unpadded 32 x 48 x 80 grid: 56.9 ms against 57.4 ms
-    // for an instantiation without the pair body: the row body happens to come out better in this one.
-    if (a.packed && (!a.order || !a.pair_rows || !a.pair_desc)) return hipErrorInvalidValue;
-    if (a.natural && a.tw % Shape<128, 128>::kRowsPerLoad != 0) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(a.static_items + a.pool_wgs)), block(256);
-    if (a.natural) hipLaunchKernelGGL((attn_bf16_kernel<128, 128, true, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((attn_bf16_kernel<128, 128, false, true>), grid, block, 0, stream, a);
-    return hipGetLastError();
-  }
-  if (a.B == 128 && a.D == 64) return launch<128, 64, 2>(a, stream);
-  if (a.B == 64 && a.D == 64) return a.simd_waves == 3 ? launch<64, 64, 3>(a, stream) : launch<64, 64, 2>(a, stream);
-  return hipErrorInvalidValue;
+  const hipError_t e = a.ways != kWaysNone ? launch_attn_bf16_ways(a, stream) : launch_rows(a, stream);
+  return e == hipSuccess && a.items ? launch_attn_bf16_merge(a, stream) : e;
 }
 
 }  // namespace ca

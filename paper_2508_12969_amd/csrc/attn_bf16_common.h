@@ -44,6 +44,26 @@ __device__ __forceinline__ int64_t launch_entry(const AttnArgs& a, int* ticket) 
   return t < a.pool_items ? a.static_items + t : -1;
 }
 
+// A workgroup's share of a launch: a launch-order entry (a row, or the complement of a workgroup of two query tiles), the
+// part of its list to walk, and where its sums go (-1: it walks all of the list and writes the output).
+struct LaunchItem {
+  int64_t entry, batch;
+  int first, count, part;
+  int64_t share;
+};
+__device__ __forceinline__ LaunchItem split_item(const AttnArgs& a) {
+  const int64_t linear = xcd_launch_order(blockIdx.x, gridDim.x, kXcdSplitChunk);
+  const auto item = CONST_PTR(int32_t, a.items + linear % a.num_items);
+  LaunchItem it;
+  it.batch = linear / a.num_items;
+  it.entry = item[0];
+  it.first = item[1];
+  it.count = item[2];
+  it.part = item[3] & 3;
+  it.share = item[3] >> 2 ? it.batch * a.shares + (item[3] >> 2) - 1 : -1;
+  return it;
+}
+
 // kWaves_: waves of a workgroup that share the tile copies (B / 32 when a workgroup owns one query
 // tile, twice that when it owns two).
 template <int B_, int D_, int kWaves_ = B_ / 32>
@@ -256,14 +276,14 @@ struct TileSource {
     }
   }
 
-  // Natural-order row of slot `slot` of query tile `q_tile` (clamped into the tensor for a padding
-  // slot, whose result is never stored).
-  __device__ __forceinline__ int64_t query_row(const AttnArgs& a, int64_t q_tile, int slot) const {
-    const int dx = slot % a.tw, run = slot / a.tw, dy = run % a.th, dt = run / a.th;
-    const int64_t row = CONST_PTR(int32_t, a.tile_origin)[q_tile] + (q_tile >= a.n_vid ? slot : (dt * a.H + dy) * a.W + dx);
-    return row < a.N_real ? row : a.N_real - 1;
-  }
 };
+
+// Natural-order row of a slot of a query tile (clamped into the tensor for a padding slot, whose result is not stored).
+__device__ __forceinline__ int64_t natural_query_row(const AttnArgs& a, int64_t q_tile, int slot) {
+  const int dx = slot % a.tw, run = slot / a.tw, dy = run % a.th, dt = run / a.th;
+  const int64_t row = CONST_PTR(int32_t, a.tile_origin)[q_tile] + (q_tile >= a.n_vid ? slot : (dt * a.H + dy) * a.W + dx);
+  return row < a.N_real ? row : a.N_real - 1;
+}
 
 // Which slot of its query tile a lane works for.  Lanes take the tile's slots in the order of
 // class_perm (the slots that hold a token first, then the padding slots), so the queries of a padded
@@ -287,6 +307,23 @@ __device__ __forceinline__ QuerySlot query_slot(const Args& a, int64_t q_tile, i
   q.real = first + qi < valid;
   q.wave_active = first < valid;
   return q;
+}
+
+// Tile-order output of a packed query tile (waves only for the slots that hold tokens): the wave with the tile's last
+// tokens writes the zero rows of the padding slots that no wave owns.
+template <int D>
+__device__ __forceinline__ void zero_unowned_rows(const AttnArgs& a, char* out_plane, int64_t q_tile, int first_slot, int lane) {
+  const int cls = CONST_PTR(int32_t, a.tile_class)[q_tile];
+  const auto mask = CONST_PTR(uint32_t, a.class_mask) + cls * 4;
+  const int valid = __builtin_popcount(mask[0]) + __builtin_popcount(mask[1]) + __builtin_popcount(mask[2]) + __builtin_popcount(mask[3]);
+  const int owned = (valid + 31) / 32 * 32;
+  if (first_slot + 32 != owned || lane >= 32) return;
+  char* tile_out = out_plane + q_tile * a.B * (int64_t)(D * 2);
+  for (int s = owned + lane; s < a.B; s += 32) {
+    uint4* row = reinterpret_cast<uint4*>(tile_out + (int64_t)a.class_perm[cls * 128 + s] * (D * 2));
+#pragma unroll
+    for (int c = 0; c < D * 2 / 16; ++c) row[c] = uint4{0, 0, 0, 0};
+  }
 }
 
 // Schedule of a product phase: the LDS reads of kLead matrix instructions are requested before the first
@@ -505,6 +542,16 @@ struct QueryWave {
   __device__ __forceinline__ void pv_tile(LdsTile lds_v, const bf16x8 (&pf)[S::kKeyBlocks][2], bool upper_keys) {
     pv<0, S::kKeyBlocks / 2>(lds_v, pf);
     if (upper_keys) pv<S::kKeyBlocks / 2, S::kKeyBlocks>(lds_v, pf);
+  }
+
+  // ---- epilogue of a row that is split along the keys: what this wave has summed up, lane by lane, as the merge
+  // kernel reads it (attn_bf16_merge.hip); wave_at: index of the wave among all waves of all shares
+  __device__ __forceinline__ void store_share(const AttnArgs& a, int64_t wave_at, int lane, bool seen) const {
+    (static_cast<float2*>(a.share_stats) + wave_at * 64)[lane] = float2{seen ? m_run : kMinusInf, l_run};
+    float4* const o = static_cast<float4*>(a.share_o) + wave_at * (D / 8) * 64;
+#pragma unroll
+    for (int i = 0; i < S::kDBlocks * 4; ++i)
+      (o + i * 64)[lane] = float4{acc_o[i / 4][i % 4 * 4], acc_o[i / 4][i % 4 * 4 + 1], acc_o[i / 4][i % 4 * 4 + 2], acc_o[i / 4][i % 4 * 4 + 3]};
   }
 
   // ---- epilogue: O = O^T / l; a padding query (q_real false) and an empty row give zeros ---------

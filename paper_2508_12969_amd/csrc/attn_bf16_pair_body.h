@@ -30,8 +30,9 @@ using PairShape = Shape<B, 128, 4>;  // four waves that share the tile copies
 
 // The work of one workgroup: entry `item` of the pair tables, batch entry `batch`; lds_k, lds_v: one
 // tile each.  kNat: q, k, v, out in natural token order, gathered and scattered here (see attn_bf16.hip).
-template <int B, bool kNat>
-__device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, int64_t batch, char* lds_k, char* lds_v) {
+// it: the part of its walk (kSplit).
+template <int B, bool kNat, bool kSplit = false>
+__device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, int64_t batch, char* lds_k, char* lds_v, const LaunchItem& it = LaunchItem()) {
   using S = PairShape<B>;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -54,8 +55,8 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, 
 
   // the pair's walk: one word per tile of the union of the two rows, ascending tile ids:
   // tile id | padding class << 24 | bit 30: kept by the first query tile | bit 31: by the second
-  const int64_t begin = a.pair_walk_ptr ? a.pair_walk_ptr[item] : 0;
-  const int count = (int)(a.pair_walk_ptr ? a.pair_walk_ptr[item + 1] - begin : a.n);
+  const int64_t begin = (a.pair_walk_ptr ? a.pair_walk_ptr[item] : 0) + (kSplit ? it.first : 0);
+  const int count = kSplit ? it.count : (int)(a.pair_walk_ptr ? a.pair_walk_ptr[item + 1] - begin : a.n);
   const auto walk = CONST_PTR(int32_t, a.pair_walk + begin);
   const auto class_mask = CONST_PTR(uint32_t, a.class_mask);  // 4 words per class
 
@@ -63,7 +64,7 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, 
   const QuerySlot qs = query_slot<S::B>(a, q_tile, first_slot, w.qi);
   // a wave without a share, without a query tile (odd tile count) or without real queries only moves tiles
   const bool wave_active = wave_used && qs.wave_active && (member == 0 || has_b);
-  const int64_t q_row = kNat ? src.query_row(a, q_tile, qs.slot) : q_tile * S::B + qs.slot;
+  const int64_t q_row = kNat ? natural_query_row(a, q_tile, qs.slot) : q_tile * S::B + qs.slot;
   w.load_q(static_cast<const char*>(a.q) + plane + q_row * S::kRowBytes);
   bool seen = false;  // this wave has processed a tile of its own list (wave-uniform)
 
@@ -131,22 +132,15 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, 
   }
 
   if (!wave_used || (member && !has_b)) return;
+  if constexpr (kSplit) {
+    if (it.share >= 0) {
+      if (wave_active) w.store_share(a, it.share * 4 + wave, lane, seen);
+      return;
+    }
+  }
   w.store(static_cast<char*>(a.out) + plane + q_row * S::kRowBytes, qs.real, !kNat || qs.real);
   if constexpr (!kNat && S::B > 64) {
-    // A packed tile has waves only for the slots that hold tokens; the wave with the tile's last
-    // tokens also writes the zero rows of the padding slots that no wave owns (tile-order output).
-    const int cls_q = CONST_PTR(int32_t, a.tile_class)[q_tile];
-    const auto mask = CONST_PTR(uint32_t, a.class_mask) + cls_q * 4;
-    const int valid = __builtin_popcount(mask[0]) + __builtin_popcount(mask[1]) + __builtin_popcount(mask[2]) + __builtin_popcount(mask[3]);
-    const int owned = (valid + 31) / 32 * 32;
-    if (first_slot + 32 == owned && w.g == 0) {
-      char* tile_out = static_cast<char*>(a.out) + plane + q_tile * (int64_t)S::kTileBytes;
-      for (int s = owned + w.qi; s < S::B; s += 32) {
-        uint4* row = reinterpret_cast<uint4*>(tile_out + (int64_t)a.class_perm[cls_q * 128 + s] * S::kRowBytes);
-#pragma unroll
-        for (int c = 0; c < S::kRowBytes / 16; ++c) row[c] = uint4{0, 0, 0, 0};
-      }
-    }
+    zero_unowned_rows<S::D>(a, static_cast<char*>(a.out) + plane, q_tile, first_slot, lane);
   }
 }
 

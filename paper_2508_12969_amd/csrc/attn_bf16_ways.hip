@@ -81,8 +81,8 @@ __device__ __forceinline__ void mask_granules(floatx16& s, int c0, int c1) {
   }
 }
 
-template <int D, int NW, int NQ, bool kNat>
-__global__ __attribute__((amdgpu_flat_work_group_size(NW * 64, NW * 64), amdgpu_waves_per_eu(D == 64 && NW == 4 ? 4 : 2)))
+template <int D, int NW, int NQ, bool kNat, bool kSplit>
+__global__ __attribute__((amdgpu_flat_work_group_size(NW * 64, NW * 64), amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
 void attn_bf16_ways_kernel(AttnArgs a, int parts) {
   using S = WayShape<D, NW, NQ>;
   __shared__ __attribute__((aligned(1024))) char lds[4 * S::kStageBytes];  // K, V of stage 0, K, V of stage 1
@@ -94,17 +94,24 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qw = wave % NQ, kw = wave / NQ;
-  const int64_t linear = xcd_launch_order(blockIdx.x, gridDim.x);  // (batch, launch-order row, part)
-  const int64_t rows = (int64_t)a.num_heads * a.n;
-  const int part = (int)(linear % parts);
-  const int64_t item = linear / parts % rows, batch = linear / parts / rows;
-  const int64_t row = a.order ? CONST_PTR(int32_t, a.order)[item] : item;
+  int64_t batch, row, share = -1;
+  int part, first_tile = 0, count;
+  if constexpr (kSplit) {
+    const LaunchItem it = split_item(a);
+    batch = it.batch, row = it.entry, part = it.part, first_tile = it.first, count = it.count, share = it.share;
+  } else {
+    const int64_t linear = xcd_launch_order(blockIdx.x, gridDim.x);  // (batch, launch-order row, part)
+    const int64_t rows = (int64_t)a.num_heads * a.n, item = linear / parts % rows;
+    part = (int)(linear % parts);
+    batch = linear / parts / rows;
+    row = a.order ? CONST_PTR(int32_t, a.order)[item] : item;
+    count = (int)(a.row_ptr ? CONST_PTR(int64_t, a.row_ptr)[row + 1] - CONST_PTR(int64_t, a.row_ptr)[row] : a.n);
+  }
   const int64_t head = row / a.n, q_tile = row - head * a.n;
   const int64_t plane = (batch * a.num_heads + head) * (kNat ? a.N_real : a.n * (int64_t)a.B) * S::kRowBytes;
   const char* Kp = static_cast<const char*>(a.k) + plane;
   const char* Vp = static_cast<const char*>(a.v) + plane;
-  const int64_t begin = a.row_ptr ? CONST_PTR(int64_t, a.row_ptr)[row] : 0;
-  const int count = (int)(a.row_ptr ? CONST_PTR(int64_t, a.row_ptr)[row + 1] - begin : a.n);
+  const int64_t begin = (a.row_ptr ? CONST_PTR(int64_t, a.row_ptr)[row] : 0) + first_tile;
   const auto meta = CONST_PTR(int32_t, a.col_meta + begin);
   const auto tile_origin = CONST_PTR(int32_t, a.tile_origin);
 
@@ -114,9 +121,7 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
   const QuerySlot qs = query_slot<128>(a, q_tile, first_slot, w.qi);
   int64_t q_row;
   if constexpr (kNat) {
-    const int dx = qs.slot % a.tw, run = qs.slot / a.tw, dy = run % a.th, dt = run / a.th;
-    q_row = tile_origin[q_tile] + (q_tile >= a.n_vid ? qs.slot : (dt * a.H + dy) * a.W + dx);
-    q_row = q_row < a.N_real ? q_row : a.N_real - 1;
+    q_row = natural_query_row(a, q_tile, qs.slot);
   } else {
     q_row = q_tile * a.B + qs.slot;
   }
@@ -261,6 +266,7 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
   // ---- merge: ways 1 .. NK - 1 hand over (reference, sum, O), way 0 adds them up and stores -----------
   constexpr int kOBytes = 32 * D * 4;
   static_assert((NW - NQ) * kOBytes <= 4 * S::kStageBytes, "the shares fit the stage buffers");
+  if (!seen) w.m_run = kMinusInf;
   if constexpr (S::NK > 1) {
     __syncthreads();  // the stage buffers are free
     if (kw > 0) {
@@ -269,16 +275,16 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
 #pragma unroll
       for (int i = 0; i < S::kDBlocks * 4; ++i)
         o[i * 64 + lane] = float4{w.acc_o[i / 4][i % 4 * 4], w.acc_o[i / 4][i % 4 * 4 + 1], w.acc_o[i / 4][i % 4 * 4 + 2], w.acc_o[i / 4][i % 4 * 4 + 3]};
-      lds_stats[from * 64 + lane] = float2{seen ? w.m_run : kMinusInf, w.l_run};
+      lds_stats[from * 64 + lane] = float2{w.m_run, w.l_run};
     }
     __syncthreads();
     if (kw > 0) return;
-    const float own_ref = seen ? w.m_run : kMinusInf;
-    float top = own_ref;
+    float top = w.m_run;
 #pragma unroll
     for (int k = 1; k < S::NK; ++k) top = fmaxf(top, lds_stats[((k - 1) * NQ + qw) * 64 + lane].x);
     // a way without a key has weight 0, also where no way has one (top is -inf)
-    const float f0 = own_ref == kMinusInf ? 0.f : __builtin_amdgcn_exp2f((own_ref - top) * w.c2);
+    const float f0 = w.m_run == kMinusInf ? 0.f : __builtin_amdgcn_exp2f((w.m_run - top) * w.c2);
+    w.m_run = top;
     w.l_run *= f0;
 #pragma unroll
     for (int db = 0; db < S::kDBlocks; ++db) w.acc_o[db] *= f0;
@@ -299,17 +305,25 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
       }
     }
   }
+  if constexpr (kSplit) {
+    if (share >= 0) {
+      if (qs.wave_active) w.store_share(a, share * NQ + qw, lane, w.m_run != kMinusInf);
+      return;
+    }
+  }
   w.store(out_row, qs.real, !kNat || qs.real);
 }
 
 template <int D, int NW, int NQ>
 hipError_t launch(const AttnArgs& a, hipStream_t stream) {
   const int parts = a.B / (32 * NQ);
-  const int64_t workgroups = (int64_t)a.batch * a.num_heads * a.n * parts;
+  const int64_t entries = a.items ? a.num_items : (int64_t)a.num_heads * a.n * parts;
+  const int64_t workgroups = a.batch * entries;
   if (parts < 1 || workgroups > 0xffffffffll / (NW * 64)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)workgroups), block(NW * 64);
-  if (a.natural) hipLaunchKernelGGL((attn_bf16_ways_kernel<D, NW, NQ, true>), grid, block, 0, stream, a, parts);
-  else hipLaunchKernelGGL((attn_bf16_ways_kernel<D, NW, NQ, false>), grid, block, 0, stream, a, parts);
+  const auto kernel = a.items ? (a.natural ? attn_bf16_ways_kernel<D, NW, NQ, true, true> : attn_bf16_ways_kernel<D, NW, NQ, false, true>)
+                              : (a.natural ? attn_bf16_ways_kernel<D, NW, NQ, true, false> : attn_bf16_ways_kernel<D, NW, NQ, false, false>);
+  hipLaunchKernelGGL(kernel, grid, block, 0, stream, a, parts);
   return hipGetLastError();
 }
 

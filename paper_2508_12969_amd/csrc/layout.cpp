@@ -426,7 +426,7 @@ struct LaunchCost {
 
 // `walks`: steps of the workgroups of one batch entry in launch order, below zero: no token, returns at once.  A launch that
 // cannot take less than `limit` is not followed to its end.
-double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t batch, double gathered, double limit) {
+double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t batch, double gathered, double limit, int64_t chunk = kXcdChunk) {
   constexpr int64_t kXcds = 8, kXcdCus = 32;
   constexpr int64_t kExact = 6000;  // workgroups; beyond, rounds and XCDs even out
   const int64_t entries = (int64_t)walks.size(), total = entries * batch;
@@ -455,7 +455,7 @@ double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t
   for (int64_t xcd : {0, 7}) {  // the ends of a round of chunks, and even and odd ids; all eight give the same choices
     free_at.clear();
     for (int64_t id = xcd; id < total; id += kXcds) {
-      const float w = walks[(size_t)(xcd_launch_order(id, total) % entries)];
+      const float w = walks[(size_t)(xcd_launch_order(id, total, chunk) % entries)];
       double t = w < 0 ? 0.1 * slot : slot * w + c.group;
       if (free_at.size() < places) {
         free_at.push_back(t);
@@ -477,11 +477,113 @@ double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t
   return c.start + longer * end;
 }
 
+constexpr double kMergeLaunch = 2.0;   // us: the second launch
+constexpr double kMergeByte = 0.6e-6;  // us per byte of the shares, written and read
+
 struct WayCost {
   Ways ways;
   int stage_keys, part_queries;
   LaunchCost cost;
 };
+
+constexpr double kSplitGain = 0.9;  // rows are split if that is predicted to take this much of the time
+
+// What a workgroup of an unsplit launch walks: an entry of its launch order and a part of the row's query slots.
+struct Unit {
+  int32_t entry, part;
+  int64_t tiles;  // of its list; 0: no token, or no key
+};
+
+// Splits the units of a launch (of one batch entry) along the keys for the kernel `ways` (kWaysNone: the one-tile or paired kernel)
+// of workgroups of `waves` 32-query waves, and takes the best such plan into `plan` (and its time into `best`) if it is predicted to
+// take less than `best`.  step_of: steps of 128 keys of so many tiles.
+template <class StepOf>
+void plan_split(const ca_layout& L, const std::vector<Unit>& units, Ways ways, int waves, const LaunchCost& cost, double gathered, StepOf step_of, double& best,
+                SplitPlan& plan) {
+  const int64_t batch = L.prob.batch, bytes = batch * share_bytes(32 * waves, L.prob.head_dim);
+  double steps = 0;
+  int64_t longest = 0;
+  for (const Unit& u : units) {
+    steps += step_of(u.tiles) * (double)batch;
+    longest = std::max(longest, u.tiles);
+  }
+  if ((int64_t)units.size() > kMaxSplitItems || longest < 2) return;
+  // what leaving a share costs its workgroup: with one to a CU nothing runs meanwhile
+  const double share_steps = ways == kWaysNone ? 0.0 : cost.per_cu == 1 ? 2.0 : 1.0;
+  const double places = 256.0 * cost.per_cu, tiles_of_step = (double)longest / step_of(longest), per_place = steps / places;
+  const double full_step = (1 + cost.gather * gathered) * std::max(cost.step * cost.per_cu, cost.walk), full_group = (1 + cost.gather * gathered) * cost.group / places;
+  if (kMergeLaunch + cost.start + full_step * per_place >= best) return;
+
+  // How a launch is cut: no item of more than `limit` tiles (a share of what a place has to do in all, two steps at least),
+  // and the last rows, those with `tail` of the work, into items of `small` tiles, which even out what the others leave.
+  struct Cut {
+    int64_t limit, small;
+    double tail;
+  } taken{0, 0, 0};
+  auto for_pieces = [&](const Cut& cut, auto&& visit) {  // visit(unit, pieces)
+    double seen = 0;
+    for (const Unit& u : units) {
+      const int64_t most = seen < (1 - cut.tail) * steps ? cut.limit : cut.small;
+      seen += step_of(u.tiles) * (double)batch;
+      visit(u, std::max<int64_t>(1, (u.tiles + most - 1) / most));
+    }
+  };
+  auto tiles_of = [&](double share) { return std::max((int64_t)std::ceil(std::max(share * per_place, 2.0) * tiles_of_step), (int64_t)1); };
+  std::vector<int32_t> whole, shared;  // items of so many tiles
+  std::vector<float> walks;
+  std::vector<std::pair<int64_t, int64_t>> tried;
+  for (double tail : {0.0, 0.12, 0.3}) {
+    for (double share : {1.1, 0.6, 0.4, 0.25}) {
+      const Cut cut{tiles_of(share), tail > 0 ? std::min(tiles_of(share), tiles_of(0.12)) : tiles_of(share), tail};
+      int64_t items = 0, shares = 0, splits = 0;
+      for_pieces(cut, [&](const Unit&, int64_t pieces) {
+        items += pieces;
+        if (pieces > 1) shares += pieces, ++splits;
+      });
+      if (splits == 0 || items > kMaxSplitItems || shares * bytes > kMaxShareBytes) continue;
+      if (std::find(tried.begin(), tried.end(), std::make_pair(items, splits)) != tried.end()) continue;
+      tried.push_back({items, splits});
+      const double room = best - kMergeLaunch - (double)(shares * bytes) * kMergeByte;
+      if (cost.start + full_step * (per_place + share_steps * (double)(shares * batch) / places) + full_group * (double)(items * batch) >= room) continue;
+      whole.assign((size_t)longest + 1, 0);
+      shared.assign((size_t)longest + 1, 0);
+      for_pieces(cut, [&](const Unit& u, int64_t pieces) {  // the sizes differ by one at most
+        (pieces > 1 ? shared : whole)[(size_t)(u.tiles / pieces)] += (int32_t)(pieces - u.tiles % pieces);
+        if (u.tiles % pieces) (pieces > 1 ? shared : whole)[(size_t)(u.tiles / pieces + 1)] += (int32_t)(u.tiles % pieces);
+      });
+      walks.clear();
+      for (int64_t t = longest; t >= 0; --t) {
+        const double w = t ? step_of(t) : 0;
+        walks.insert(walks.end(), (size_t)whole[(size_t)t], t ? (float)w : -1.f);
+        walks.insert(walks.end(), (size_t)shared[(size_t)t], (float)(w + share_steps));
+      }
+      const double t = launch_time(cost, walks, batch, gathered, room, kXcdSplitChunk);
+      if (t < room) {
+        best -= room - t;
+        taken = cut;
+      }
+    }
+  }
+  if (taken.limit == 0) return;
+  plan = SplitPlan{};
+  plan.ways = ways;
+  plan.waves = waves;
+  for_pieces(taken, [&](const Unit& u, int64_t pieces) {
+    if (pieces > 1) plan.merges.push_back({u.entry, u.part, plan.shares, (int32_t)pieces});
+    for (int64_t k = 0; k < pieces; ++k) {
+      const int64_t first = u.tiles * k / pieces, end = u.tiles * (k + 1) / pieces;
+      const int32_t share_id = pieces > 1 ? ++plan.shares : 0;
+      plan.items.push_back({u.entry, (int32_t)first, (int32_t)(end - first), u.part | share_id << 2});
+    }
+  });
+  // longest first; of equal ones, those that read the same keys together (xcd_launch_order keeps neighbours on one XCD)
+  auto head_of = [&](int64_t e) { return (e < 0 ? L.pair_rows[2 * ~e] : e) / L.n; };
+  std::stable_sort(plan.items.begin(), plan.items.end(), [&](const WorkItem& x, const WorkItem& y) {
+    if (x.count != y.count) return x.count > y.count;
+    const int64_t hx = head_of(x.entry), hy = head_of(y.entry);
+    return hx != hy ? hx < hy : x.first < y.first;
+  });
+}
 
 }  // namespace
 
@@ -529,7 +631,8 @@ std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int6
 // none of these is slower; of the 480 one is, by 3 %.  A model of the sums and the longest walk alone (residual
 // 10-18 %), from a predicted 10 % on, made twelve of the 480 slower by up to 25 %, eleven of them launches of one to
 // three rounds of workgroups.
-Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words) {
+Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* plan) {
+  if (plan) *plan = SplitPlan{};
   const ca_problem& p = L.prob;
   if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
   // 32-bit lane offsets inside a tile of the natural order; a grid dimension of fewer than 2^32 threads
@@ -558,7 +661,8 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words) {
     const int64_t tiles = dense ? L.n : e < 0 ? L.pair_walk_ptr[~e + 1] - L.pair_walk_ptr[~e] : L.row_ptr[e + 1] - L.row_ptr[e];
     walks.push_back(paired ? (float)tiles : (float)(tiles * L.B) / 128);
   }
-  double best = 0.87 * launch_time(kPlain[big_d][big_b], walks, p.batch, 0, HUGE_VAL);
+  constexpr double kPlainBias = 0.87;
+  double best = kPlainBias * launch_time(kPlain[big_d][big_b], walks, p.batch, 0, HUGE_VAL);
   Ways ways = kWaysNone;
 
   // the workgroups of the others: every part of every row
@@ -580,6 +684,29 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words) {
     }
     const double t = launch_time(w.cost, walks, p.batch, padded, best);
     if (t < best) best = t, ways = w.ways;
+  }
+  if (plan) {
+    best *= kSplitGain / (ways == kWaysNone ? kPlainBias : 1.0);
+    std::vector<Unit> units;
+    for (int64_t i = 0; i < plain_groups; ++i) {
+      const int64_t e = paired ? ~i : dense && !L.packed_faces ? i : launched[i];
+      units.push_back({(int32_t)e, 0, dense ? L.n : e < 0 ? L.pair_walk_ptr[~e + 1] - L.pair_walk_ptr[~e] : L.row_ptr[e + 1] - L.row_ptr[e]});
+    }
+    // only in the place of themselves: they multiply the padding slots of K and V too (by zero), the others never read them
+    if (ways == kWaysNone) plan_split(L, units, kWaysNone, paired ? 4 : (int)L.B / 32, kPlain[big_d][big_b], 0, [&](int64_t tiles) { return paired ? (double)tiles : (double)(tiles * L.B) / 128; },
+                                      best, *plan);
+    for (int i = 0; i < count; ++i) {
+      const WayCost& w = options[i];
+      const int parts = (int)L.B / w.part_queries;
+      const double stage = w.stage_keys / 16;
+      units.clear();
+      for (int64_t j = 0; j < (int64_t)L.order.size(); ++j) {
+        const int64_t r = dense ? j : L.order[j];
+        const int held = (tokens[L.tile_class[r % L.n]] + w.part_queries - 1) / w.part_queries;
+        for (int part = 0; part < parts; ++part) units.push_back({(int32_t)r, part, part >= held ? 0 : dense ? L.n : L.row_ptr[r + 1] - L.row_ptr[r]});
+      }
+      plan_split(L, units, w.ways, w.part_queries / 32, w.cost, padded, [&](int64_t tiles) { return std::ceil((double)tiles * per_tile / stage) * stage / 8; }, best, *plan);
+    }
   }
   return ways;
 }
@@ -640,8 +767,8 @@ void finish_host_tables(ca_layout& L) {
   build_launch_splits(L);
   L.simd_waves = choose_simd_waves(L, false);
   L.simd_waves_dense = choose_simd_waves(L, true);
-  L.ways = choose_ways(L, false, kSampledWords);
-  L.ways_dense = choose_ways(L, true, kSampledWords);
+  L.ways = choose_ways(L, false, kSampledWords, &L.split);
+  L.ways_dense = choose_ways(L, true, kSampledWords, &L.split_dense);
 }
 
 int import_host_tables(ca_layout& L, const int64_t* const* row_ptr, const int32_t* const* col_idx) {

@@ -41,6 +41,7 @@ constexpr int64_t kPoolMinItems = 4096; // smaller launches are dealt statically
 // `work[i]`: cost of launch-order entry i (tile steps); returns the split of one batch entry's launch.
 LaunchSplit split_launch(const int64_t* work, int64_t entries);
 
+constexpr int kXcdSplitChunk = 32;      // the same where rows are split along the keys: such launches are small
 constexpr int kXcdChunk = 64;           // consecutive launch-order entries handed to one XCD
 
 // Launch-order entry of a workgroup id.  Workgroup ids are dealt round-robin to the 8 XCDs, each
@@ -52,18 +53,46 @@ constexpr int kXcdChunk = 64;           // consecutive launch-order entries hand
 // alternating direction, which evens out the work per XCD (measured at the 130K-token layouts:
 // 1.4 % faster at 65 % sparsity, 2.3 % at 80 %, against chunks of 32 always dealt in the same
 // direction).  Ids past the last full round keep their place.
-constexpr int64_t xcd_launch_order(int64_t id, int64_t total) {
-  const int64_t span = 8 * (int64_t)kXcdChunk;
+constexpr int64_t xcd_launch_order(int64_t id, int64_t total, int64_t chunk = kXcdChunk) {
+  const int64_t span = 8 * chunk;
   if (id >= total / span * span) return id;
-  const int64_t xcd = id & 7, seq = id >> 3, round = seq / kXcdChunk;
-  return round * span + ((round & 1) ? 7 - xcd : xcd) * kXcdChunk + seq % kXcdChunk;
+  const int64_t xcd = id & 7, seq = id >> 3, round = seq / chunk;
+  return round * span + ((round & 1) ? 7 - xcd : xcd) * chunk + seq % chunk;
 }
 
 // The kernels of attn_bf16_ways.hip: waves of a workgroup x 32-query waves side by side.
 enum Ways : int32_t { kWaysNone = 0, kWays4x4, kWays8x4, kWays8x2 };
 
-// Device-resident tables.  All pointers are device memory owned by the layout.
+// Launches whose longest rows would outlast everything else, or that leave CUs without work, are split along the
+// keys: a workgroup takes `count` tiles of the list of a launch-order
+// entry (a row, or the complement of a workgroup of two query tiles), from its `first` on, and leaves what it has summed up to then in
+// a workspace, from which a second kernel adds up the shares of a row.  place: part of the row's query slots | (share + 1) << 2,
+// without a share for a row that is one item and writes its output itself.
+struct WorkItem {
+  int32_t entry, first, count, place;
+};
+struct MergeItem {
+  int32_t entry, part, first_share, shares;
+};
+struct SplitPlan {  // of one batch entry; empty: rows are not split
+  Ways ways = kWaysNone;
+  std::vector<WorkItem> items;    // longest first
+  std::vector<MergeItem> merges;
+  int32_t shares = 0;
+  int32_t waves = 0;              // 32-query waves of an item
+};
+constexpr int64_t kMaxSplitItems = 8192;
+constexpr int64_t kMaxShareBytes = (int64_t)64 << 20;  // of all batch entries
+// A share of `queries` queries: (reference, sum) of every lane of its 32-query waves, and O in fp32.
+constexpr int64_t share_stats_bytes(int64_t queries) { return queries / 32 * 64 * 8; }
+constexpr int64_t share_bytes(int64_t queries, int64_t head_dim) { return share_stats_bytes(queries) + queries * head_dim * 4; }
+inline int64_t workspace_bytes(const SplitPlan& plan, int64_t batch, int64_t head_dim) {
+  return plan.shares * batch * share_bytes(32 * plan.waves, head_dim);
+}
+
+// Device-resident tables, parts of one block of device memory owned by the layout.
 struct DeviceTables {
+  unsigned char* block = nullptr;
   int64_t* row_ptr = nullptr;    // [num_heads*n + 1] offsets into col_idx (global over heads)
   int32_t* col_meta = nullptr;   // [nnz] kept key tiles, ascending inside each row: tile id | class << 24
   int32_t* dense_meta = nullptr; // [n] the same packing for the list 0..n-1 (dense walk)
@@ -80,6 +109,8 @@ struct DeviceTables {
   SlotMask* class_mask = nullptr; // [num_classes]
   uint8_t* class_perm = nullptr;  // [num_classes * 128] per class: its valid slots ascending, then its padding slots ascending
   int32_t* tile_origin = nullptr; // [n] natural-order row of slot 0 of every tile
+  WorkItem *split_items = nullptr, *split_items_dense = nullptr;      // SplitPlan of the sparse and of the dense walk
+  MergeItem *split_merges = nullptr, *split_merges_dense = nullptr;
   int32_t* pool_counters = nullptr; // [pool_slots] tickets of the dynamically drawn tail of a launch; zero between launches
   int32_t pool_slots = 0;           // concurrent launches on one layout take different counters, round-robin
   float* mass_partial = nullptr;  // workspace of the tile-mass kernel, mass_partial_rows (= most workgroups of its launch) * n * kMassQueries * 2 floats; allocated at its first call
@@ -119,6 +150,7 @@ struct ca_layout {
   ca::LaunchSplit split_rows, split_rows_dense, split_pairs, split_pairs_dense;
   int32_t simd_waves = 2, simd_waves_dense = 2;               // waves per SIMD of the one-tile kernel (choose_simd_waves)
   ca::Ways ways = ca::kWaysNone, ways_dense = ca::kWaysNone;  // kernel of the sparse and of the dense walk, natural order included
+  ca::SplitPlan split, split_dense;                           // rows split along the keys, for calls that bring a workspace
   mutable std::atomic<uint32_t> launch_seq{0};  // picks the pool counter of a launch
 
   // device tables, created once
@@ -133,7 +165,7 @@ struct ca_layout {
   std::vector<unsigned char> static_image;
   struct StaticOffsets {
     size_t row_ptr = 0, col_meta = 0, order = 0, pair_rows = 0, pair_walk_ptr = 0, pair_walk = 0, tile_class = 0,
-           class_mask = 0, class_perm = 0, pool_counter = 0, pair_desc = 0, launch_rows = 0;
+           class_mask = 0, class_perm = 0, pool_counter = 0, pair_desc = 0, launch_rows = 0, split_items = 0, split_merges = 0;
   } static_off;
 };
 
@@ -164,7 +196,7 @@ int pack_device_tables(const ca_layout& layout, bool forward_only, PackedTables&
 // Kernel of the sparse or the dense walk, and the figures of the tiles it goes by; at most about `max_words` kept
 // tiles are looked at.
 constexpr int64_t kSampledWords = 500000;
-Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words);
+Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* plan = nullptr);
 std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int64_t max_words);
 // Derived tables (per-head views, launch order, padding classes) once row_ptr / col_idx are set.
 void finish_host_tables(ca_layout& L);

@@ -1197,3 +1197,89 @@ def test_random_problems_on_every_bf16_kernel(kernel, D, B):
         if done == 4:
             return
     assert False, f"only {done} random problems reach the {kernel} kernel"
+
+
+# ---------------------------------------------------------------- rows split along the keys
+
+_GLOBAL, _LOCAL, _NEAR = [(99, (99, 99), ABSENT)], [(1, (1, 1), ABSENT)], [(0, (0, 1), ABSENT)]
+_MIXED = [_GLOBAL, [], _NEAR]
+
+
+@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,heads,batch", [
+    # few tiles and one head: shares of one or two tiles, tiles of a few tokens
+    ("one-tile", 64, (2, 8, 29), (1, 8, 8), 0, [_GLOBAL], 1),
+    ("one-tile", 64, (2, 8, 40), (2, 8, 8), 0, [_GLOBAL], 1),
+    ("one-tile", 128, (1, 21, 8), (2, 8, 8), 1, [_GLOBAL], 1),
+    ("packed-faces", 128, (1, 8, 20), (2, 8, 8), 1, [_GLOBAL], 1),
+    ("paired", 128, (1, 8, 29), (1, 8, 8), 1, [_GLOBAL], 1),
+    ("ways-4x4", 128, (5, 21, 8), (2, 8, 8), 1, [_GLOBAL], 1),
+    ("ways-8x2", 64, (3, 16, 12), (2, 8, 8), 1, [_GLOBAL], 1),
+    ("ways-8x2", 64, (2, 21, 20), (1, 8, 8), 0, [_GLOBAL], 1),
+    ("ways-8x2", 128, (5, 8, 20), (2, 8, 8), 1, [_GLOBAL], 1),
+    # split and whole rows, empty rows
+    ("one-tile", 64, (7, 8, 8), (1, 8, 8), 1, _MIXED, 2),
+    ("one-tile-3", 64, (16, 8, 20), (1, 8, 8), 1, [_GLOBAL, _GLOBAL, _GLOBAL, _GLOBAL, _LOCAL, _LOCAL, [], _NEAR] * 2, 2),
+    ("one-tile", 128, (2, 30, 8), (2, 8, 8), 1, _MIXED, 2),
+    ("packed-faces", 128, (2, 13, 20), (2, 8, 8), 1, _MIXED, 2),
+    ("paired", 128, (2, 21, 8), (1, 8, 8), 1, _MIXED, 2),
+    ("ways-4x4", 64, (9, 21, 8), (2, 8, 8), 1, _MIXED, 2),
+    ("ways-4x4", 128, (5, 30, 8), (2, 8, 8), 1, _MIXED, 2),
+    ("ways-8x4", 128, (5, 8, 40), (2, 8, 8), 1, _MIXED, 2),
+    ("ways-8x2", 64, (9, 13, 8), (2, 8, 8), 1, _MIXED, 2),
+    ("ways-8x2", 128, (16, 30, 8), (1, 8, 8), 1, _MIXED, 2),
+])
+def test_rows_split_along_the_keys(kernel, D, grid, tile, text_tiles, heads, batch):
+    """Launches whose rows are shared by several workgroups: against the oracle with peaked rows, whatever the workspace holds
+    before the call; natural order, the static entry point, a second stream and a replayed graph bit for bit; the C call without a
+    workspace to within the rounding of bf16 probabilities."""
+    import ctypes
+    import dataclasses
+    _say("split rows", kernel, D, grid, tile, batch)
+    B = tile[0] * tile[1] * tile[2]
+    wl = dataclasses.replace(make_workload("split", *grid, tile, text_tiles * B, len(heads), D, "bf16", heads), batch=batch)
+    g = geometry_of(wl)
+    lay = build_layout(ca, wl)
+    nbytes, name = ca.compact_attn_layout_split(lay)
+    assert name == kernel and nbytes > 0
+    q, k, v = make_qkv(wl, DEV, q_gain=3.0)
+    del_me = torch.full((nbytes // 2,), float("nan"), dtype=torch.bfloat16, device=DEV)  # the allocator's next block of that size
+    del del_me
+    out, out_tiled = gpu_attention(ca, wl, lay, q, k, v)
+    for h in range(len(heads)):
+        qkv = [to_f64(x[batch - 1, h])[None] for x in (q, k, v)]
+        _say(h, compare(to_f64(out[batch - 1, h])[None], OA.masked_attention(g, [heads[h]], *qkv), *tolerances("bf16"), what=kernel))
+    held = ca.compact_attn_permute(torch.ones_like(q), lay) != 0
+    assert torch.all(out_tiled[~held] == 0)
+    assert torch.equal(ca.compact_attn_forward_natural(q, k, v, lay, out=torch.full_like(q, float("nan"))), out)
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    again = torch.full_like(qp, float("nan"))
+    assert torch.equal(ca.compact_attn_forward_static(qp, kp, vp, lay, out=again), out_tiled)
+    side = torch.cuda.Stream()
+    on_side = [torch.full_like(qp, float("nan")) for _ in range(2)]
+    side.wait_stream(torch.cuda.current_stream())
+    for x in on_side:
+        ca.compact_attn_forward(qp, kp, vp, lay, out=x, stream=side)
+    with_main = ca.compact_attn_forward(qp, kp, vp, lay)            # may overlap with them
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, out_tiled) for x in (*on_side, with_main))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ca.compact_attn_forward(qp, kp, vp, lay, out=again)
+    for rep in range(3):
+        again.fill_(float("nan"))
+        graph.replay()
+        assert torch.equal(ca.compact_attn_forward(qp, kp, vp, lay), out_tiled)
+        torch.cuda.synchronize()
+        assert torch.equal(again, out_tiled), f"replay {rep}"
+    # the C calls: without a workspace, and with one that will not do
+    lib, stream = ca.load_library(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    ptrs = [ctypes.c_void_p(x.data_ptr()) for x in (qp, kp, vp)]
+    assert lib.compact_attn_forward(*ptrs, lay.handle, ctypes.c_void_p(again.data_ptr()), stream) == 0
+    compare(to_f64(again), to_f64(out_tiled), *tolerances("bf16"), what="without a workspace")
+    work = torch.empty(nbytes + 16, dtype=torch.uint8, device=DEV)
+    before = again.clone()
+    for at, size in ((None, nbytes), (work.data_ptr(), nbytes - 1), (work.data_ptr() + 1, nbytes), (qp.data_ptr(), nbytes)):
+        status = lib.compact_attn_forward_with_workspace(*ptrs, lay.handle, ctypes.c_void_p(again.data_ptr()), 0, ctypes.c_void_p(at), size, stream)
+        assert status == -1, (at, size)
+    torch.cuda.synchronize()
+    assert torch.equal(again, before)
