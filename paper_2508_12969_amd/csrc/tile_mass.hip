@@ -233,10 +233,10 @@ void tile_mass_kernel(MassArgs a) {
     lds_inv[mine] = (qs.real && l_row > 0.f) ? 1.0f / l_row : 0.f;  // a padding query adds nothing
     lds_ref[mine] = w.m_run;
   }
-  // The stored pairs are read back by other waves of this workgroup only, so the barrier's own order (workgroup scope: the
-  // stores are waited for, the waves share an L1) is enough.  A device-wide fence in every wave writes back the XCD's L2
-  // each time, for all of its workgroups: 0.1 us
-  // per group of queries and launch, 12 heads of 12.5K tokens of head dim 64 627 -> 482 us, 6 heads of 4K 57 -> 44 us.
+  // The stored pairs are read back by other waves of this workgroup only, which share an L1: waiting for the stores and the
+  // barrier's order are enough.  A device-wide fence in every wave writes back the XCD's L2 each time, for all of its
+  // workgroups, 0.1 us per group of queries: 12 heads of 12.5K tokens of head dim 64 627 -> 482 us without it, 6 heads of 4K 57 -> 44 us.
+  WAIT_VMCNT(0);
   __syncthreads();
   constexpr int kLanesPerTile = Q / 4;  // a key tile's Q pairs, four per lane
   constexpr int kTilesPerPass = 256 / kLanesPerTile;
