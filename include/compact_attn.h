@@ -298,9 +298,11 @@ int compact_attn_forward_with_workspace(const void* q, const void* k, const void
  *   device memory, W = the workgroups the device holds at a time: two per compute unit for 128-token
  *   tiles of head dim 128 (0.54 GB for 130K tokens on 256 compute units), else three (0.99 GB for 75.6K
  *   tokens in 64-token tiles), or two where the device has no room for three (the calls of that layout
- *   then run with two workgroups per compute unit).  It does so synchronously (refused with
- *   CA_ERR_INVALID_ARG on a stream under capture: call once before capturing), and the layout owns the
- *   workspace until compact_attn_free_layout.  Calls on the same
+ *   then run with two workgroups per compute unit).  Where the rows leave places empty, up to 1.5 W groups
+ *   of 128 queries, several workgroups share the key tiles of a group: then it is
+ *   batch * heads * ceil(n * B / 128) * (n + 4) * 1024 bytes, if the device has room for that.  It does so
+ *   synchronously (refused with CA_ERR_INVALID_ARG on a stream under capture: call once before capturing),
+ *   and the layout owns the workspace until compact_attn_free_layout.  Calls on the same
  *   layout that overlap in time (different streams) would share that workspace and race: give
  *   concurrent calls a layout each.  CA_ERR_ALLOC if the allocation fails.
  * Supported: bf16 with (B, D) in {64,128} x {64,128}; otherwise CA_ERR_UNSUPPORTED. */

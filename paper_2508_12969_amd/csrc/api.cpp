@@ -189,18 +189,23 @@ int ensure_mass_workspace(ca_layout* L, hipStream_t stream) {
   if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
   if (cus < 1) cus = 1;
   const int64_t rows_total = (int64_t)L->prob.batch * L->prob.num_heads * ca::mass_row_groups(L->n, L->B);
-  int64_t rows = 0;
-  size_t bytes = 0;
+  const int64_t places = (int64_t)cus * ca::mass_workgroups_per_cu(L->B, L->prob.head_dim);
+  const int64_t step_tiles = ca::mass_step_keys(L->B, L->prob.head_dim) / L->B;
+  const int64_t wanted_shares = ca::mass_shares(rows_total, places, (L->n + step_tiles - 1) / step_tiles);
+  int64_t rows = 0, shares = 1;
+  size_t bytes = 0;  // of the workspace; the ticket counter follows
   void* p = nullptr;
-  // If memory is short, blocks for two workgroups per CU: any number will do, but the layout keeps what it
+  // A block for every row group where its key tiles are shared by several workgroups.  If memory is short, for
+  // as many as run at a time, then for two workgroups per CU: any number will do, but the layout keeps what it
   // gets here, and fewer would slow down every later call.
-  for (int per_cu = ca::mass_workgroups_per_cu(L->B, L->prob.head_dim);; --per_cu) {
-    rows = std::max<int64_t>(1, std::min(rows_total, (int64_t)cus * per_cu));
-    bytes = (size_t)rows * (size_t)L->n * ca::kMassQueries * 2 * sizeof(float);
-    e = hipMalloc(&p, bytes + 256);  // the ticket counter follows the workspace
+  for (int per_cu = ca::mass_workgroups_per_cu(L->B, L->prob.head_dim), shared = wanted_shares > 1;; shared ? shared = 0 : --per_cu) {
+    shares = shared ? wanted_shares : 1;
+    rows = shared ? rows_total : std::max<int64_t>(1, std::min(rows_total, (int64_t)cus * per_cu));
+    bytes = (size_t)rows * (size_t)(L->n + (shares > 1 ? shares : 0)) * ca::kMassQueries * 2 * sizeof(float);
+    e = hipMalloc(&p, bytes + 256);
     if (e == hipSuccess) break;
     (void)hipGetLastError();
-    if (e == hipErrorOutOfMemory && per_cu > 2) continue;
+    if (e == hipErrorOutOfMemory && (shared || per_cu > 2)) continue;
     set_error("hipMalloc of the tile-mass workspace (%zu bytes): %s", bytes, hipGetErrorString(e));
     return CA_ERR_ALLOC;
   }
@@ -211,6 +216,9 @@ int ensure_mass_workspace(ca_layout* L, hipStream_t stream) {
   }
   L->dev.mass_partial = static_cast<float*>(p);
   L->dev.mass_partial_rows = rows;
+  L->dev.mass_places = places;
+  L->dev.mass_shares = (int32_t)shares;
+  L->dev.mass_share_stats = L->dev.mass_partial + rows * L->n * ca::kMassQueries * 2;
   L->dev.mass_counter = reinterpret_cast<int32_t*>(static_cast<char*>(p) + bytes);
   return CA_OK;
 }
@@ -784,6 +792,9 @@ int compact_attn_tile_mass(const void* q, const void* k, ca_layout* L, float* ma
   a.partial = L->dev.mass_partial;
   a.partial_rows = L->dev.mass_partial_rows;
   a.counter = L->dev.mass_counter;
+  a.places = L->dev.mass_places;
+  a.shares = L->dev.mass_shares;
+  a.share_stats = L->dev.mass_share_stats;
   a.dense_meta = L->dev.dense_meta;
   a.tile_class = L->dev.tile_class;
   a.class_mask = L->dev.class_mask;

@@ -86,13 +86,29 @@ inline int64_t mass_row_groups(int64_t n, int64_t B) { return (n * B + kMassQuer
 // Workgroups of four waves that a CU holds: the kernel is bound by the vector ALU (an exponential per
 // score), and a third wave per SIMD fills what two leave; 128-token tiles of head dim 128 take too much LDS.
 constexpr int mass_workgroups_per_cu(int64_t B, int D) { return B == 128 && D == 128 ? 2 : 3; }
+constexpr int mass_step_keys(int64_t B, int D) { return B == 64 && D == 128 ? 64 : 128; }  // keys a workgroup stages at a time
+constexpr int kMassMergeTiles = 32;  // key tiles that a workgroup of the merge adds up
+// Workgroups that share the key tiles of a row group, `steps` steps of the kernel.  Four where that fills the card better: up to
+// 1.5 launches of as many workgroups as it holds, of which at least 15 % of the places would stay empty, and a walk long enough to
+// pay for the merge (4 us).  Measured, whole / four shares: head dim 64, 320 groups on 768 places 491 / 324 us, 565 256 / 210 us,
+// 1120 496 / 428 us; head dim 128, 280 groups on 512 255 / 182 us, 560 459 / 313 us, 882 on 768 1191 / 1141 us.  Past the lines:
+// 704 on 768 217 / 218 us, 1356 479 / 495 us, 1808 623 / 658 us, 192 groups of 16 steps 26 / 31 us (32 steps: 41 / 38, 32 groups
+// of 16 steps 22 / 15).  Two or eight shares are 0-30 % slower, but for a few shapes where eight are up to 6 % faster.
+inline int64_t mass_shares(int64_t groups, int64_t places, int64_t steps) {
+  const int64_t rounds = (groups + places - 1) / places;
+  if (2 * groups > 3 * places || 20 * groups > 17 * rounds * places) return 1;
+  return steps >= (16 * groups <= places ? 16 : 32) ? 4 : 1;
+}
 
 struct MassArgs {
   const void* q;               // [batch, heads, N_pad, D] tile order, bf16
   const void* k;
   float* mass;                 // [batch, heads, n, n]
-  float* partial;              // device workspace, partial_rows * n * kMassQueries * 2 floats: per query and key tile (sum, reference) of the row group a workgroup is working on
-  int64_t partial_rows;        // blocks of the workspace = most workgroups a launch may have
+  float* partial;              // device workspace, partial_rows * n * kMassQueries * 2 floats: per query and key tile (sum, reference) of the row group a workgroup is working on (of every row group, where these have several shares)
+  int64_t partial_rows;        // blocks of the workspace = most workgroups a launch may have, or the row groups where these have several shares
+  int64_t places;              // workgroups that the device holds at a time
+  int32_t shares;              // workgroups that share the key tiles of a row group, see mass_shares
+  float* share_stats;          // device, where shares > 1: [row groups][shares][kMassQueries] (sum, reference)
   int32_t* counter;            // device; the ticket counter, zero before and after every launch
   const int32_t* dense_meta;   // device [n + 2]; per key tile: tile id | padding class << 24 | bit 31: upper key blocks empty
   const int32_t* tile_class;   // device [n]

@@ -115,7 +115,10 @@ struct DeviceTables {
   int32_t pool_slots = 0;           // concurrent launches on one layout take different counters, round-robin
   float* mass_partial = nullptr;  // workspace of the tile-mass kernel, mass_partial_rows (= most workgroups of its launch) * n * kMassQueries * 2 floats; allocated at its first call
   int64_t mass_partial_rows = 0;
-  int32_t* mass_counter = nullptr; // its ticket counter (inside the same allocation)
+  int64_t mass_places = 0;         // workgroups of it that the device holds at a time
+  int32_t mass_shares = 1;         // workgroups that share the key tiles of a row group
+  float* mass_share_stats = nullptr;  // inside the same allocation, as the counter is
+  int32_t* mass_counter = nullptr; // its ticket counter
 };
 
 }  // namespace ca

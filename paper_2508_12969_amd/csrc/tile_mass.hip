@@ -30,6 +30,10 @@
 namespace ca {
 namespace {
 
+// exp2 of a reference against the final one.  None lies above that but those of shares without a finite score, whose sums
+// are zero and must stay so; NaN stays NaN.
+__device__ __forceinline__ float ref_factor(float x) { return __builtin_amdgcn_exp2f(x > 0.f ? 0.f : x); }
+
 constexpr float kSumLimit = 0x1p40f;  // a tile's row sum beyond this moves the query's exponent reference
 
 // 128 queries per workgroup: one query tile of 128 tokens or two neighbours of 64 (the walk is the same
@@ -42,7 +46,7 @@ constexpr float kSumLimit = 0x1p40f;  // a tile's row sum beyond this moves the 
 template <int B, int D>
 struct MassShape {
   static constexpr int kQueries = kMassQueries, kRowTiles = kQueries / B;
-  static constexpr int kStepKeys = B == 64 && D == 128 ? 64 : 128, kStepTiles = kStepKeys / B;
+  static constexpr int kStepKeys = mass_step_keys(B, D), kStepTiles = kStepKeys / B;
   struct Tile : Shape<B, D, 4> {        // what a wave multiplies at a time
     // without it the reads of a whole tile are requested at once (212 instead of 186 registers), and the
     // call takes 53.0 instead of 50.0 ms at the 119K-token layout of 12 heads
@@ -51,7 +55,48 @@ struct MassShape {
   using Step = Shape<kStepKeys, D, 4>;  // what the workgroup copies at a time
 };
 
-template <int B, int D>
+// mass[a, b] = sum_i e[b][i] * exp2(scale' * (m[b][i] - m_i)) / l_i of the key tiles begin .. end - 1 of a row group, by 256
+// threads; part: its block of the workspace, rows: query tiles from its first one to the last of the plane.
+template <int B>
+__device__ __forceinline__ void reduce_tiles(const float2* part, const float* inv_of, const float* ref_of, float c2, int begin, int end, int n,
+                                             int64_t rows, float* out) {
+  constexpr int kLanesPerTile = kMassQueries / 4;  // a key tile's pairs, four per lane
+  constexpr int kTilesPerPass = 256 / kLanesPerTile;
+  const int sub = threadIdx.x / kLanesPerTile, l4 = threadIdx.x % kLanesPerTile;
+  const int row_of_lane = l4 * 4 / B;   // which of the workgroup's query tiles
+  const bool stores = l4 * 4 % B == 0 && row_of_lane < rows;
+  const float4 inv = *reinterpret_cast<const float4*>(&inv_of[4 * l4]);
+  const float4 ref = *reinterpret_cast<const float4*>(&ref_of[4 * l4]);
+  // kBatch key tiles per lane at a time, all loads requested before the first is used
+  constexpr int kBatch = 4;
+  static_assert(kBatch * kTilesPerPass == kMassMergeTiles, "a workgroup of the merge takes one batch");
+  for (int b0 = begin + sub; b0 < end; b0 += kBatch * kTilesPerPass) {
+    float4 p01[kBatch], p23[kBatch];  // (e0, m0, e1, m1), (e2, m2, e3, m3)
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int b = min(b0 + u * kTilesPerPass, end - 1);  // past the end: a valid tile, not stored
+      const float4* p = reinterpret_cast<const float4*>(part + (int64_t)b * kMassQueries + 4 * l4);
+      p01[u] = p[0];
+      p23[u] = p[1];
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int b = b0 + u * kTilesPerPass;
+      const float t0 = p01[u].x * ref_factor((p01[u].y - ref.x) * c2) * inv.x;
+      const float t1 = p01[u].z * ref_factor((p01[u].w - ref.y) * c2) * inv.y;
+      const float t2 = p23[u].x * ref_factor((p23[u].y - ref.z) * c2) * inv.z;
+      const float t3 = p23[u].z * ref_factor((p23[u].w - ref.w) * c2) * inv.w;
+      float s = (t0 + t1) + (t2 + t3);
+#pragma unroll
+      for (int sh = B / 8; sh >= 1; sh >>= 1) s += __shfl_xor(s, sh, 64);
+      if (stores && b < end) out[row_of_lane * (int64_t)n + b] = s;
+    }
+  }
+}
+
+// kSplit: the key tiles of a row group are shared by several workgroups, see mass_shares.  Each leaves its sums and, for
+// every query, its total and reference; tile_mass_merge_kernel finishes.
+template <int B, int D, bool kSplit>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(mass_workgroups_per_cu(B, D), mass_workgroups_per_cu(B, D))))
 void tile_mass_kernel(MassArgs a) {
   using M = MassShape<B, D>;
@@ -65,9 +110,8 @@ void tile_mass_kernel(MassArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t groups = (a.n + M::kRowTiles - 1) / M::kRowTiles;  // per head
-  const int total = (int)((int64_t)a.batch * a.num_heads * groups);
-  // this workgroup's block of the workspace: [n][Q] pairs (sum, reference), reused item after item
-  float2* part = reinterpret_cast<float2*>(a.partial) + (int64_t)blockIdx.x * a.n * Q;
+  const int shares = kSplit ? a.shares : 1;  // items per row group, each a part of its key tiles
+  const int total = (int)((int64_t)a.batch * a.num_heads * groups) * shares;
   // one packed word per key tile 0..n-1: tile id | padding class << 24 | bit 31: upper key blocks empty
   const auto meta = CONST_PTR(int32_t, a.dense_meta);
   const auto class_mask = CONST_PTR(uint32_t, a.class_mask);  // 4 words per class
@@ -79,7 +123,7 @@ void tile_mass_kernel(MassArgs a) {
   const LdsTile k_tile = (LdsTile)lds_k;
 
   // The grid is at most as many workgroups as the card holds at a time; each takes (batch, head, row
-  // group) items of the launch by ticket until none is left, so an XCD that runs faster takes more.
+  // group, share) items of the launch by ticket until none is left, so an XCD that runs faster takes more.
   // Every workgroup draws once more than it has items; whoever draws the last ticket of all zeroes the
   // counter for the next launch.
   for (;;) {
@@ -90,7 +134,13 @@ void tile_mass_kernel(MassArgs a) {
   }
   __syncthreads();
   if (lds_ticket >= total) return;  // all threads of the workgroup alike
-  const int64_t item = lds_ticket;  // (batch, head, row group), row-major
+  const int64_t item = kSplit ? lds_ticket / shares : lds_ticket;  // (batch, head, row group), row-major
+  const int share = kSplit ? lds_ticket % shares : 0;
+  const int first_step = kSplit ? (int)((int64_t)share * steps / shares) : 0;
+  const int end_step = kSplit ? (int)((int64_t)(share + 1) * steps / shares) : steps;
+  // the block of the workspace, [n][Q] pairs (sum, reference): the row group's if several workgroups fill it, else the
+  // workgroup's own, reused item after item
+  float2* part = reinterpret_cast<float2*>(a.partial) + (kSplit ? item : (int64_t)blockIdx.x) * a.n * Q;
   const int64_t plane_id = item / groups;        // (batch, head)
   const int64_t first_row = item % groups * M::kRowTiles;
   const int64_t plane = plane_id * a.n * (int64_t)S::kTileBytes;
@@ -108,25 +158,26 @@ void tile_mass_kernel(MassArgs a) {
   const int mine = wave * 32 + w.qi;  // this lane's query in the workspace block and in lds_inv
   const bool writer = w.g == 0;       // both lanes of a pair hold the query's sum; the lower one stores it
 
-  if (my_key_tile < n) k_loader.issue(Kp, lds_k_addr, wave);
+  if (first_step * KT + my_key_tile < n)
+    k_loader.issue(Kp + (int64_t)first_step * M::Step::kTileBytes, lds_k_addr + (first_step & 1) * M::Step::kTileBytes, wave);
   float2 prev[KT];     // the previous step's sums and their references, stored at the head of the next step
-  float l_row = 0.f;   // the query's running sum over all key tiles (both lanes of a pair hold it)
+  float l_row = 0.f;   // the query's running sum over the item's key tiles (both lanes of a pair hold it)
   auto store_step = [&](int step) {
 #pragma unroll
     for (int t = 0; t < KT; ++t)
       if (writer && step * KT + t < n) part[(int64_t)(step * KT + t) * Q + mine] = prev[t];
   };
 
-  for (int j = 0; j < steps; ++j) {
+  for (int j = first_step; j < end_step; ++j) {
     int32_t words[KT];  // past the end: tile 0's, not used
 #pragma unroll
     for (int t = 0; t < KT; ++t) words[t] = meta[j * KT + t < n ? j * KT + t : 0];
     // K(j) landed and visible, buffer (j+1)%2 free, the previous step's stores have been written
     WAIT_VMCNT(0);
     BARRIER();
-    if ((j + 1) * KT + my_key_tile < n)
+    if ((!kSplit || j + 1 < end_step) && (j + 1) * KT + my_key_tile < n)
       k_loader.issue(Kp + (int64_t)(j + 1) * M::Step::kTileBytes, lds_k_addr + ((j + 1) & 1) * M::Step::kTileBytes, wave);
-    if (j > 0) store_step(j - 1);  // a whole step to complete
+    if (j > first_step) store_step(j - 1);  // a whole step to complete
     const LdsTile k_step = k_tile + (j & 1) * M::Step::kTileBytes;
 
     auto row_sum = [&](const floatx16 (&acc)[S::kKeyBlocks]) {
@@ -147,7 +198,7 @@ void tile_mass_kernel(MassArgs a) {
       // with the tile's row maximum as the new reference of such queries.  Numerator and denominator
       // of a query always share one reference after the final pass, so the masses are those of the
       // exact softmax.
-      bool by_tile = j == 0 || (j + 1) * KT > n;
+      bool by_tile = j == first_step || (j + 1) * KT > n;
       if (!by_tile) {
         bool move = false;
         int padding = 0;
@@ -191,7 +242,7 @@ void tile_mass_kernel(MassArgs a) {
           w.qk_tile(k_step + t * S::kTileBytes, acc_s, words[t] >= 0);
           w.mask_padding_keys(acc_s, (words[t] >> 24) & 0x7f, class_mask);
           bool move = true;  // this lane's query takes a new reference (every query on the first tile)
-          if (j + t > 0) {
+          if (j > first_step || t > 0) {
             e[t] = row_sum(acc_s);
             move = !(e[t] <= kSumLimit);
           }
@@ -228,7 +279,13 @@ void tile_mass_kernel(MassArgs a) {
   }
 
   // ---- mass[a, b] = sum_i e[b][i] * exp2(scale' * (m[b][i] - m_i)) / l_i --------------------------
-  store_step(steps - 1);
+  store_step(end_step - 1);
+  if constexpr (kSplit) {
+    if (writer) reinterpret_cast<float2*>(a.share_stats)[(item * shares + share) * Q + mine] = float2{qs.real ? l_row : 0.f, w.m_run};
+    WAIT_VMCNT(0);
+    __syncthreads();  // as below: the next item writes the staged tiles
+    continue;
+  }
   if (writer) {
     lds_inv[mine] = (qs.real && l_row > 0.f) ? 1.0f / l_row : 0.f;  // a padding query adds nothing
     lds_ref[mine] = w.m_run;
@@ -238,45 +295,46 @@ void tile_mass_kernel(MassArgs a) {
   // workgroups, 0.1 us per group of queries: 12 heads of 12.5K tokens of head dim 64 627 -> 482 us without it, 6 heads of 4K 57 -> 44 us.
   WAIT_VMCNT(0);
   __syncthreads();
-  constexpr int kLanesPerTile = Q / 4;  // a key tile's Q pairs, four per lane
-  constexpr int kTilesPerPass = 256 / kLanesPerTile;
-  const int sub = threadIdx.x / kLanesPerTile, l4 = threadIdx.x % kLanesPerTile;
-  const int row_of_lane = l4 * 4 / B;   // which of the workgroup's query tiles
-  const bool stores = l4 * 4 % B == 0 && first_row + row_of_lane < a.n;
-  const float4 inv = *reinterpret_cast<const float4*>(&lds_inv[4 * l4]);
-  const float4 ref = *reinterpret_cast<const float4*>(&lds_ref[4 * l4]);
-  const float c2 = w.c2;
-  // kBatch key tiles per lane at a time, all loads requested before the first is used
-  constexpr int kBatch = 4;
-  for (int b0 = sub; b0 < n; b0 += kBatch * kTilesPerPass) {
-    float4 p01[kBatch], p23[kBatch];  // (e0, m0, e1, m1), (e2, m2, e3, m3)
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int b = min(b0 + u * kTilesPerPass, n - 1);  // past the end: a valid tile, not stored
-      const float4* p = reinterpret_cast<const float4*>(part + (int64_t)b * Q + 4 * l4);
-      p01[u] = p[0];
-      p23[u] = p[1];
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int b = b0 + u * kTilesPerPass;
-      const float t0 = p01[u].x * __builtin_amdgcn_exp2f((p01[u].y - ref.x) * c2) * inv.x;
-      const float t1 = p01[u].z * __builtin_amdgcn_exp2f((p01[u].w - ref.y) * c2) * inv.y;
-      const float t2 = p23[u].x * __builtin_amdgcn_exp2f((p23[u].y - ref.z) * c2) * inv.z;
-      const float t3 = p23[u].z * __builtin_amdgcn_exp2f((p23[u].w - ref.w) * c2) * inv.w;
-      float s = (t0 + t1) + (t2 + t3);
-#pragma unroll
-      for (int sh = B / 8; sh >= 1; sh >>= 1) s += __shfl_xor(s, sh, 64);
-      if (stores && b < n) out[row_of_lane * a.n + b] = s;
-    }
-  }
+  reduce_tiles<B>(part, lds_inv, lds_ref, w.c2, 0, n, n, a.n - first_row, out);
   __syncthreads();  // the item is done: its ticket and its LDS tables may be overwritten
   }
 }
 
+// The last pass over row groups whose key tiles were shared: kMassMergeTiles key tiles of one row group per workgroup.  The
+// shares are added in their order, so the result is run-to-run identical.  Bound: latency and the launch.
+template <int B>
+__global__ __launch_bounds__(256) void tile_mass_merge_kernel(MassArgs a) {
+  constexpr int Q = kMassQueries;
+  __shared__ __attribute__((aligned(16))) float lds_inv[Q], lds_ref[Q];
+  const int64_t groups = (a.n + Q / B - 1) / (Q / B), item = blockIdx.x;
+  const int64_t plane_id = item / groups, first_row = item % groups * (Q / B);
+  const int n = (int)a.n, begin = blockIdx.y * kMassMergeTiles;
+  const float c2 = a.scale * kLog2e;
+  if (threadIdx.x < Q) {
+    const float2* stats = reinterpret_cast<const float2*>(a.share_stats) + item * a.shares * Q + threadIdx.x;
+    float top = kMinusInf, sum = 0.f;
+    for (int s = 0; s < a.shares; ++s)
+      if (!(stats[s * Q].x <= 0.f)) top = fmaxf(top, stats[s * Q].y);  // a share without a finite score has no reference of its own
+    if (top == -kMinusInf) top = __builtin_nanf("");  // an infinite score leaves the query no softmax in any share
+    for (int s = 0; s < a.shares; ++s) sum += stats[s * Q].x * ref_factor((stats[s * Q].y - top) * c2);
+    lds_inv[threadIdx.x] = sum > 0.f ? 1.0f / sum : 0.f;
+    lds_ref[threadIdx.x] = top;
+  }
+  __syncthreads();
+  reduce_tiles<B>(reinterpret_cast<const float2*>(a.partial) + item * a.n * Q, lds_inv, lds_ref, c2, begin, min(begin + kMassMergeTiles, n), n,
+                  a.n - first_row, a.mass + (plane_id * a.n + first_row) * a.n);
+}
+
 template <int B, int D>
-hipError_t launch(const MassArgs& a, int64_t grid, hipStream_t stream) {
-  hipLaunchKernelGGL((tile_mass_kernel<B, D>), dim3((unsigned)grid), dim3(256), 0, stream, a);
+hipError_t launch(const MassArgs& a, int64_t items, hipStream_t stream) {
+  if (a.shares == 1) {
+    hipLaunchKernelGGL((tile_mass_kernel<B, D, false>), dim3((unsigned)std::min(items, a.partial_rows)), dim3(256), 0, stream, a);
+    return hipGetLastError();
+  }
+  const int64_t chunks = (a.n + kMassMergeTiles - 1) / kMassMergeTiles;
+  if (chunks > 65535 || items > 0x7fffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((tile_mass_kernel<B, D, true>), dim3((unsigned)std::min(items * a.shares, a.places)), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL((tile_mass_merge_kernel<B>), dim3((unsigned)items, (unsigned)chunks), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -286,12 +344,12 @@ hipError_t launch_tile_mass(const MassArgs& a, hipStream_t stream) {
   const int64_t items = (int64_t)a.batch * a.num_heads * mass_row_groups(a.n, a.B);
   if (items == 0) return hipSuccess;
   if (!a.partial || !a.counter || a.partial_rows < 1) return hipErrorInvalidValue;
-  if (items + a.partial_rows > 0x7fffffff) return hipErrorInvalidValue;
-  const int64_t grid = std::min(items, a.partial_rows);
-  if (a.B == 128 && a.D == 128) return launch<128, 128>(a, grid, stream);
-  if (a.B == 128 && a.D == 64) return launch<128, 64>(a, grid, stream);
-  if (a.B == 64 && a.D == 128) return launch<64, 128>(a, grid, stream);
-  if (a.B == 64 && a.D == 64) return launch<64, 64>(a, grid, stream);
+  if (a.shares < 1 || items * a.shares + std::max(a.places, a.partial_rows) > 0x7fffffff) return hipErrorInvalidValue;
+  if (a.shares > 1 && (items > a.partial_rows || a.places < 1 || !a.share_stats)) return hipErrorInvalidValue;
+  if (a.B == 128 && a.D == 128) return launch<128, 128>(a, items, stream);
+  if (a.B == 128 && a.D == 64) return launch<128, 64>(a, items, stream);
+  if (a.B == 64 && a.D == 128) return launch<64, 128>(a, items, stream);
+  if (a.B == 64 && a.D == 64) return launch<64, 64>(a, items, stream);
   return hipErrorInvalidValue;
 }
 

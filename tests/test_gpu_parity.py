@@ -566,6 +566,53 @@ def test_tile_mass_with_more_rows_than_workgroups(D, tile):
         assert err.max() <= MASS_ABS
 
 
+@pytest.mark.parametrize("D,tile,T,H,W,n_text,Hd,batch", [
+    (64, (1, 8, 8), 5, 30, 52, 64, 1, 1),      # 141 tiles in 71 steps, the last of one tile
+    (64, (1, 8, 8), 2, 25, 40, 0, 3, 2),       # 40 tiles, 20 steps and 120 groups: not split
+    (64, (1, 8, 8), 4, 8, 64, 0, 2, 1),        # 32 tiles, 16 steps: the shortest walk that is split
+    (128, (1, 8, 8), 3, 20, 27, 0, 2, 1),      # steps of one 64-token tile
+    (64, (2, 8, 8), 11, 13, 20, 128, 2, 2),
+    (128, (2, 8, 8), 9, 26, 20, 0, 6, 2),      # 720 groups, more than run at a time
+])
+def test_tile_mass_of_few_rows(D, tile, T, H, W, n_text, Hd, batch):
+    """Launches that leave compute units without work split the key tiles of a row group over several workgroups:
+    the masses are the definition's, the same on every call, and keys whose scores are minus infinity or far below all others
+    (more of them than a share has) change nothing but their own masses."""
+    import dataclasses
+    from oracle import search as OS
+    _say("tile mass, few rows", D, tile, T, H, W, n_text, Hd, batch)
+    B = tile[0] * tile[1] * tile[2]
+    wl = dataclasses.replace(make_workload("massfew", T, H, W, tile, n_text, Hd, D, "bf16", [[]] * Hd), batch=batch)
+    g = geometry_of(wl)
+    lay = build_layout(ca, wl)
+    q, k, _ = make_qkv(wl, DEV, q_gain=2.0)
+    for hidden in (False, True):
+        if hidden:
+            q[..., 0] = 1.0
+            tile_of = torch.from_numpy(np.asarray(g.token_tile_and_slot()[0])).to(DEV)
+            gone = tile_of < g.n // 2 + 1
+            # padding queries are zero, and zero times an infinity is not: the infinity where there are none
+            k[:, :, gone, 0] = float("-inf") if g.n * B == g.N_real else -4096.0
+        qp, kp = ca.compact_attn_permute(q, lay), ca.compact_attn_permute(k, lay)
+        mass = ca.compact_attn_tile_mass(qp, kp, lay)
+        for _ in range(3):
+            assert torch.equal(mass, ca.compact_attn_tile_mass(qp, kp, lay))
+        got = mass.double().cpu().numpy()
+        for b in range(batch):
+            for h in range(Hd):
+                if not hidden:
+                    want = OS.tile_mass(g, to_f64(q[b, h]), to_f64(k[b, h]))
+                else:
+                    p = torch.softmax(q[b, h].double() @ k[b, h].double().t() / D ** 0.5, dim=1)
+                    want = torch.zeros(g.n, g.n, dtype=torch.float64, device=DEV)
+                    cols = torch.zeros(p.shape[0], g.n, dtype=torch.float64, device=DEV).index_add_(1, tile_of, p)
+                    want = want.index_add_(0, tile_of, cols).cpu().numpy()
+                    assert (got[b, h][:, :g.n // 2 + 1] == 0).all()
+                err = np.abs(got[b, h] - want)
+                _say("hidden", hidden, "batch", b, "head", h, "max err", err.max())
+                assert err.max() <= MASS_ABS
+
+
 @pytest.mark.parametrize("name", ["cfg3", "cfg4-S65"])
 def test_tile_mass_every_pair_at_full_size_two_level_probe(name):
     """Every tile pair of every head at the benchmark sizes (24 and 50 launches per call).  Queries
