@@ -486,7 +486,9 @@ struct WayCost {
   LaunchCost cost;
 };
 
-constexpr double kSplitGain = 0.9;  // rows are split if that is predicted to take this much of the time
+// Rows are split if that is predicted to take this much of the time.  Measured, whole / split: 3 heads x 15K of head dim 128 250 /
+// 221 us, 2 x 12 heads x 20K of head dim 64 1286 / 1162 us, 102 rows 153 / 38 us; no drawn call became more than 5 % slower.
+constexpr double kSplitGain = 0.9;
 
 // What a workgroup of an unsplit launch walks: an entry of its launch order and a part of the row's query slots.
 struct Unit {

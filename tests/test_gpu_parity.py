@@ -597,6 +597,16 @@ def test_tile_mass_of_few_rows(D, tile, T, H, W, n_text, Hd, batch):
         mass = ca.compact_attn_tile_mass(qp, kp, lay)
         for _ in range(3):
             assert torch.equal(mass, ca.compact_attn_tile_mass(qp, kp, lay))
+        replayed = torch.empty_like(mass)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            ca.compact_attn_tile_mass(qp, kp, lay, out=replayed)
+        for _ in range(3):
+            replayed.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(mass, replayed)
         got = mass.double().cpu().numpy()
         for b in range(batch):
             for h in range(Hd):
