@@ -108,7 +108,7 @@ __device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, in
 
     bf16x8 pf[S::kKeyBlocks][2];
     w.mask_padding_keys(acc_s, cls, class_mask);
-    w.softmax(acc_s, j == 0, pf);
+    w.softmax(acc_s, pf, j == 0);
 
     // ---- O^T += V^T P^T ------------------------------------------------------------------------
     if (j + 1 < count) WAIT_VMCNT(S::kLoadsPerThread);  // V(j) landed (K(j+1) may be in flight)
@@ -124,7 +124,7 @@ __device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, in
 
   if constexpr (kSplit) {
     if (it.share >= 0) {
-      if (wave_active) w.store_share(a, it.share * (B / 32) + wave, lane, count > 0);
+      if (wave_active) w.store_share(a, it.share * (B / 32) + wave, lane, w.reference());
       return;
     }
   }

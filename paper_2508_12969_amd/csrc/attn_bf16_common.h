@@ -360,8 +360,9 @@ struct QueryWave {
   // afterwards a lagging running maximum.  neg_m holds -m_run in all 16 registers and is the C
   // operand of the first contraction step, so the score accumulator comes out as (score - reference).
   floatx16 neg_m;
-  float m_run, l_run;          // l_run: this lane's share of the running sum (partner lane holds the rest)
-  float c2, lazy_raw;          // scale * log2(e); kLazyLog2 in raw score units
+  float l_run;                 // this lane's share of the running sum (partner lane holds the rest)
+  float c2;                    // scale * log2(e)
+  float moves_above;           // a score further above the reference than this moves it: kLazyLog2 in raw score units, or -inf while the query has met no finite score
   int qi, g;
   // per-lane LDS read offsets
   int k_lane_row_off, k_lane_swz;                              // K: row (32*kb + qi), logical chunk 2*step + g
@@ -371,8 +372,7 @@ struct QueryWave {
     qi = lane & 31;
     g = lane >> 5;
     c2 = scale * kLog2e;
-    lazy_raw = kLazyLog2 / c2;
-    m_run = 0.f;
+    moves_above = kMinusInf;
     l_run = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) neg_m[r] = 0.f;
@@ -459,14 +459,17 @@ struct QueryWave {
 
   // ---- online softmax (one query per lane) -------------------------------------------------------
   // acc_s holds score - reference in raw units.  The reference is set to the row maximum on the
-  // first tile of the row (`first`, wave-uniform) and afterwards moves only for rows whose maximum
+  // first tile with a finite score (a walk may begin with tiles whose scores are all minus infinity; a reference
+  // of zero would make weights of nothing of what lies far below zero) and afterwards moves only for rows whose maximum
   // exceeds it by more than 2^kLazyLog2 (probabilities then stay below that factor, far inside fp32
   // and bf16 range); the accumulator rescale O *= alpha is then a rarely taken wave-uniform branch
   // and the common path per score is one multiply and one exp2.  The result is still the exact
   // softmax: numerator and denominator share the same reference.  Probabilities are rounded to bf16
   // (the B operand of the second product); the row sum adds up the rounded values, two per v_dot2, so
   // numerator and denominator see the same numbers.
-  __device__ __forceinline__ void softmax(floatx16 (&acc_s)[S::kKeyBlocks], bool first, bf16x8 (&pf)[S::kKeyBlocks][2]) {
+  // `first`: the walk's first tile, wave-uniform, where a reference is taken anyway.  No result depends on it; the 64 x 64 one-tile
+  // kernel takes 145 registers without it and 124 with it.
+  __device__ __forceinline__ void softmax(floatx16 (&acc_s)[S::kKeyBlocks], bf16x8 (&pf)[S::kKeyBlocks][2], bool first = false) {
     float mx = acc_s[0][0];
 #pragma unroll
     for (int kb = 0; kb < S::kKeyBlocks; ++kb)
@@ -474,12 +477,13 @@ struct QueryWave {
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc_s[kb][r]);
     mx = max_with_partner(mx);
     {
-      const uint64_t over = __builtin_amdgcn_ballot_w64(mx > lazy_raw);
+      const uint64_t over = __builtin_amdgcn_ballot_w64(mx > moves_above);
       if (first || __builtin_amdgcn_readfirstlane((uint32_t)over | (uint32_t)(over >> 32)) != 0) {
-        float delta = (first || mx > lazy_raw) ? mx : 0.f;
-        if (delta == kMinusInf) delta = 0.f;  // a row that has seen no real key yet keeps its reference
-        const float alpha = first ? 1.0f : __builtin_amdgcn_exp2f(-delta * c2);
-        m_run += delta;
+        const bool moves = mx > moves_above;
+        const float delta = moves ? mx : 0.f;
+        const float alpha = moves_above == kMinusInf ? 1.0f : __builtin_amdgcn_exp2f(-delta * c2);
+        if (moves) moves_above = kLazyLog2 / c2;
+        const float m_run = delta - neg_m[0];
         l_run *= alpha;
 #pragma unroll
         for (int kb = 0; kb < S::kKeyBlocks; ++kb)
@@ -544,10 +548,13 @@ struct QueryWave {
     if (upper_keys) pv<S::kKeyBlocks / 2, S::kKeyBlocks>(lds_v, pf);
   }
 
+  // The query's exponent reference, for sums that are added to others: minus infinity, the reference of no sum, before the first finite score.
+  __device__ __forceinline__ float reference() const { return moves_above == kMinusInf ? kMinusInf : -neg_m[0]; }
+
   // ---- epilogue of a row that is split along the keys: what this wave has summed up, lane by lane, as the merge
   // kernel reads it (attn_bf16_merge.hip); wave_at: index of the wave among all waves of all shares
-  __device__ __forceinline__ void store_share(const AttnArgs& a, int64_t wave_at, int lane, bool seen) const {
-    (static_cast<float2*>(a.share_stats) + wave_at * 64)[lane] = float2{seen ? m_run : kMinusInf, l_run};
+  __device__ __forceinline__ void store_share(const AttnArgs& a, int64_t wave_at, int lane, float ref) const {
+    (static_cast<float2*>(a.share_stats) + wave_at * 64)[lane] = float2{ref, l_run};
     float4* const o = static_cast<float4*>(a.share_o) + wave_at * (D / 8) * 64;
 #pragma unroll
     for (int i = 0; i < S::kDBlocks * 4; ++i)

@@ -66,7 +66,6 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, 
   const bool wave_active = wave_used && qs.wave_active && (member == 0 || has_b);
   const int64_t q_row = kNat ? natural_query_row(a, q_tile, qs.slot) : q_tile * S::B + qs.slot;
   w.load_q(static_cast<const char*>(a.q) + plane + q_row * S::kRowBytes);
-  bool seen = false;  // this wave has processed a tile of its own list (wave-uniform)
 
   const TileLoader<S, false> k_loader(wave, lane);
   const TileLoader<S, true> v_loader(wave, lane);
@@ -115,8 +114,7 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, 
 
       bf16x8 pf[S::kKeyBlocks][2];
       w.mask_padding_keys(acc_s, cls, class_mask);
-      w.softmax(acc_s, !seen, pf);
-      seen = true;
+      w.softmax(acc_s, pf);
 
       // ---- O^T += V^T P^T ------------------------------------------------------------------------
       if (more) WAIT_VMCNT(S::kLoadsPerThread);  // V landed (the next K may be in flight)
@@ -134,7 +132,7 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, 
   if (!wave_used || (member && !has_b)) return;
   if constexpr (kSplit) {
     if (it.share >= 0) {
-      if (wave_active) w.store_share(a, it.share * 4 + wave, lane, seen);
+      if (wave_active) w.store_share(a, it.share * 4 + wave, lane, w.reference());
       return;
     }
   }

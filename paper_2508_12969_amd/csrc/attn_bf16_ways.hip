@@ -214,8 +214,7 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
     }
   };
 
-  bool seen = false;  // this wave has multiplied a key (wave-uniform)
-  __syncthreads();    // the tables in LDS are complete
+  __syncthreads();  // the tables in LDS are complete
   // Tokens of the stage's granules, one byte each.  On a grid without padded tiles all granules are full
   // and the number of stages is known; else each wave publishes the counts of what it copies.
   uint64_t keys = 0;
@@ -254,8 +253,7 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
         if (c0 + c1 != 32) mask_granules(acc_s[kb], c0, c1);
       }
       bf16x8 pf[S::kKeyBlocks][2];
-      w.softmax(acc_s, !seen, pf);
-      seen = true;
+      w.softmax(acc_s, pf);
       __builtin_amdgcn_sched_barrier(0);
       w.pv_tile(v_tile, pf, true);
       __builtin_amdgcn_sched_barrier(0);
@@ -266,7 +264,7 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
   // ---- merge: ways 1 .. NK - 1 hand over (reference, sum, O), way 0 adds them up and stores -----------
   constexpr int kOBytes = 32 * D * 4;
   static_assert((NW - NQ) * kOBytes <= 4 * S::kStageBytes, "the shares fit the stage buffers");
-  if (!seen) w.m_run = kMinusInf;
+  float ref = w.reference();
   if constexpr (S::NK > 1) {
     __syncthreads();  // the stage buffers are free
     if (kw > 0) {
@@ -275,16 +273,16 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
 #pragma unroll
       for (int i = 0; i < S::kDBlocks * 4; ++i)
         o[i * 64 + lane] = float4{w.acc_o[i / 4][i % 4 * 4], w.acc_o[i / 4][i % 4 * 4 + 1], w.acc_o[i / 4][i % 4 * 4 + 2], w.acc_o[i / 4][i % 4 * 4 + 3]};
-      lds_stats[from * 64 + lane] = float2{w.m_run, w.l_run};
+      lds_stats[from * 64 + lane] = float2{ref, w.l_run};
     }
     __syncthreads();
     if (kw > 0) return;
-    float top = w.m_run;
+    float top = ref;
 #pragma unroll
     for (int k = 1; k < S::NK; ++k) top = fmaxf(top, lds_stats[((k - 1) * NQ + qw) * 64 + lane].x);
     // a way without a key has weight 0, also where no way has one (top is -inf)
-    const float f0 = w.m_run == kMinusInf ? 0.f : __builtin_amdgcn_exp2f((w.m_run - top) * w.c2);
-    w.m_run = top;
+    const float f0 = ref == kMinusInf ? 0.f : __builtin_amdgcn_exp2f((ref - top) * w.c2);
+    ref = top;
     w.l_run *= f0;
 #pragma unroll
     for (int db = 0; db < S::kDBlocks; ++db) w.acc_o[db] *= f0;
@@ -307,7 +305,7 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
   }
   if constexpr (kSplit) {
     if (share >= 0) {
-      if (qs.wave_active) w.store_share(a, share * NQ + qw, lane, w.m_run != kMinusInf);
+      if (qs.wave_active) w.store_share(a, share * NQ + qw, lane, ref);
       return;
     }
   }

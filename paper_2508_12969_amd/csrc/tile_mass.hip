@@ -162,6 +162,7 @@ void tile_mass_kernel(MassArgs a) {
   if (first_step * KT + my_key_tile < n)
     k_loader.issue(Kp + (int64_t)first_step * M::Step::kTileBytes, lds_k_addr + (first_step & 1) * M::Step::kTileBytes, wave);
   float2 prev[KT];     // the previous step's sums and their references, stored at the head of the next step
+  float m_run = 0.f;   // its exponent reference
   float l_row = 0.f;   // the query's running sum over the item's key tiles (both lanes of a pair hold it)
   auto store_step = [&](int step) {
 #pragma unroll
@@ -230,7 +231,7 @@ void tile_mass_kernel(MassArgs a) {
         if (!by_tile) {
 #pragma unroll
           for (int t = 0; t < KT; ++t) {
-            prev[t] = float2{e[t], w.m_run};
+            prev[t] = float2{e[t], m_run};
             l_row += e[t];
           }
         }
@@ -257,7 +258,7 @@ void tile_mass_kernel(MassArgs a) {
             mx = max_with_partner(mx);
             float delta = move ? mx : 0.f;
             if (delta == kMinusInf) delta = 0.f;  // a row that has seen no real key yet keeps its reference
-            w.m_run += delta;
+            m_run += delta;
             // the reference only rises after the first tile; there nothing is summed yet, and a first maximum
             // far below zero must not make the factor infinite
             l_row *= __builtin_amdgcn_exp2f(fminf(-delta * w.c2, 0.f));
@@ -266,11 +267,11 @@ void tile_mass_kernel(MassArgs a) {
 #pragma unroll
               for (int r = 0; r < 16; ++r) acc_s[kb][r] -= delta;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) w.neg_m[r] = -w.m_run;
+            for (int r = 0; r < 16; ++r) w.neg_m[r] = -m_run;
             e[t] = row_sum(acc_s);
           }
           l_row += e[t];
-          prev[t] = float2{e[t], w.m_run};
+          prev[t] = float2{e[t], m_run};
         }
       }
     } else {
@@ -282,14 +283,14 @@ void tile_mass_kernel(MassArgs a) {
   // ---- mass[a, b] = sum_i e[b][i] * exp2(scale' * (m[b][i] - m_i)) / l_i --------------------------
   store_step(end_step - 1);
   if constexpr (kSplit) {
-    if (writer) reinterpret_cast<float2*>(a.share_stats)[(item * shares + share) * Q + mine] = float2{qs.real ? l_row : 0.f, w.m_run};
+    if (writer) reinterpret_cast<float2*>(a.share_stats)[(item * shares + share) * Q + mine] = float2{qs.real ? l_row : 0.f, m_run};
     WAIT_VMCNT(0);
     __syncthreads();  // as below: the next item writes the staged tiles
     continue;
   }
   if (writer) {
     lds_inv[mine] = (qs.real && l_row > 0.f) ? 1.0f / l_row : 0.f;  // a padding query adds nothing
-    lds_ref[mine] = w.m_run;
+    lds_ref[mine] = m_run;
   }
   // The stored pairs are read back by other waves of this workgroup only, which share an L1: waiting for the stores and the
   // barrier's order are enough.  A device-wide fence in every wave writes back the XCD's L2 each time, for all of its

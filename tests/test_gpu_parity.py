@@ -1262,7 +1262,7 @@ _GLOBAL, _LOCAL, _NEAR = [(99, (99, 99), ABSENT)], [(1, (1, 1), ABSENT)], [(0, (
 _MIXED = [_GLOBAL, [], _NEAR]
 
 
-@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,heads,batch", [
+_SPLIT_LAUNCHES = [
     # few tiles and one head: shares of one or two tiles, tiles of a few tokens
     ("one-tile", 64, (2, 8, 29), (1, 8, 8), 0, [_GLOBAL], 1),
     ("one-tile", 64, (2, 8, 40), (2, 8, 8), 0, [_GLOBAL], 1),
@@ -1284,7 +1284,10 @@ _MIXED = [_GLOBAL, [], _NEAR]
     ("ways-8x4", 128, (5, 8, 40), (2, 8, 8), 1, _MIXED, 2),
     ("ways-8x2", 64, (9, 13, 8), (2, 8, 8), 1, _MIXED, 2),
     ("ways-8x2", 128, (16, 30, 8), (1, 8, 8), 1, _MIXED, 2),
-])
+]
+
+
+@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,heads,batch", _SPLIT_LAUNCHES)
 def test_rows_split_along_the_keys(kernel, D, grid, tile, text_tiles, heads, batch):
     """Launches whose rows are shared by several workgroups: against the oracle with peaked rows, whatever the workspace holds
     before the call; natural order, the static entry point, a second stream and a replayed graph bit for bit; the C call without a
@@ -1340,3 +1343,37 @@ def test_rows_split_along_the_keys(kernel, D, grid, tile, text_tiles, heads, bat
         assert status == -1, (at, size)
     torch.cuda.synchronize()
     assert torch.equal(again, before)
+
+
+@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,heads,batch", _SPLIT_LAUNCHES)
+@pytest.mark.parametrize("hidden", ["whole shares", "first tiles of a share"])
+def test_minus_infinite_scores_in_split_rows(kernel, D, grid, tile, text_tiles, heads, batch, hidden):
+    """Keys whose scores are minus infinity have no weight, and those beside them keep theirs however far below zero they lie
+    (-512 scaled here: exp2 of such a score against a reference of zero is zero), whether such keys fill a share or only its first
+    tiles.  The same for whole rows, which the C call without a workspace walks."""
+    import ctypes
+    import dataclasses
+    _say("minus infinity", kernel, D, grid, tile, batch, hidden)
+    B = tile[0] * tile[1] * tile[2]
+    wl = dataclasses.replace(make_workload("split", *grid, tile, text_tiles * B, len(heads), D, "bf16", heads), batch=batch)
+    g = geometry_of(wl)
+    lay = build_layout(ca, wl)
+    assert ca.compact_attn_layout_split(lay)[1] == kernel
+    q, k, v = make_qkv(wl, DEV)
+    tile_of = torch.from_numpy(np.asarray(g.token_tile_and_slot()[0])).to(DEV)
+    q[..., 0] = 16.0
+    k[..., 0] = -32.0 * D ** 0.5
+    k[:, :, tile_of < g.n // 2 + 1 if hidden == "whole shares" else tile_of % 3 != 2, 0] = float("-inf")
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    split = ca.compact_attn_forward(qp, kp, vp, lay)
+    whole = torch.empty_like(split)
+    status = ca.load_library().compact_attn_forward(*(ctypes.c_void_p(x.data_ptr()) for x in (qp, kp, vp)), lay.handle, ctypes.c_void_p(whole.data_ptr()),
+                                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert status == 0
+    for what, x in (("split", split), ("whole", whole)):
+        out = ca.compact_attn_permute(x, lay, inverse=True)
+        for h in range(len(heads)):
+            with np.errstate(invalid="ignore"):
+                want = OA.masked_attention(g, [heads[h]], *(to_f64(t[batch - 1, h])[None] for t in (q, k, v)))
+            want = np.nan_to_num(want, nan=0.0)   # a query all of whose keys are hidden has no softmax, and gets zeros
+            _say(what, h, compare(to_f64(out[batch - 1, h])[None], want, *tolerances("bf16"), what=what))
