@@ -308,6 +308,11 @@ int compact_attn_forward_with_workspace(const void* q, const void* k, const void
  * Supported: bf16 with (B, D) in {64,128} x {64,128}; otherwise CA_ERR_UNSUPPORTED. */
 int compact_attn_tile_mass(const void* q, const void* k, ca_layout* layout, float* mass, void* stream);
 
+/* *shares = how many workgroups share the key tiles of a group of 128 queries in the layout's tile-mass calls, 1 where a
+ * workgroup takes them all, 0 before the first call for the layout, which decides it.  No part of the interface; this is for
+ * tests and profiles.  Errors: CA_ERR_INVALID_ARG. */
+int compact_attn_layout_mass_shares(ca_layout* layout, int32_t* shares);
+
 /* Window search of one head by boundary contraction (Sec. 4.2), host only.
  *   layout         any layout of the problem (only its geometry is used).
  *   mass           host pointer, float32 [n*n]: one head's attention mass per tile pair, row-major

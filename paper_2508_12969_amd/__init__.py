@@ -17,6 +17,7 @@ from .binding import (  # noqa: F401
     compact_attn_layout_from_csr,
     compact_attn_layout_info,
     compact_attn_layout_kernel,
+    compact_attn_layout_mass_shares,
     compact_attn_layout_order,
     compact_attn_layout_pairs,
     compact_attn_layout_packing,

@@ -44,6 +44,7 @@ EXPORTED = (
     "compact_attn_layout_split",
     "compact_attn_forward_with_workspace",
     "compact_attn_tile_mass",
+    "compact_attn_layout_mass_shares",
     "compact_attn_search_head",
     "compact_attn_last_error",
 )
@@ -121,6 +122,7 @@ def load_library():
     lib.compact_attn_layout_split.argtypes = [vp, i32, i64p, ctypes.POINTER(ctypes.c_char_p)]
     lib.compact_attn_forward_with_workspace.argtypes = [vp, vp, vp, vp, vp, i32, vp, ctypes.c_int64, vp]
     lib.compact_attn_tile_mass.argtypes = [vp, vp, vp, vp, vp]
+    lib.compact_attn_layout_mass_shares.argtypes = [vp, ctypes.POINTER(i32)]
     lib.compact_attn_search_head.argtypes = [vp, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(i32), i32, ctypes.c_double,
                                              ctypes.c_double, i32, ctypes.POINTER(ca_group), ctypes.POINTER(ctypes.c_double),
                                              ctypes.POINTER(ctypes.c_double)]
@@ -295,6 +297,13 @@ def compact_attn_layout_split(layout, dense=False):
     """(bytes, kernel): workspace of the layout's sparse (or dense) calls, which the binding allocates, and the name of the
     kernel that splits their rows along the keys; (0, None) if rows are not split."""
     return _layout_split(layout.handle, int(bool(dense)))
+
+
+def compact_attn_layout_mass_shares(layout):
+    """Workgroups that share the key tiles of a group of queries in the layout's tile-mass calls; 0 before the first."""
+    shares = ctypes.c_int32()
+    _check(load_library().compact_attn_layout_mass_shares(layout.handle, ctypes.byref(shares)))
+    return shares.value
 
 
 def compact_attn_layout_upload(layout):

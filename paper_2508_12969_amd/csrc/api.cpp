@@ -810,6 +810,14 @@ int compact_attn_tile_mass(const void* q, const void* k, ca_layout* L, float* ma
   return CA_OK;
 }
 
+int compact_attn_layout_mass_shares(ca_layout* L, int32_t* shares) {
+  ca::clear_error();
+  if (!L || !shares) return fail(CA_ERR_INVALID_ARG, "null argument");
+  std::lock_guard<std::mutex> lock(L->upload_mutex);
+  *shares = L->dev.mass_partial ? L->dev.mass_shares : 0;
+  return CA_OK;
+}
+
 int compact_attn_search_head(const ca_layout* L, const float* mass, const int32_t* group_max_dt, int32_t num_groups,
                              double tau, double lambda, int32_t pattern, ca_group* groups, double* recall,
                              double* kept_fraction) {

@@ -442,6 +442,24 @@ void check_mass_workspace() {
       compact_attn_free_layout(L);
     }
   }
+  // 70 groups of 140 tiles: four workgroups share a group's tiles, or one takes them all if memory is short
+  const ca_problem p{5, 30, 52, 1, 8, 8, 0, 1, 1, 64, CA_BF16, 0.f};
+  const ca_head all{0, 0, nullptr};
+  for (size_t short_by : {0, 1}) {
+    ca_layout* L = nullptr;
+    int32_t shares = -1;
+    CHECK(compact_attn_build_layout(&p, &all, &L) == CA_OK);
+    if (!L) return;
+    CHECK(compact_attn_layout_upload(L) == CA_OK);
+    CHECK(compact_attn_layout_mass_shares(L, &shares) == CA_OK && shares == 0);
+    CHECK(compact_attn_layout_mass_shares(L, nullptr) == CA_ERR_INVALID_ARG);
+    g_alloc_limit = (size_t)70 * (140 + 4) * 128 * 2 * sizeof(float) + 256 + 1 - short_by;  // refuses that many bytes
+    g_alloc_error = hipErrorOutOfMemory;
+    CHECK(compact_attn_tile_mass((const void*)(1ull << 40), (const void*)(2ull << 40), L, (float*)(3ull << 40), nullptr) == CA_OK);
+    g_alloc_limit = SIZE_MAX;
+    CHECK(compact_attn_layout_mass_shares(L, &shares) == CA_OK && shares == (short_by ? 1 : 4) && ca::g_mass_rows == 70);
+    compact_attn_free_layout(L);
+  }
 }
 
 // What the choice of kernel knows of a large layout comes from a sample of its rows; grids whose extents share factors

@@ -566,15 +566,15 @@ def test_tile_mass_with_more_rows_than_workgroups(D, tile):
         assert err.max() <= MASS_ABS
 
 
-@pytest.mark.parametrize("D,tile,T,H,W,n_text,Hd,batch", [
-    (64, (1, 8, 8), 5, 30, 52, 64, 1, 1),      # 141 tiles in 71 steps, the last of one tile
-    (64, (1, 8, 8), 2, 25, 40, 0, 3, 2),       # 40 tiles, 20 steps and 120 groups: not split
-    (64, (1, 8, 8), 4, 8, 64, 0, 2, 1),        # 32 tiles, 16 steps: the shortest walk that is split
-    (128, (1, 8, 8), 3, 20, 27, 0, 2, 1),      # steps of one 64-token tile
-    (64, (2, 8, 8), 11, 13, 20, 128, 2, 2),
-    (128, (2, 8, 8), 9, 26, 20, 0, 6, 2),      # 720 groups, more than run at a time
+@pytest.mark.parametrize("D,tile,T,H,W,n_text,Hd,batch,shares", [
+    (64, (1, 8, 8), 5, 30, 52, 64, 1, 1, 4),      # 141 tiles in 71 steps, the last of one tile
+    (64, (1, 8, 8), 2, 25, 40, 0, 3, 2, 1),       # 40 tiles, 20 steps and 120 groups: not split
+    (64, (1, 8, 8), 4, 8, 64, 0, 2, 1, 4),        # 32 tiles, 16 steps: the shortest walk that is split
+    (128, (1, 8, 8), 3, 20, 27, 0, 2, 1, 4),      # steps of one 64-token tile
+    (64, (2, 8, 8), 11, 13, 20, 128, 2, 2, 4),
+    (128, (2, 8, 8), 9, 26, 20, 0, 6, 2, 4),      # 720 groups, more than run at a time
 ])
-def test_tile_mass_of_few_rows(D, tile, T, H, W, n_text, Hd, batch):
+def test_tile_mass_of_few_rows(D, tile, T, H, W, n_text, Hd, batch, shares):
     """Launches that leave compute units without work split the key tiles of a row group over several workgroups:
     the masses are the definition's, the same on every call, and keys whose scores are minus infinity or far below all others
     (more of them than a share has) change nothing but their own masses."""
@@ -595,6 +595,7 @@ def test_tile_mass_of_few_rows(D, tile, T, H, W, n_text, Hd, batch):
             k[:, :, gone, 0] = float("-inf") if g.n * B == g.N_real else -4096.0
         qp, kp = ca.compact_attn_permute(q, lay), ca.compact_attn_permute(k, lay)
         mass = ca.compact_attn_tile_mass(qp, kp, lay)
+        assert ca.compact_attn_layout_mass_shares(lay) == shares
         for _ in range(3):
             assert torch.equal(mass, ca.compact_attn_tile_mass(qp, kp, lay))
         replayed = torch.empty_like(mass)
