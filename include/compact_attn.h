@@ -187,7 +187,8 @@ int compact_attn_layout_pairs(const ca_layout* layout, const int32_t** pairs, in
 int compact_attn_layout_packing(const ca_layout* layout, const int32_t** desc, const int32_t** launch_rows,
                                 int64_t* num_launch_rows);
 
-/* Name of the kernel that serves the layout's attention calls: the sparse walk (dense = 0; forward,
+/* Name of the kernel that serves the layout's attention calls where rows are not split along the keys
+ * (compact_attn_layout_split names it where they are): the sparse walk (dense = 0; forward,
  * forward_natural and forward_static alike) or the dense one (dense = 1).  *name receives a string
  * with static storage, one of
  *   "f32"

@@ -27,10 +27,11 @@ def make_workload(name, T, H, W, tile, n_text, num_heads, head_dim, dtype, heads
 
 def layout_for_kernel(ca, kernel, build, dense=False):
     """(copies, build(copies)) with the first number of copies of a head list for which the layout's sparse (or dense)
-    calls are served by the named kernel (which one that is depends on the size of the launch), or None."""
+    calls are served by the named kernel (which one that is depends on the size of the launch) and its rows are not split
+    along the keys (by another kernel, as may be), or None."""
     for copies in (*range(1, 33), 40, 48, 64, 80, 96, 128, 160, 200, 240):
         layout = build(copies)
-        if ca.compact_attn_layout_kernel(layout, dense=dense) == kernel:
+        if ca.compact_attn_layout_kernel(layout, dense=dense) == kernel and ca.compact_attn_layout_split(layout, dense=dense) == (0, None):
             return copies, layout
         layout.free()
     return None
