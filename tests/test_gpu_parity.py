@@ -624,6 +624,53 @@ def test_tile_mass_of_few_rows(D, tile, T, H, W, n_text, Hd, batch, shares):
                 assert err.max() <= MASS_ABS
 
 
+# grids without padding: a padding query is zero, and zero times an infinity is not
+_MASS_WITHOUT_PADDING = [
+    (64, (1, 8, 8), 5, 32, 56, 64, 1, 1, 4),
+    (64, (1, 8, 8), 4, 8, 64, 0, 2, 1, 4),
+    (128, (1, 8, 8), 3, 24, 32, 0, 2, 1, 4),
+    (64, (2, 8, 8), 12, 16, 24, 128, 2, 2, 4),
+    (128, (2, 8, 8), 10, 24, 24, 0, 6, 2, 4),
+    # a workgroup takes all key tiles of a group of queries
+    (64, (1, 8, 8), 2, 24, 40, 0, 3, 2, 1),
+    (128, (1, 8, 8), 2, 16, 24, 0, 2, 1, 1),
+    (64, (2, 8, 8), 4, 16, 24, 128, 2, 1, 1),
+    (128, (2, 8, 8), 6, 16, 24, 0, 2, 1, 1),
+]
+
+
+@pytest.mark.parametrize("hidden", ["a half of the tiles", "two of three tiles"])
+@pytest.mark.parametrize("D,tile,T,H,W,n_text,Hd,batch,shares", _MASS_WITHOUT_PADDING)
+def test_tile_mass_beside_minus_infinite_scores(D, tile, T, H, W, n_text, Hd, batch, shares, hidden):
+    """Keys whose scores are minus infinity have no mass, and those beside them keep theirs however far below zero they lie (-512
+    scaled here: exp2 of such a score against a reference of zero is zero), whether such keys fill the first tiles of a walk, all
+    that a workgroup walks, or only its first tiles.  Rounding: as for scores far below zero, with sums of 2^13 in raw units at head
+    dim 128, in the tiles that are multiplied before there is a reference: 4e-4 relative in a probability."""
+    import dataclasses
+    _say("tile mass beside minus infinity", D, tile, T, H, W, n_text, Hd, batch, hidden)
+    wl = dataclasses.replace(make_workload("massinf", T, H, W, tile, n_text, Hd, D, "bf16", [[]] * Hd), batch=batch)
+    g = geometry_of(wl)
+    assert g.n * tile[0] * tile[1] * tile[2] == g.N_real
+    lay = build_layout(ca, wl)
+    q, k, _ = make_qkv(wl, DEV)
+    tile_of = torch.from_numpy(np.asarray(g.token_tile_and_slot()[0])).to(DEV)
+    gone = torch.arange(g.n, device=DEV) < g.n // 2 + 1 if hidden == "a half of the tiles" else torch.arange(g.n, device=DEV) % 3 != 2
+    q[..., 0] = 16.0
+    k[..., 0] = -32.0 * D ** 0.5
+    k[:, :, gone[tile_of], 0] = float("-inf")
+    mass = ca.compact_attn_tile_mass(ca.compact_attn_permute(q, lay), ca.compact_attn_permute(k, lay), lay)
+    assert ca.compact_attn_layout_mass_shares(lay) == shares
+    for b in range(batch):
+        for h in range(Hd):
+            p = torch.softmax(q[b, h].double() @ k[b, h].double().t() / D ** 0.5, dim=1)
+            cols = torch.zeros(p.shape[0], g.n, dtype=torch.float64, device=DEV).index_add_(1, tile_of, p)
+            want = torch.zeros(g.n, g.n, dtype=torch.float64, device=DEV).index_add_(0, tile_of, cols)
+            assert (mass[b, h][:, gone] == 0).all()
+            err = (mass[b, h].double() - want).abs().max().item()
+            _say("batch", b, "head", h, "max err", err, "max mass", want.max().item())
+            assert err <= MASS_ABS + 4e-4 * want.max().item()
+
+
 @pytest.mark.parametrize("name", ["cfg3", "cfg4-S65"])
 def test_tile_mass_every_pair_at_full_size_two_level_probe(name):
     """Every tile pair of every head at the benchmark sizes (24 and 50 launches per call).  Queries
