@@ -58,9 +58,10 @@ struct MassShape {
 
 // mass[a, b] = sum_i e[b][i] * exp2(scale' * (m[b][i] - m_i)) / l_i of the key tiles begin .. end - 1 of a row group, by 256
 // threads; part: its block of the workspace, rows: query tiles from its first one to the last of the plane.
-template <int B>
-__device__ __forceinline__ void reduce_tiles(const float2* part, const float* inv_of, const float* ref_of, float c2, int begin, int end, int n,
-                                             int64_t rows, float* out) {
+// nan_from (shared key tiles): per query tile the first key tile of a later share than one with an infinite score.
+template <int B, bool kSplit>
+__device__ __forceinline__ void reduce_tiles(const float2* part, const float* inv_of, const float* ref_of, const int* nan_from, float c2, int begin,
+                                             int end, int n, int64_t rows, float* out) {
   constexpr int kLanesPerTile = kMassQueries / 4;  // a key tile's pairs, four per lane
   constexpr int kTilesPerPass = 256 / kLanesPerTile;
   const int sub = threadIdx.x / kLanesPerTile, l4 = threadIdx.x % kLanesPerTile;
@@ -90,6 +91,7 @@ __device__ __forceinline__ void reduce_tiles(const float2* part, const float* in
       float s = (t0 + t1) + (t2 + t3);
 #pragma unroll
       for (int sh = B / 8; sh >= 1; sh >>= 1) s += __shfl_xor(s, sh, 64);
+      if constexpr (kSplit) s = b < nan_from[row_of_lane] ? s : __builtin_nanf("");
       if (stores && b < end) out[row_of_lane * (int64_t)n + b] = s;
     }
   }
@@ -304,34 +306,45 @@ void tile_mass_kernel(MassArgs a) {
   // workgroups, 0.1 us per group of queries: 12 heads of 12.5K tokens of head dim 64 627 -> 482 us without it, 6 heads of 4K 57 -> 44 us.
   WAIT_VMCNT(0);
   __syncthreads();
-  reduce_tiles<B>(part, lds_inv, lds_ref, w.c2, 0, n, n, a.n - first_row, out);
+  reduce_tiles<B, false>(part, lds_inv, lds_ref, nullptr, w.c2, 0, n, n, a.n - first_row, out);
   __syncthreads();  // the item is done: its ticket and its LDS tables may be overwritten
   }
 }
 
 // The last pass over row groups whose key tiles were shared: kMassMergeTiles key tiles of one row group per workgroup.  The
 // shares are added in their order, so the result is run-to-run identical.  Bound: latency and the launch.
+// Scores without a softmax come out as a single walk leaves them: after an infinity the reference is infinite, which gives
+// zeros before its key tile and NaN from there on; a tile of NaN makes the reference NaN, and with it every mass.
 template <int B>
 __global__ __launch_bounds__(256) void tile_mass_merge_kernel(MassArgs a) {
   constexpr int Q = kMassQueries;
   __shared__ __attribute__((aligned(16))) float lds_inv[Q], lds_ref[Q];
+  __shared__ int lds_nan_from[Q / B];
   const int64_t groups = (a.n + Q / B - 1) / (Q / B), item = blockIdx.x;
   const int64_t plane_id = item / groups, first_row = item % groups * (Q / B);
   const int n = (int)a.n, begin = blockIdx.y * kMassMergeTiles;
   const float c2 = a.scale * kLog2e;
+  if (threadIdx.x < Q / B) lds_nan_from[threadIdx.x] = n;
+  __syncthreads();
   if (threadIdx.x < Q) {
     const float2* stats = reinterpret_cast<const float2*>(a.share_stats) + item * a.shares * Q + threadIdx.x;
     float top = kMinusInf, sum = 0.f;
-    for (int s = 0; s < a.shares; ++s)
-      if (!(stats[s * Q].x <= 0.f)) top = fmaxf(top, stats[s * Q].y);  // a share without a finite score has no reference of its own
-    if (top == -kMinusInf) top = __builtin_nanf("");  // an infinite score leaves the query no softmax in any share
+    for (int s = 0; s < a.shares; ++s) {
+      const float2 st = stats[s * Q];
+      if (st.x <= 0.f) continue;  // a share without a finite score has no reference of its own
+      if (st.y == -kMinusInf && top != st.y) {  // the first infinite one: the walk of the tile's later shares would go on with it
+        const int step_tiles = mass_step_keys(B, a.D) / B, steps = (n + step_tiles - 1) / step_tiles;
+        atomicMin(&lds_nan_from[threadIdx.x / B], (int)((int64_t)(s + 1) * steps / a.shares) * step_tiles);
+      }
+      top = st.y > top || st.y != st.y ? st.y : top;
+    }
     for (int s = 0; s < a.shares; ++s) sum += stats[s * Q].x * ref_factor((stats[s * Q].y - top) * c2);
     lds_inv[threadIdx.x] = sum > 0.f ? 1.0f / sum : 0.f;
     lds_ref[threadIdx.x] = top;
   }
   __syncthreads();
-  reduce_tiles<B>(reinterpret_cast<const float2*>(a.partial) + item * a.n * Q, lds_inv, lds_ref, c2, begin, min(begin + kMassMergeTiles, n), n,
-                  a.n - first_row, a.mass + (plane_id * a.n + first_row) * a.n);
+  reduce_tiles<B, true>(reinterpret_cast<const float2*>(a.partial) + item * a.n * Q, lds_inv, lds_ref, lds_nan_from, c2, begin,
+                        min(begin + kMassMergeTiles, n), n, a.n - first_row, a.mass + (plane_id * a.n + first_row) * a.n);
 }
 
 template <int B, int D>

@@ -671,6 +671,39 @@ def test_tile_mass_beside_minus_infinite_scores(D, tile, T, H, W, n_text, Hd, ba
             assert err <= MASS_ABS + 4e-4 * want.max().item()
 
 
+@pytest.mark.parametrize("D,tile,T,H,W,n_text,Hd,batch,shares", _MASS_WITHOUT_PADDING)
+def test_tile_mass_of_scores_without_a_softmax(D, tile, T, H, W, n_text, Hd, batch, shares):
+    """A score of infinity and a NaN leave a query no softmax.  Where the kernel shows it does not depend on how the key tiles are
+    dealt out: infinity from its key tile on, with zeros before, a tile of NaN everywhere, a single NaN in its own tile.
+    The masses of other queries stay as they are, bit for bit."""
+    import dataclasses
+    _say("tile mass without a softmax", D, tile, T, H, W, n_text, Hd, batch)
+    wl = dataclasses.replace(make_workload("massnan", T, H, W, tile, n_text, Hd, D, "bf16", [[]] * Hd), batch=batch)
+    g = geometry_of(wl)
+    assert g.n * tile[0] * tile[1] * tile[2] == g.N_real
+    lay = build_layout(ca, wl)
+    q, k, _ = make_qkv(wl, DEV)
+    tile_of = torch.from_numpy(np.asarray(g.token_tile_and_slot()[0])).to(DEV)
+    row, col = g.n // 2, 2 * g.n // 3            # tile of the infinite score's query, and of its key
+    q[..., 0] = -1.0
+    key = int(torch.nonzero(tile_of == col)[3])
+    k[:, :, key, 0] = float("inf")               # minus infinity for every query but one
+    def masses():
+        return ca.compact_attn_tile_mass(ca.compact_attn_permute(q, lay), ca.compact_attn_permute(k, lay), lay)
+    plain = masses()
+    assert torch.isfinite(plain).all() and ca.compact_attn_layout_mass_shares(lay) == shares
+    others = torch.arange(g.n, device=DEV) != row
+    q[:, :, tile_of == row, 0] = 1.0
+    mass = masses()
+    assert torch.equal(mass[:, :, others], plain[:, :, others])
+    assert torch.isnan(mass[:, :, row, col:]).all() and (mass[:, :, row, :col] == 0).all()
+    k[:, :, key, 0] = float("nan")
+    mass = masses()
+    assert torch.isnan(mass[..., col]).all() and (mass[..., :col] == 0).all() and (mass[..., col + 1:] == 0).all()
+    k[:, :, tile_of == col] = float("nan")
+    assert torch.isnan(masses()).all()
+
+
 @pytest.mark.parametrize("name", ["cfg3", "cfg4-S65"])
 def test_tile_mass_every_pair_at_full_size_two_level_probe(name):
     """Every tile pair of every head at the benchmark sizes (24 and 50 launches per call).  Queries
