@@ -327,6 +327,15 @@ def _stream_ptr(stream):
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+def _torch_stream(stream, device):
+    """The torch stream of anything that has the handle of one (all that a call asks of its `stream`)."""
+    import torch
+    if isinstance(stream, torch.cuda.Stream):
+        return stream
+    handle = stream.cuda_stream
+    return torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)
+
+
 def _check_tensor(t, layout, padded, name):
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
@@ -363,7 +372,7 @@ def _attention(fn, call, q, k, v, layout, out, stream, padded=True):
             workspace = q.new_empty(need // q.element_size())
         else:  # from that stream's memory: what is free there has no work pending on another
             import torch
-            with torch.cuda.stream(stream):
+            with torch.cuda.stream(_torch_stream(stream, q.device)):
                 workspace = q.new_empty(need // q.element_size())
         _check(load_library().compact_attn_forward_with_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), layout.handle, out.data_ptr(), call,
                                                                   workspace.data_ptr(), need, _stream_ptr(stream)))

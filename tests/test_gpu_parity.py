@@ -1458,3 +1458,26 @@ def test_minus_infinite_scores_in_split_rows(kernel, D, grid, tile, text_tiles, 
                 want = OA.masked_attention(g, [heads[h]], *(to_f64(t[batch - 1, h])[None] for t in (q, k, v)))
             want = np.nan_to_num(want, nan=0.0)   # a query all of whose keys are hidden has no softmax, and gets zeros
             _say(what, h, compare(to_f64(out[batch - 1, h])[None], want, *tolerances("bf16"), what=what))
+
+
+@pytest.mark.parametrize("which", ["side", "default"])
+def test_split_rows_on_a_stream_known_by_its_handle(which):
+    """`stream` is anything with a `cuda_stream`, also where the binding takes a workspace from that stream's memory."""
+    class Handle:
+        pass
+    wl = make_workload("handle", 3, 16, 12, (2, 8, 8), 128, 1, 64, "bf16", [_GLOBAL])
+    lay = build_layout(ca, wl)
+    assert ca.compact_attn_layout_split(lay)[0] > 0
+    q, k, v = make_qkv(wl, DEV)
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    want = ca.compact_attn_forward(qp, kp, vp, lay)
+    out = torch.full_like(qp, float("nan"))
+    stream = torch.cuda.Stream() if which == "side" else torch.cuda.default_stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    handle = Handle()
+    handle.cuda_stream = stream.cuda_stream
+    ca.compact_attn_forward(qp, kp, vp, lay, out=out, stream=handle)
+    nat = ca.compact_attn_forward_natural(q, k, v, lay, stream=handle)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    assert torch.equal(nat, ca.compact_attn_permute(want, lay, inverse=True))
