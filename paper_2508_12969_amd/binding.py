@@ -164,7 +164,7 @@ class Layout:
         self._shapes = tuple((problem.batch, problem.num_heads, tokens, problem.head_dim) for tokens in (n_real.value, n_pad.value))
         self._is_bf16 = problem.dtype == CA_BF16
         # bytes a call lends the library: the sparse walk, the dense one
-        self._workspace = tuple(_layout_split(handle, dense)[0] for dense in (0, 1))
+        self._workspace = [_layout_split(handle, dense)[0] for dense in (0, 1)]
 
     def free(self):
         if self.handle is not None:
@@ -359,6 +359,33 @@ def compact_attn_permute(src, layout, inverse=False, out=None, stream=None):
     return out
 
 
+def _lend(q, need, layout, call, stream):
+    """`need` bytes for a call on `stream`, from that stream's memory (what is free there has no work pending on another), or
+    None where there is no such memory to lend; the call then leaves its rows whole, as the C call without a workspace does."""
+    import torch
+    if stream is not None:
+        with torch.cuda.stream(_torch_stream(stream, q.device)):
+            return _lend(q, need, layout, call, None)
+    try:
+        workspace = q.new_empty(need // q.element_size())
+    except torch.cuda.OutOfMemoryError:
+        # torch has emptied its cache before it gave up, which no later call shall pay for again
+        layout._workspace[call == CA_CALL_DENSE] = 0
+        return None
+    if torch.cuda.is_current_stream_capturing() and not _in_graph_pool(workspace):
+        return None
+    return workspace
+
+
+def _in_graph_pool(t):
+    """Is the tensor in memory that torch keeps for a captured graph?  A capture that torch does not run gets ordinary memory, which
+    somebody else owns by the time the graph is replayed."""
+    import torch
+    address = t.data_ptr()
+    return any(s["address"] <= address < s["address"] + s["total_size"] and tuple(s.get("segment_pool_id", (0, 0))) != (0, 0)
+               for s in torch.cuda.memory_snapshot())
+
+
 def _attention(fn, call, q, k, v, layout, out, stream, padded=True):
     for name, t in (("q", q), ("k", k), ("v", v)):
         _check_tensor(t, layout, padded, name)
@@ -367,13 +394,8 @@ def _attention(fn, call, q, k, v, layout, out, stream, padded=True):
     else:
         _check_tensor(out, layout, padded, "out")
     need = 0 if call is None else layout._workspace[call == CA_CALL_DENSE]
-    if need:
-        if stream is None:
-            workspace = q.new_empty(need // q.element_size())
-        else:  # from that stream's memory: what is free there has no work pending on another
-            import torch
-            with torch.cuda.stream(_torch_stream(stream, q.device)):
-                workspace = q.new_empty(need // q.element_size())
+    workspace = _lend(q, need, layout, call, stream) if need else None
+    if workspace is not None:
         _check(load_library().compact_attn_forward_with_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), layout.handle, out.data_ptr(), call,
                                                                   workspace.data_ptr(), need, _stream_ptr(stream)))
         return out

@@ -1481,3 +1481,75 @@ def test_split_rows_on_a_stream_known_by_its_handle(which):
     torch.cuda.synchronize()
     assert torch.equal(out, want)
     assert torch.equal(nat, ca.compact_attn_permute(want, lay, inverse=True))
+
+
+def _whole_rows(qp, kp, vp, lay):
+    """The C call without a workspace."""
+    import ctypes
+    out = torch.empty_like(qp)
+    status = ca.load_library().compact_attn_forward(*(ctypes.c_void_p(x.data_ptr()) for x in (qp, kp, vp)), lay.handle, ctypes.c_void_p(out.data_ptr()),
+                                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert status == 0
+    return out
+
+
+def _split_layout_and_inputs():
+    wl = make_workload("lend", 5, 32, 40, (2, 8, 8), 0, 2, 128, "bf16", [_GLOBAL] * 2)
+    lay = build_layout(ca, wl)
+    assert ca.compact_attn_layout_split(lay)[0] > 1 << 20
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in make_qkv(wl, DEV))
+    return lay, qp, kp, vp, ca.compact_attn_layout_split(lay)[0]
+
+
+def test_split_rows_without_memory_for_a_workspace():
+    """A call that has its output in hand is served also where the allocator has nothing left: with whole rows."""
+    lay, qp, kp, vp, need = _split_layout_and_inputs()
+    split, whole, out = ca.compact_attn_forward(qp, kp, vp, lay), _whole_rows(qp, kp, vp, lay), torch.empty_like(qp)
+    assert not torch.equal(split, whole)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hogs = []
+    torch.cuda.set_per_process_memory_fraction(0.0)
+    try:
+        for size in (need, need // 2, need // 4):         # what is left of the segments in use
+            try:
+                while True:
+                    hogs.append(torch.empty(size, dtype=torch.uint8, device=DEV))
+            except torch.cuda.OutOfMemoryError:
+                pass
+        ca.compact_attn_forward(qp, kp, vp, lay, out=out)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(out, whole)
+    del hogs
+    assert torch.equal(ca.compact_attn_forward(qp, kp, vp, lay), whole)   # and the layout asks no more
+
+
+def test_split_rows_in_a_capture_that_torch_does_not_run():
+    """Memory lent by torch belongs to somebody else when such a graph is replayed: the call leaves its rows whole, and a replay
+    writes nothing but the output."""
+    import ctypes
+    lay, qp, kp, vp, need = _split_layout_and_inputs()
+    whole, out = _whole_rows(qp, kp, vp, lay), torch.full_like(qp, float("nan"))
+    lib = ca.load_library()                               # the HIP runtime is among what it links
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ca.compact_attn_forward(qp, kp, vp, lay)          # leaves a free block of the workspace's size
+    torch.cuda.synchronize()
+    handle, graph, launch = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p()
+    assert lib.hipStreamBeginCapture(handle, 0) == 0
+    try:
+        ca.compact_attn_forward(qp, kp, vp, lay, out=out, stream=stream)
+    finally:
+        assert lib.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert lib.hipGraphInstantiate(ctypes.byref(launch), graph, None, None, ctypes.c_size_t(0)) == 0
+    with torch.cuda.stream(stream):
+        owned = [torch.full((need // 4,), 7.0, device=DEV) for _ in range(4)]   # one of them where the workspace would be
+        for _ in range(3):
+            out.fill_(float("nan"))
+            assert lib.hipGraphLaunch(launch, handle) == 0
+            assert torch.equal(out, whole)
+    torch.cuda.synchronize()
+    assert all(bool((x == 7.0).all()) for x in owned)
+    assert lib.hipGraphExecDestroy(launch) == 0 and lib.hipGraphDestroy(graph) == 0
