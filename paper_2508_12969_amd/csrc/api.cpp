@@ -276,7 +276,7 @@ int check_attention_args(const void* q, const void* k, const void* v, const ca_l
 // Fills the kernel arguments from the problem and a set of device tables, and launches.
 int launch_attention(const void* q, const void* k, const void* v, const ca_layout* L, const ca::DeviceTables& t, void* out,
                      void* stream, bool dense, bool natural, void* workspace) {
-  ca::AttnArgs a{};
+  ca::SplitArgs a{};
   a.q = q;
   a.k = k;
   a.v = v;

@@ -31,7 +31,7 @@ namespace {
 // permutation passes.
 // it: the part of the row's list to walk (kSplit).
 template <int B, int D, bool kNat, bool kSplit = false>
-__device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, int64_t batch, char* lds_k, char* lds_v, const LaunchItem& it = LaunchItem()) {
+__device__ __forceinline__ void attn_row_body(const LaunchArgs<kSplit>& a, int64_t row, int64_t batch, char* lds_k, char* lds_v, const LaunchItem& it = LaunchItem()) {
   using S = Shape<B, D>;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -134,7 +134,7 @@ __device__ __forceinline__ void attn_row_body(const AttnArgs& a, int64_t row, in
 // kPacked: the launch order may hold workgroups of two packed query tiles (entries below zero)
 template <int B, int D, bool kNat, bool kPacked, int kSimdWaves = 2, bool kSplit = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(B * 2, B * 2), amdgpu_waves_per_eu(kSimdWaves, kSimdWaves)))
-void attn_bf16_kernel(AttnArgs a) {
+void attn_bf16_kernel(LaunchArgs<kSplit> a) {
   using S = Shape<B, D>;
   __shared__ __attribute__((aligned(1024))) char lds_k[S::kTileBytes];
   __shared__ __attribute__((aligned(1024))) char lds_v[S::kTileBytes];
@@ -166,18 +166,22 @@ void attn_bf16_kernel(AttnArgs a) {
 }
 
 template <int B, int D, bool kPacked, int kSimdWaves>
-hipError_t launch(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch(const SplitArgs& a, hipStream_t stream) {
   if (a.natural && a.tw % Shape<B, D>::kRowsPerLoad != 0) return hipErrorInvalidValue;  // a KiB block must stay inside one run
   const int64_t workgroups = a.items ? a.batch * a.num_items : a.static_items + a.pool_wgs;
   if (workgroups < 1 || workgroups > 0x7fffffff) return hipErrorInvalidValue;
-  const auto kernel =
-      a.items ? (a.natural ? attn_bf16_kernel<B, D, true, kPacked, kSimdWaves, true> : attn_bf16_kernel<B, D, false, kPacked, kSimdWaves, true>)
-              : (a.natural ? attn_bf16_kernel<B, D, true, kPacked, kSimdWaves> : attn_bf16_kernel<B, D, false, kPacked, kSimdWaves>);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)workgroups), dim3(B * 2), 0, stream, a);
+  const dim3 grid((unsigned)workgroups), block(B * 2);
+  if (a.items) {
+    const auto kernel = a.natural ? attn_bf16_kernel<B, D, true, kPacked, kSimdWaves, true> : attn_bf16_kernel<B, D, false, kPacked, kSimdWaves, true>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, a);
+  } else {
+    const auto kernel = a.natural ? attn_bf16_kernel<B, D, true, kPacked, kSimdWaves> : attn_bf16_kernel<B, D, false, kPacked, kSimdWaves>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, static_cast<const AttnArgs&>(a));
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_rows(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_rows(const SplitArgs& a, hipStream_t stream) {
   const int64_t items = (int64_t)a.batch * a.entries;
   if (items == 0) return hipSuccess;
   if (!a.items && a.static_items + a.pool_items != items) return hipErrorInvalidValue;
@@ -195,7 +199,7 @@ hipError_t launch_rows(const AttnArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_attn_bf16(const SplitArgs& a, hipStream_t stream) {
   const hipError_t e = a.ways != kWaysNone ? launch_attn_bf16_ways(a, stream) : launch_rows(a, stream);
   return e == hipSuccess && a.items ? launch_attn_bf16_merge(a, stream) : e;
 }

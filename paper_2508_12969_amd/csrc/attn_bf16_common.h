@@ -51,7 +51,7 @@ struct LaunchItem {
   int first, count, part;
   int64_t share;
 };
-__device__ __forceinline__ LaunchItem split_item(const AttnArgs& a) {
+__device__ __forceinline__ LaunchItem split_item(const SplitArgs& a) {
   const int64_t linear = xcd_launch_order(blockIdx.x, gridDim.x, kXcdSplitChunk);
   const auto item = CONST_PTR(int32_t, a.items + linear % a.num_items);
   LaunchItem it;
@@ -553,7 +553,7 @@ struct QueryWave {
 
   // ---- epilogue of a row that is split along the keys: what this wave has summed up, lane by lane, as the merge
   // kernel reads it (attn_bf16_merge.hip); wave_at: index of the wave among all waves of all shares
-  __device__ __forceinline__ void store_share(const AttnArgs& a, int64_t wave_at, int lane, float ref) const {
+  __device__ __forceinline__ void store_share(const SplitArgs& a, int64_t wave_at, int lane, float ref) const {
     (static_cast<float2*>(a.share_stats) + wave_at * 64)[lane] = float2{ref, l_run};
     float4* const o = static_cast<float4*>(a.share_o) + wave_at * (D / 8) * 64;
 #pragma unroll

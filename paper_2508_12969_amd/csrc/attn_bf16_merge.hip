@@ -10,7 +10,7 @@ namespace ca {
 namespace {
 
 template <int D, bool kNat>
-__global__ __launch_bounds__(D * 2) void attn_bf16_merge_kernel(AttnArgs a) {
+__global__ __launch_bounds__(D * 2) void attn_bf16_merge_kernel(SplitArgs a) {
   constexpr int kRowBytes = D * 2;
   const int lane = threadIdx.x & 63, db = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int waves = a.share_waves, wave = (int)(blockIdx.x % (unsigned)waves);
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(D * 2) void attn_bf16_merge_kernel(AttnArgs a) {
 
 }  // namespace
 
-hipError_t launch_attn_bf16_merge(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_attn_bf16_merge(const SplitArgs& a, hipStream_t stream) {
   const int64_t blocks = a.batch * a.num_merges * a.share_waves;
   if (blocks < 1 || blocks > 0x7fffff || !a.merges || !a.share_stats || !a.share_o) return hipErrorInvalidValue;
   if (a.D != 64 && a.D != 128) return hipErrorInvalidValue;

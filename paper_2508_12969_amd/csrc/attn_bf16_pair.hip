@@ -7,7 +7,7 @@ namespace {
 
 template <bool kNat, bool kSplit>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
-void attn_bf16_pair_kernel(AttnArgs a) {
+void attn_bf16_pair_kernel(LaunchArgs<kSplit> a) {
   using S = PairShape<64>;
   __shared__ __attribute__((aligned(1024))) char lds_k[S::kTileBytes];
   __shared__ __attribute__((aligned(1024))) char lds_v[S::kTileBytes];
@@ -24,7 +24,7 @@ void attn_bf16_pair_kernel(AttnArgs a) {
 
 }  // namespace
 
-hipError_t launch_attn_bf16_pair(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_attn_bf16_pair(const SplitArgs& a, hipStream_t stream) {
   const int64_t items = (int64_t)a.batch * a.num_pairs;
   if (items == 0) return hipSuccess;
   if (a.B != 64 || a.D != 128 || !a.pair_rows || !a.pair_desc) return hipErrorInvalidValue;
@@ -38,7 +38,7 @@ hipError_t launch_attn_bf16_pair(const AttnArgs& a, hipStream_t stream) {
   }
   if (a.static_items + a.pool_wgs > 0x7fffffff || a.static_items + a.pool_items != items) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(a.static_items + a.pool_wgs)), block(256);
-  hipLaunchKernelGGL((a.natural ? attn_bf16_pair_kernel<true, false> : attn_bf16_pair_kernel<false, false>), grid, block, 0, stream, a);
+  hipLaunchKernelGGL((a.natural ? attn_bf16_pair_kernel<true, false> : attn_bf16_pair_kernel<false, false>), grid, block, 0, stream, static_cast<const AttnArgs&>(a));
   return hipGetLastError();
 }
 

@@ -32,7 +32,7 @@ using PairShape = Shape<B, 128, 4>;  // four waves that share the tile copies
 // tile each.  kNat: q, k, v, out in natural token order, gathered and scattered here (see attn_bf16.hip).
 // it: the part of its walk (kSplit).
 template <int B, bool kNat, bool kSplit = false>
-__device__ __forceinline__ void attn_pair_body(const AttnArgs& a, int64_t item, int64_t batch, char* lds_k, char* lds_v, const LaunchItem& it = LaunchItem()) {
+__device__ __forceinline__ void attn_pair_body(const LaunchArgs<kSplit>& a, int64_t item, int64_t batch, char* lds_k, char* lds_v, const LaunchItem& it = LaunchItem()) {
   using S = PairShape<B>;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

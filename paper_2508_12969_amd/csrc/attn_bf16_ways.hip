@@ -82,8 +82,8 @@ __device__ __forceinline__ void mask_granules(floatx16& s, int c0, int c1) {
 }
 
 template <int D, int NW, int NQ, bool kNat, bool kSplit>
-__global__ __attribute__((amdgpu_flat_work_group_size(NW * 64, NW * 64), amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
-void attn_bf16_ways_kernel(AttnArgs a, int parts) {
+__global__ __attribute__((amdgpu_flat_work_group_size(NW * 64, NW * 64), amdgpu_waves_per_eu(D == 64 && (NW == 4 || kSplit) ? 4 : 2)))
+void attn_bf16_ways_kernel(LaunchArgs<kSplit> a, int parts) {
   using S = WayShape<D, NW, NQ>;
   __shared__ __attribute__((aligned(1024))) char lds[4 * S::kStageBytes];  // K, V of stage 0, K, V of stage 1
   __shared__ float2 lds_stats[S::NK > 1 ? (NW - NQ) * 64 : 1];
@@ -313,21 +313,25 @@ void attn_bf16_ways_kernel(AttnArgs a, int parts) {
 }
 
 template <int D, int NW, int NQ>
-hipError_t launch(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch(const SplitArgs& a, hipStream_t stream) {
   const int parts = a.B / (32 * NQ);
   const int64_t entries = a.items ? a.num_items : (int64_t)a.num_heads * a.n * parts;
   const int64_t workgroups = a.batch * entries;
   if (parts < 1 || workgroups > 0xffffffffll / (NW * 64)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)workgroups), block(NW * 64);
-  const auto kernel = a.items ? (a.natural ? attn_bf16_ways_kernel<D, NW, NQ, true, true> : attn_bf16_ways_kernel<D, NW, NQ, false, true>)
-                              : (a.natural ? attn_bf16_ways_kernel<D, NW, NQ, true, false> : attn_bf16_ways_kernel<D, NW, NQ, false, false>);
-  hipLaunchKernelGGL(kernel, grid, block, 0, stream, a, parts);
+  if (a.items) {
+    const auto kernel = a.natural ? attn_bf16_ways_kernel<D, NW, NQ, true, true> : attn_bf16_ways_kernel<D, NW, NQ, false, true>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, a, parts);
+  } else {
+    const auto kernel = a.natural ? attn_bf16_ways_kernel<D, NW, NQ, true, false> : attn_bf16_ways_kernel<D, NW, NQ, false, false>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, static_cast<const AttnArgs&>(a), parts);
+  }
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_attn_bf16_ways(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_attn_bf16_ways(const SplitArgs& a, hipStream_t stream) {
   if ((int64_t)a.batch * a.num_heads * a.n == 0) return hipSuccess;
   if (a.num_classes < 1 || a.num_classes > 8) return hipErrorInvalidValue;
   if (a.D == 128 && a.ways == kWays4x4) return launch<128, 4, 4>(a, stream);

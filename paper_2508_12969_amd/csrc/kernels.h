@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "layout.h"
 
@@ -32,13 +33,6 @@ struct AttnArgs {
   int64_t entries;             // launch-order entries per batch entry (num_heads * n rows, or fewer entries when query tiles are packed)
   int32_t simd_waves;          // one-tile kernel, 64-token tiles of head dim 64: waves per SIMD, 2 or 3
   Ways ways;                   // bf16 kernels: which of the kernels of attn_bf16_ways.hip, on `order` as rows, or kWaysNone = the others
-  const WorkItem* items;       // device [num_items]; rows split along the keys (with `ways`), or null
-  const MergeItem* merges;     // device [num_merges]
-  int64_t num_items, num_merges; // of one batch entry
-  int32_t share_waves;         // 32-query waves of a share
-  int64_t shares;              // of one batch entry
-  void* share_stats;           // device workspace of batch * shares shares: (reference, sum) of the lanes, and O
-  void* share_o;
   int32_t packed;              // 1: `order` also holds workgroups of two packed query tiles, as the complement of their index in the pair tables
   const int32_t* pair_rows;    // device [2*num_pairs]; row ids of the two query tiles of a workgroup (-1: none), paired kernel only
   int64_t num_pairs;
@@ -68,17 +62,30 @@ struct AttnArgs {
   int32_t pool_items, pool_wgs;
   int32_t* pool_counter;       // device; zero before and after every launch
 };
+// What the kernels of rows split along the keys are given besides; the others do not get it, so that their arguments lie
+// as they did and their code is what it was.
+struct SplitArgs : AttnArgs {
+  const WorkItem* items;       // device [num_items]; null: rows are not split
+  const MergeItem* merges;     // device [num_merges]
+  int64_t num_items, num_merges; // of one batch entry
+  int32_t share_waves;         // 32-query waves of a share
+  int64_t shares;              // of one batch entry
+  void* share_stats;           // device workspace of batch * shares shares: (reference, sum) of the lanes, and O
+  void* share_o;
+};
+template <bool kSplit>
+using LaunchArgs = std::conditional_t<kSplit, SplitArgs, AttnArgs>;
 // fp32 problems, B <= 128, D in {32, 64, 128}
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream);
 // bf16 problems, (B, D) in {64,128} x {64,128}
-hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream);
+hipError_t launch_attn_bf16(const SplitArgs& a, hipStream_t stream);
 // the part of it with a.ways != kWaysNone
-hipError_t launch_attn_bf16_ways(const AttnArgs& a, hipStream_t stream);
+hipError_t launch_attn_bf16_ways(const SplitArgs& a, hipStream_t stream);
 // adds up the shares of split rows (after the launch that left them)
-hipError_t launch_attn_bf16_merge(const AttnArgs& a, hipStream_t stream);
+hipError_t launch_attn_bf16_merge(const SplitArgs& a, hipStream_t stream);
 // bf16 problems with D = 128: workgroups that serve two query tiles (B = 64: every pair of neighbours; B = 128: the
 // packed tiles of the grid's padded faces)
-hipError_t launch_attn_bf16_pair(const AttnArgs& a, hipStream_t stream);
+hipError_t launch_attn_bf16_pair(const SplitArgs& a, hipStream_t stream);
 
 // The tile-mass kernel works on kMassQueries queries at a time: one query tile of 128 tokens, or two neighbours of 64.
 constexpr int kMassQueries = 128;

@@ -20,8 +20,8 @@
 namespace ca {
 hipError_t launch_permute(const PermuteArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_attn_f32(const AttnArgs&, hipStream_t) { return hipErrorInvalidValue; }
-hipError_t launch_attn_bf16(const AttnArgs&, hipStream_t) { return hipErrorInvalidValue; }
-hipError_t launch_attn_bf16_pair(const AttnArgs&, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_attn_bf16(const SplitArgs&, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_attn_bf16_pair(const SplitArgs&, hipStream_t) { return hipErrorInvalidValue; }
 int64_t g_mass_rows = 0;  // workgroups that the last tile-mass launch was given
 hipError_t launch_tile_mass(const MassArgs& a, hipStream_t) {
   g_mass_rows = a.partial_rows;
