@@ -467,8 +467,9 @@ struct QueryWave {
   // softmax: numerator and denominator share the same reference.  Probabilities are rounded to bf16
   // (the B operand of the second product); the row sum adds up the rounded values, two per v_dot2, so
   // numerator and denominator see the same numbers.
-  // `first`: the walk's first tile, wave-uniform, where a reference is taken anyway.  No result depends on it; the 64 x 64 one-tile
-  // kernel takes 145 registers without it and 124 with it.
+  // `first`: the wave's first tile, wave-uniform, where a reference is taken anyway.  No result depends on it, but the code does: the
+  // 64 x 64 one-tile kernel takes 145 registers without it and 124 with it (step of 8K tokens 213.6 / 209.6 us), and a dense walk of
+  // packed faces (19 heads x 16K) 4.36 / 4.32 ms.  The kernels of attn_bf16_ways.hip come out the same and go without.
   __device__ __forceinline__ void softmax(floatx16 (&acc_s)[S::kKeyBlocks], bf16x8 (&pf)[S::kKeyBlocks][2], bool first = false) {
     float mx = acc_s[0][0];
 #pragma unroll

@@ -66,6 +66,7 @@ __device__ __forceinline__ void attn_pair_body(const LaunchArgs<kSplit>& a, int6
   const bool wave_active = wave_used && qs.wave_active && (member == 0 || has_b);
   const int64_t q_row = kNat ? natural_query_row(a, q_tile, qs.slot) : q_tile * S::B + qs.slot;
   w.load_q(static_cast<const char*>(a.q) + plane + q_row * S::kRowBytes);
+  bool seen = false;  // this wave has processed a tile of its own list (wave-uniform)
 
   const TileLoader<S, false> k_loader(wave, lane);
   const TileLoader<S, true> v_loader(wave, lane);
@@ -114,7 +115,8 @@ __device__ __forceinline__ void attn_pair_body(const LaunchArgs<kSplit>& a, int6
 
       bf16x8 pf[S::kKeyBlocks][2];
       w.mask_padding_keys(acc_s, cls, class_mask);
-      w.softmax(acc_s, pf);
+      w.softmax(acc_s, pf, !seen);
+      seen = true;
 
       // ---- O^T += V^T P^T ------------------------------------------------------------------------
       if (more) WAIT_VMCNT(S::kLoadsPerThread);  // V landed (the next K may be in flight)
