@@ -1,15 +1,18 @@
 // Host-side exercise of the C ABI for a build with AddressSanitizer and UndefinedBehaviorSanitizer
 // (host code only; no kernel is launched and no GPU is needed).  It walks the pointer-heavy host
 // paths: the layout builder, CSR import with malformed input, union, similarity, query-tile pairs,
-// the window search, the size of the tile-mass workspace, and the packing of the device tables including the two padding words the
+// the plans of rows split along the keys, the window search, the size of the tile-mass workspace, and the packing of the device tables including the two padding words the
 // kernels are allowed to read past the end of every list.  Any sanitizer report aborts the run;
 // a wrong result prints a message and exits with status 1.
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <random>
+#include <utility>
 #include <vector>
 
 #include "compact_attn.h"
@@ -267,6 +270,97 @@ void check_split_function() {
   }
 }
 
+// Rows split along the keys: the items of a plan cover every list of the unsplit launch exactly once, the shares are numbered
+// as the merges expect them, and the limits hold.  Returns whether the layout has a plan for that walk.
+bool check_split_plan(const ca_layout* L, bool dense) {
+  const ca::SplitPlan& plan = dense ? L->split_dense : L->split;
+  if (plan.shares == 0) {
+    CHECK(plan.items.empty() && plan.merges.empty());
+    return false;
+  }
+  CHECK((int64_t)plan.items.size() <= ca::kMaxSplitItems);
+  CHECK(ca::workspace_bytes(plan, L->prob.batch, L->prob.head_dim) <= ca::kMaxShareBytes);
+  const bool ways = plan.ways != ca::kWaysNone, paired = !ways && !L->pair_rows.empty() && !L->packed_faces;
+  const int parts = ways ? (int)L->B / (32 * plan.waves) : 1;
+  std::vector<int32_t> entries;
+  if (paired)
+    for (int64_t i = 0; i < (int64_t)L->pair_rows.size() / 2; ++i) entries.push_back((int32_t)~i);
+  else
+    entries = !ways && L->packed_faces ? L->launch_rows : L->order;
+  CHECK(parts >= 1 && parts <= 4);
+  if (!ways) CHECK(plan.waves == (paired ? 4 : (int)L->B / 32));
+  std::map<std::pair<int32_t, int>, std::vector<const ca::WorkItem*>> of;
+  for (const ca::WorkItem& it : plan.items) of[{it.entry, it.place & 3}].push_back(&it);
+  std::map<std::pair<int32_t, int>, const ca::MergeItem*> merged;
+  for (const ca::MergeItem& m : plan.merges) CHECK(merged.emplace(std::make_pair(m.entry, (int)m.part), &m).second);
+  size_t items = 0;
+  std::vector<char> taken((size_t)plan.shares, 0);
+  for (int32_t e : entries) {
+    const int64_t length = dense ? L->n : e < 0 ? L->pair_walk_ptr[~e + 1] - L->pair_walk_ptr[~e] : L->row_ptr[e + 1] - L->row_ptr[e];
+    for (int part = 0; part < parts; ++part) {
+      int tokens = 1;  // a part of the row's query slots without a token has nothing to walk
+      if (ways) {
+        tokens = -part * 32 * plan.waves;
+        for (uint32_t w : L->class_mask[L->tile_class[e % L->n]].w) tokens += __builtin_popcount(w);
+      }
+      auto& mine = of[{e, part}];
+      std::sort(mine.begin(), mine.end(), [](const ca::WorkItem* x, const ca::WorkItem* y) { return x->first < y->first; });
+      CHECK(!mine.empty());
+      items += mine.size();
+      int64_t at = 0;
+      for (const ca::WorkItem* it : mine) {
+        CHECK(it->first == at && it->count >= (mine.size() > 1 ? 1 : 0));
+        at += it->count;
+      }
+      CHECK(at == (tokens > 0 ? length : 0));
+      const auto m = merged.find({e, part});
+      CHECK((m != merged.end()) == (mine.size() > 1));
+      if (mine.size() <= 1) {
+        for (const ca::WorkItem* it : mine) CHECK(it->place >> 2 == 0);
+      } else if (m != merged.end()) {
+        CHECK(m->second->shares == (int32_t)mine.size());
+        for (size_t k = 0; k < mine.size(); ++k) {
+          const int32_t share = (mine[k]->place >> 2) - 1;
+          CHECK(share == m->second->first_share + (int32_t)k && share >= 0 && share < plan.shares && !taken[(size_t)share]);
+          if (share >= 0 && share < plan.shares) taken[(size_t)share] = 1;
+        }
+      }
+    }
+  }
+  CHECK(items == plan.items.size());
+  for (char c : taken) CHECK(c);
+  for (size_t i = 1; i < plan.items.size(); ++i) CHECK(plan.items[i].count <= plan.items[i - 1].count);
+  return true;
+}
+
+// A plan of every kernel, on grids padded along several axes, with long, short and empty rows.
+void check_split_plans() {
+  const struct {
+    const char* kernel;
+    int D, T, H, W, tt, text_tiles, heads, batch;
+  } plans[] = {{"one-tile", 64, 2, 8, 40, 2, 0, 1, 1},    {"one-tile", 64, 7, 8, 8, 1, 1, 3, 2},       {"one-tile", 128, 2, 30, 8, 2, 1, 3, 2},
+               {"packed-faces", 128, 1, 8, 20, 2, 1, 1, 1}, {"packed-faces", 128, 2, 13, 20, 2, 1, 3, 2}, {"paired", 128, 2, 21, 8, 1, 1, 3, 2},
+               {"ways-4x4", 128, 5, 30, 8, 2, 1, 3, 2},     {"ways-4x4", 64, 9, 21, 8, 2, 1, 3, 2},       {"ways-8x4", 128, 5, 8, 40, 2, 1, 3, 2},
+               {"ways-8x2", 64, 9, 13, 8, 2, 1, 3, 2},      {"ways-8x2", 128, 16, 30, 8, 1, 1, 3, 2},     {"ways-8x2", 64, 2, 21, 20, 1, 0, 1, 1}};
+  const ca_group all{99, {99, 99}, {-1, -1}}, near{0, {0, 1}, {-1, -1}};
+  int dense_plans = 0;
+  for (const auto& s : plans) {
+    const ca_problem p{s.T, s.H, s.W, s.tt, 8, 8, s.text_tiles * s.tt * 64, s.batch, s.heads, s.D, CA_BF16, 0.f};
+    const ca_head heads[3] = {{1, 0, &all}, {0, 0, nullptr}, {1, 0, &near}};
+    ca_layout* L = nullptr;
+    CHECK(compact_attn_build_layout(&p, heads, &L) == CA_OK);
+    if (!L) continue;
+    int64_t bytes = 0;
+    const char* name = nullptr;
+    CHECK(compact_attn_layout_split(L, 0, &bytes, &name) == CA_OK && bytes > 0 && name && std::strcmp(name, s.kernel) == 0);
+    CHECK(bytes == ca::workspace_bytes(L->split, p.batch, p.head_dim));
+    CHECK(check_split_plan(L, false));
+    dense_plans += check_split_plan(L, true);
+    compact_attn_free_layout(L);
+  }
+  CHECK(dense_plans > 0);
+}
+
 void check_layout_views(const ca_layout* L, const ca_problem& p) {
   int64_t n = 0, B = 0, n_real = 0, n_pad = 0, nnz = 0;
   CHECK(compact_attn_layout_info(L, &n, &B, &n_real, &n_pad, &nnz) == CA_OK);
@@ -315,6 +409,7 @@ void run_case(std::mt19937& rng, ca_problem p) {
   check_layout_views(L, p);
   check_packing(L);
   check_layout_splits(L);
+  for (bool dense : {false, true}) check_split_plan(L, dense);
   check_wave_assignment(L);
 
   // round trip through the CSR import, then union with a second random layout and similarity
@@ -334,6 +429,7 @@ void run_case(std::mt19937& rng, ca_problem p) {
     check_layout_views(merged, p);
     check_packing(merged);
     check_layout_splits(merged);
+    for (bool dense : {false, true}) check_split_plan(merged, dense);
     check_wave_assignment(merged);
     double sim = -1;
     CHECK(compact_attn_layout_similarity(merged, 0, merged, 0, &sim) == CA_OK && sim == 1.0);
@@ -523,6 +619,7 @@ int main() {
   for (const ca_problem& p : cases)
     for (int rep = 0; rep < 3; ++rep) run_case(rng, p);
   check_split_function();
+  check_split_plans();
   check_mass_workspace();
   check_sampling();
 
