@@ -234,11 +234,13 @@ int compact_attn_forward(const void* q, const void* k, const void* v, ca_layout*
 
 /* compact_attn_forward for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and the same
- * result, bit for bit (that of compact_attn_forward_with_workspace where rows are split along the keys), but
- * the layout's tables (row offsets, packed tile words, launch order, padding masks, pair walks) are read from a fixed 8 MiB device array inside the library instead of from
- * memory allocated at compact_attn_layout_upload; the call makes no hipMalloc / hipFree and needs no
- * prior upload.  Every GPU the library runs on holds one such array until the process ends, and one of 64 MiB for the
- * partial sums of split rows.
+ * result, bit for bit (that of compact_attn_forward_with_workspace where rows are split along the keys;
+ * compact_attn_forward itself leaves rows whole, which differs from it by the rounding of bf16
+ * probabilities), but the layout's tables (row offsets, packed tile words, launch order, padding masks,
+ * pair walks) are read from a fixed 8 MiB device array inside the library instead of from memory
+ * allocated at compact_attn_layout_upload; the call makes no hipMalloc / hipFree and needs no prior
+ * upload.  Every GPU the library runs on holds one such array until the process ends, and one of 64 MiB
+ * for the partial sums of split rows.
  *   - A layout whose tables exceed the array (about 1.9 million kept tile pairs) is rejected with
  *     CA_ERR_UNSUPPORTED and a message that states both sizes; nothing is enqueued.
  *   - The array keeps the tables of the layout the previous call on this GPU used.  A call with the

@@ -363,6 +363,7 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
     set_split(a.entries, dense ? L->split_rows_dense : L->split_rows);
     e = bf16 ? ca::launch_attn_bf16(a, (hipStream_t)stream) : ca::launch_attn_f32(a, (hipStream_t)stream);
   }
+  if (e == hipSuccess && a.items) e = ca::launch_attn_bf16_merge(a, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, dense ? "dense attention launch" : "sparse attention launch");
   return CA_OK;
 }

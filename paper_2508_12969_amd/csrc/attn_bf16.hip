@@ -200,8 +200,7 @@ hipError_t launch_rows(const SplitArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_attn_bf16(const SplitArgs& a, hipStream_t stream) {
-  const hipError_t e = a.ways != kWaysNone ? launch_attn_bf16_ways(a, stream) : launch_rows(a, stream);
-  return e == hipSuccess && a.items ? launch_attn_bf16_merge(a, stream) : e;
+  return a.ways != kWaysNone ? launch_attn_bf16_ways(a, stream) : launch_rows(a, stream);
 }
 
 }  // namespace ca

@@ -362,7 +362,8 @@ struct QueryWave {
   floatx16 neg_m;
   float l_run;                 // this lane's share of the running sum (partner lane holds the rest)
   float c2;                    // scale * log2(e)
-  float moves_above;           // a score further above the reference than this moves it: kLazyLog2 in raw score units, or -inf while the query has met no finite score
+  float moves_above;           // a score further above the reference than this moves it: kLazyLog2 in raw score units, or
+                               // -inf while the query has met no finite score
   int qi, g;
   // per-lane LDS read offsets
   int k_lane_row_off, k_lane_swz;                              // K: row (32*kb + qi), logical chunk 2*step + g
@@ -549,7 +550,8 @@ struct QueryWave {
     if (upper_keys) pv<S::kKeyBlocks / 2, S::kKeyBlocks>(lds_v, pf);
   }
 
-  // The query's exponent reference, for sums that are added to others: minus infinity, the reference of no sum, before the first finite score.
+  // The query's exponent reference, for sums that are added to others: minus infinity, the reference of no sum, before the
+  // first finite score.
   __device__ __forceinline__ float reference() const { return moves_above == kMinusInf ? kMinusInf : -neg_m[0]; }
 
   // ---- epilogue of a row that is split along the keys: what this wave has summed up, lane by lane, as the merge

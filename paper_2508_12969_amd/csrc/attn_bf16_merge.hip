@@ -1,8 +1,8 @@
 // Rows split along the keys (SplitPlan in layout.h): adds up what the shares of a row have left in the workspace and
 // writes the output.
 //
-// Bound: latency.  A share of 32 queries is 16 KB at head dim 128, a launch leaves at most 32 MiB, and most leave a tenth
-// of that.  A workgroup takes 32 queries, a wave 32 channels of them, lane by lane as the attention kernels left them,
+// Bound: latency.  A share of 32 queries is 16.5 KB at head dim 128, a launch leaves kMaxShareBytes at most, and most leave a
+// tenth of that.  A workgroup takes 32 queries, a wave 32 channels of them, lane by lane as the attention kernels left them,
 // so that all reads are whole lines; the shares are added in their order, so the result is run-to-run identical.
 #include "attn_bf16_common.h"
 

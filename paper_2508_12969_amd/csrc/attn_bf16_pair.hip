@@ -33,8 +33,7 @@ hipError_t launch_attn_bf16_pair(const SplitArgs& a, hipStream_t stream) {
     const int64_t workgroups = a.batch * a.num_items;
     if (workgroups < 1 || workgroups > 0x7fffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL((a.natural ? attn_bf16_pair_kernel<true, true> : attn_bf16_pair_kernel<false, true>), dim3((unsigned)workgroups), dim3(256), 0, stream, a);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? launch_attn_bf16_merge(a, stream) : e;
+    return hipGetLastError();
   }
   if (a.static_items + a.pool_wgs > 0x7fffffff || a.static_items + a.pool_items != items) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(a.static_items + a.pool_wgs)), block(256);

@@ -111,7 +111,9 @@ struct MassArgs {
   const void* q;               // [batch, heads, N_pad, D] tile order, bf16
   const void* k;
   float* mass;                 // [batch, heads, n, n]
-  float* partial;              // device workspace, partial_rows * n * kMassQueries * 2 floats: per query and key tile (sum, reference) of the row group a workgroup is working on (of every row group, where these have several shares)
+  float* partial;              // device workspace, partial_rows * n * kMassQueries * 2 floats: per query and key tile (sum,
+                               // reference) of the row group a workgroup is working on (of every row group, where these
+                               // have several shares)
   int64_t partial_rows;        // blocks of the workspace = most workgroups a launch may have, or the row groups where these have several shares
   int64_t places;              // workgroups that the device holds at a time
   int32_t shares;              // workgroups that share the key tiles of a row group, see mass_shares

@@ -498,7 +498,8 @@ struct Unit {
 
 // Splits the units of a launch (of one batch entry) along the keys for the kernel `ways` (kWaysNone: the one-tile or paired kernel)
 // of workgroups of `waves` 32-query waves, and takes the best such plan into `plan` (and its time into `best`) if it is predicted to
-// take less than `best`.  step_of: steps of 128 keys of so many tiles.
+// take less than `best`.  step_of: steps of 128 keys of so many tiles.  The one-tile kernel for 64-token tiles of head dim 64 is
+// priced with two waves per SIMD, for which its cost was fitted, also where choose_simd_waves gives the launch three.
 template <class StepOf>
 void plan_split(const ca_layout& L, const std::vector<Unit>& units, Ways ways, int waves, const LaunchCost& cost, double gathered, StepOf step_of, double& best,
                 SplitPlan& plan) {
@@ -687,7 +688,7 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* p
     const double t = launch_time(w.cost, walks, p.batch, padded, best);
     if (t < best) best = t, ways = w.ways;
   }
-  if (plan) {
+  if (plan && std::min(plain_groups, (int64_t)L.order.size()) <= kMaxSplitItems) {
     best *= kSplitGain / (ways == kWaysNone ? kPlainBias : 1.0);
     std::vector<Unit> units;
     for (int64_t i = 0; i < plain_groups; ++i) {

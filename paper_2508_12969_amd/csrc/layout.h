@@ -41,8 +41,8 @@ constexpr int64_t kPoolMinItems = 4096; // smaller launches are dealt statically
 // `work[i]`: cost of launch-order entry i (tile steps); returns the split of one batch entry's launch.
 LaunchSplit split_launch(const int64_t* work, int64_t entries);
 
-constexpr int kXcdSplitChunk = 32;      // the same where rows are split along the keys: such launches are small
 constexpr int kXcdChunk = 64;           // consecutive launch-order entries handed to one XCD
+constexpr int kXcdSplitChunk = 32;      // the same where rows are split along the keys: such launches are small
 
 // Launch-order entry of a workgroup id.  Workgroup ids are dealt round-robin to the 8 XCDs, each
 // with an L2 of its own; they are remapped so that the workgroups resident on one XCD at a time

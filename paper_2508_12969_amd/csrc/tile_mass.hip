@@ -17,8 +17,8 @@
 // One product per tile pair.  The normaliser l_i of a query is known only after its last key tile,
 // so the walk over the n key tiles keeps what it cannot finish: per query i and key tile b the
 // unnormalised sum  e[b][i] = sum_{j in b} exp2(scale' * (s_ij - m)), together with the exponent
-// reference m it was taken against (it moves when a sum outgrows it, rarely), two floats, written to a workspace in device memory (2 * n * 128 floats per
-// workgroup).  After the walk the workgroup reads its
+// reference m it was taken against (it moves when a sum outgrows it, rarely), two floats, written to a workspace in
+// device memory (2 * n * 128 floats per workgroup).  After the walk the workgroup reads its
 // block back (or, where a launch would leave places empty and several workgroups share the key tiles, a second kernel
 // reads theirs), brings every sum to the query's final reference and reduces over the queries,
 //     mass[a, b] = sum_i e[b][i] * exp2(scale' * (m[b][i] - m_i)) / l_i,
@@ -40,8 +40,8 @@ constexpr float kSumLimit = 0x1p40f;  // a tile's row sum beyond this moves the 
 // 128 queries per workgroup: one query tile of 128 tokens or two neighbours of 64 (the walk is the same
 // for all rows of a head), and 128 keys per step, two tiles of 64 tokens; 64 keys where only that leaves
 // LDS for a third workgroup on the CU (64-token tiles, head dim 128).
-// Measured (all with 0.1 us more per group than now, see the end of the kernel), against one query tile and one key tile at a time and two waves per SIMD: 64-token tiles of
-// head dim 64, 14.4K queries x 14.4K keys, 12 heads 771 -> 623 us, 80.6K x 80.6K, 8 heads 12.1 -> 10.0 ms;
+// Measured (all with 0.1 us more per group than now, see the end of the kernel), against one query tile and one key tile
+// at a time and two waves per SIMD: 64-token tiles of head dim 64, 14.4K queries x 14.4K keys, 12 heads 771 -> 623 us, 80.6K x 80.6K, 8 heads 12.1 -> 10.0 ms;
 // of head dim 128, 8 heads of 75.6K 17.9 -> 14.4 ms (15.7 ms with two workgroups of 128-key steps).
 // 256-key steps at head dim 64 with two workgroups: 685 us and 11.1 ms; four workgroups: 625 us, 10.2 ms.
 template <int B, int D>

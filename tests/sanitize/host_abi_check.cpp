@@ -1,8 +1,8 @@
 // Host-side exercise of the C ABI for a build with AddressSanitizer and UndefinedBehaviorSanitizer
 // (host code only; no kernel is launched and no GPU is needed).  It walks the pointer-heavy host
 // paths: the layout builder, CSR import with malformed input, union, similarity, query-tile pairs,
-// the plans of rows split along the keys, the window search, the size of the tile-mass workspace, and the packing of the device tables including the two padding words the
-// kernels are allowed to read past the end of every list.  Any sanitizer report aborts the run;
+// the plans of rows split along the keys, the window search, the size of the tile-mass workspace, and the
+// packing of the device tables including the two padding words the kernels are allowed to read past the end of every list.  Any sanitizer report aborts the run;
 // a wrong result prints a message and exits with status 1.
 #include <algorithm>
 #include <cmath>
@@ -25,6 +25,7 @@ hipError_t launch_permute(const PermuteArgs&, hipStream_t) { return hipErrorInva
 hipError_t launch_attn_f32(const AttnArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_attn_bf16(const SplitArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_attn_bf16_pair(const SplitArgs&, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_attn_bf16_merge(const SplitArgs&, hipStream_t) { return hipErrorInvalidValue; }
 int64_t g_mass_rows = 0;  // workgroups that the last tile-mass launch was given
 hipError_t launch_tile_mass(const MassArgs& a, hipStream_t) {
   g_mass_rows = a.partial_rows;
