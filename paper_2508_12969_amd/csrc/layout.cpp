@@ -487,8 +487,11 @@ struct WayCost {
 };
 
 // Rows are split if that is predicted to take this much of the time.  Measured, whole / split: 3 heads x 15K of head dim 128 250 /
-// 221 us, 2 x 12 heads x 20K of head dim 64 1286 / 1162 us, 102 rows 153 / 38 us; no drawn call became more than 5 % slower.
-constexpr double kSplitGain = 0.9;
+// 218 us, 2 x 12 heads x 20K of head dim 64 1267 / 1142 us, 102 rows 153 / 38 us; of 630 split launches, 1.35 times faster as a whole
+// (geometric mean), 14 are 2 to 9 % slower, all but two of kWays8x2 at head dim 64.
+// With three waves per SIMD whole rows take 0.68 to 1.05 of what is predicted for them, so that more has to be gained: five of 28
+// such launches were 4 to 9 % slower priced as with two waves and with the first limit, none of 23 is now (1.03 to 1.65 times faster).
+constexpr double kSplitGain = 0.9, kSplitGainThree = 0.77;
 
 // What a workgroup of an unsplit launch walks: an entry of its launch order and a part of the row's query slots.
 struct Unit {
@@ -498,8 +501,7 @@ struct Unit {
 
 // Splits the units of a launch (of one batch entry) along the keys for the kernel `ways` (kWaysNone: the one-tile or paired kernel)
 // of workgroups of `waves` 32-query waves, and takes the best such plan into `plan` (and its time into `best`) if it is predicted to
-// take less than `best`.  step_of: steps of 128 keys of so many tiles.  The one-tile kernel for 64-token tiles of head dim 64 is
-// priced with two waves per SIMD, for which its cost was fitted, also where choose_simd_waves gives the launch three.
+// take less than `best`.  step_of: steps of 128 keys of so many tiles.
 template <class StepOf>
 void plan_split(const ca_layout& L, const std::vector<Unit>& units, Ways ways, int waves, const LaunchCost& cost, double gathered, StepOf step_of, double& best,
                 SplitPlan& plan) {
@@ -689,16 +691,27 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* p
     if (t < best) best = t, ways = w.ways;
   }
   if (plan && std::min(plain_groups, (int64_t)L.order.size()) <= kMaxSplitItems) {
-    best *= kSplitGain / (ways == kWaysNone ? kPlainBias : 1.0);
+    if (ways == kWaysNone) best /= kPlainBias;
+    // Rows of 64-token tiles of head dim 64 run with three waves per SIMD where choose_simd_waves says so, and so do their items,
+    // which no other kernel is tried for (kWays8x2, the one that was predicted to gain there, did not).
+    static const LaunchCost kThreeWaves{6, 2.99, 0.54, 1.89, 0.65, 0};
+    const bool three_waves = ways == kWaysNone && !big_d && !big_b && (dense ? L.simd_waves_dense : L.simd_waves) == 3;
+    const LaunchCost& plain = three_waves ? kThreeWaves : kPlain[big_d][big_b];
+    if (three_waves) {
+      walks.clear();
+      for (int64_t i = 0; i < plain_groups; ++i) walks.push_back((float)((dense ? L.n : L.row_ptr[launched[i] + 1] - L.row_ptr[launched[i]]) * L.B) / 128);
+      best = launch_time(plain, walks, p.batch, 0, HUGE_VAL);
+    }
+    best *= three_waves ? kSplitGainThree : kSplitGain;
     std::vector<Unit> units;
     for (int64_t i = 0; i < plain_groups; ++i) {
       const int64_t e = paired ? ~i : dense && !L.packed_faces ? i : launched[i];
       units.push_back({(int32_t)e, 0, dense ? L.n : e < 0 ? L.pair_walk_ptr[~e + 1] - L.pair_walk_ptr[~e] : L.row_ptr[e + 1] - L.row_ptr[e]});
     }
     // only in the place of themselves: they multiply the padding slots of K and V too (by zero), the others never read them
-    if (ways == kWaysNone) plan_split(L, units, kWaysNone, paired ? 4 : (int)L.B / 32, kPlain[big_d][big_b], 0, [&](int64_t tiles) { return paired ? (double)tiles : (double)(tiles * L.B) / 128; },
+    if (ways == kWaysNone) plan_split(L, units, kWaysNone, paired ? 4 : (int)L.B / 32, plain, 0, [&](int64_t tiles) { return paired ? (double)tiles : (double)(tiles * L.B) / 128; },
                                       best, *plan);
-    for (int i = 0; i < count; ++i) {
+    for (int i = 0; i < (three_waves ? 0 : count); ++i) {
       const WayCost& w = options[i];
       const int parts = (int)L.B / w.part_queries;
       const double stage = w.stage_keys / 16;

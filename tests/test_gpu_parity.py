@@ -1356,7 +1356,7 @@ _SPLIT_LAUNCHES = [
     ("ways-8x2", 128, (5, 8, 20), (2, 8, 8), 1, [_GLOBAL], 1),
     # split and whole rows, empty rows
     ("one-tile", 64, (7, 8, 8), (1, 8, 8), 1, _MIXED, 2),
-    ("one-tile-3", 64, (16, 8, 20), (1, 8, 8), 1, [_GLOBAL, _GLOBAL, _GLOBAL, _GLOBAL, _LOCAL, _LOCAL, [], _NEAR] * 2, 2),
+    ("one-tile-3", 64, (24, 8, 20), (1, 8, 8), 1, [_GLOBAL, _GLOBAL, _GLOBAL, _GLOBAL, _LOCAL, _LOCAL, [], _NEAR] * 2, 2),
     ("one-tile", 128, (2, 30, 8), (2, 8, 8), 1, _MIXED, 2),
     ("packed-faces", 128, (2, 13, 20), (2, 8, 8), 1, _MIXED, 2),
     ("paired", 128, (2, 21, 8), (1, 8, 8), 1, _MIXED, 2),
