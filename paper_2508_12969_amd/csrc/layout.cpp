@@ -709,8 +709,8 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* p
       units.push_back({(int32_t)e, 0, dense ? L.n : e < 0 ? L.pair_walk_ptr[~e + 1] - L.pair_walk_ptr[~e] : L.row_ptr[e + 1] - L.row_ptr[e]});
     }
     // only in the place of themselves: they multiply the padding slots of K and V too (by zero), the others never read them
-    if (ways == kWaysNone) plan_split(L, units, kWaysNone, paired ? 4 : (int)L.B / 32, plain, 0, [&](int64_t tiles) { return paired ? (double)tiles : (double)(tiles * L.B) / 128; },
-                                      best, *plan);
+    const auto walk = [&](int64_t tiles) { return paired ? (double)tiles : (double)(tiles * L.B) / 128; };
+    if (ways == kWaysNone) plan_split(L, units, kWaysNone, paired ? 4 : (int)L.B / 32, plain, 0, walk, best, *plan);
     for (int i = 0; i < (three_waves ? 0 : count); ++i) {
       const WayCost& w = options[i];
       const int parts = (int)L.B / w.part_queries;

@@ -113,7 +113,8 @@ struct DeviceTables {
   MergeItem *split_merges = nullptr, *split_merges_dense = nullptr;
   int32_t* pool_counters = nullptr; // [pool_slots] tickets of the dynamically drawn tail of a launch; zero between launches
   int32_t pool_slots = 0;           // concurrent launches on one layout take different counters, round-robin
-  float* mass_partial = nullptr;  // workspace of the tile-mass kernel, mass_partial_rows (= most workgroups of its launch) * n * kMassQueries * 2 floats; allocated at its first call
+  float* mass_partial = nullptr;   // workspace of the tile-mass kernel, allocated at its first call: mass_partial_rows (= most
+                                   // workgroups of its launch) * n * kMassQueries * 2 floats
   int64_t mass_partial_rows = 0;
   int64_t mass_places = 0;         // workgroups of it that the device holds at a time
   int32_t mass_shares = 1;         // workgroups that share the key tiles of a row group
