@@ -234,13 +234,13 @@ int compact_attn_forward(const void* q, const void* k, const void* v, ca_layout*
 
 /* compact_attn_forward for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and the same
- * result, bit for bit (that of compact_attn_forward_with_workspace where rows are split along the keys;
- * compact_attn_forward itself leaves rows whole, which differs from it by the rounding of bf16
- * probabilities), but the layout's tables (row offsets, packed tile words, launch order, padding masks,
+ * result, bit for bit (that of compact_attn_forward_with_workspace where that uses a workspace of at most 64 MiB;
+ * compact_attn_forward itself, and an f32 call whose workspace would be larger, differ from it by the rounding of bf16
+ * probabilities or of fp32 sums), but the layout's tables (row offsets, packed tile words, launch order, padding masks,
  * pair walks) are read from a fixed 8 MiB device array inside the library instead of from memory
  * allocated at compact_attn_layout_upload; the call makes no hipMalloc / hipFree and needs no prior
  * upload.  Every GPU the library runs on holds one such array until the process ends, and one of 64 MiB
- * for the partial sums of split rows.
+ * for the workspace.
  *   - A layout whose tables exceed the array (about 1.9 million kept tile pairs) is rejected with
  *     CA_ERR_UNSUPPORTED and a message that states both sizes; nothing is enqueued.
  *   - The array keeps the tables of the layout the previous call on this GPU used.  A call with the
@@ -271,13 +271,18 @@ int compact_attn_forward_natural(const void* q, const void* k, const void* v, ca
 int compact_attn_dense(const void* q, const void* k, const void* v, ca_layout* layout, void* out,
                        void* stream);
 
-/* The three calls above for callers that can lend device memory.  Launches too small to fill the device, or
+/* The three calls above for callers that can lend device memory.  bf16 launches too small to fill the device, or
  * that would end with a few long rows, are split along the keys: several workgroups share a row, leave their partial
  * sums in the workspace, and a second kernel adds them up (always in the same order, so results are
- * run-to-run identical; compact_attn_forward_static does the same with a fixed device array).
- *   compact_attn_layout_split: *workspace_bytes = what such a call needs, at most 64 MiB, 0 where rows are not split;
+ * run-to-run identical; compact_attn_forward_static does the same with a fixed device array).  f32 launches of tiles of
+ * more than 32 tokens that are large enough to pay for it run on the bf16 matrix instructions: K and V are split into three
+ * bf16 values each, which hold all of their 24 bits, and every product is the sum of the six partial products down to
+ * 2^-24 of it, in fp32 (measured error against 64 bits: 0.3 to 0.8 of that of the kernel without a workspace).
+ *   compact_attn_layout_split: *workspace_bytes = what such a call needs, 0 where it has no use for one: at most 64 MiB for
+ *   the partial sums of bf16 rows; for f32 12 * batch * heads * n * ceil(B / 16) * 16 * D bytes, at most 8 GiB;
  *   sparse walk (dense = 0: forward and natural) or dense walk (dense = 1).  kernel may be NULL; *kernel receives the
- *   name (see compact_attn_layout_kernel) of the kernel that serves the split launch, NULL where there is none.
+ *   name of the kernel that serves such a call (see compact_attn_layout_kernel, or "f32-planes-2x2", "f32-planes-2x4",
+ *   "f32-planes-1x4": 32-query waves of a workgroup side by side x waves that share the keys of a query), NULL where there is none.
  *   workspace: device memory of at least that size, 16-byte aligned, not overlapping the tensors; its contents
  *   before and after the call mean nothing.  It must not be used by anything else until the call's work on `stream` has
  *   run.  Ignored (and may be NULL) where *workspace_bytes is 0.

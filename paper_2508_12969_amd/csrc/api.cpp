@@ -353,7 +353,13 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
     a.share_stats = workspace;
     a.share_o = static_cast<char*>(workspace) + a.batch * a.shares * ca::share_stats_bytes(32 * plan.waves);
   }
-  if (a.ways != ca::kWaysNone) {
+  const ca::Ways planes = dense ? L->planes_dense : L->planes;
+  if (workspace && planes != ca::kWaysNone) {
+    ca::PlaneArgs planar{a};
+    planar.ways = planes;
+    planar.units = workspace;
+    e = ca::launch_attn_f32(planar, (hipStream_t)stream);
+  } else if (a.ways != ca::kWaysNone) {
     a.order = dense ? nullptr : t.order;
     e = ca::launch_attn_bf16(a, (hipStream_t)stream);
   } else if (all_paired) {
@@ -721,6 +727,7 @@ int compact_attn_forward_static(const void* q, const void* k, const void* v, ca_
     t.split_merges = reinterpret_cast<ca::MergeItem*>(sc.ptr + o.split_merges);
     workspace = sc.workspace;
   }
+  if (L->planes != ca::kWaysNone && ca::call_workspace_bytes(*L, false) <= ca::kMaxShareBytes) workspace = sc.workspace;
   st = launch_attention(q, k, v, L, t, out, stream, false, false, workspace);
   if (st != CA_OK) sc.owner = 0;
   return st;
@@ -739,8 +746,12 @@ int compact_attn_layout_split(const ca_layout* L, int32_t dense, int64_t* worksp
   if (!L || !workspace_bytes) return fail(CA_ERR_INVALID_ARG, "null argument");
   if (dense != 0 && dense != 1) return fail(CA_ERR_INVALID_ARG, "dense must be 0 or 1");
   const ca::SplitPlan& plan = dense ? L->split_dense : L->split;
-  *workspace_bytes = ca::workspace_bytes(plan, L->prob.batch, L->prob.head_dim);
-  if (kernel) *kernel = plan.shares == 0 ? nullptr : kernel_name(L, plan.ways, dense != 0);
+  *workspace_bytes = ca::call_workspace_bytes(*L, dense != 0);
+  const ca::Ways planes = dense ? L->planes_dense : L->planes;
+  if (!kernel) return CA_OK;
+  if (*workspace_bytes == 0) *kernel = nullptr;
+  else if (planes == ca::kWaysNone) *kernel = kernel_name(L, plan.ways, dense != 0);
+  else *kernel = planes == ca::kPlanes2x2 ? "f32-planes-2x2" : planes == ca::kPlanes2x4 ? "f32-planes-2x4" : "f32-planes-1x4";
   return CA_OK;
 }
 
@@ -751,7 +762,7 @@ int compact_attn_forward_with_workspace(const void* q, const void* k, const void
   const bool dense = call == CA_CALL_DENSE, natural = call == CA_CALL_NATURAL;
   if (L) {
     const ca_problem& p = L->prob;
-    const int64_t need = ca::workspace_bytes(dense ? L->split_dense : L->split, p.batch, p.head_dim);
+    const int64_t need = ca::call_workspace_bytes(*L, dense);
     if (need == 0) {
       workspace = nullptr;
     } else {

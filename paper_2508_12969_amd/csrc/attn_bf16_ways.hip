@@ -68,19 +68,6 @@ __device__ __forceinline__ void copy_granule(uint32_t m0, const char* base, cons
   }
 }
 
-// Masks the keys of a 32-key block past the c0 tokens of its first granule and the c1 of its second: the
-// lane mask of each score register is built on the scalar unit (lanes 0-31 hold key 8*(r/4) + r%4 of the
-// block, lanes 32-63 that key + 4).
-__device__ __forceinline__ void mask_granules(floatx16& s, int c0, int c1) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int key = 8 * (r / 4 % 2) + r % 4, c = r < 8 ? c0 : c1;
-    const uint32_t lo = key < c ? 0xffffffffu : 0u, hi = key + 4 < c ? 0xffffffffu : 0u;
-    const uint64_t keep = (uint64_t)lo | ((uint64_t)hi << 32);
-    asm("v_cndmask_b32 %0, %1, %0, %2" : "+v"(s[r]) : "v"(kMinusInf), "s"(keep));
-  }
-}
-
 template <int D, int NW, int NQ, bool kNat, bool kSplit>
 __global__ __attribute__((amdgpu_flat_work_group_size(NW * 64, NW * 64), amdgpu_waves_per_eu(D == 64 && (NW == 4 || kSplit) ? 4 : 2)))
 void attn_bf16_ways_kernel(LaunchArgs<kSplit> a, int parts) {

@@ -360,18 +360,8 @@ void attn_f32_kernel(AttnArgs a, int parts, int64_t workgroups) {
 
 template <int D>
 hipError_t launch(const AttnArgs& a, hipStream_t stream) {
-  // As many query groups side by side as the tile has, because they share the staged keys; fewer, with
-  // the keys of a query split over the waves instead, while the launch has less than five workgroups
-  // per CU.  Measured: 1128 rows of 64 tokens at D = 128, QW 4 / 2: 1.27 / 1.20 ms; 732 rows of 60 at
-  // D = 32, QW 4 / 2 / 1: 0.63 / 0.65 / 0.69 ms, where the one line for all head dims takes 2 and is 3 % off.  At D = 128, QW = 1 fills the LDS of a CU with one
-  // workgroup and waits for copies (240 rows of 128 tokens, QW 2 / 1: 0.31 / 0.37 ms): small tiles only.
-  constexpr int64_t kMinWorkgroups = 1280;
-  constexpr int kFewest = D == 128 ? 2 : 1;
   const int64_t rows = (int64_t)a.batch * a.num_heads * a.n;
-  auto parts_of = [&](int qw) { return (a.B + 16 * qw - 1) / (16 * qw); };
-  int qw = a.B <= 16 ? 1 : a.B <= 32 ? 2 : 4;
-  while (qw > kFewest && rows * parts_of(qw) < kMinWorkgroups) qw /= 2;
-  const int parts = parts_of(qw);
+  const int qw = f32_query_groups(rows, a.B, D), parts = (a.B + 16 * qw - 1) / (16 * qw);
   const int64_t workgroups = rows * parts, width = std::min(workgroups, (int64_t)1 << 23);  // a grid dimension holds fewer than 2^32 threads
   if (workgroups > (int64_t)1 << 38) return hipErrorInvalidValue;
   const dim3 grid((unsigned)width, (unsigned)((workgroups + width - 1) / width)), block(256);
@@ -384,6 +374,7 @@ hipError_t launch(const AttnArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream) {
+  if (a.ways != kWaysNone) return launch_attn_f32_planes(static_cast<const PlaneArgs&>(a), stream);
   if ((int64_t)a.batch * a.num_heads * a.n == 0) return hipSuccess;
   if (a.B > 128 || a.num_classes < 1 || a.num_classes > 8) return hipErrorInvalidValue;
   switch (a.D) {

@@ -32,7 +32,7 @@ struct AttnArgs {
   const int32_t* order;        // device [entries]; the launch order: row ids; null = identity
   int64_t entries;             // launch-order entries per batch entry (num_heads * n rows, or fewer entries when query tiles are packed)
   int32_t simd_waves;          // one-tile kernel, 64-token tiles of head dim 64: waves per SIMD, 2 or 3
-  Ways ways;                   // bf16 kernels: which of the kernels of attn_bf16_ways.hip, on `order` as rows, or kWaysNone = the others
+  Ways ways;                   // bf16 kernels: which of the kernels of attn_bf16_ways.hip, on `order` as rows, or kWaysNone = the others; fp32: which of attn_f32_planes.hip
   int32_t packed;              // 1: `order` also holds workgroups of two packed query tiles, as the complement of their index in the pair tables
   const int32_t* pair_rows;    // device [2*num_pairs]; row ids of the two query tiles of a workgroup (-1: none), paired kernel only
   int64_t num_pairs;
@@ -73,10 +73,16 @@ struct SplitArgs : AttnArgs {
   void* share_stats;           // device workspace of batch * shares shares: (reference, sum) of the lanes, and O
   void* share_o;
 };
+// The same for fp32 on the bf16 matrix instructions.
+struct PlaneArgs : AttnArgs {
+  void* units;                 // device workspace of plane_bytes (layout.h)
+};
 template <bool kSplit>
 using LaunchArgs = std::conditional_t<kSplit, SplitArgs, AttnArgs>;
 // fp32 problems, B <= 128, D in {32, 64, 128}
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream);
+// the part of it with a.ways != kWaysNone, which says that `a` is a PlaneArgs
+hipError_t launch_attn_f32_planes(const PlaneArgs& a, hipStream_t stream);
 // bf16 problems, (B, D) in {64,128} x {64,128}
 hipError_t launch_attn_bf16(const SplitArgs& a, hipStream_t stream);
 // the part of it with a.ways != kWaysNone

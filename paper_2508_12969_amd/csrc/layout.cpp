@@ -727,6 +727,62 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* p
   return ways;
 }
 
+// Kernel of fp32 calls that bring a workspace: the one of attn_f32_planes.hip with the shortest predicted time, or attn_f32.hip,
+// unless the former is predicted to be at least 13 % better.  Tiles of at most 32 tokens, which leave 32 queries of a wave
+// without work, stay with attn_f32.hip (16 tokens: 1.25 times faster to 2.5 times slower).
+// The constants are a fit over 276 launches of under 0.1 TFLOP (1-40 heads, head dims 32-128, tiles of 60-128 tokens, masks from 5 %
+// to dense), per kernel and head dim, a step being 128 keys; residual 5-16 %.  On these the choice is 1.36 times faster than
+// attn_f32.hip (geometric mean; 1.41 is the best choice in hindsight), and four of them, calls of one head, are slower, by up to 8 %.
+// Without the 13 % ten are slower, by up to 20 %.
+Ways choose_planes(const ca_layout& L, bool dense, int64_t max_words) {
+  const ca_problem& p = L.prob;
+  if (p.dtype != CA_F32 || L.B <= 32 || L.B > 128 || (p.head_dim != 32 && p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
+  if (plane_bytes((int64_t)p.batch * p.num_heads, L.n, L.B, p.head_dim) > kMaxPlaneBytes) return kWaysNone;
+  struct PlaneCost {
+    Ways planes;
+    int part_queries;
+    LaunchCost cost;
+    double split;  // us per million elements of K, to split K and V
+  };
+  static const PlaneCost kOptions[3][3] = {
+      {{kPlanes2x2, 64, {4, 7.4, 1.08, 2.97, 1.0, 0}, 9.3}, {kPlanes2x4, 64, {2, 7.8, 1.26, 2.14, 1.0, 0}, 10.5}, {kPlanes1x4, 32, {3, 7.2, 0.73, 1.61, 1.0, 0}, 12.3}},
+      {{kPlanes2x2, 64, {3, 5.6, 1.85, 3.81, 4.34, 0}, 6.6}, {kPlanes2x4, 64, {1, 7.6, 0, 2.76, 3.23, 0}, 7.9}},
+      {{kPlanes2x2, 64, {2, 12.0, 4.09, 6.18, 1.0, 0}, 6.3}, {kPlanes2x4, 64, {1, 6.7, 0, 4.76, 7.67, 0}, 6.4}, {kPlanes1x4, 32, {1, 7.9, 0, 4.18, 1.02, 0}, 14.7}}};
+  // attn_f32.hip with 16, 32 and 64 queries to a workgroup (the split of 64 at head dim 128 is that of 32 with twice the work)
+  static const LaunchCost kF32[3][3] = {{{2, 5.5, 0.69, 1.86, 0.5, 0}, {2, 4.4, 0.46, 2.66, 6.0, 0}, {2, 27.0, 2.12, 3.53, 5.2, 0}},
+                                        {{2, 1.0, 0.79, 2.9, 4.2, 0}, {2, 27.0, 2.78, 3.83, 0.5, 0}, {2, 30.0, 4.02, 4.0, 16.0, 0}},
+                                        {{2, 1.0, 5.11, 6.92, 7.2, 0}, {2, 1.0, 5.11, 6.92, 7.2, 0}, {2, 1.0, 10.2, 13.8, 14.0, 0}}};
+  constexpr double kF32Bias = 0.87;
+  const int d = p.head_dim == 32 ? 0 : p.head_dim == 64 ? 1 : 2;
+  std::vector<int> tokens(L.class_mask.size());
+  for (size_t c = 0; c < tokens.size(); ++c)
+    for (uint32_t w : L.class_mask[c].w) tokens[c] += __builtin_popcount(w);
+  const double per_tile = granules_per_tile(L, dense, max_words).first;
+  std::vector<float> walks;
+  auto cut = [&](int part_queries) {  // the workgroups of a launch
+    const int parts = (int)(L.B + part_queries - 1) / part_queries;
+    walks.clear();
+    for (int64_t j = 0; j < (int64_t)L.order.size(); ++j) {
+      const int64_t r = dense ? j : L.order[j];
+      const float steps = (float)((double)(dense ? L.n : L.row_ptr[r + 1] - L.row_ptr[r]) * per_tile / 8);
+      const int held = (tokens[L.tile_class[r % L.n]] + part_queries - 1) / part_queries;
+      for (int part = 0; part < parts; ++part) walks.push_back(part < held ? steps : -1.f);
+    }
+  };
+  const int qw = f32_query_groups((int64_t)p.batch * p.num_heads * L.n, L.B, p.head_dim);
+  cut(16 * qw);
+  double best = kF32Bias * launch_time(kF32[d][qw / 2], walks, p.batch, 0, HUGE_VAL);
+  Ways planes = kWaysNone;
+  const double elements = 1e-6 * (double)plane_bytes((int64_t)p.batch * p.num_heads, L.n, L.B, p.head_dim) / 12;
+  for (const PlaneCost& o : kOptions[d]) {
+    if (o.planes == kWaysNone) continue;  // 1x4 at head dim 64: never the best by more than a few per cent
+    cut(o.part_queries);
+    const double t = o.split * elements + launch_time(o.cost, walks, p.batch, 0, HUGE_VAL);
+    if (t < best) best = t, planes = o.planes;
+  }
+  return planes;
+}
+
 namespace {
 
 // Waves per SIMD of the one-tile kernel for 64-token tiles of head dim 64: 2, or 3.  The third makes a full card
@@ -785,6 +841,8 @@ void finish_host_tables(ca_layout& L) {
   L.simd_waves_dense = choose_simd_waves(L, true);
   L.ways = choose_ways(L, false, kSampledWords, &L.split);
   L.ways_dense = choose_ways(L, true, kSampledWords, &L.split_dense);
+  L.planes = choose_planes(L, false, kSampledWords);
+  L.planes_dense = choose_planes(L, true, kSampledWords);
 }
 
 int import_host_tables(ca_layout& L, const int64_t* const* row_ptr, const int32_t* const* col_idx) {

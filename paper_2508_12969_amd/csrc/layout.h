@@ -60,8 +60,9 @@ constexpr int64_t xcd_launch_order(int64_t id, int64_t total, int64_t chunk = kX
   return round * span + ((round & 1) ? 7 - xcd : xcd) * chunk + seq % chunk;
 }
 
-// The kernels of attn_bf16_ways.hip: waves of a workgroup x 32-query waves side by side.
-enum Ways : int32_t { kWaysNone = 0, kWays4x4, kWays8x4, kWays8x2 };
+// The kernels of attn_bf16_ways.hip: waves of a workgroup x 32-query waves side by side; and those of attn_f32_planes.hip:
+// 32-query waves side by side x waves that share the keys of a query.
+enum Ways : int32_t { kWaysNone = 0, kWays4x4, kWays8x4, kWays8x2, kPlanes2x2, kPlanes2x4, kPlanes1x4 };
 
 // Launches whose longest rows would outlast everything else, or that leave CUs without work, are split along the
 // keys: a workgroup takes `count` tiles of the list of a launch-order
@@ -89,6 +90,24 @@ constexpr int64_t share_bytes(int64_t queries, int64_t head_dim) { return share_
 inline int64_t workspace_bytes(const SplitPlan& plan, int64_t batch, int64_t head_dim) {
   return plan.shares * batch * share_bytes(32 * plan.waves, head_dim);
 }
+
+// 16-query groups side by side in a workgroup of attn_f32.hip: as many as the tile has, because they share the staged keys; fewer, with
+// the keys of a query split over the waves instead, while the launch has less than five workgroups
+// per CU.  Measured: 1128 rows of 64 tokens at D = 128, 4 / 2 groups: 1.27 / 1.20 ms; 732 rows of 60 at
+// D = 32, 4 / 2 / 1: 0.63 / 0.65 / 0.69 ms, where the one line for all head dims takes 2 and is 3 % off.  At D = 128, one group fills the LDS of a CU with one
+// workgroup and waits for copies (240 rows of 128 tokens, 2 / 1 groups: 0.31 / 0.37 ms): small tiles only.
+inline int f32_query_groups(int64_t rows, int64_t B, int64_t head_dim) {
+  constexpr int64_t kMinWorkgroups = 1280;
+  const int fewest = head_dim == 128 ? 2 : 1;
+  int qw = B <= 16 ? 1 : B <= 32 ? 2 : 4;
+  while (qw > fewest && rows * ((B + 16 * qw - 1) / (16 * qw)) < kMinWorkgroups) qw /= 2;
+  return qw;
+}
+
+// fp32 attention on the bf16 matrix instructions (attn_f32_planes.hip): K and V are split into three bf16 values each, in units
+// of 16 tokens.
+constexpr int64_t kMaxPlaneBytes = (int64_t)8 << 30;  // of a call
+inline int64_t plane_bytes(int64_t planes, int64_t n, int64_t B, int64_t head_dim) { return planes * n * ((B + 15) / 16) * 16 * head_dim * 12; }
 
 // Device-resident tables, parts of one block of device memory owned by the layout.
 struct DeviceTables {
@@ -155,6 +174,7 @@ struct ca_layout {
   int32_t simd_waves = 2, simd_waves_dense = 2;               // waves per SIMD of the one-tile kernel (choose_simd_waves)
   ca::Ways ways = ca::kWaysNone, ways_dense = ca::kWaysNone;  // kernel of the sparse and of the dense walk, natural order included
   ca::SplitPlan split, split_dense;                           // rows split along the keys, for calls that bring a workspace
+  ca::Ways planes = ca::kWaysNone, planes_dense = ca::kWaysNone;  // fp32: kernel of calls that bring a workspace, kWaysNone = attn_f32.hip
   mutable std::atomic<uint32_t> launch_seq{0};  // picks the pool counter of a launch
 
   // device tables, created once
@@ -201,7 +221,14 @@ int pack_device_tables(const ca_layout& layout, bool forward_only, PackedTables&
 // tiles are looked at.
 constexpr int64_t kSampledWords = 500000;
 Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* plan = nullptr);
+Ways choose_planes(const ca_layout& L, bool dense, int64_t max_words);
 std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int64_t max_words);
+// Bytes that a sparse or a dense attention call can make use of.
+inline int64_t call_workspace_bytes(const ca_layout& L, bool dense) {
+  const ca_problem& p = L.prob;
+  if (dense ? L.planes_dense : L.planes) return plane_bytes((int64_t)p.batch * p.num_heads, L.n, L.B, p.head_dim);
+  return workspace_bytes(dense ? L.split_dense : L.split, p.batch, p.head_dim);
+}
 // Derived tables (per-head views, launch order, padding classes) once row_ptr / col_idx are set.
 void finish_host_tables(ca_layout& L);
 

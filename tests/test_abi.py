@@ -531,3 +531,19 @@ def test_kernel_choice_where_it_is_slower(grid, tile, text_tiles, heads, batch, 
     """Launches that a kernel with more workgroups or shorter walks would serve more slowly do not go to it."""
     lay = ca.compact_attn_build_layout(*grid, tile, text_tiles * tile[0] * tile[1] * tile[2], batch, len(heads), D, "bf16", heads)
     assert ca.compact_attn_layout_kernel(lay, dense=dense) != slower
+
+
+def test_fp32_workspace_sizes():
+    """What an fp32 call can make use of: three bf16 parts of K and V in units of 16 tokens, for tiles of 33 to 128 tokens, for calls
+    large enough, up to 8 GiB."""
+    def split(D, tile, grid, heads, batch=1, dense=False):
+        lay = ca.compact_attn_build_layout(*grid, tile, 0, batch, heads, D, "f32", [[(99, (99, 99), (-1, -1))]] * heads)
+        return ca.compact_attn_layout_split(lay, dense=dense), lay.n_tiles
+    for tile, units in (((1, 8, 8), 4), ((1, 6, 10), 4), ((3, 3, 4), 3), ((2, 8, 8), 8), ((1, 1, 33), 3)):
+        for dense in (False, True):
+            (nbytes, name), n = split(64, tile, (6, 40, 66), 3, batch=2, dense=dense)
+            assert nbytes == 12 * 2 * 3 * n * units * 16 * 64 and name.startswith("f32-planes-")
+    assert split(64, (1, 4, 8), (6, 40, 64), 3)[0] == (0, None)      # 32 tokens: half a workgroup's queries
+    assert split(128, (1, 8, 8), (1, 8, 8), 1)[0] == (0, None)       # one tile
+    assert split(128, (2, 8, 8), (64, 128, 128), 5)[0][0] == 8053063680
+    assert split(128, (2, 8, 8), (64, 128, 128), 6)[0] == (0, None)  # 9 GiB

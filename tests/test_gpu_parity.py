@@ -1553,3 +1553,113 @@ def test_split_rows_in_a_capture_that_torch_does_not_run():
     torch.cuda.synchronize()
     assert all(bool((x == 7.0).all()) for x in owned)
     assert lib.hipGraphExecDestroy(launch) == 0 and lib.hipGraphDestroy(graph) == 0
+
+
+# ---------------------------------------------------------------- fp32 on the bf16 matrix instructions
+
+_PLANE_LAUNCHES = [
+    # tiles of 60, 64 and 128 tokens, padded down to a few tokens, and of 36 (units of 16, 16 and 4 tokens)
+    ("2x2", 128, (9, 30, 25), (1, 8, 8), 0, 1),
+    ("2x4", 128, (3, 17, 29), (1, 6, 10), 0, 2),
+    ("1x4", 128, (3, 17, 29), (3, 3, 4), 0, 1),
+    ("1x4", 128, (5, 13, 21), (2, 8, 8), 0, 1),
+    ("2x2", 64, (7, 20, 33), (3, 3, 4), 0, 2),
+    ("2x4", 64, (3, 17, 29), (1, 6, 10), 1, 4),
+    ("2x2", 64, (9, 30, 25), (2, 8, 8), 0, 1),
+    ("2x2", 32, (9, 30, 25), (1, 6, 10), 0, 4),
+    ("2x4", 32, (7, 20, 33), (3, 3, 4), 0, 2),
+    ("1x4", 32, (9, 30, 25), (1, 8, 8), 0, 1),
+]
+
+
+def _plane_problem(kernel, D, grid, tile, text_tiles, copies, batch=1):
+    import dataclasses
+    heads = [[(99, (99, 99), ABSENT)], *_EDGE_HEADS[1:]] * copies
+    wl = dataclasses.replace(make_workload("planes", *grid, tile, text_tiles * tile[0] * tile[1] * tile[2], len(heads), D, "f32", heads), batch=batch)
+    lay = build_layout(ca, wl)
+    assert ca.compact_attn_layout_split(lay)[1] == "f32-planes-" + kernel
+    return wl, lay
+
+
+@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,copies", _PLANE_LAUNCHES)
+def test_fp32_in_three_planes(kernel, D, grid, tile, text_tiles, copies):
+    """fp32 operands as three bf16 values: against the oracle with peaked rows, whatever the padding slots and the workspace hold,
+    and no further from it than the kernel on the fp32 matrix instructions (the C call without a workspace); the static
+    entry point, a second stream and a replayed graph bit for bit."""
+    import ctypes
+    _say("fp32 planes", kernel, D, grid, tile)
+    wl, lay = _plane_problem(kernel, D, grid, tile, text_tiles, copies)
+    g, heads = geometry_of(wl), wl.heads
+    q, k, v = make_qkv(wl, DEV, q_gain=2.0)
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    held = ca.compact_attn_permute(torch.ones_like(q), lay) != 0
+    kp[~held] = float("nan")
+    vp[~held] = float("nan")
+    nbytes = ca.compact_attn_layout_split(lay)[0]
+    del_me = torch.full((nbytes // 4,), float("nan"), device=DEV)  # the allocator's next block of that size
+    del del_me
+    out = ca.compact_attn_forward(qp, kp, vp, lay, out=torch.full_like(qp, float("nan")))
+    assert torch.all(out[~held] == 0)
+    got = ca.compact_attn_permute(out, lay, inverse=True)
+    lib, stream = ca.load_library(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    other = torch.full_like(qp, float("nan"))
+    assert lib.compact_attn_forward(*(ctypes.c_void_p(x.data_ptr()) for x in (qp, kp, vp)), lay.handle, ctypes.c_void_p(other.data_ptr()), stream) == 0
+    before = ca.compact_attn_permute(other, lay, inverse=True)
+    for h in range(4):
+        want = OA.masked_attention(g, [heads[h]], *(to_f64(x[0, h])[None] for x in (q, k, v)))
+        err = [np.linalg.norm(to_f64(x[0, h])[None] - want) for x in (got, before)]
+        _say(h, compare(to_f64(got[0, h])[None], want, *tolerances("f32"), what=kernel), [e / max(np.linalg.norm(want), 1e-30) for e in err])
+        assert err[0] <= err[1]
+    again = torch.full_like(qp, float("nan"))
+    assert nbytes <= 64 << 20 and torch.equal(ca.compact_attn_forward_static(qp, kp, vp, lay, out=again), out)
+    side = torch.cuda.Stream()
+    on_side = torch.full_like(qp, float("nan"))
+    side.wait_stream(torch.cuda.current_stream())
+    ca.compact_attn_forward(qp, kp, vp, lay, out=on_side, stream=side)
+    with_main = ca.compact_attn_forward(qp, kp, vp, lay)            # may overlap with it
+    torch.cuda.synchronize()
+    assert torch.equal(on_side, out) and torch.equal(with_main, out)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ca.compact_attn_forward(qp, kp, vp, lay, out=again)
+    for rep in range(3):
+        again.fill_(float("nan"))
+        graph.replay()
+        assert torch.equal(ca.compact_attn_forward(qp, kp, vp, lay), out)
+        torch.cuda.synchronize()
+        assert torch.equal(again, out), f"replay {rep}"
+
+
+@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,copies", [_PLANE_LAUNCHES[i] for i in (0, 3, 5, 8, 9)])
+@pytest.mark.parametrize("short", [False, True])
+def test_fp32_in_three_planes_infinities(kernel, D, grid, tile, text_tiles, copies, short):
+    """Infinities and NaN in q, k and v appear where the fp32 matrix instructions have them, also where the finite
+    values are bf16 numbers (`short`), whose second and third parts hold nothing."""
+    import ctypes
+    wl, lay = _plane_problem(kernel, D, grid, tile, text_tiles, copies)
+    q, k, v = make_qkv(wl, DEV)
+    if short:
+        q, k, v = (x.bfloat16().float() for x in (q, k, v))
+    q, k, v = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    held = (ca.compact_attn_permute(torch.ones(q.shape[:2] + (wl.T * wl.H * wl.W + wl.n_text, D), device=DEV), lay) != 0)[0, 0, :, 0].nonzero().flatten()
+    inf, nan = float("inf"), float("nan")
+    some = held[torch.linspace(0, len(held) - 1, 7, device=DEV).long()]
+    v[:, :, some[1], 3], v[:, :, some[2], 5], v[:, :, some[3], 5], v[:, :, some[4], 7] = inf, inf, -inf, nan
+    v[:, :, held[-1], 9] = -inf
+    v[:, :, some[1], 11] = torch.tensor(0x7f800001, dtype=torch.int32, device=DEV).view(torch.float32)  # a NaN with its payload in the lower half
+    k[:, 0, some[5], 2] = -inf        # scores of both signs of infinity
+    q[:, 0, some[0], 4] = inf
+    q[:, 0, some[6], 4] = nan
+    v[:, :, some[2], 6] = 0.0
+    lib, stream = ca.load_library(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    want = torch.empty_like(q)
+    assert lib.compact_attn_forward(*(ctypes.c_void_p(x.data_ptr()) for x in (q, k, v)), lay.handle, ctypes.c_void_p(want.data_ptr()), stream) == 0
+    got = ca.compact_attn_forward(q, k, v, lay)
+    padding = torch.ones(q.shape[2], dtype=torch.bool, device=DEV)
+    padding[held] = False
+    assert torch.all(got[:, :, padding] == 0)
+    got, want = got[:, :, held], want[:, :, held]
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.isnan(want).any()
+    assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.isinf(want).any()
+    finite = ~torch.isnan(want)
+    assert finite.any() and torch.allclose(got[finite], want[finite], rtol=1e-5, atol=1e-5)
