@@ -266,8 +266,10 @@ int compact_attn_forward_static(const void* q, const void* k, const void* v, ca_
 int compact_attn_forward_natural(const void* q, const void* k, const void* v, ca_layout* layout, void* out,
                                  void* stream);
 
-/* Same kernel with every query tile keeping all n tiles (the full-attention starting point of
- * Sec. 4.2 and the baseline of Sec. 5.1); the per-head windows of the layout are ignored. */
+/* The same with every query tile keeping all n tiles (the full-attention starting point of
+ * Sec. 4.2 and the baseline of Sec. 5.1); the per-head windows of the layout are ignored, and so may be its
+ * tiles: unpadded 64-token tiles are taken two by two, and a call with a workspace (below) may run on
+ * copies of the tokens alone.  Results differ by the rounding of bf16 probabilities. */
 int compact_attn_dense(const void* q, const void* k, const void* v, ca_layout* layout, void* out,
                        void* stream);
 
@@ -278,11 +280,14 @@ int compact_attn_dense(const void* q, const void* k, const void* v, ca_layout* l
  * more than 32 tokens that are large enough to pay for it run on the bf16 matrix instructions: K and V are split into three
  * bf16 values each, which hold all of their 24 bits, and every product is the sum of the six partial products down to
  * 2^-24 of it, in fp32 (measured error against 64 bits: 0.3 to 0.8 of that of the kernel without a workspace).
+ * Dense bf16 launches whose tiles are padded leave the padding out if that pays: q, k, v and the result are copied.
  *   compact_attn_layout_split: *workspace_bytes = what such a call needs, 0 where it has no use for one: at most 64 MiB for
- *   the partial sums of bf16 rows; for f32 12 * batch * heads * n * ceil(B / 16) * 16 * D bytes, at most 8 GiB;
+ *   the partial sums of bf16 rows, and four tensors of the tokens in natural order for a dense launch on copies (at most 8 GiB); for
+ *   f32 12 * batch * heads * n * ceil(B / 16) * 16 * D bytes, at most 8 GiB;
  *   sparse walk (dense = 0: forward and natural) or dense walk (dense = 1).  kernel may be NULL; *kernel receives the
  *   name of the kernel that serves such a call (see compact_attn_layout_kernel, or "f32-planes-2x2", "f32-planes-2x4",
- *   "f32-planes-1x4": 32-query waves of a workgroup side by side x waves that share the keys of a query), NULL where there is none.
+ *   "f32-planes-1x4": 32-query waves of a workgroup side by side x waves that share the keys of a query; "closed-" and a name:
+ *   that kernel on copies, in tiles of 128 tokens), NULL where there is none.
  *   workspace: device memory of at least that size, 16-byte aligned, not overlapping the tensors; its contents
  *   before and after the call mean nothing.  It must not be used by anything else until the call's work on `stream` has
  *   run.  Ignored (and may be NULL) where *workspace_bytes is 0.

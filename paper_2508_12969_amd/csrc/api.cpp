@@ -151,7 +151,25 @@ int ensure_uploaded(ca_layout* L, hipStream_t stream) {
     if (!t.tile_origin.empty()) tables.push_back(table(t.tile_origin, &d.tile_origin));
     if (L->split.shares) tables.push_back(table(L->split.items, &d.split_items)), tables.push_back(table(L->split.merges, &d.split_merges));
     if (L->split_dense.shares) tables.push_back(table(L->split_dense.items, &d.split_items_dense)), tables.push_back(table(L->split_dense.merges, &d.split_merges_dense));
-    st = upload_tables(tables, &d.block);
+    // what a dense walk of the closed layout reads
+    ca::PackedTables tc;
+    ca::DeviceTables dc;
+    if (ca_layout* c = L->closed.get()) {
+      st = ca::pack_device_tables(*c, false, tc);
+      dc.num_pairs = (int64_t)c->pair_rows.size() / 2;
+      dc.num_launch_rows = c->packed_faces ? (int64_t)c->launch_rows.size() : 0;
+      dc.pool_slots = ca::kPoolSlots;
+      for (const Table& x : {table(tc.dense_meta, &dc.dense_meta), table(c->tile_class, &dc.tile_class), table(c->class_mask, &dc.class_mask),
+                             table(tc.class_perm, &dc.class_perm), table(pool_counters, &dc.pool_counters)})
+        tables.push_back(x);
+      if (dc.num_pairs)
+        for (const Table& x : {table(c->pair_rows, &dc.pair_rows), table(c->pair_desc, &dc.pair_desc), table(tc.dense_pair_walk, &dc.dense_pair_walk)})
+          tables.push_back(x);
+      if (c->packed_faces) tables.push_back(table(c->launch_rows, &dc.launch_rows));
+      if (c->split_dense.shares) tables.push_back(table(c->split_dense.items, &dc.split_items_dense)), tables.push_back(table(c->split_dense.merges, &dc.split_merges_dense));
+    }
+    if (st == CA_OK) st = upload_tables(tables, &d.block);
+    if (L->closed && st == CA_OK) L->closed->dev = dc;  // its memory is part of d.block
   } catch (const std::bad_alloc&) {
     set_error("out of host memory while packing the device tables");
     st = CA_ERR_ALLOC;
@@ -374,6 +392,46 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
   return CA_OK;
 }
 
+ca::PermuteArgs permute_args(const void* src, void* dst, const ca_layout* L, int32_t inverse) {
+  const ca_problem& p = L->prob;
+  ca::PermuteArgs a{};
+  a.src = src;
+  a.dst = dst;
+  a.T = p.T; a.H = p.H; a.W = p.W;
+  a.tt = p.tt; a.th = p.th; a.tw = p.tw;
+  a.nH = L->nH; a.nW = L->nW;
+  a.n_vid = L->n_vid;
+  a.B = L->B;
+  a.N_real = L->N_real;
+  a.N_pad = L->N_pad;
+  a.N_video = (int64_t)p.T * p.H * p.W;
+  a.planes = (int64_t)p.batch * p.num_heads;
+  a.row_bytes = p.head_dim * elem_size(p.dtype);
+  a.inverse = inverse;
+  return a;
+}
+
+// A dense call on L->closed: on copies in the workspace, which the padding is left out of, or on the tensors as they are.
+int launch_closed(const void* q, const void* k, const void* v, const ca_layout* L, void* out, void* stream, void* workspace) {
+  const ca_layout* c = L->closed.get();
+  if (L->closed_in_place) return launch_attention(q, k, v, c, c->dev, out, stream, true, false, workspace);
+  const int64_t bytes = ca::tensor_bytes(*c);
+  char* const w = static_cast<char*>(workspace);
+  ca::PermuteManyArgs a{permute_args(nullptr, nullptr, L, ca::kPermuteMany + 1), 3, {q, k, v}, {w, w + bytes, w + 2 * bytes}, c->N_pad};
+  hipError_t e = ca::launch_permute(a, (hipStream_t)stream);
+  if (e != hipSuccess) return hip_fail(e, "launch of the copies for the dense walk");
+  const int st = launch_attention(w, w + bytes, w + 2 * bytes, c, c->dev, w + 3 * bytes, stream, true, false,
+                                  c->split_dense.shares > 0 ? w + 4 * bytes : nullptr);
+  if (st != CA_OK) return st;
+  a.inverse = ca::kPermuteMany;
+  a.tensors = 1;
+  a.srcs[0] = w + 3 * bytes;
+  a.dsts[0] = out;
+  e = ca::launch_permute(a, (hipStream_t)stream);
+  if (e != hipSuccess) return hip_fail(e, "launch of the copy from the dense walk");
+  return CA_OK;
+}
+
 int run_attention(const void* q, const void* k, const void* v, ca_layout* L, void* out, void* stream, bool dense,
                   bool natural = false, void* workspace = nullptr) {
   ca::clear_error();
@@ -381,6 +439,7 @@ int run_attention(const void* q, const void* k, const void* v, ca_layout* L, voi
   if (st != CA_OK) return st;
   st = ensure_uploaded(L, (hipStream_t)stream);
   if (st != CA_OK) return st;
+  if (dense && L->closed && (workspace || L->closed_in_place)) return launch_closed(q, k, v, L, out, stream, workspace);
   return launch_attention(q, k, v, L, L->dev, out, stream, dense, natural, workspace);
 }
 
@@ -433,7 +492,11 @@ int build_static_image(ca_layout* L) {
 }
 
 // The kernel of a layout's attention calls; the order of the tests is that of launch_attention.
-const char* kernel_name(const ca_layout* L, ca::Ways ways, bool dense) {
+const char* kernel_name(const ca_layout* L, ca::Ways ways, bool dense, bool on_copies = false) {
+  if (on_copies) {  // 128-token tiles
+    if (ways != ca::kWaysNone) return ways == ca::kWays4x4 ? "closed-ways-4x4" : ways == ca::kWays8x4 ? "closed-ways-8x4" : "closed-ways-8x2";
+    return L->packed_faces ? "closed-packed-faces" : "closed-one-tile";
+  }
   if (ways != ca::kWaysNone) return ways == ca::kWays4x4 ? "ways-4x4" : ways == ca::kWays8x4 ? "ways-8x4" : "ways-8x2";
   if (L->prob.dtype != CA_BF16) return "f32";
   if (L->B == 64 && L->prob.head_dim == 128) return "paired";
@@ -602,6 +665,7 @@ int compact_attn_layout_kernel(const ca_layout* L, int32_t dense, const char** n
   if (dense != 0 && dense != 1) return fail(CA_ERR_INVALID_ARG, "dense must be 0 or 1");
   const int st = check_attn_support(L);
   if (st != CA_OK) return st;
+  if (dense && L->closed_in_place) L = L->closed.get();
   *name = kernel_name(L, dense ? L->ways_dense : L->ways, dense != 0);
   return CA_OK;
 }
@@ -630,20 +694,7 @@ int compact_attn_permute(const void* src, void* dst, ca_layout* L, int32_t inver
     if (ranges_overlap(src, inverse ? tiled_bytes : natural_bytes, dst, inverse ? natural_bytes : tiled_bytes))
       return fail(CA_ERR_INVALID_ARG, "src and dst must not overlap");
   }
-  ca::PermuteArgs a{};
-  a.src = src;
-  a.dst = dst;
-  a.T = p.T; a.H = p.H; a.W = p.W;
-  a.tt = p.tt; a.th = p.th; a.tw = p.tw;
-  a.nH = L->nH; a.nW = L->nW;
-  a.n_vid = L->n_vid;
-  a.B = L->B;
-  a.N_real = L->N_real;
-  a.N_pad = L->N_pad;
-  a.N_video = (int64_t)p.T * p.H * p.W;
-  a.planes = (int64_t)p.batch * p.num_heads;
-  a.row_bytes = p.head_dim * elem_size(p.dtype);
-  a.inverse = inverse;
+  const ca::PermuteArgs a = permute_args(src, dst, L, inverse);
   const hipError_t e = ca::launch_permute(a, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "permute launch");
   return CA_OK;
@@ -745,12 +796,13 @@ int compact_attn_layout_split(const ca_layout* L, int32_t dense, int64_t* worksp
   ca::clear_error();
   if (!L || !workspace_bytes) return fail(CA_ERR_INVALID_ARG, "null argument");
   if (dense != 0 && dense != 1) return fail(CA_ERR_INVALID_ARG, "dense must be 0 or 1");
-  const ca::SplitPlan& plan = dense ? L->split_dense : L->split;
+  const ca_layout* const runs = dense && L->closed ? L->closed.get() : L;
+  const ca::SplitPlan& plan = dense ? runs->split_dense : runs->split;
   *workspace_bytes = ca::call_workspace_bytes(*L, dense != 0);
   const ca::Ways planes = dense ? L->planes_dense : L->planes;
   if (!kernel) return CA_OK;
   if (*workspace_bytes == 0) *kernel = nullptr;
-  else if (planes == ca::kWaysNone) *kernel = kernel_name(L, plan.ways, dense != 0);
+  else if (planes == ca::kWaysNone) *kernel = kernel_name(runs, plan.shares > 0 ? plan.ways : dense ? runs->ways_dense : runs->ways, dense != 0, runs != L && !L->closed_in_place);
   else *kernel = planes == ca::kPlanes2x2 ? "f32-planes-2x2" : planes == ca::kPlanes2x4 ? "f32-planes-2x4" : "f32-planes-1x4";
   return CA_OK;
 }

@@ -18,7 +18,15 @@ struct PermuteArgs {
   int64_t n_vid, B, N_real, N_pad, N_video;
   int64_t planes;     // batch * num_heads
   int32_t row_bytes;  // head_dim * sizeof(element), a multiple of 16
-  int32_t inverse;
+  int32_t inverse;    // 0, 1, or one of these + kPermuteMany: then this is a PermuteManyArgs
+};
+constexpr int32_t kPermuteMany = 2;
+// Several tensors in a launch, and room at the end of a plane of the tensors in natural order.
+struct PermuteManyArgs : PermuteArgs {
+  int32_t tensors;       // 1 to 3
+  const void* srcs[3];   // in the place of src and dst
+  void* dsts[3];
+  int64_t natural_rows;  // of a plane, at least N_real; inverse: rows past N_real are written as zero
 };
 hipError_t launch_permute(const PermuteArgs& a, hipStream_t stream);
 

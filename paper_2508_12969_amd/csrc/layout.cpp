@@ -480,6 +480,11 @@ double launch_time(const LaunchCost& c, const std::vector<float>& walks, int64_t
 constexpr double kMergeLaunch = 2.0;   // us: the second launch
 constexpr double kMergeByte = 0.6e-6;  // us per byte of the shares, written and read
 
+// Dense calls on closed-up copies: us of two launches (q, k and v at once; the result), us per byte of the four tensors, each read
+// and written once, what has to be gained, and the shortest walk (shorter ones wait for launches and first copies).
+constexpr double kCloseLaunches = 7.0, kCloseByte = 1 / 5.3e6, kCloseGain = 0.92;
+constexpr int64_t kCloseTokens = 2048;
+
 struct WayCost {
   Ways ways;
   int stage_keys, part_queries;
@@ -636,8 +641,9 @@ std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int6
 // none of these is slower; of the 480 one is, by 3 %.  A model of the sums and the longest walk alone (residual
 // 10-18 %), from a predicted 10 % on, made twelve of the 480 slower by up to 25 %, eleven of them launches of one to
 // three rounds of workgroups.
-Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* plan) {
+Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* plan, double* predicted_us) {
   if (plan) *plan = SplitPlan{};
+  if (predicted_us) *predicted_us = 0;
   const ca_problem& p = L.prob;
   if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
   // 32-bit lane offsets inside a tile of the natural order; a grid dimension of fewer than 2^32 threads
@@ -690,6 +696,7 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* p
     const double t = launch_time(w.cost, walks, p.batch, padded, best);
     if (t < best) best = t, ways = w.ways;
   }
+  if (predicted_us) *predicted_us = ways == kWaysNone ? best / kPlainBias : best;
   if (plan && std::min(plain_groups, (int64_t)L.order.size()) <= kMaxSplitItems) {
     if (ways == kWaysNone) best /= kPlainBias;
     // Rows of 64-token tiles of head dim 64 run with three waves per SIMD where choose_simd_waves says so, and so do their items,
@@ -723,6 +730,7 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* p
       }
       plan_split(L, units, w.ways, w.part_queries / 32, w.cost, padded, [&](int64_t tiles) { return std::ceil((double)tiles * per_tile / stage) * stage / 8; }, best, *plan);
     }
+    if (predicted_us && plan->shares > 0) *predicted_us = best;
   }
   return ways;
 }
@@ -817,6 +825,47 @@ int choose_simd_waves(const ca_layout& L, bool dense) {
 
 }  // namespace
 
+namespace {
+
+// Sets L.closed, if dense calls are predicted to be faster there.  `dense_us`: what they take as they are.
+// A padded grid multiplies its padding in queries and keys (13 x 30 x 52 tokens in 1 x 8 x 8 tiles: 32 % more products), and the
+// kernel for 128-token tiles beats those for 64 also where nothing is padded.  Measured with the copies: 16 heads x 20K in 64-token
+// tiles 4.09 / 3.10 ms (copies 0.11); 18 heads x 44K of a grid filled to 0.79 23.5 / 15.5 ms; 8 heads x 8K without padding 259 /
+// 247 us.  50 launches of 11 us to 24 ms take 1.18 times less as a whole (1.20 is the best choice in hindsight), one 3 % more.
+void close_dense(ca_layout& L, double dense_us) {
+  const ca_problem& p = L.prob;
+  const bool padded = L.class_mask.size() > 1;
+  if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || (!padded && L.B == 128)) return;
+  if (L.N_real < kCloseTokens || L.N_real >= ((int64_t)1 << 31) - 128) return;
+  const bool in_place = !padded && L.N_pad % 128 == 0;
+  const double bytes = (double)p.batch * p.num_heads * (double)L.N_real * p.head_dim * 2;
+  const double copies = in_place ? 0 : kCloseLaunches + 8 * bytes * kCloseByte;
+  const double fill = (double)L.N_real / (double)L.N_pad;
+  if (kCloseGain * dense_us - copies < 0.5 * fill * fill * dense_us) return;  // not even if closing did more than it ever does
+  auto c = std::make_unique<ca_layout>();
+  c->is_closed = true;
+  c->prob = p;
+  c->prob.T = c->prob.H = c->prob.tt = c->prob.th = 1;
+  c->prob.W = (int32_t)L.N_real;
+  c->prob.tw = 128;
+  c->prob.n_text = 0;
+  c->B = 128;
+  c->nT = c->nH = 1;
+  c->n = c->n_vid = (L.N_real + 127) / 128;
+  c->nW = (int32_t)c->n;
+  c->N_real = L.N_real;
+  c->N_pad = c->n * 128;
+  c->scale = L.scale;
+  if (!in_place && 4 * tensor_bytes(*c) > kMaxPlaneBytes) return;
+  c->row_ptr.assign((size_t)p.num_heads * (size_t)c->n + 1, 0);
+  finish_host_tables(*c);
+  if (c->closed_us + copies > kCloseGain * dense_us) return;
+  L.closed_in_place = in_place;
+  L.closed = std::move(c);
+}
+
+}  // namespace
+
 void finish_host_tables(ca_layout& L) {
   const int32_t Hd = L.prob.num_heads;
   // per-head relative offsets for the C-ABI view
@@ -839,8 +888,12 @@ void finish_host_tables(ca_layout& L) {
   build_launch_splits(L);
   L.simd_waves = choose_simd_waves(L, false);
   L.simd_waves_dense = choose_simd_waves(L, true);
-  L.ways = choose_ways(L, false, kSampledWords, &L.split);
-  L.ways_dense = choose_ways(L, true, kSampledWords, &L.split_dense);
+  L.ways = L.is_closed ? kWaysNone : choose_ways(L, false, kSampledWords, &L.split);
+  double dense_us = 0;
+  L.ways_dense = choose_ways(L, true, kSampledWords, &L.split_dense, &dense_us);
+  L.closed_us = dense_us;
+  L.closed.reset();
+  if (!L.is_closed) close_dense(L, dense_us);
   L.planes = choose_planes(L, false, kSampledWords);
   L.planes_dense = choose_planes(L, true, kSampledWords);
 }

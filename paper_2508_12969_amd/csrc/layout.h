@@ -4,6 +4,7 @@
 
 #include <atomic>
 #include <cstdint>
+#include <memory>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -106,7 +107,7 @@ inline int f32_query_groups(int64_t rows, int64_t B, int64_t head_dim) {
 
 // fp32 attention on the bf16 matrix instructions (attn_f32_planes.hip): K and V are split into three bf16 values each, in units
 // of 16 tokens.
-constexpr int64_t kMaxPlaneBytes = (int64_t)8 << 30;  // of a call
+constexpr int64_t kMaxPlaneBytes = (int64_t)8 << 30;  // of a call; of the copies of a dense call too
 inline int64_t plane_bytes(int64_t planes, int64_t n, int64_t B, int64_t head_dim) { return planes * n * ((B + 15) / 16) * 16 * head_dim * 12; }
 
 // Device-resident tables, parts of one block of device memory owned by the layout.
@@ -175,6 +176,12 @@ struct ca_layout {
   ca::Ways ways = ca::kWaysNone, ways_dense = ca::kWaysNone;  // kernel of the sparse and of the dense walk, natural order included
   ca::SplitPlan split, split_dense;                           // rows split along the keys, for calls that bring a workspace
   ca::Ways planes = ca::kWaysNone, planes_dense = ca::kWaysNone;  // fp32: kernel of calls that bring a workspace, kWaysNone = attn_f32.hip
+  // Dense walks do not depend on the tiles.  Where that is predicted to be faster, dense calls run on this layout of the same tokens
+  // in natural order, cut into tiles of 128 without padding but at the end: on copies in a workspace, or on the tensors as
+  // they are (closed_in_place: no tile is padded and 64-token tiles are taken two by two).  Only its dense tables are used.
+  std::unique_ptr<ca_layout> closed;
+  bool closed_in_place = false, is_closed = false;
+  double closed_us = 0;  // predicted time of dense calls
   mutable std::atomic<uint32_t> launch_seq{0};  // picks the pool counter of a launch
 
   // device tables, created once
@@ -220,12 +227,15 @@ int pack_device_tables(const ca_layout& layout, bool forward_only, PackedTables&
 // Kernel of the sparse or the dense walk, and the figures of the tiles it goes by; at most about `max_words` kept
 // tiles are looked at.
 constexpr int64_t kSampledWords = 500000;
-Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* plan = nullptr);
+Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* plan = nullptr, double* predicted_us = nullptr);
 Ways choose_planes(const ca_layout& L, bool dense, int64_t max_words);
 std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int64_t max_words);
+// Bytes of a tensor of a bf16 layout in tile order.
+inline int64_t tensor_bytes(const ca_layout& L) { return (int64_t)L.prob.batch * L.prob.num_heads * L.N_pad * L.prob.head_dim * 2; }
 // Bytes that a sparse or a dense attention call can make use of.
 inline int64_t call_workspace_bytes(const ca_layout& L, bool dense) {
   const ca_problem& p = L.prob;
+  if (dense && L.closed) return (L.closed_in_place ? 0 : 4 * tensor_bytes(*L.closed)) + workspace_bytes(L.closed->split_dense, p.batch, p.head_dim);
   if (dense ? L.planes_dense : L.planes) return plane_bytes((int64_t)p.batch * p.num_heads, L.n, L.B, p.head_dim);
   return workspace_bytes(dense ? L.split_dense : L.split, p.batch, p.head_dim);
 }

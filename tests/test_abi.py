@@ -547,3 +547,20 @@ def test_fp32_workspace_sizes():
     assert split(128, (1, 8, 8), (1, 8, 8), 1)[0] == (0, None)       # one tile
     assert split(128, (2, 8, 8), (64, 128, 128), 5)[0][0] == 8053063680
     assert split(128, (2, 8, 8), (64, 128, 128), 6)[0] == (0, None)  # 9 GiB
+
+
+def test_dense_calls_that_leave_out_the_padding():
+    """Copies of padded grids hold the tokens in tiles of 128, up to 8 GiB; unpadded 64-token tiles need none, 128-token tiles and short
+    walks stay as they are."""
+    def split(D, tile, grid, heads, batch=1, text=0):
+        lay = ca.compact_attn_build_layout(*grid, tile, text * tile[0] * tile[1] * tile[2], batch, heads, D, "bf16", [[]] * heads)
+        return ca.compact_attn_layout_split(lay, dense=True), ca.compact_attn_layout_kernel(lay, dense=True), lay.n_tokens_real
+    for D in (64, 128):
+        for tile in ((1, 8, 8), (2, 8, 8), (2, 4, 8), (4, 4, 8)):
+            (nbytes, name), _, tokens = split(D, tile, (13, 30, 52), 16)
+            assert name.startswith("closed-") and nbytes == 4 * 16 * -(-tokens // 128) * 128 * D * 2
+    assert split(128, (1, 8, 8), (8, 32, 64), 8)[:2] == ((0, None), "one-tile")          # in place
+    assert split(128, (2, 8, 8), (8, 32, 64), 8)[:2] == ((0, None), "one-tile")          # nothing to gain
+    assert split(128, (2, 8, 8), (5, 13, 21), 40)[0] == (0, None)                        # 1365 tokens
+    assert split(128, (2, 8, 8), (65, 60, 100), 20)[0][1] == "closed-one-tile"           # 7.4 GiB
+    assert split(128, (2, 8, 8), (65, 60, 100), 22)[0] == (0, None)                      # 8.2 GiB

@@ -1663,3 +1663,64 @@ def test_fp32_in_three_planes_infinities(kernel, D, grid, tile, text_tiles, copi
     assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.isinf(want).any()
     finite = ~torch.isnan(want)
     assert finite.any() and torch.allclose(got[finite], want[finite], rtol=1e-5, atol=1e-5)
+
+
+# ---------------------------------------------------------------- dense calls without the padding
+
+@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,num_heads,batch", [
+    # on copies: with and without rows split along the keys; the last: no tile is padded, but they do not pair up
+    ("closed-one-tile", 128, (1, 45, 49), (2, 8, 8), 0, 4, 2),
+    ("closed-one-tile", 128, (1, 45, 49), (1, 8, 8), 1, 1, 1),
+    ("closed-one-tile", 64, (5, 17, 27), (1, 8, 8), 0, 12, 1),
+    ("closed-one-tile", 64, (5, 17, 27), (2, 8, 8), 1, 1, 2),
+    ("closed-ways-4x4", 64, (7, 20, 33), (2, 4, 8), 0, 1, 2),
+    ("closed-ways-8x2", 128, (7, 20, 33), (2, 4, 8), 0, 3, 1),
+    ("closed-ways-8x4", 128, (4, 32, 32), (1, 8, 8), 1, 1, 1),
+    # in place: tiles of 64 tokens two by two
+    ("one-tile", 128, (4, 32, 32), (1, 8, 8), 0, 3, 2),
+    ("ways-4x4", 128, (4, 32, 32), (1, 8, 8), 0, 3, 1),
+    ("ways-4x4", 64, (4, 32, 32), (1, 8, 8), 0, 3, 1),
+])
+def test_dense_calls_without_the_padding(kernel, D, grid, tile, text_tiles, num_heads, batch):
+    """Dense calls on the tokens alone: against the oracle with peaked rows, whatever the padding slots and the workspace hold; a
+    second stream and a replayed graph bit for bit; the C call without a workspace to within the rounding of bf16."""
+    import ctypes
+    import dataclasses
+    _say("closed-up dense", kernel, D, grid, tile, num_heads, batch)
+    n_text = text_tiles * tile[0] * tile[1] * tile[2]
+    wl = dataclasses.replace(make_workload("closed", *grid, tile, n_text, num_heads, D, "bf16", [[]] * num_heads), batch=batch)
+    lay = build_layout(ca, wl)
+    nbytes, name = ca.compact_attn_layout_split(lay, dense=True)
+    assert kernel in (name, ca.compact_attn_layout_kernel(lay, dense=True)) and (not kernel.startswith("closed") or name == kernel)
+    q, k, v = make_qkv(wl, DEV, q_gain=3.0)
+    qp, kp, vp = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    held = ca.compact_attn_permute(torch.ones_like(q), lay) != 0
+    lib, stream = ca.load_library(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    again = torch.full_like(qp, float("nan"))
+    assert lib.compact_attn_dense(*(ctypes.c_void_p(x.data_ptr()) for x in (qp, kp, vp)), lay.handle, ctypes.c_void_p(again.data_ptr()), stream) == 0
+    for x in (qp, kp, vp):
+        x[~held] = float("nan")                                      # on copies they are never read
+    del_me = torch.full((nbytes // 2,), float("nan"), dtype=torch.bfloat16, device=DEV)
+    del del_me
+    out = ca.compact_attn_dense(qp, kp, vp, lay, out=torch.full_like(qp, float("nan")))
+    assert torch.all(out[~held] == 0)
+    compare(to_f64(again), to_f64(out), *tolerances("bf16"), what="without a workspace")
+    got = ca.compact_attn_permute(out, lay, inverse=True)
+    for b in range(batch):
+        _say(b, compare(to_f64(got[b]), OA.dense_attention(to_f64(q[b]), to_f64(k[b]), to_f64(v[b])), *tolerances("bf16"), what=kernel))
+    side = torch.cuda.Stream()
+    on_side = torch.full_like(qp, float("nan"))
+    side.wait_stream(torch.cuda.current_stream())
+    ca.compact_attn_dense(qp, kp, vp, lay, out=on_side, stream=side)
+    with_main = ca.compact_attn_dense(qp, kp, vp, lay)               # may overlap with it
+    torch.cuda.synchronize()
+    assert torch.equal(on_side, out) and torch.equal(with_main, out)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ca.compact_attn_dense(qp, kp, vp, lay, out=again)
+    for rep in range(3):
+        again.fill_(float("nan"))
+        graph.replay()
+        assert torch.equal(ca.compact_attn_dense(qp, kp, vp, lay), out)
+        torch.cuda.synchronize()
+        assert torch.equal(again, out), f"replay {rep}"
