@@ -1,4 +1,5 @@
-"""ctypes binding of libcompact_attn.so: argument marshalling only.
+"""Binding of libcompact_attn.so: argument marshalling only, with ctypes; the calls that a program makes
+at every layer go through the extension _calls where their arguments are the usual ones.
 
 Every function has the name of the C entry point it calls (see
 include/compact_attn.h).  Tensors are torch tensors used purely as device
@@ -21,6 +22,7 @@ CA_ERR_HIP = -4
 CA_F32 = 0
 CA_BF16 = 1
 CA_CALL_FORWARD, CA_CALL_NATURAL, CA_CALL_DENSE = 0, 1, 2
+CA_CALL_STATIC = 3   # not a ca_call: has an entry point of its own
 CA_MAX_GROUPS = 8
 
 EXPORTED = (
@@ -165,8 +167,10 @@ class Layout:
         self._is_bf16 = problem.dtype == CA_BF16
         # bytes a call lends the library: the sparse walk, the dense one
         self._workspace = [_layout_split(handle, dense)[0] for dense in (0, 1)]
+        self._calls = None
 
     def free(self):
+        self._calls = None
         if self.handle is not None:
             load_library().compact_attn_free_layout(self.handle)
             self.handle = None
@@ -347,8 +351,33 @@ def _check_tensor(t, layout, padded, name):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {layout.shape(padded)}")
 
 
+_calls_bound = False
+
+
+def _make_calls(layout):
+    """The extension's calls on a layout.  The extension is built with the library and looked for beside it; there is no fallback."""
+    global _calls_bound
+    import torch
+    from . import _calls
+    if not _calls_bound:
+        lib = load_library()
+        _calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.compact_attn_permute, lib.compact_attn_forward, lib.compact_attn_forward_natural, lib.compact_attn_dense,
+            lib.compact_attn_forward_static, lib.compact_attn_forward_with_workspace, lib.compact_attn_tile_mass)),
+            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch._C._cuda_isCurrentStreamCapturing)
+        _calls_bound = True
+    p = layout.problem
+    layout._calls = _calls.calls(layout.handle.value, p.batch, p.num_heads, layout.n_tokens_real, layout.n_tokens_padded, p.head_dim,
+                                 layout.n_tiles, layout._is_bf16)
+    return layout._calls
+
+
 def compact_attn_permute(src, layout, inverse=False, out=None, stream=None):
     """natural order -> tile order (inverse=False) or back (inverse=True)."""
+    if out is None and stream is None and layout.handle is not None:
+        done = (layout._calls or _make_calls(layout)).permute(src, inverse)
+        if done is not None:
+            return done
     inverse = bool(inverse)
     _check_tensor(src, layout, inverse, "src")
     if out is None:
@@ -387,13 +416,18 @@ def _in_graph_pool(t):
 
 
 def _attention(fn, call, q, k, v, layout, out, stream, padded=True):
+    need = 0 if call == CA_CALL_STATIC else layout._workspace[call == CA_CALL_DENSE]
+    if out is None and stream is None and layout.handle is not None:
+        done = (layout._calls or _make_calls(layout)).attention(call, q, k, v, need)
+        if done is not None:
+            return done
+    fn = getattr(load_library(), fn)
     for name, t in (("q", q), ("k", k), ("v", v)):
         _check_tensor(t, layout, padded, name)
     if out is None:
         out = q.new_empty(q.shape)
     else:
         _check_tensor(out, layout, padded, "out")
-    need = 0 if call is None else layout._workspace[call == CA_CALL_DENSE]
     workspace = _lend(q, need, layout, call, stream) if need else None
     if workspace is not None:
         _check(load_library().compact_attn_forward_with_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), layout.handle, out.data_ptr(), call,
@@ -405,22 +439,26 @@ def _attention(fn, call, q, k, v, layout, out, stream, padded=True):
 
 def compact_attn_forward(q, k, v, layout, out=None, stream=None):
     """Sparse attention over tile-ordered, padded q/k/v [batch, heads, N_pad, D]."""
-    return _attention(load_library().compact_attn_forward, CA_CALL_FORWARD, q, k, v, layout, out, stream)
+    return _attention("compact_attn_forward", CA_CALL_FORWARD, q, k, v, layout, out, stream)
 
 
 def compact_attn_forward_static(q, k, v, layout, out=None, stream=None):
     """compact_attn_forward with the layout tables in the library's fixed device array (no allocation
     inside the call; pass `out`, or the binding allocates it before the call)."""
-    return _attention(load_library().compact_attn_forward_static, None, q, k, v, layout, out, stream)
+    return _attention("compact_attn_forward_static", CA_CALL_STATIC, q, k, v, layout, out, stream)
 
 
 def compact_attn_forward_natural(q, k, v, layout, out=None, stream=None):
     """Sparse attention over natural-order q/k/v [batch, heads, N_real, D]; the result is in natural order too."""
-    return _attention(load_library().compact_attn_forward_natural, CA_CALL_NATURAL, q, k, v, layout, out, stream, padded=False)
+    return _attention("compact_attn_forward_natural", CA_CALL_NATURAL, q, k, v, layout, out, stream, padded=False)
 
 
 def compact_attn_tile_mass(q, k, layout, out=None, stream=None):
     """q, k: tile-ordered padded device tensors -> float32 [batch, heads, n, n] attention mass per tile pair."""
+    if out is None and stream is None and layout.handle is not None:
+        done = (layout._calls or _make_calls(layout)).mass(q, k)
+        if done is not None:
+            return done
     import torch
     _check_tensor(q, layout, True, "q")
     _check_tensor(k, layout, True, "k")
@@ -457,4 +495,4 @@ def compact_attn_search_head(layout, mass, group_max_dt, tau, lam, pattern="dual
 
 def compact_attn_dense(q, k, v, layout, out=None, stream=None):
     """Same kernel with every query tile keeping all tiles."""
-    return _attention(load_library().compact_attn_dense, CA_CALL_DENSE, q, k, v, layout, out, stream)
+    return _attention("compact_attn_dense", CA_CALL_DENSE, q, k, v, layout, out, stream)

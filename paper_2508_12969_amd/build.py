@@ -1,4 +1,4 @@
-"""Builds libcompact_attn.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libcompact_attn.so (HIP kernels + C ABI) for gfx950 with hipcc, and the extension _calls (host code), in-tree."""
 import os
 import shutil
 import subprocess
@@ -10,6 +10,7 @@ LIB_PATH = os.path.join(PKG_DIR, "libcompact_attn.so")
 SOURCES = ["layout.cpp", "search.cpp", "api.cpp", "permute.hip", "attn_f32.hip", "attn_f32_planes.hip", "attn_bf16.hip", "attn_bf16_pair.hip", "attn_bf16_ways.hip",
            "attn_bf16_merge.hip",
            "tile_mass.hip"]
+CALLS_PATH = os.path.join(PKG_DIR, "_calls.so")
 PER_FILE_FLAGS = {}   # extra hipcc flags for single sources, if any
 ARCH = "gfx950"
 
@@ -50,7 +51,22 @@ def build(verbose=False, extra_flags=(), out=None):
         run(common + PER_FILE_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     run([hipcc_path(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", out or LIB_PATH])
+    if out is None:
+        build_calls(run)
     return out or LIB_PATH
+
+
+def build_calls(run):
+    """The CPython extension of csrc/calls.cpp, against the installed torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    lib = cpp_extension.TORCH_LIB_PATH
+    run([shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+         *(x for path in (*cpp_extension.include_paths(), sysconfig.get_paths()["include"]) for x in ("-isystem", path)),
+         os.path.join(CSRC, "calls.cpp"), "-o", CALLS_PATH, "-L", lib, f"-Wl,-rpath,{lib}", "-lc10", "-ltorch_cpu", "-ltorch_python"])
 
 
 if __name__ == "__main__":

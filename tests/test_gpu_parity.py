@@ -1724,3 +1724,48 @@ def test_dense_calls_without_the_padding(kernel, D, grid, tile, text_tiles, num_
         assert torch.equal(ca.compact_attn_dense(qp, kp, vp, lay), out)
         torch.cuda.synchronize()
         assert torch.equal(again, out), f"replay {rep}"
+
+
+# ---------------------------------------------------------------- calls through the extension
+
+def test_calls_with_other_than_the_usual_arguments():
+    """What the extension does not take is served, or refused with its reason, by the binding: given outputs and streams, subclasses and
+    tensors under a torch function mode, wrong types, shapes and strides, freed layouts."""
+    from torch.overrides import TorchFunctionMode
+
+    class Sub(torch.Tensor):
+        pass
+
+    class Mode(TorchFunctionMode):
+        seen = 0
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            Mode.seen += 1
+            return func(*args, **(kwargs or {}))
+
+    wl = make_workload("usual", 3, 9, 17, (1, 8, 8), 64, 2, 64, "bf16", [[(1, (1, 1), ABSENT)]] * 2)
+    lay = build_layout(ca, wl)
+    q, k, v = make_qkv(wl, DEV)
+    x = [ca.compact_attn_permute(t, lay) for t in (q, k, v)]
+    want, back = ca.compact_attn_forward(*x, lay), ca.compact_attn_permute(x[0], lay, inverse=True)
+    assert torch.equal(back, q) and want.shape == x[0].shape and want.dtype == torch.bfloat16 and not want.requires_grad
+    assert torch.equal(ca.compact_attn_forward(*x, lay, out=torch.empty_like(want)), want)
+    assert torch.equal(ca.compact_attn_forward(*x, lay, stream=torch.cuda.current_stream()), want)
+    assert torch.equal(ca.compact_attn_forward(x[0].clone().requires_grad_(), *x[1:], lay), want)
+    sub = ca.compact_attn_permute(q.as_subclass(Sub), lay)
+    assert type(sub) is Sub and torch.equal(sub.as_subclass(torch.Tensor), x[0])
+    with Mode():
+        got = ca.compact_attn_forward(*x, lay)
+    assert Mode.seen > 0 and torch.equal(got, want)
+    mass = ca.compact_attn_tile_mass(x[0], x[1], lay)
+    assert torch.equal(mass, ca.compact_attn_tile_mass(x[0], x[1], lay, out=torch.empty_like(mass))) and mass.dtype == torch.float32
+    for bad in (x[0].float(), x[0][:, :, :-1], x[0].transpose(0, 1).contiguous(), x[0].transpose(2, 3).contiguous().transpose(2, 3), x[0].cpu()):
+        with pytest.raises(ValueError):
+            ca.compact_attn_forward(bad, x[1], x[2], lay)
+        with pytest.raises(ValueError):
+            ca.compact_attn_permute(bad, lay, inverse=True)
+        with pytest.raises(ValueError):
+            ca.compact_attn_tile_mass(bad, x[1], lay)
+    lay.free()
+    with pytest.raises(ca.CompactAttnError):
+        ca.compact_attn_forward(*x, lay)
