@@ -38,6 +38,12 @@ struct WayShape : Shape<128, D, NW> {
   static constexpr int kRowsPerLoad = 1024 / (D * 2);
   static constexpr int kLoads = 16 / kRowsPerLoad;           // of K, and of V, per wave and stage
   static constexpr int kLeadK = 6, kLeadV = 4;               // 3 - 6 % against the compiler's order at head dim 128
+  // Eight waves and a stage of 64 KB.  Copies are asked for after the scores instead of before, because the waves wait for their turn at
+  // asking and would start their products late; and a wave without a real query has a loop of its own, without which the
+  // compiler copied all of O (64 registers) once a stage in 8x2.  Together, 192 rows of 64 tiles, 8x2, 62.2 / 56.3 us (57.1 with the
+  // loop alone), 256 rows of 256 tiles 222 / 199 us (203); nine drawn launches of 8x2 1.09 times, three of 8x4 1.03.  With four waves or half
+  // the bytes (head dim 64) neither gains anything (0.98 to 1.03), and the keys' branch stays.
+  static constexpr bool kLateCopies = D == 128 && NW == 8;
   static_assert(kKeyBlocks >= 1 && kKeyBlocks * 32 * NK == kStageKeys && NW <= 8, "whole blocks per way, a byte of every granule's count");
 };
 
@@ -223,17 +229,29 @@ void attn_bf16_ways_kernel(LaunchArgs<kSplit> a, int parts) {
     issue(0);
     landed(0);
   }
+  if constexpr (S::kLateCopies) {
+    if (!qs.wave_active)  // takes part in the copies and barriers only
+      for (int buf = 0; (keys & 0xff) != 0; buf ^= 1) {
+        advance(NW);
+        issue(buf ^ 1);
+        landed(buf ^ 1);
+      }
+  }
   for (int buf = 0; (keys & 0xff) != 0; buf ^= 1) {
     advance(NW);
-    issue(buf ^ 1);
-    // this way's granules: 2 * kKeyBlocks bytes
+    if constexpr (!S::kLateCopies) issue(buf ^ 1);
+    // this way's granules: 2 * kKeyBlocks bytes; in the last stage they may all be empty
     const uint64_t own = keys >> (16 * S::kKeyBlocks * kw);
-    if (qs.wave_active && (own & 0xff) != 0) {
+    if (S::kLateCopies || (qs.wave_active && (own & 0xff) != 0)) {
       const int share = buf * 2 * S::kStageBytes + kw * S::kKeyBlocks * 32 * S::kRowBytes;
       const LdsTile k_tile = (LdsTile)lds + share, v_tile = k_tile + S::kStageBytes;
       floatx16 acc_s[S::kKeyBlocks];
       w.qk_tile(k_tile, acc_s, true);
       __builtin_amdgcn_sched_barrier(0);  // V fragments requested before the softmax would spill
+      if constexpr (S::kLateCopies) {
+        issue(buf ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int kb = 0; kb < S::kKeyBlocks; ++kb) {
         const int c0 = (int)(own >> (16 * kb)) & 0xff, c1 = (int)(own >> (16 * kb + 8)) & 0xff;
