@@ -291,6 +291,17 @@ int check_attention_args(const void* q, const void* k, const void* v, const ca_l
   return CA_OK;
 }
 
+// Byte c: tokens of a tile of padding class c.
+uint64_t class_tokens(const ca_layout* L) {
+  uint64_t valid = 0;
+  for (size_t c = 0; c < L->class_mask.size() && c < 8; ++c) {
+    uint64_t tokens = 0;
+    for (uint32_t w : L->class_mask[c].w) tokens += (uint64_t)__builtin_popcount(w);
+    valid |= tokens << (8 * c);
+  }
+  return valid;
+}
+
 // Fills the kernel arguments from the problem and a set of device tables, and launches.
 int launch_attention(const void* q, const void* k, const void* v, const ca_layout* L, const ca::DeviceTables& t, void* out,
                      void* stream, bool dense, bool natural, void* workspace) {
@@ -310,11 +321,7 @@ int launch_attention(const void* q, const void* k, const void* v, const ca_layou
   a.class_mask = t.class_mask;
   a.class_perm = t.class_perm;
   a.num_classes = (int32_t)L->class_mask.size();
-  for (size_t c = 0; c < L->class_mask.size() && c < 8; ++c) {
-    uint64_t tokens = 0;
-    for (uint32_t w : L->class_mask[c].w) tokens += (uint64_t)__builtin_popcount(w);
-    a.class_valid |= tokens << (8 * c);
-  }
+  a.class_valid = class_tokens(L);
   a.batch = L->prob.batch;
   a.num_heads = L->prob.num_heads;
   a.n = L->n;
@@ -869,6 +876,9 @@ int compact_attn_tile_mass(const void* q, const void* k, ca_layout* L, float* ma
   a.B = (int32_t)L->B;
   a.D = p.head_dim;
   a.scale = L->scale;
+  a.num_classes = (int32_t)L->class_mask.size();
+  a.class_valid = class_tokens(L);
+  a.tokens_first = L->mass_tokens_first;
   const hipError_t e = ca::launch_tile_mass(a, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "tile mass launch");
   return CA_OK;

@@ -141,6 +141,9 @@ struct MassArgs {
   int64_t n;
   int32_t B, D;
   float scale;
+  int32_t num_classes;         // at most eight
+  uint64_t class_valid;        // byte c: tokens of a tile of padding class c
+  int32_t tokens_first;        // read where B is 128: the rows of padded tiles are brought into the order of class_perm
 };
 // bf16 problems, (B, D) in {64,128} x {64,128}
 hipError_t launch_tile_mass(const MassArgs& a, hipStream_t stream);

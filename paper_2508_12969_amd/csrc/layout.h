@@ -167,6 +167,7 @@ struct ca_layout {
   std::vector<int32_t> pair_walk;           // per pair: union of its two rows, tile id | kPairInFirst | kPairInSecond
   std::vector<int32_t> tile_class;          // [n]
   std::vector<ca::SlotMask> class_mask;     // class 0 = all valid
+  bool mass_tokens_first = false;           // tile mass: the padded tiles' tokens are brought to the front, see build_slot_masks
 
   // A launch deals most of its workgroups to the XCDs statically and
   // leaves the cheapest entries at the end of the launch order to be drawn by whichever XCD gets there

@@ -25,6 +25,7 @@
 // in a fixed order, so the result is run-to-run identical.  (The alternative without a workspace
 // walks every row twice and multiplies twice; it measured twice the time per product.)
 #include <algorithm>
+#include <type_traits>
 
 #include "attn_bf16_common.h"
 
@@ -97,9 +98,58 @@ __device__ __forceinline__ void reduce_tiles(const float2* part, const float* in
   }
 }
 
+// The slots of a tile, those that hold a token first, of every padding class.
+__device__ __forceinline__ uint8_t* lds_perm() {
+  __shared__ uint8_t perm[8 * 128];
+  return perm;
+}
+
+__device__ __forceinline__ int class_of(int32_t word) { return (word >> 24) & 0x7f; }
+
+__device__ __forceinline__ int tokens_of(int32_t word, uint64_t class_valid) { return (int)((class_valid >> (8 * class_of(word))) & 0xffu); }
+
+// f(blocks of 32 keys that hold a token, tokens of the last of them) for a tile of 128
+template <class F>
+__device__ __forceinline__ auto by_blocks(int tokens, F&& f) {
+  if (tokens > 96) return f(std::integral_constant<int, 4>{}, tokens - 96);
+  if (tokens > 64) return f(std::integral_constant<int, 3>{}, tokens - 64);
+  if (tokens > 32) return f(std::integral_constant<int, 2>{}, tokens - 32);
+  return f(std::integral_constant<int, 1>{}, tokens);
+}
+
+template <class W, class Blocks, class Acc>
+__device__ __forceinline__ void scores_tokens_first(W& w, LdsTile tile, Blocks blocks, int last, Acc& acc) {
+  w.template qk<0, blocks()>(tile, acc);
+  if (last < 32) mask_granules(acc[blocks() - 1], min(16, last), max(0, last - 16));
+}
+
+// This wave's part of key tile `step`, whose word it is, into its buffer.
+template <class M, class Loader>
+__device__ __forceinline__ void issue_tokens_first(const Loader& loader, const char* Kp, int32_t word, int step, uint32_t lds_k_addr, int wave) {
+  using S = typename M::Step;
+  static_assert(M::kStepTiles == 1, "a step is one tile");
+  const char* const from = Kp + (int64_t)step * S::kTileBytes;
+  const uint32_t to = lds_k_addr + (step & 1) * S::kTileBytes;
+  const int c = class_of(word);
+  if (c == 0) {
+    loader.issue(from, to, wave);
+    return;
+  }
+  const int in_block = (threadIdx.x & 63) / S::kChunksPerRow;
+#pragma unroll
+  for (int i = 0; i < S::kLoadsPerThread; ++i) {
+    const int block = wave * S::kLoadsPerThread + i;
+    const int slot = lds_perm()[c * 128 + block * S::kRowsPerLoad + in_block];
+    copy_rows(to + (uint32_t)block * 1024u, from, (uint32_t)((slot - in_block) * S::kRowBytes) + loader.voff[i & 3]);
+  }
+}
+
 // kSplit: the key tiles of a row group are shared by several workgroups, see mass_shares.  Each leaves its sums and, for
 // every query, its total and reference; tile_mass_merge_kernel finishes.
-template <int B, int D, bool kSplit>
+// kTokensFirst (128-token tiles, chosen by build_slot_masks): the rows of a padded tile are copied token-holding slots first,
+// each from an address of its own, and blocks of 32 keys that are then without a token are neither multiplied nor summed; else
+// the tile's order and a mask per slot.
+template <int B, int D, bool kSplit, bool kTokensFirst>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(mass_workgroups_per_cu(B, D), mass_workgroups_per_cu(B, D))))
 void tile_mass_kernel(MassArgs a) {
   using M = MassShape<B, D>;
@@ -109,6 +159,9 @@ void tile_mass_kernel(MassArgs a) {
   __shared__ __attribute__((aligned(16))) float lds_inv[Q];  // 1 / l_i
   __shared__ __attribute__((aligned(16))) float lds_ref[Q];  // m_i
   __shared__ int lds_ticket;
+  if constexpr (kTokensFirst) {
+    for (int e = threadIdx.x; e < a.num_classes * 128; e += 256) lds_perm()[e] = a.class_perm[e];  // visible from the first ticket on
+  }
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -161,8 +214,10 @@ void tile_mass_kernel(MassArgs a) {
   const int mine = wave * 32 + w.qi;  // this lane's query in the workspace block and in lds_inv
   const bool writer = w.g == 0;       // both lanes of a pair hold the query's sum; the lower one stores it
 
-  if (first_step * KT + my_key_tile < n)
-    k_loader.issue(Kp + (int64_t)first_step * M::Step::kTileBytes, lds_k_addr + (first_step & 1) * M::Step::kTileBytes, wave);
+  if (first_step * KT + my_key_tile < n) {
+    if constexpr (kTokensFirst) issue_tokens_first<M>(k_loader, Kp, meta[first_step], first_step, lds_k_addr, wave);
+    else k_loader.issue(Kp + (int64_t)first_step * M::Step::kTileBytes, lds_k_addr + (first_step & 1) * M::Step::kTileBytes, wave);
+  }
   float2 prev[KT];     // the previous step's sums and their references, stored at the head of the next step
   float m_run = 0.f;   // its exponent reference
   float l_row = 0.f;   // the query's running sum over the item's key tiles (both lanes of a pair hold it)
@@ -181,18 +236,23 @@ void tile_mass_kernel(MassArgs a) {
     int32_t words[KT];  // past the end: tile 0's, not used
 #pragma unroll
     for (int t = 0; t < KT; ++t) words[t] = meta[j * KT + t < n ? j * KT + t : 0];
+    int32_t next_word = 0;
+    if constexpr (kTokensFirst) next_word = meta[min(j + 1, n - 1)];
     // K(j) landed and visible, buffer (j+1)%2 free, the previous step's stores have been written
     WAIT_VMCNT(0);
     BARRIER();
-    if ((!kSplit || j + 1 < end_step) && (j + 1) * KT + my_key_tile < n)
-      k_loader.issue(Kp + (int64_t)(j + 1) * M::Step::kTileBytes, lds_k_addr + ((j + 1) & 1) * M::Step::kTileBytes, wave);
+    if ((!kSplit || j + 1 < end_step) && (j + 1) * KT + my_key_tile < n) {
+      if constexpr (kTokensFirst) issue_tokens_first<M>(k_loader, Kp, next_word, j + 1, lds_k_addr, wave);
+      else k_loader.issue(Kp + (int64_t)(j + 1) * M::Step::kTileBytes, lds_k_addr + ((j + 1) & 1) * M::Step::kTileBytes, wave);
+    }
     if (j > first_step) store_step(j - 1);  // a whole step to complete
     const LdsTile k_step = k_tile + (j & 1) * M::Step::kTileBytes;
 
-    auto row_sum = [&](const floatx16 (&acc)[S::kKeyBlocks]) {
+    constexpr std::integral_constant<int, S::kKeyBlocks> all_blocks;
+    auto row_sum = [&](const floatx16 (&acc)[S::kKeyBlocks], auto blocks) {
       float e4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kb = 0; kb < S::kKeyBlocks; ++kb)
+      for (int kb = 0; kb < blocks(); ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) e4[r & 3] += __builtin_amdgcn_exp2f(acc[kb][r] * w.c2);
       return sum_with_partner((e4[0] + e4[1]) + (e4[2] + e4[3]));
@@ -221,16 +281,23 @@ void tile_mass_kernel(MassArgs a) {
           for (int t = 0; t < KT; ++t) {
             floatx16 acc_s[S::kKeyBlocks];
             w.template qk<0, S::kKeyBlocks>(k_step + t * S::kTileBytes, acc_s);
-            e[t] = row_sum(acc_s);
+            e[t] = row_sum(acc_s, all_blocks);
             move = move || !(e[t] <= limit);  // also true for inf and NaN
           }
+        } else if constexpr (kTokensFirst) {
+          e[0] = by_blocks(tokens_of(words[0], a.class_valid), [&](auto blocks, int last) {
+            floatx16 acc_s[S::kKeyBlocks];
+            scores_tokens_first(w, k_step, blocks, last, acc_s);
+            return row_sum(acc_s, blocks);
+          });
+          move = !(e[0] <= limit);
         } else {
 #pragma unroll
           for (int t = 0; t < KT; ++t) {
             floatx16 acc_s[S::kKeyBlocks];
             w.qk_tile(k_step + t * S::kTileBytes, acc_s, words[t] >= 0);
             w.mask_padding_keys(acc_s, (words[t] >> 24) & 0x7f, class_mask);
-            e[t] = row_sum(acc_s);
+            e[t] = row_sum(acc_s, all_blocks);
             move = move || !(e[t] <= limit);
           }
         }
@@ -249,11 +316,21 @@ void tile_mass_kernel(MassArgs a) {
         for (int t = 0; t < KT; ++t) {
           if (j * KT + t >= n) break;
           floatx16 acc_s[S::kKeyBlocks];
-          w.qk_tile(k_step + t * S::kTileBytes, acc_s, words[t] >= 0);
-          w.mask_padding_keys(acc_s, (words[t] >> 24) & 0x7f, class_mask);
+          if constexpr (kTokensFirst) {
+            by_blocks(tokens_of(words[t], a.class_valid), [&](auto blocks, int last) {
+              scores_tokens_first(w, k_step, blocks, last, acc_s);
+#pragma unroll
+              for (int kb = blocks(); kb < S::kKeyBlocks; ++kb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc_s[kb][r] = kMinusInf;
+            });
+          } else {
+            w.qk_tile(k_step + t * S::kTileBytes, acc_s, words[t] >= 0);
+            w.mask_padding_keys(acc_s, (words[t] >> 24) & 0x7f, class_mask);
+          }
           bool move = true;  // this lane's query takes a new reference (every query on the first tile)
           if (j > first_step || t > 0) {
-            e[t] = row_sum(acc_s);
+            e[t] = row_sum(acc_s, all_blocks);
             move = !(e[t] <= limit);
           }
           const uint64_t movers = __builtin_amdgcn_ballot_w64(move);
@@ -276,7 +353,7 @@ void tile_mass_kernel(MassArgs a) {
               for (int r = 0; r < 16; ++r) acc_s[kb][r] -= delta;
 #pragma unroll
             for (int r = 0; r < 16; ++r) w.neg_m[r] = -m_run;
-            e[t] = row_sum(acc_s);
+            e[t] = row_sum(acc_s, all_blocks);
           }
           l_row += e[t];
           if (l_row != 0.f) limit = kSumLimit;
@@ -347,15 +424,18 @@ __global__ __launch_bounds__(256) void tile_mass_merge_kernel(MassArgs a) {
                         min(begin + kMassMergeTiles, n), n, a.n - first_row, a.mass + (plane_id * a.n + first_row) * a.n);
 }
 
-template <int B, int D>
+template <int B, int D, bool kTokensFirst = false>
 hipError_t launch(const MassArgs& a, int64_t items, hipStream_t stream) {
+  if constexpr (B == 128 && !kTokensFirst) {
+    if (a.tokens_first) return launch<B, D, true>(a, items, stream);
+  }
   if (a.shares == 1) {
-    hipLaunchKernelGGL((tile_mass_kernel<B, D, false>), dim3((unsigned)std::min(items, a.partial_rows)), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((tile_mass_kernel<B, D, false, kTokensFirst>), dim3((unsigned)std::min(items, a.partial_rows)), dim3(256), 0, stream, a);
     return hipGetLastError();
   }
   const int64_t chunks = (a.n + kMassMergeTiles - 1) / kMassMergeTiles;
   if (chunks > 65535 || items > 0x7fffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((tile_mass_kernel<B, D, true>), dim3((unsigned)std::min(items * a.shares, a.places)), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL((tile_mass_kernel<B, D, true, kTokensFirst>), dim3((unsigned)std::min(items * a.shares, a.places)), dim3(256), 0, stream, a);
   hipLaunchKernelGGL((tile_mass_merge_kernel<B>), dim3((unsigned)items, (unsigned)chunks), dim3(256), 0, stream, a);
   return hipGetLastError();
 }

@@ -536,6 +536,32 @@ def test_tile_mass_of_scores_far_below_zero(D, tile):
         assert np.abs(mass[0, h].double().cpu().numpy() - want).max() <= MASS_ABS + 1e-4 * want.max()
 
 
+@pytest.mark.parametrize("T,Hd", [(5, 2), (60, 24)])
+@pytest.mark.parametrize("tokens", [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127])
+@pytest.mark.parametrize("D", [64, 128])
+def test_tile_mass_of_padded_tiles(D, tokens, T, Hd):
+    """Every second tile of 128 holds `tokens` tokens: up to 96 its tokens are brought to the front and whole blocks of 32 keys left
+    out.  Few rows, whose key tiles are shared by workgroups, and enough for one workgroup each; padding rows of K hold NaN."""
+    from oracle import search as OS
+    _say("tile mass, padded tiles", D, tokens, T, Hd)
+    wl = make_workload("masspad", T, 1, 128 + tokens, (1, 1, 128), 0, Hd, D, "bf16", [[]] * Hd)
+    g = geometry_of(wl)
+    lay = build_layout(ca, wl)
+    q, k, _ = make_qkv(wl, DEV, q_gain=2.0)
+    qp, kp = ca.compact_attn_permute(q, lay), ca.compact_attn_permute(k, lay)
+    tok_tile, tok_slot = (np.asarray(x) for x in g.token_tile_and_slot())
+    padding = torch.ones(g.n * 128, dtype=torch.bool, device=DEV)
+    padding[torch.from_numpy(tok_tile * 128 + tok_slot).to(DEV)] = False
+    kp[:, :, padding] = float("nan")
+    mass = ca.compact_attn_tile_mass(qp, kp, lay)
+    assert torch.equal(mass, ca.compact_attn_tile_mass(qp, kp, lay))
+    got = mass[0].double().cpu().numpy()
+    assert np.allclose(got.sum(axis=2), np.bincount(tok_tile, minlength=g.n)[None, :].repeat(Hd, 0), atol=1e-2)
+    for h in (0, Hd - 1):
+        want = OS.tile_mass(g, to_f64(q[0, h]), to_f64(k[0, h]))
+        assert np.abs(got[h] - want).max() <= MASS_ABS
+
+
 @pytest.mark.parametrize("D,tile", [(64, (1, 8, 8)), (128, (1, 8, 8)), (64, (2, 8, 8)), (128, (2, 8, 8))])
 def test_tile_mass_with_more_rows_than_workgroups(D, tile):
     """More groups of 128 queries than the launch has workgroups (two or three per compute unit), so
