@@ -93,7 +93,7 @@ void attn_bf16_ways_kernel(LaunchArgs<kSplit> a, int parts) {
     const LaunchItem it = split_item(a);
     batch = it.batch, row = it.entry, part = it.part, first_tile = it.first, count = it.count, share = it.share;
   } else {
-    const int64_t linear = xcd_launch_order(blockIdx.x, gridDim.x);  // (batch, launch-order row, part)
+    const int64_t linear = xcd_launch_order(blockIdx.x, gridDim.x, NW == 4 ? xcd_chunk(gridDim.x) : kXcdChunk);  // (batch, launch-order row, part)
     const int64_t rows = (int64_t)a.num_heads * a.n, item = linear / parts % rows;
     part = (int)(linear % parts);
     batch = linear / parts / rows;

@@ -3,7 +3,7 @@
 //
 // What bounds it: v_mfma_f32_16x16x4_f32 (a multiply-add in full fp32; a large fp32 matrix product
 // reaches 152 TFLOP/s on this card).  8 heads of 7K tokens, head dim 128, 0.094 TFLOP on real tokens:
-// 1.18 ms, 21.4 ms with one thread per query; 2 heads of 256 tokens: 11 us, 222 us.  Per 16 keys and 16 queries a wave
+// 1.18 ms (launches dealt in chunks of 64 rows, see xcd_chunk), 21.4 ms with one thread per query; 2 heads of 256 tokens: 11 us, 222 us.  Per 16 keys and 16 queries a wave
 // issues D / 2 of them, 32 cycles each, beside D / 8 16-byte LDS reads and four exponentials, so
 // everything else fits beside the matrix pipe.
 //
@@ -96,7 +96,7 @@ void attn_f32_kernel(AttnArgs a, int parts, int64_t workgroups) {
   const int qi = lane & 15, g = lane >> 4;
   const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
   if (id >= workgroups) return;
-  const int64_t linear = xcd_launch_order(id, workgroups);
+  const int64_t linear = xcd_launch_order(id, workgroups, xcd_chunk(workgroups));
   const int64_t rows = (int64_t)a.num_heads * a.n;
   const int part = (int)(linear % parts);
   const int64_t item = (linear / parts) % rows, batch = linear / parts / rows;

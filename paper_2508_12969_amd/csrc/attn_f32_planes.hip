@@ -25,7 +25,7 @@
 //
 // What bounds it: the bf16 matrix instructions.  Measured, attn_f32.hip / this with the split of K and V: 8 heads of 8K tokens,
 // dense, head dim 128 2.47 / 1.38 ms (1200 TFLOP/s of bf16 products), 64 1.29 / 0.73 ms, 32 0.65 / 0.42 ms; 8 heads of 7K tokens, head
-// dim 128, 1128 rows of unequal length 1.18 / 0.72 ms (of which the split takes 0.026); 1 head of 1.9K 115 / 80 us.  Four ways and
+// dim 128, 1128 rows of unequal length 1.18 / 0.64 ms (of which the split takes 0.026; 0.72 with launches of few rounds dealt in chunks of 64, see xcd_chunk); 1 head of 1.9K 115 / 80 us.  Four ways and
 // one wave of queries (1x4) make the walk of a small launch shortest, two and two a full card fastest (choose_planes in layout.cpp).
 #include <algorithm>
 #include <type_traits>
@@ -205,7 +205,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
   const int qi = lane & 31, g = lane >> 5;
   const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
   if (id >= workgroups) return;
-  const int64_t linear = xcd_launch_order(id, workgroups);
+  const int64_t linear = xcd_launch_order(id, workgroups, xcd_chunk(workgroups));
   const int64_t rows = (int64_t)a.num_heads * a.n;
   const int part = (int)(linear % parts);
   const int64_t item = (linear / parts) % rows, batch = linear / parts / rows;

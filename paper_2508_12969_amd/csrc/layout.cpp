@@ -422,6 +422,18 @@ void build_launch_splits(ca_layout& L) {
 
 namespace {
 
+// Every entry has one workgroup.
+constexpr bool is_a_permutation(int64_t total) {
+  bool taken[4200] = {};
+  for (int64_t id = 0; id < total; ++id) {
+    const int64_t entry = xcd_launch_order(id, total, xcd_chunk(total));
+    if (entry < 0 || entry >= total || taken[entry]) return false;
+    taken[entry] = true;
+  }
+  return true;
+}
+static_assert(is_a_permutation(511) && is_a_permutation(512) && is_a_permutation(577) && is_a_permutation(4095) && is_a_permutation(4097), "");
+
 // Predicted time of a launch in us.  Its workgroups are dealt to the XCDs by id and to the free places of their
 // XCD in order, which decides it for launches of a few rounds: one workgroup more than the card holds, or the
 // long rows on the XCD that has the first of them, are worth up to half of the time.  A step is 128 keys, or one

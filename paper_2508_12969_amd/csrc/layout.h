@@ -61,6 +61,15 @@ constexpr int64_t xcd_launch_order(int64_t id, int64_t total, int64_t chunk = kX
   return round * span + ((round & 1) ? 7 - xcd : xcd) * chunk + seq % chunk;
 }
 
+// Chunk of launches of few rounds: with kXcdChunk the XCD of the first chunk gets the 64 longest rows and ends last.  Measured, 64 / 8, fp32 and
+// ways-4x4 launches from 512 to 4095 workgroups: 1.04 times as fast over 44 of them (0.985 to 1.25); 8 heads of 7K tokens, fp32, head dim
+// 128 754 / 660 us.  4 and 16 gave the same.  Below one span of large chunks all ids keep their place, which is the best there (chunks of 4, 8, 16: up to
+// 1.08, but 0.78 to 0.86 on three of 20 launches of little more than one workgroup per CU); the kernels of eight waves were between 0.965 and 1.04
+// and keep kXcdChunk.  launch_time goes on with kXcdChunk, which its constants were fitted with.
+constexpr int64_t kXcdFewRows = 4096;
+constexpr int kXcdFewChunk = 8;
+constexpr int64_t xcd_chunk(int64_t total) { return total < kXcdFewRows && total >= 8 * kXcdChunk ? kXcdFewChunk : kXcdChunk; }
+
 // The kernels of attn_bf16_ways.hip: waves of a workgroup x 32-query waves side by side; and those of attn_f32_planes.hip:
 // 32-query waves side by side x waves that share the keys of a query.
 enum Ways : int32_t { kWaysNone = 0, kWays4x4, kWays8x4, kWays8x2, kPlanes2x2, kPlanes2x4, kPlanes1x4 };

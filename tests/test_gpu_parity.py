@@ -448,6 +448,20 @@ def test_imported_random_mask_and_union(shape):
     _say(compare(to_f64(out[0]), want, *tolerances(dtype), what="merged mask"))
 
 
+@pytest.mark.parametrize("tile,D,dtype", [((1, 4, 4), 32, "f32"), ((1, 8, 8), 64, "f32"), ((2, 8, 8), 64, "bf16")])
+@pytest.mark.parametrize("heads", [127, 128, 129, 255, 1023, 1024])
+def test_launches_of_few_rounds(heads, tile, D, dtype):
+    """Launches around 512 and 4096 rows, where the order of their workgroups changes: every row of every head."""
+    _say("few rounds", heads, tile, D, dtype)
+    wl = make_workload("rounds", tile[0], 2 * tile[1], 2 * tile[2] - 1, tile, 0, heads, D, dtype, [[]] * heads)
+    lay = build_layout(ca, wl)
+    q, k, v = make_qkv(wl, DEV)
+    out = ca.compact_attn_permute(ca.compact_attn_dense(*(ca.compact_attn_permute(x, lay) for x in (q, k, v)), lay), lay, inverse=True)
+    s = q[0].double().cpu() @ k[0].double().cpu().transpose(1, 2) * D ** -0.5
+    err = (out[0].double().cpu() - torch.softmax(s, dim=2) @ v[0].double().cpu()).abs().max().item()
+    assert err <= (1e-4 if dtype == "f32" else 2e-2)      # the bounds of the other forward tests
+
+
 # ---------------------------------------------------------------- attention mass per tile pair
 
 MASS_ABS = 2e-4      # per tile pair, in units of "query tokens": a pair sums up to 128*128 probabilities in
