@@ -6,9 +6,9 @@
 //
 // The split.  a = a1 + a2 + a3 with a1 the upper 16 bits of a (truncated, so nothing overflows), a2 those of
 // a - a1 and a3 those of the rest: 24 bits, which is all of a.  Left out of a product are a2 b3, a3 b2 and a3 b3, about 4e-8 of it.
-// Infinities and NaN come out as they do in one fp32 product: the parts of a value other than zero have its sign and are
-// never zero (2^-40 and 2^-48 of it are added to what is split off), so an infinity meets no zero that the value it is
-// multiplied with does not hold, and an infinity or a NaN is its own second and third part.
+// Infinities and NaN: the parts of a value other than zero have its sign and, down to 2^-85, are
+// not zero (2^-40 and 2^-48 of it are added to what is split off), and an infinity or a NaN is its own second and third part.
+// Queries whose sums are infinite or NaN all the same are walked a second time, on the f32 matrix instructions.
 //
 // K and V are split once per call by a kernel of their own, into a workspace, as "units" of 16 tokens in
 // the order in which the matrix instructions read them; the slots of a padded tile are taken token-holding slots
@@ -198,6 +198,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
   constexpr int kMine = (U::kLoads + QN - 1) / QN;  // of a unit's copies one wave issues this many (or one less)
   __shared__ __attribute__((aligned(1024))) char lds[NK * U::kPlaces * U::kBytes];
   __shared__ float2 lds_stats[(NK - 1) * QN * 64];
+  __shared__ int lds_again[QN];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -422,54 +423,141 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
     u1 = w1;
   }
 
-  // ---- merge of the ways: all hold the same queries and channels in the same lanes ----------------------
-  if constexpr (NK > 1) {
-    constexpr int kOBytes = 32 * D * 4;
-    static_assert((NK - 1) * QN * kOBytes <= NK * U::kPlaces * U::kBytes, "the shares fit the places of the units");
-    __syncthreads();
-    if (kw > 0) {
-      f32x4* const o = reinterpret_cast<f32x4*>(lds + (wave - QN) * kOBytes);
+  // ---- merge of the ways: all hold the same queries and channels in the same lanes; way 0 gets the sums ------
+  auto merge = [&] {
+    if constexpr (NK > 1) {
+      constexpr int kOBytes = 32 * D * 4;
+      static_assert((NK - 1) * QN * kOBytes <= NK * U::kPlaces * U::kBytes, "the shares fit the places of the units");
+      __syncthreads();
+      if (kw > 0) {
+        f32x4* const o = reinterpret_cast<f32x4*>(lds + (wave - QN) * kOBytes);
 #pragma unroll
-      for (int i = 0; i < U::kDBlocks * 4; ++i)
-        o[i * 64 + lane] = f32x4{acc_o[i / 4][i % 4 * 4], acc_o[i / 4][i % 4 * 4 + 1], acc_o[i / 4][i % 4 * 4 + 2], acc_o[i / 4][i % 4 * 4 + 3]};
-      lds_stats[(wave - QN) * 64 + lane] = float2{ref, l_run};
+        for (int i = 0; i < U::kDBlocks * 4; ++i)
+          o[i * 64 + lane] = f32x4{acc_o[i / 4][i % 4 * 4], acc_o[i / 4][i % 4 * 4 + 1], acc_o[i / 4][i % 4 * 4 + 2], acc_o[i / 4][i % 4 * 4 + 3]};
+        lds_stats[(wave - QN) * 64 + lane] = float2{ref, l_run};
+      }
+      __syncthreads();
+      if (kw > 0) return;
+      float top = ref;
+#pragma unroll
+      for (int k = 1; k < NK; ++k) top = fmaxf(top, lds_stats[((k - 1) * QN + qw) * 64 + lane].x);
+      const float own = __builtin_amdgcn_exp2f(ref - top);
+      l_run *= own;
+#pragma unroll
+      for (int db = 0; db < U::kDBlocks; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc_o[db][r] *= own;
+#pragma unroll 1
+      for (int k = 1; k < NK; ++k) {
+        const int from = (k - 1) * QN + qw;
+        const float2 st = lds_stats[from * 64 + lane];
+        const float f = __builtin_amdgcn_exp2f(st.x - top);
+        l_run += st.y * f;
+        const f32x4* const o = reinterpret_cast<const f32x4*>(lds + from * kOBytes);
+#pragma unroll
+        for (int i = 0; i < U::kDBlocks * 4; ++i) {
+          const f32x4 x = o[i * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc_o[i / 4][i % 4 * 4 + e] += x[e] * f;
+        }
+      }
     }
-    __syncthreads();
-    if (kw > 0) return;
-    float top = ref;
+  };
+  const bool real = q_pos < q_valid;  // a padding row is zero whatever its sums are
+  auto store = [&](float l) {
+    const float inv = l > 0.f ? 1.0f / l : 0.f;
 #pragma unroll
-    for (int k = 1; k < NK; ++k) top = fmaxf(top, lds_stats[((k - 1) * QN + qw) * 64 + lane].x);
-    const float own = __builtin_amdgcn_exp2f(ref - top);
-    l_run *= own;
+    for (int i = 0; i < U::kDBlocks * 4; ++i) {  // channels 32 db + 8 r4 + 4 g .. + 3
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = real ? acc_o[i / 4][i % 4 * 4 + e] * inv : 0.f;
+      *reinterpret_cast<f32x4*>(out_row + (8 * i + 4 * g) * 4) = o;
+    }
+  };
+  merge();
+  bool again = false;  // this query did not come out finite, see the second walk
+  if (kw == 0) {
+    const float l = sum_with_partner(l_run);
+    float z = 0.f * l;  // NaN if the sum or a channel is infinite or NaN
 #pragma unroll
     for (int db = 0; db < U::kDBlocks; ++db)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc_o[db][r] *= own;
+      for (int r = 0; r < 16; ++r) z = fmaf(acc_o[db][r], 0.f, z);
+    again = real && count > 0 && !(sum_with_partner(z) == 0.f && l > 0.f);
+    const bool any = __any(again);
+    if (lane == 0) lds_again[qw] = any;
+    if (q_in) store(l);
+  }
+  __syncthreads();
+  bool once_more = false;
+#pragma unroll
+  for (int i = 0; i < QN; ++i) once_more = once_more || lds_again[i];
+  if (!once_more) return;
+
+  // ---- second walk: queries whose sums are infinite, NaN or zero, on the f32 matrix instructions -------------
+  // What six partial products and a lagging reference cannot do as fp32 does it (an infinity against a part that is zero, V near the
+  // top of the range times a weight above one) ends in such sums, and so do infinities and NaN of q, k and v, which are
+  // thereby where attn_f32.hip has them.  Operands come straight from memory: 8 heads of 7K tokens, head dim 128, 0.75 ms
+  // without such queries, 1.8 with one, 3.7 if all are (1.22 in attn_f32.hip; in one run); the check costs nothing (638 / 639 us).
+  {
+    const bool mine = lds_again[qw];
+    const char* const plane_k = static_cast<const char*>(a.k) + plane_tiles * a.B * (int64_t)(D * 4);
+    const char* const plane_v = static_cast<const char*>(a.v) + plane_tiles * a.B * (int64_t)(D * 4);
+    const float* const q_row = reinterpret_cast<const float*>(static_cast<const char*>(a.q) + tile_at + (int64_t)q_slot * (D * 4)) + g * (D / 2);
+    ref = -1e30f;
+    l_run = 0.f;
+#pragma unroll
+    for (int db = 0; db < U::kDBlocks; ++db) acc_o[db] = zeros();
+    int turn = 0;
 #pragma unroll 1
-    for (int k = 1; k < NK; ++k) {
-      const int from = (k - 1) * QN + qw;
-      const float2 st = lds_stats[from * 64 + lane];
-      const float f = __builtin_amdgcn_exp2f(st.x - top);
-      l_run += st.y * f;
-      const f32x4* const o = reinterpret_cast<const f32x4*>(lds + from * kOBytes);
+    for (int j = 0; j < count; ++j) {
+      const int32_t word = meta[j];
+      const int valid = tokens_of(word);
+      const int64_t tile_bytes = (int64_t)(word & 0xffffff) * a.B * (D * 4);
+      const uint8_t* const perm = a.class_perm + (((uint32_t)word >> 24) & 7) * 128;
+#pragma unroll 1
+      for (int first = 0; first < valid; first += 32, turn = turn + 1 < NK ? turn + 1 : 0) {
+        if (turn != kw || !mine) continue;
+        const int keys = min(32, valid - first);
+        floatx16 sc = zeros();
+        const float* const k_row = reinterpret_cast<const float*>(plane_k + tile_bytes + (int64_t)perm[first + min(qi, keys - 1)] * (D * 4)) + g * (D / 2);
+#pragma unroll 2
+        for (int c = 0; c < D / 2; c += 4) {
+          const f32x4 kf = *reinterpret_cast<const f32x4*>(k_row + c), qx = *reinterpret_cast<const f32x4*>(q_row + c);
 #pragma unroll
-      for (int i = 0; i < U::kDBlocks * 4; ++i) {
-        const f32x4 x = o[i * 64 + lane];
+          for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qx[e], sc, 0, 0, 0);
+        }
+        float mx = kMinusInf;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc_o[i / 4][i % 4 * 4 + e] += x[e] * f;
+        for (int r = 0; r < 16; ++r) {
+          sc[r] = r / 4 * 8 + 4 * g + r % 4 < keys ? sc[r] : kMinusInf;
+          mx = fmaxf(mx, sc[r]);
+        }
+        const float ref_new = fmaxf(ref, max_with_partner(mx) * c2), alpha = __builtin_amdgcn_exp2f(ref - ref_new);
+        if (__any(ref_new > ref)) {
+          l_run *= alpha;
+#pragma unroll
+          for (int db = 0; db < U::kDBlocks; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc_o[db][r] *= alpha;
+          ref = ref_new;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = r / 4 * 8 + 4 * g + r % 4;
+          const float p = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -ref));
+          l_run += p;
+          const float* const v_row = reinterpret_cast<const float*>(plane_v + tile_bytes + (int64_t)perm[first + min(key, keys - 1)] * (D * 4)) + qi;
+#pragma unroll
+          for (int db = 0; db < U::kDBlocks; ++db)
+            acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(key < keys ? v_row[32 * db] : 0.f, p, acc_o[db], 0, 0, 0);
+        }
       }
     }
-  }
-  const float l = sum_with_partner(l_run);
-  const float inv = l > 0.f ? 1.0f / l : 0.f;
-  const bool real = q_pos < q_valid;  // a padding row is zero whatever its sums are
-  if (!q_in) return;
-#pragma unroll
-  for (int i = 0; i < U::kDBlocks * 4; ++i) {  // channels 32 db + 8 r4 + 4 g .. + 3
-    f32x4 o;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = real ? acc_o[i / 4][i % 4 * 4 + e] * inv : 0.f;
-    *reinterpret_cast<f32x4*>(out_row + (8 * i + 4 * g) * 4) = o;
+    merge();
+    if (kw > 0) return;
+    const float l = sum_with_partner(l_run);
+    if (again) store(l);
   }
 }
 

@@ -3,6 +3,8 @@
 Layouts and permutations are compared bit for bit; attention outputs within
 max-abs 2e-2 / mean-abs 2e-3 for bf16 and 1e-4 / 1e-5 for fp32.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -1703,6 +1705,51 @@ def test_fp32_in_three_planes_infinities(kernel, D, grid, tile, text_tiles, copi
     assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.isinf(want).any()
     finite = ~torch.isnan(want)
     assert finite.any() and torch.allclose(got[finite], want[finite], rtol=1e-5, atol=1e-5)
+
+
+def _without_workspace(q, k, v, lay, call="forward"):
+    """The C call without a workspace: the kernel on the fp32 matrix instructions."""
+    import ctypes
+    lib, out = ca.load_library(), torch.full_like(q, float("nan"))
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert getattr(lib, "compact_attn_" + call)(*(ctypes.c_void_p(x.data_ptr()) for x in (q, k, v)), lay.handle, ctypes.c_void_p(out.data_ptr()), stream) == 0
+    return out
+
+
+@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,copies", _PLANE_LAUNCHES)
+@pytest.mark.parametrize("what", ["huge values", "infinite value of a small weight", "infinite query of small keys"])
+def test_fp32_in_three_planes_at_the_ends_of_the_range(kernel, D, grid, tile, text_tiles, copies, what):
+    """Values that fp32 products take and three bf16 parts or a lagging exponent reference do not: as the fp32 matrix instructions give them."""
+    _say("ends of the range", kernel, D, grid, tile, what)
+    wl, lay = _plane_problem(kernel, D, grid, tile, text_tiles, copies)
+    q, k, v = make_qkv(wl, DEV)
+    tokens = q.shape[2]
+    if what == "huge values":
+        # scores rise from 0 to 7 bits over the walk, so that a reference of its beginning makes weights of up to 2^7; with weights of up to 1 the
+        # sums stay below tokens * 2e38 / tokens
+        q, k = 1e-3 * q, 1e-3 * k
+        q[..., 0] = 1.0
+        k[..., 0] = torch.linspace(0, 7 * math.log(2) * D ** 0.5, tokens, device=DEV)
+        v = (v.abs().clamp(0.1, 1.0) * (2e38 / tokens)).contiguous()
+    elif what == "infinite value of a small weight":
+        # e^-70 of the largest weight of a row: 2^-101, whose second and third parts are below what a bf16 value can be
+        q, k = 0.1 * q, 0.1 * k
+        q[..., 0], k[..., 0] = 1.0, 0.0
+        k[:, :, tokens // 2, 0] = -70.0 * D ** 0.5
+        v[:, :, tokens // 2, 3] = float("inf")
+    else:
+        q[:, :, ::3, 4] = float("-inf")
+        k[..., 4] = 2.0 ** -100
+    q, k, v = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
+    want, got = (ca.compact_attn_permute(x, lay, inverse=True) for x in (_without_workspace(q, k, v, lay), ca.compact_attn_forward(q, k, v, lay)))
+    if what == "huge values":
+        assert torch.isfinite(want).all() and want.max() > 1e37 / tokens
+    else:
+        assert torch.isinf(want).any() == (what == "infinite value of a small weight") and not torch.isnan(want).any()
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+    finite = torch.isfinite(want)
+    scale = want[finite].abs().max()
+    assert (got[finite] / scale - want[finite] / scale).abs().max() <= 1e-5
 
 
 # ---------------------------------------------------------------- dense calls without the padding
