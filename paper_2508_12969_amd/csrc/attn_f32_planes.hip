@@ -4,11 +4,13 @@
 // Why: the f32 matrix instructions, on which attn_f32.hip runs, do 1/16 of the bf16 rate; six bf16 products per
 // fp32 one are 2.7 times as fast.
 //
-// The split.  a = a1 + a2 + a3 with a1 the upper 16 bits of a (truncated, so nothing overflows), a2 those of
-// a - a1 and a3 those of the rest: 24 bits, which is all of a.  Left out of a product are a2 b3, a3 b2 and a3 b3, about 4e-8 of it.
-// Infinities and NaN: the parts of a value other than zero have its sign and, down to 2^-85, are
-// not zero (2^-40 and 2^-48 of it are added to what is split off), and an infinity or a NaN is its own second and third part.
-// Queries whose sums are infinite or NaN all the same are walked a second time, on the f32 matrix instructions.
+// The split.  a = a1 + a2 + a3 with a1 the bf16 value nearest to a, a2 the one nearest to a - a1 and a3 the rest, at most 2^-8
+// and 2^-17 of the power of two below a: 24 bits, which is all of a.  (Three-way bf16 splits: Henry, Tang, Heinecke, Leveraging
+// the bfloat16 artificial intelligence datatype for higher-precision computations, ARITH 2019.)  Left out of a product are
+// a2 b3, a3 b2 and a3 b3, at most 2^-24 of it and of either sign; with parts cut off instead of rounded it would be 2^-21,
+// always to the same side.
+// Infinities, NaN and values from 2^96 on are NaN in all three parts; queries whose sums are infinite or NaN are walked a
+// second time, on the f32 matrix instructions.
 //
 // K and V are split once per call by a kernel of their own, into a workspace, as "units" of 16 tokens in
 // the order in which the matrix instructions read them; the slots of a padded tile are taken token-holding slots
@@ -37,6 +39,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+constexpr float kTop = 0x1p96f;  // operands from here on go the second way
 
 template <int D>
 struct UnitShape {
@@ -49,27 +52,19 @@ struct UnitShape {
 };
 
 // Parts of two values, packed for the matrix instructions: word i holds part i + 1 of `even` below that of `odd`.
-template <bool kMayBeInfinite>
+// kAnyValue: operands; else weights, which are 0 to 2^kLazyLog2, or NaN.
+template <bool kAnyValue>
 __device__ __forceinline__ void split_pair(float even, float odd, uint32_t (&word)[3]) {
-  const float x[2] = {even, odd};
-  uint32_t part[3][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const uint32_t bits = __builtin_bit_cast(uint32_t, x[i]), b1 = bits & 0xffff0000u;
-    const float a1 = __builtin_bit_cast(float, b1);
-    const float rest = fmaf(a1, 0x1p-40f, x[i] - a1);
-    const float a2 = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, rest) & 0xffff0000u);
-    const float last = fmaf(a1, 0x1p-48f, rest - a2);
-    part[0][i] = b1;
-    part[1][i] = __builtin_bit_cast(uint32_t, a2);
-    part[2][i] = __builtin_bit_cast(uint32_t, last);
-    if (kMayBeInfinite && (bits & 0x7f800000u) == 0x7f800000u) {
-      // a NaN may have all of its payload in the lower half
-      part[0][i] = part[1][i] = part[2][i] = x[i] == x[i] ? b1 : 0x7fc00000u;
-    }
+  if constexpr (kAnyValue) {
+    even = fabsf(even) < kTop ? even : __builtin_nanf("");
+    odd = fabsf(odd) < kTop ? odd : __builtin_nanf("");
   }
 #pragma unroll
-  for (int p = 0; p < 3; ++p) word[p] = __builtin_amdgcn_perm(part[p][1], part[p][0], 0x07060302u);
+  for (int p = 0; p < 3; ++p) {
+    word[p] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)even, (__bf16)odd});  // to nearest
+    even -= __builtin_bit_cast(float, word[p] << 16);
+    odd -= __builtin_bit_cast(float, word[p] & 0xffff0000u);
+  }
 }
 
 // ---- K and V to units ---------------------------------------------------------------------------------
@@ -495,9 +490,9 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
   if (!once_more) return;
 
   // ---- second walk: queries whose sums are infinite, NaN or zero, on the f32 matrix instructions -------------
-  // What six partial products and a lagging reference cannot do as fp32 does it (an infinity against a part that is zero, V near the
-  // top of the range times a weight above one) ends in such sums, and so do infinities and NaN of q, k and v, which are
-  // thereby where attn_f32.hip has them.  Operands come straight from memory: 8 heads of 7K tokens, head dim 128, 0.75 ms
+  // What six partial products and a lagging reference cannot do as fp32 does it ends in such sums: an infinity, which would meet parts
+  // that are zero or of the other sign, and V near the top of the range times a weight above one.  So infinities and NaN are
+  // where attn_f32.hip has them.  Operands come straight from memory: 8 heads of 7K tokens, head dim 128, 0.75 ms
   // without such queries, 1.8 with one, 3.7 if all are (1.22 in attn_f32.hip; in one run); the check costs nothing (638 / 639 us).
   {
     const bool mine = lds_again[qw];

@@ -1752,6 +1752,25 @@ def test_fp32_in_three_planes_at_the_ends_of_the_range(kernel, D, grid, tile, te
     assert (got[finite] / scale - want[finite] / scale).abs().max() <= 1e-5
 
 
+@pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,copies", _PLANE_LAUNCHES)
+def test_fp32_in_three_planes_of_the_least_favourable_values(kernel, D, grid, tile, text_tiles, copies):
+    """Operands of 1 + 2^-7 - 2^-23: cut off after 8 and 16 bits they leave as much as there can be, and always to one side.  No further from
+    the oracle than the kernel on the fp32 matrix instructions."""
+    _say("least favourable values", kernel, D, grid, tile)
+    wl, lay = _plane_problem(kernel, D, grid, tile, text_tiles, copies)
+    g, heads = geometry_of(wl), wl.heads
+    worst = 1 + 2.0 ** -7 - 2.0 ** -23
+    q, k, v = (torch.where(x < 0, -worst, worst).float() for x in make_qkv(wl, DEV))
+    q *= 8.0                                                           # scores of 8 on average
+    p = [ca.compact_attn_permute(x, lay) for x in (q, k, v)]
+    got, plain = (ca.compact_attn_permute(x, lay, inverse=True) for x in (ca.compact_attn_forward(*p, lay), _without_workspace(*p, lay)))
+    for h in range(4):
+        want = OA.masked_attention(g, [heads[h]], *(to_f64(x[0, h])[None] for x in (q, k, v)))
+        err = [np.linalg.norm(to_f64(x[0, h])[None] - want) / max(np.linalg.norm(want), 1e-30) for x in (got, plain)]
+        _say(h, err)
+        assert err[0] <= err[1]
+
+
 # ---------------------------------------------------------------- dense calls without the padding
 
 @pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,num_heads,batch", [
