@@ -278,8 +278,10 @@ int compact_attn_dense(const void* q, const void* k, const void* v, ca_layout* l
  * sums in the workspace, and a second kernel adds them up (always in the same order, so results are
  * run-to-run identical; compact_attn_forward_static does the same with a fixed device array).  f32 launches of tiles of
  * more than 32 tokens that are large enough to pay for it run on the bf16 matrix instructions: K and V are split into three
- * bf16 values each, which hold all of their 24 bits, and every product is the sum of the six partial products down to
- * 2^-24 of it, in fp32 (measured error against 64 bits: 0.3 to 0.8 of that of the kernel without a workspace).
+ * bf16 values each, which hold all of their 24 bits, and every product is the sum in fp32 of six of the nine partial products; the
+ * others are at most 2^-24 of it (measured error against 64 bits: 0.01 to 0.95 of that of the kernel without a workspace).
+ * Queries whose sums are infinite or NaN that way, infinite and NaN operands among the reasons, are computed a second time without
+ * it and are what a call without a workspace gives.
  * Dense bf16 launches whose tiles are padded leave the padding out if that pays: q, k, v and the result are copied.
  *   compact_attn_layout_split: *workspace_bytes = what such a call needs, 0 where it has no use for one: at most 64 MiB for
  *   the partial sums of bf16 rows, and four tensors of the tokens in natural order for a dense launch on copies (at most 8 GiB); for

@@ -9,8 +9,9 @@
 // the bfloat16 artificial intelligence datatype for higher-precision computations, ARITH 2019.)  Left out of a product are
 // a2 b3, a3 b2 and a3 b3, at most 2^-24 of it and of either sign; with parts cut off instead of rounded it would be 2^-21,
 // always to the same side.
-// Infinities, NaN and values from 2^96 on are NaN in all three parts; queries whose sums are infinite or NaN are walked a
-// second time, on the f32 matrix instructions.
+// What is split is multiplied by 2^24 first, so that the parts of small values, subnormals included, hold all of their bits too.
+// Infinities, NaN and values from 2^96 on are NaN in all three parts; queries whose sums are infinite or NaN, which
+// they also become by V above about 2^60 and products of q and k above 2^79, are walked a second time, on the f32 matrix instructions.
 //
 // K and V are split once per call by a kernel of their own, into a workspace, as "units" of 16 tokens in
 // the order in which the matrix instructions read them; the slots of a padded tile are taken token-holding slots
@@ -39,7 +40,10 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-constexpr float kTop = 0x1p96f;  // operands from here on go the second way
+constexpr float kTop = 0x1p96f;             // operands from here on go the second way
+constexpr float kLift = 0x1p24f;            // what is split is multiplied by this: third parts of the smallest values are no subnormals
+constexpr float kDropScores = 0x1p-48f;     // and what comes of it by one of these
+constexpr float kDropResult = 0x1p-24f;
 
 template <int D>
 struct UnitShape {
@@ -52,12 +56,12 @@ struct UnitShape {
 };
 
 // Parts of two values, packed for the matrix instructions: word i holds part i + 1 of `even` below that of `odd`.
-// kAnyValue: operands; else weights, which are 0 to 2^kLazyLog2, or NaN.
+// kAnyValue: operands; else weights, which are 0 to 2^kLazyLog2, or NaN, and already multiplied by kLift.
 template <bool kAnyValue>
 __device__ __forceinline__ void split_pair(float even, float odd, uint32_t (&word)[3]) {
   if constexpr (kAnyValue) {
-    even = fabsf(even) < kTop ? even : __builtin_nanf("");
-    odd = fabsf(odd) < kTop ? odd : __builtin_nanf("");
+    even = fabsf(even) < kTop ? even * kLift : __builtin_nanf("");
+    odd = fabsf(odd) < kTop ? odd * kLift : __builtin_nanf("");
   }
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
@@ -254,7 +258,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
   for (int db = 0; db < U::kDBlocks; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_o[db][r] = 0.f;
-  const float c2 = a.scale * kLog2e;
+  const float c2 = a.scale * kLog2e * kDropScores;
   float ref = -1e30f, l_run = 0.f;  // exponent reference of the query in log2 units; this lane's share of its row sum
 
   // ---- the walk ----------------------------------------------------------------------------------------
@@ -378,7 +382,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
         float sum[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[8 * t + 2 * i], c2, -ref)), p1 = __builtin_amdgcn_exp2f(fmaf(sc[8 * t + 2 * i + 1], c2, -ref));
+          const float p0 = kLift * __builtin_amdgcn_exp2f(fmaf(sc[8 * t + 2 * i], c2, -ref)), p1 = kLift * __builtin_amdgcn_exp2f(fmaf(sc[8 * t + 2 * i + 1], c2, -ref));
           sum[i] = p0 + p1;
           uint32_t word[3];
           split_pair<false>(p0, p1, word);
@@ -459,8 +463,8 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
     }
   };
   const bool real = q_pos < q_valid;  // a padding row is zero whatever its sums are
-  auto store = [&](float l) {
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
+  auto store = [&](float l, float drop) {
+    const float inv = l > 0.f ? 1.0f / l * drop : 0.f;
 #pragma unroll
     for (int i = 0; i < U::kDBlocks * 4; ++i) {  // channels 32 db + 8 r4 + 4 g .. + 3
       f32x4 o;
@@ -481,7 +485,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
     again = real && count > 0 && !(sum_with_partner(z) == 0.f && l > 0.f);
     const bool any = __any(again);
     if (lane == 0) lds_again[qw] = any;
-    if (q_in) store(l);
+    if (q_in) store(l, kDropResult);
   }
   __syncthreads();
   bool once_more = false;
@@ -499,6 +503,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
     const char* const plane_k = static_cast<const char*>(a.k) + plane_tiles * a.B * (int64_t)(D * 4);
     const char* const plane_v = static_cast<const char*>(a.v) + plane_tiles * a.B * (int64_t)(D * 4);
     const float* const q_row = reinterpret_cast<const float*>(static_cast<const char*>(a.q) + tile_at + (int64_t)q_slot * (D * 4)) + g * (D / 2);
+    const float c2_plain = a.scale * kLog2e;
     ref = -1e30f;
     l_run = 0.f;
 #pragma unroll
@@ -528,7 +533,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
           sc[r] = r / 4 * 8 + 4 * g + r % 4 < keys ? sc[r] : kMinusInf;
           mx = fmaxf(mx, sc[r]);
         }
-        const float ref_new = fmaxf(ref, max_with_partner(mx) * c2), alpha = __builtin_amdgcn_exp2f(ref - ref_new);
+        const float ref_new = fmaxf(ref, max_with_partner(mx) * c2_plain), alpha = __builtin_amdgcn_exp2f(ref - ref_new);
         if (__any(ref_new > ref)) {
           l_run *= alpha;
 #pragma unroll
@@ -540,7 +545,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = r / 4 * 8 + 4 * g + r % 4;
-          const float p = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -ref));
+          const float p = __builtin_amdgcn_exp2f(fmaf(sc[r], c2_plain, -ref));
           l_run += p;
           const float* const v_row = reinterpret_cast<const float*>(plane_v + tile_bytes + (int64_t)perm[first + min(key, keys - 1)] * (D * 4)) + qi;
 #pragma unroll
@@ -552,7 +557,7 @@ void attn_f32_planes_kernel(AttnArgs a, const char* units, int tile_units, int p
     merge();
     if (kw > 0) return;
     const float l = sum_with_partner(l_run);
-    if (again) store(l);
+    if (again) store(l, 1.f);
   }
 }
 

@@ -1717,7 +1717,8 @@ def _without_workspace(q, k, v, lay, call="forward"):
 
 
 @pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,copies", _PLANE_LAUNCHES)
-@pytest.mark.parametrize("what", ["huge values", "infinite value of a small weight", "infinite query of small keys"])
+@pytest.mark.parametrize("what", ["huge values", "infinite value of a small weight", "infinite query of small keys", "values near the smallest",
+                                  "weights near the smallest", "large values"])
 def test_fp32_in_three_planes_at_the_ends_of_the_range(kernel, D, grid, tile, text_tiles, copies, what):
     """Values that fp32 products take and three bf16 parts or a lagging exponent reference do not: as the fp32 matrix instructions give them."""
     _say("ends of the range", kernel, D, grid, tile, what)
@@ -1737,19 +1738,30 @@ def test_fp32_in_three_planes_at_the_ends_of_the_range(kernel, D, grid, tile, te
         q[..., 0], k[..., 0] = 1.0, 0.0
         k[:, :, tokens // 2, 0] = -70.0 * D ** 0.5
         v[:, :, tokens // 2, 3] = float("inf")
-    else:
+    elif what == "infinite query of small keys":
         q[:, :, ::3, 4] = float("-inf")
         k[..., 4] = 2.0 ** -100
+    elif what == "values near the smallest":
+        # all rows of a head and channel alike: whatever their parts lose, the sums lose too
+        v = ((1 + torch.rand(v.shape[0], v.shape[1], 1, D, device=DEV)) * 2.0 ** -122).expand(v.shape).contiguous()
+    elif what == "large values":
+        v = v.abs().clamp(0.1, 1.0) * 2.0 ** 95
+    else:
+        # one key has values, and e^-86 of the largest weight, 2^-124
+        q, k, v = torch.zeros_like(q), torch.zeros_like(k), torch.zeros_like(v)
+        q[..., 0] = 1.0
+        k[:, :, tokens // 2, 0] = -86.0 * D ** 0.5
+        v[:, :, tokens // 2] = 1e10 * (1 + torch.rand(v.shape[0], v.shape[1], D, device=DEV))
     q, k, v = (ca.compact_attn_permute(x, lay) for x in (q, k, v))
     want, got = (ca.compact_attn_permute(x, lay, inverse=True) for x in (_without_workspace(q, k, v, lay), ca.compact_attn_forward(q, k, v, lay)))
     if what == "huge values":
         assert torch.isfinite(want).all() and want.max() > 1e37 / tokens
     else:
-        assert torch.isinf(want).any() == (what == "infinite value of a small weight") and not torch.isnan(want).any()
+        assert torch.isinf(want).any() == (what == "infinite value of a small weight") and not torch.isnan(want).any(), what
     assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
     finite = torch.isfinite(want)
-    scale = want[finite].abs().max()
-    assert (got[finite] / scale - want[finite] / scale).abs().max() <= 1e-5
+    got, want = got[finite].double(), want[finite].double()
+    assert want.abs().max() > 0 and (got - want).abs().max() <= 1e-5 * want.abs().max()
 
 
 @pytest.mark.parametrize("kernel,D,grid,tile,text_tiles,copies", _PLANE_LAUNCHES)
