@@ -364,7 +364,7 @@ def _make_calls(layout):
         _calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
             lib.compact_attn_permute, lib.compact_attn_forward, lib.compact_attn_forward_natural, lib.compact_attn_dense,
             lib.compact_attn_forward_static, lib.compact_attn_forward_with_workspace, lib.compact_attn_tile_mass)),
-            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch._C._cuda_isCurrentStreamCapturing)
+            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch._C._cuda_isCurrentStreamCapturing, _check)
         _calls_bound = True
     p = layout.problem
     layout._calls = _calls.calls(layout.handle.value, p.batch, p.num_heads, layout.n_tokens_real, layout.n_tokens_padded, p.head_dim,

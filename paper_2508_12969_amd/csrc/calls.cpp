@@ -1,7 +1,8 @@
 // The calls of binding.py that a program makes at every layer, for the usual arguments, as a CPython extension: tensors of
 // torch's own class, contiguous, of the layout's type and shape, on the current device, the result allocated here, the current
-// stream.  Anything else, a failing call included, returns None, and binding.py goes through it step by step and reports what is
-// wrong; so this file checks, but explains nothing.
+// stream.  Anything else returns None before the library is called, and binding.py goes through it step by step and reports what is
+// wrong; so this file checks, but explains nothing.  Once the library has been called, the outcome stands: a status other
+// than zero becomes binding.py's exception here, because a second call could succeed where the first one's error is consumed, or enqueue work twice.
 //
 // What it is for: small calls are bound by the host.  A call of binding.py through ctypes takes about 6 us, of which the launch is 2;
 // one from here 4 (a step of 256 tokens, four permutations and an attention call, 29.3 / 22.6 us).
@@ -24,6 +25,7 @@ struct Library {
   WithWorkspace with_workspace;
   Mass mass;
   PyObject *device, *stream, *capturing;  // torch._C: current device, handle of its current stream, is that stream being captured
+  PyObject* check;                        // of binding.py: raises for a status other than zero
 } lib;
 
 struct Calls {
@@ -58,30 +60,41 @@ const at::Tensor* usual(const Calls* c, PyObject* arg, bool padded, int64_t devi
 
 bool modes() { return at::impl::torch_function_mode_enabled() || c10::impl::dispatch_mode_enabled(); }
 
+// The outcome of a call; None where it has not come to `made`.
 template <class Call>
 PyObject* guarded(Call&& call) {
   PyObject* result = nullptr;
+  bool made = false;
   try {
-    result = call();
+    result = call(made);
+  } catch (const std::exception& e) {
+    if (made) PyErr_SetString(PyExc_RuntimeError, e.what());
   } catch (...) {
+    if (made) PyErr_SetString(PyExc_RuntimeError, "unknown exception");
   }
-  if (result) return result;
+  if (result || made) return result;
   PyErr_Clear();
   Py_RETURN_NONE;
 }
 
+// Makes the call; false with a Python error set if it fails.
 template <class Launch>
-bool launched(Launch&& launch) {
+bool launched(bool& made, Launch&& launch) {
   int status = -1;
+  made = true;
   Py_BEGIN_ALLOW_THREADS  // as ctypes does
   status = launch();
   Py_END_ALLOW_THREADS
-  return status == 0;
+  if (status == 0) return true;
+  PyObject* raised = PyObject_CallFunction(lib.check, "i", status);
+  if (raised) PyErr_Format(PyExc_RuntimeError, "compact_attn status %d", status);
+  Py_XDECREF(raised);
+  return false;
 }
 
 // permute(src, inverse)
 PyObject* calls_permute(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-  return guarded([&]() -> PyObject* {
+  return guarded([&](bool& made) -> PyObject* {
     const Calls* c = reinterpret_cast<Calls*>(self);
     int64_t device;
     void* stream;
@@ -92,14 +105,14 @@ PyObject* calls_permute(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     at::Tensor out = at::empty({c->batch, c->heads, c->tokens[!inverse], c->head_dim}, src->options());
     const void* from = src->const_data_ptr();
     void* to = out.mutable_data_ptr();
-    if (!launched([&] { return lib.permute(from, to, c->layout, inverse, stream); })) return nullptr;
+    if (!launched(made, [&] { return lib.permute(from, to, c->layout, inverse, stream); })) return nullptr;
     return THPVariable_Wrap(std::move(out));
   });
 }
 
 // attention(call, q, k, v, workspace bytes): call 0 to 3 as in Library
 PyObject* calls_attention(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-  return guarded([&]() -> PyObject* {
+  return guarded([&](bool& made) -> PyObject* {
     const Calls* c = reinterpret_cast<Calls*>(self);
     int64_t device;
     void* stream;
@@ -119,7 +132,7 @@ PyObject* calls_attention(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     if (need > 0) workspace = at::empty({(int64_t)(need / (long long)q->element_size())}, q->options());
     const void *qp = q->const_data_ptr(), *kp = k->const_data_ptr(), *vp = v->const_data_ptr();
     void *op = out.mutable_data_ptr(), *wp = need > 0 ? workspace.mutable_data_ptr() : nullptr;
-    if (!launched([&] {
+    if (!launched(made, [&] {
           return need > 0 ? lib.with_workspace(qp, kp, vp, c->layout, op, (int32_t)call, wp, need, stream) : lib.attention[call](qp, kp, vp, c->layout, op, stream);
         }))
       return nullptr;
@@ -129,7 +142,7 @@ PyObject* calls_attention(PyObject* self, PyObject* const* args, Py_ssize_t n) {
 
 // mass(q, k)
 PyObject* calls_mass(PyObject* self, PyObject* const* args, Py_ssize_t n) {
-  return guarded([&]() -> PyObject* {
+  return guarded([&](bool& made) -> PyObject* {
     const Calls* c = reinterpret_cast<Calls*>(self);
     int64_t device;
     void* stream;
@@ -139,7 +152,7 @@ PyObject* calls_mass(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     at::Tensor out = at::empty({c->batch, c->heads, c->tiles, c->tiles}, q->options().dtype(at::kFloat));
     const void *qp = q->const_data_ptr(), *kp = k->const_data_ptr();
     float* op = static_cast<float*>(out.mutable_data_ptr());
-    if (!launched([&] { return lib.mass(qp, kp, c->layout, op, stream); })) return nullptr;
+    if (!launched(made, [&] { return lib.mass(qp, kp, c->layout, op, stream); })) return nullptr;
     return THPVariable_Wrap(std::move(out));
   });
 }
@@ -171,11 +184,11 @@ PyObject* make_calls(PyObject*, PyObject* args) {
   return reinterpret_cast<PyObject*>(c);
 }
 
-// bind(addresses of permute, forward, natural, dense, static, with_workspace, mass; torch's device, stream and capture functions)
+// bind(addresses of permute, forward, natural, dense, static, with_workspace, mass; torch's device, stream and capture functions; check)
 PyObject* bind(PyObject*, PyObject* args) {
   unsigned long long f[7];
-  PyObject *device, *stream, *capturing;
-  if (!PyArg_ParseTuple(args, "KKKKKKKOOO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &device, &stream, &capturing)) return nullptr;
+  PyObject *device, *stream, *capturing, *check;
+  if (!PyArg_ParseTuple(args, "KKKKKKKOOOO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &device, &stream, &capturing, &check)) return nullptr;
   lib.permute = reinterpret_cast<Permute>(f[0]);
   for (int i = 0; i < 4; ++i) lib.attention[i] = reinterpret_cast<Attention>(f[1 + i]);
   lib.with_workspace = reinterpret_cast<WithWorkspace>(f[5]);
@@ -183,9 +196,11 @@ PyObject* bind(PyObject*, PyObject* args) {
   Py_INCREF(device);
   Py_INCREF(stream);
   Py_INCREF(capturing);
+  Py_INCREF(check);
   lib.device = device;
   lib.stream = stream;
   lib.capturing = capturing;
+  lib.check = check;
   Py_RETURN_NONE;
 }
 

@@ -1887,3 +1887,31 @@ def test_calls_with_other_than_the_usual_arguments():
     lay.free()
     with pytest.raises(ca.CompactAttnError):
         ca.compact_attn_forward(*x, lay)
+
+
+def test_a_call_that_the_library_fails_is_made_once():
+    """The status of the first call is what the program sees: another call could succeed, or enqueue work a second time.  Functions that
+    report an error in the place of the library's."""
+    import ctypes
+    from paper_2508_12969_amd import _calls, binding
+    wl = make_workload("once", 3, 9, 17, (1, 8, 8), 64, 2, 64, "bf16", [[(1, (1, 1), ABSENT)]] * 2)
+    lay = build_layout(ca, wl)
+    q, k, v = make_qkv(wl, DEV)
+    x = [ca.compact_attn_permute(t, lay) for t in (q, k, v)]
+    made = []
+    vp, i32 = ctypes.c_void_p, ctypes.c_int32
+    forms = ([vp, vp, vp, i32, vp], *[[vp] * 6] * 4, [vp, vp, vp, vp, vp, i32, vp, ctypes.c_int64, vp], [vp] * 5)
+    stubs = [ctypes.CFUNCTYPE(ctypes.c_int, *form)(lambda *a, n=n: made.append(n) or ca.binding.CA_ERR_HIP) for n, form in enumerate(forms)]
+    try:
+        _calls.bind(*(ctypes.cast(f, vp).value for f in stubs), torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
+                    torch._C._cuda_isCurrentStreamCapturing, binding._check)
+        for call in (lambda: ca.compact_attn_permute(q, lay), lambda: ca.compact_attn_forward(*x, lay), lambda: ca.compact_attn_forward_natural(q, k, v, lay),
+                     lambda: ca.compact_attn_dense(*x, lay), lambda: ca.compact_attn_forward_static(*x, lay), lambda: ca.compact_attn_tile_mass(*x[:2], lay)):
+            made.clear()
+            with pytest.raises(ca.CompactAttnError) as e:
+                call()
+            assert e.value.status == ca.binding.CA_ERR_HIP and len(made) == 1
+    finally:
+        binding._calls_bound = False
+        binding._make_calls(lay)
+    assert torch.equal(ca.compact_attn_permute(ca.compact_attn_permute(q, lay), lay, inverse=True), q)
