@@ -165,9 +165,35 @@ class Layout:
         # tensor shapes, natural and padded: every call compares them
         self._shapes = tuple((problem.batch, problem.num_heads, tokens, problem.head_dim) for tokens in (n_real.value, n_pad.value))
         self._is_bf16 = problem.dtype == CA_BF16
-        # bytes a call lends the library: the sparse walk, the dense one
-        self._workspace = [_layout_split(handle, dense)[0] for dense in (0, 1)]
+        # bytes a call lends the library, and the kernel that gets them: the sparse walk, the dense one.  None: not for some calls, see _short_of_memory
+        self._splits = [_layout_split(handle, dense) for dense in (0, 1)]
+        self._workspace = [nbytes for nbytes, _ in self._splits]
+        self._wait = [0, 0]      # calls to be made without after a shortage
+        self._without = [0, 0]   # of these, still to be made
         self._calls = None
+
+    def _short_of_memory(self, dense):
+        """No memory for a workspace.  torch has emptied its cache before it gave up, which not every later call shall pay for again.  Rows
+        split along the keys stay whole from then on.  Copies and planes, which take as much as the call's own tensors and give much more, are
+        tried again after one call without, then after 3, 7, ... 63."""
+        nbytes, kernel = self._splits[dense]
+        if not kernel.startswith(("closed-", "f32-planes-")):
+            self._workspace[dense] = 0
+            return
+        if not self._wait[dense]:
+            import warnings
+            warnings.warn(f"no memory for a workspace of {nbytes} bytes: compact_attn calls run without it, slower and with other rounding, until there is",
+                          RuntimeWarning, stacklevel=4)
+        self._wait[dense] = min(2 * self._wait[dense] + 1, 63)
+        self._without[dense] = self._wait[dense]
+        self._workspace[dense] = None
+
+    def _need_after_shortage(self, dense):
+        self._without[dense] -= 1
+        if self._without[dense] >= 0:
+            return 0
+        self._workspace[dense] = self._splits[dense][0]
+        return self._workspace[dense]
 
     def free(self):
         self._calls = None
@@ -388,19 +414,17 @@ def compact_attn_permute(src, layout, inverse=False, out=None, stream=None):
     return out
 
 
-def _lend(q, need, layout, call, stream):
+def _lend(q, need, stream):
     """`need` bytes for a call on `stream`, from that stream's memory (what is free there has no work pending on another), or
-    None where there is no such memory to lend; the call then leaves its rows whole, as the C call without a workspace does."""
+    None where that is not ours to lend, NotImplemented where there is none; the call then is that without a workspace."""
     import torch
     if stream is not None:
         with torch.cuda.stream(_torch_stream(stream, q.device)):
-            return _lend(q, need, layout, call, None)
+            return _lend(q, need, None)
     try:
         workspace = q.new_empty(need // q.element_size())
     except torch.cuda.OutOfMemoryError:
-        # torch has emptied its cache before it gave up, which no later call shall pay for again
-        layout._workspace[call == CA_CALL_DENSE] = 0
-        return None
+        return NotImplemented
     if torch.cuda.is_current_stream_capturing() and not _in_graph_pool(workspace):
         return None
     return workspace
@@ -417,8 +441,15 @@ def _in_graph_pool(t):
 
 def _attention(fn, call, q, k, v, layout, out, stream, padded=True):
     need = 0 if call == CA_CALL_STATIC else layout._workspace[call == CA_CALL_DENSE]
+    if need is None:
+        need = layout._need_after_shortage(call == CA_CALL_DENSE)
     if out is None and stream is None and layout.handle is not None:
-        done = (layout._calls or _make_calls(layout)).attention(call, q, k, v, need)
+        calls = layout._calls or _make_calls(layout)
+        done = calls.attention(call, q, k, v, need)
+        if done is NotImplemented:
+            layout._short_of_memory(call == CA_CALL_DENSE)
+            need = 0
+            done = calls.attention(call, q, k, v, 0)
         if done is not None:
             return done
     fn = getattr(load_library(), fn)
@@ -428,8 +459,10 @@ def _attention(fn, call, q, k, v, layout, out, stream, padded=True):
         out = q.new_empty(q.shape)
     else:
         _check_tensor(out, layout, padded, "out")
-    workspace = _lend(q, need, layout, call, stream) if need else None
-    if workspace is not None:
+    workspace = _lend(q, need, stream) if need else None
+    if workspace is NotImplemented:
+        layout._short_of_memory(call == CA_CALL_DENSE)
+    elif workspace is not None:
         _check(load_library().compact_attn_forward_with_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), layout.handle, out.data_ptr(), call,
                                                                   workspace.data_ptr(), need, _stream_ptr(stream)))
         return out

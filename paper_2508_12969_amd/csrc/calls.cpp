@@ -110,7 +110,7 @@ PyObject* calls_permute(PyObject* self, PyObject* const* args, Py_ssize_t n) {
   });
 }
 
-// attention(call, q, k, v, workspace bytes): call 0 to 3 as in Library
+// attention(call, q, k, v, workspace bytes): call 0 to 3 as in Library; NotImplemented if there is no memory for the workspace
 PyObject* calls_attention(PyObject* self, PyObject* const* args, Py_ssize_t n) {
   return guarded([&](bool& made) -> PyObject* {
     const Calls* c = reinterpret_cast<Calls*>(self);
@@ -129,7 +129,13 @@ PyObject* calls_attention(PyObject* self, PyObject* const* args, Py_ssize_t n) {
       if (!plain) return nullptr;
     }
     at::Tensor out = at::empty(q->sizes(), q->options()), workspace;
-    if (need > 0) workspace = at::empty({(int64_t)(need / (long long)q->element_size())}, q->options());
+    if (need > 0) {
+      try {
+        workspace = at::empty({(int64_t)(need / (long long)q->element_size())}, q->options());
+      } catch (const c10::OutOfMemoryError&) {
+        Py_RETURN_NOTIMPLEMENTED;
+      }
+    }
     const void *qp = q->const_data_ptr(), *kp = k->const_data_ptr(), *vp = v->const_data_ptr();
     void *op = out.mutable_data_ptr(), *wp = need > 0 ? workspace.mutable_data_ptr() : nullptr;
     if (!launched(made, [&] {

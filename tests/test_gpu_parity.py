@@ -1915,3 +1915,50 @@ def test_a_call_that_the_library_fails_is_made_once():
         binding._calls_bound = False
         binding._make_calls(lay)
     assert torch.equal(ca.compact_attn_permute(ca.compact_attn_permute(q, lay), lay, inverse=True), q)
+
+
+@pytest.mark.parametrize("call", ["planes", "closed"])
+@pytest.mark.parametrize("given_out", [False, True])
+def test_a_passing_shortage_of_memory_for_planes_and_copies(call, given_out):
+    """Calls that find no memory for their workspace run without one, say so once, ask for it once each time that they do, and
+    have it again when there is memory."""
+    import warnings
+    dtype = "f32" if call == "planes" else "bf16"
+    wl = make_workload("short", 9, 30, 25, (1, 8, 8), 0, 4, 128, dtype, [_GLOBAL] * 4)
+    lay = build_layout(ca, wl)
+    fn = ca.compact_attn_forward if call == "planes" else ca.compact_attn_dense
+    need, kernel = ca.compact_attn_layout_split(lay, dense=call == "closed")
+    assert kernel.startswith("f32-planes-" if call == "planes" else "closed-")
+    x = [ca.compact_attn_permute(t, lay) for t in make_qkv(wl, DEV)]
+    want, plain = fn(*x, lay), _without_workspace(*x, lay, call="forward" if call == "planes" else "dense")
+    assert not torch.equal(want, plain)
+    outs = [torch.empty_like(want) for _ in range(8)]
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hogs, asked = [], []
+    torch.cuda.set_per_process_memory_fraction(0.0)
+    try:
+        for size in (need, need // 2, need // 4):         # what is left of the segments in use
+            try:
+                while True:
+                    hogs.append(torch.empty(size, dtype=torch.uint8, device=DEV))
+            except torch.cuda.OutOfMemoryError:
+                pass
+        with warnings.catch_warnings(record=True) as said:
+            warnings.simplefilter("always")
+            for i in range(8):
+                out = outs[i] if given_out else None
+                if not given_out:
+                    outs[i] = None                       # room for a result, not for the workspace
+                before = torch.cuda.memory_stats()["num_ooms"]
+                outs[i] = fn(*x, lay, out=out)
+                asked.append(torch.cuda.memory_stats()["num_ooms"] - before)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    torch.cuda.synchronize()
+    assert asked == [1, 0, 1, 0, 0, 0, 1, 0]              # one call without, then three, seven
+    assert len(said) == 1 and "no memory for a workspace" in str(said[0].message) and said[0].filename == __file__
+    assert all(torch.equal(o, plain) for o in outs)
+    del hogs
+    later = [fn(*x, lay) for _ in range(7)]               # six of the seven are left
+    assert all(torch.equal(o, plain) for o in later[:6]) and torch.equal(later[6], want)
