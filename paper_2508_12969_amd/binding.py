@@ -4,7 +4,7 @@ at every layer go through the extension _calls where their arguments are the usu
 Every function has the name of the C entry point it calls (see
 include/compact_attn.h).  Tensors are torch tensors used purely as device
 buffers; their data pointers and the current torch stream are handed to the
-library.  There is no fallback: if the shared library is missing or a call
+library.  There is no fallback for the library: if it is missing or a call
 fails, an exception is raised.
 """
 import ctypes
@@ -380,11 +380,33 @@ def _check_tensor(t, layout, padded, name):
 _calls_bound = False
 
 
+class _NoCalls:
+    """In the place of the extension's calls where it was not built for this Python and torch: every call goes the general way."""
+
+    def permute(self, src, inverse):
+        return None
+
+    def attention(self, call, q, k, v, need):
+        return None
+
+    def mass(self, q, k):
+        return None
+
+
 def _make_calls(layout):
-    """The extension's calls on a layout.  The extension is built with the library and looked for beside it; there is no fallback."""
+    """The extension's calls on a layout.  The extension is built with the library and looked for beside it; it saves host time, the kernels are
+    the library's with or without it."""
     global _calls_bound
     import torch
-    from . import _calls
+    try:
+        from . import _calls
+        if _calls.torch_version != torch.__version__:
+            raise ImportError(f"built for torch {_calls.torch_version}, this is {torch.__version__}")
+    except (ImportError, AttributeError) as e:
+        import warnings
+        warnings.warn(f"compact_attn calls take the longer way through ctypes: {e} (build with `python -m paper_2508_12969_amd.build`)", RuntimeWarning)
+        layout._calls = _NoCalls()
+        return layout._calls
     if not _calls_bound:
         lib = load_library()
         _calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (

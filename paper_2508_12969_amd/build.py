@@ -2,6 +2,7 @@
 import os
 import shutil
 import subprocess
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
@@ -10,7 +11,7 @@ LIB_PATH = os.path.join(PKG_DIR, "libcompact_attn.so")
 SOURCES = ["layout.cpp", "search.cpp", "api.cpp", "permute.hip", "attn_f32.hip", "attn_f32_planes.hip", "attn_bf16.hip", "attn_bf16_pair.hip", "attn_bf16_ways.hip",
            "attn_bf16_merge.hip",
            "tile_mass.hip"]
-CALLS_PATH = os.path.join(PKG_DIR, "_calls.so")
+CALLS_PATH = os.path.join(PKG_DIR, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))   # of this Python
 PER_FILE_FLAGS = {}   # extra hipcc flags for single sources, if any
 ARCH = "gfx950"
 
@@ -57,14 +58,12 @@ def build(verbose=False, extra_flags=(), out=None):
 
 
 def build_calls(run):
-    """The CPython extension of csrc/calls.cpp, against the installed torch."""
-    import sysconfig
-
+    """The CPython extension of csrc/calls.cpp, for this Python and the installed torch.  It works with any build of the library."""
     import torch
     from torch.utils import cpp_extension
 
     lib = cpp_extension.TORCH_LIB_PATH
-    run([shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    run([shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DCALLS_TORCH="{torch.__version__}"',
          *(x for path in (*cpp_extension.include_paths(), sysconfig.get_paths()["include"]) for x in ("-isystem", path)),
          os.path.join(CSRC, "calls.cpp"), "-o", CALLS_PATH, "-L", lib, f"-Wl,-rpath,{lib}", "-lc10", "-ltorch_cpu", "-ltorch_python"])
 

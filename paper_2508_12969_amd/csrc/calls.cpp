@@ -221,5 +221,7 @@ PyMODINIT_FUNC PyInit__calls() {
   calls_type.tp_flags = Py_TPFLAGS_DEFAULT;
   calls_type.tp_methods = calls_methods;
   if (PyType_Ready(&calls_type) < 0) return nullptr;
-  return PyModule_Create(&module);
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "torch_version", CALLS_TORCH) < 0) Py_CLEAR(m);
+  return m;
 }

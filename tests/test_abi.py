@@ -564,3 +564,27 @@ def test_dense_calls_that_leave_out_the_padding():
     assert split(128, (2, 8, 8), (5, 13, 21), 40)[0] == (0, None)                        # 1365 tokens
     assert split(128, (2, 8, 8), (65, 60, 100), 20)[0][1] == "closed-one-tile"           # 7.4 GiB
     assert split(128, (2, 8, 8), (65, 60, 100), 22)[0] == (0, None)                      # 8.2 GiB
+
+
+@pytest.mark.parametrize("wrong", ["missing", "other torch"])
+def test_calls_without_an_extension_for_this_python_and_torch(monkeypatch, wrong):
+    """The library alone serves every call, as it does without the extension; the program is told that calls take longer."""
+    import sys
+    import types
+
+    import torch
+    import paper_2508_12969_amd
+    other = types.ModuleType("_calls")
+    other.torch_version = "0.1"
+    monkeypatch.setitem(sys.modules, "paper_2508_12969_amd._calls", None if wrong == "missing" else other)
+    monkeypatch.delattr(paper_2508_12969_amd, "_calls", raising=False)
+    if wrong != "missing":
+        monkeypatch.setattr(paper_2508_12969_amd, "_calls", other, raising=False)
+    lay = ca.compact_attn_build_layout(2, 8, 8, (1, 8, 8), 0, 1, 1, 64, "bf16", [[]])
+    x = torch.zeros(1, 1, 128, 64, dtype=torch.bfloat16)
+    with pytest.warns(RuntimeWarning, match="longer way"):
+        with pytest.raises(ValueError, match="device tensor"):     # this machine has none; the check is the binding's own
+            ca.compact_attn_permute(x, lay)
+    for call in (lambda: ca.compact_attn_forward(x, x, x, lay), lambda: ca.compact_attn_tile_mass(x, x, lay)):
+        with pytest.raises(ValueError, match="device tensor"):
+            call()
