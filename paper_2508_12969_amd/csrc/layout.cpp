@@ -666,7 +666,7 @@ std::pair<double, double> granules_per_tile(const ca_layout& L, bool dense, int6
 // three rounds of workgroups.
 Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* plan, double* predicted_us) {
   if (plan) *plan = SplitPlan{};
-  if (predicted_us) *predicted_us = 0;
+  if (predicted_us) *predicted_us = HUGE_VAL;  // not priced
   const ca_problem& p = L.prob;
   if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
   // 32-bit lane offsets inside a tile of the natural order; a grid dimension of fewer than 2^32 threads
@@ -859,7 +859,7 @@ void close_dense(ca_layout& L, double dense_us) {
   const ca_problem& p = L.prob;
   const bool padded = L.class_mask.size() > 1;
   if (p.dtype != CA_BF16 || (L.B != 64 && L.B != 128) || (p.head_dim != 64 && p.head_dim != 128) || (!padded && L.B == 128)) return;
-  if (L.N_real < kCloseTokens || L.N_real >= ((int64_t)1 << 31) - 128) return;
+  if (!std::isfinite(dense_us) || L.N_real < kCloseTokens || L.N_real >= ((int64_t)1 << 31) - 128) return;
   const bool in_place = !padded && L.N_pad % 128 == 0;
   const double bytes = (double)p.batch * p.num_heads * (double)L.N_real * p.head_dim * 2;
   const double copies = in_place ? 0 : kCloseLaunches + 8 * bytes * kCloseByte;
@@ -882,7 +882,7 @@ void close_dense(ca_layout& L, double dense_us) {
   if (!in_place && 4 * tensor_bytes(*c) > kMaxPlaneBytes) return;
   c->row_ptr.assign((size_t)p.num_heads * (size_t)c->n + 1, 0);
   finish_host_tables(*c);
-  if (c->closed_us + copies > kCloseGain * dense_us) return;
+  if (!(c->closed_us + copies <= kCloseGain * dense_us)) return;
   L.closed_in_place = in_place;
   L.closed = std::move(c);
 }
@@ -912,7 +912,7 @@ void finish_host_tables(ca_layout& L) {
   L.simd_waves = choose_simd_waves(L, false);
   L.simd_waves_dense = choose_simd_waves(L, true);
   L.ways = L.is_closed ? kWaysNone : choose_ways(L, false, kSampledWords, &L.split);
-  double dense_us = 0;
+  double dense_us = HUGE_VAL;
   L.ways_dense = choose_ways(L, true, kSampledWords, &L.split_dense, &dense_us);
   L.closed_us = dense_us;
   L.closed.reset();

@@ -191,7 +191,7 @@ struct ca_layout {
   // they are (closed_in_place: no tile is padded and 64-token tiles are taken two by two).  Only its dense tables are used.
   std::unique_ptr<ca_layout> closed;
   bool closed_in_place = false, is_closed = false;
-  double closed_us = 0;  // predicted time of dense calls
+  double closed_us = 0;  // predicted time of dense calls, infinite if they are not priced
   mutable std::atomic<uint32_t> launch_seq{0};  // picks the pool counter of a launch
 
   // device tables, created once

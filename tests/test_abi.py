@@ -588,3 +588,12 @@ def test_calls_without_an_extension_for_this_python_and_torch(monkeypatch, wrong
     for call in (lambda: ca.compact_attn_forward(x, x, x, lay), lambda: ca.compact_attn_tile_mass(x, x, lay)):
         with pytest.raises(ValueError, match="device tensor"):
             call()
+
+
+def test_dense_calls_that_are_not_priced_stay_as_they_are():
+    """Unpadded 64-token tiles are taken two by two where that is predicted to pay; launches of 4 million workgroups are not priced."""
+    def kernel(batch):
+        lay = ca.compact_attn_build_layout(64, 32, 64, (1, 8, 8), 0, batch, 1, 128, "bf16", [[]])
+        return ca.compact_attn_layout_kernel(lay, dense=True)
+    assert kernel(16) == "one-tile"
+    assert kernel(4096) == "paired"   # 8 million rows of 64 tokens, 4 million of 128
