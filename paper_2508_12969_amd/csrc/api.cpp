@@ -151,21 +151,15 @@ int ensure_uploaded(ca_layout* L, hipStream_t stream) {
     if (!t.tile_origin.empty()) tables.push_back(table(t.tile_origin, &d.tile_origin));
     if (L->split.shares) tables.push_back(table(L->split.items, &d.split_items)), tables.push_back(table(L->split.merges, &d.split_merges));
     if (L->split_dense.shares) tables.push_back(table(L->split_dense.items, &d.split_items_dense)), tables.push_back(table(L->split_dense.merges, &d.split_merges_dense));
-    // what a dense walk of the closed layout reads
+    // what a dense walk of the closed layout reads (its tiles are never paired or packed: they hold 128 tokens, and its sparse walk is empty)
     ca::PackedTables tc;
     ca::DeviceTables dc;
     if (ca_layout* c = L->closed.get()) {
       st = ca::pack_device_tables(*c, false, tc);
-      dc.num_pairs = (int64_t)c->pair_rows.size() / 2;
-      dc.num_launch_rows = c->packed_faces ? (int64_t)c->launch_rows.size() : 0;
       dc.pool_slots = ca::kPoolSlots;
       for (const Table& x : {table(tc.dense_meta, &dc.dense_meta), table(c->tile_class, &dc.tile_class), table(c->class_mask, &dc.class_mask),
                              table(tc.class_perm, &dc.class_perm), table(pool_counters, &dc.pool_counters)})
         tables.push_back(x);
-      if (dc.num_pairs)
-        for (const Table& x : {table(c->pair_rows, &dc.pair_rows), table(c->pair_desc, &dc.pair_desc), table(tc.dense_pair_walk, &dc.dense_pair_walk)})
-          tables.push_back(x);
-      if (c->packed_faces) tables.push_back(table(c->launch_rows, &dc.launch_rows));
       if (c->split_dense.shares) tables.push_back(table(c->split_dense.items, &dc.split_items_dense)), tables.push_back(table(c->split_dense.merges, &dc.split_merges_dense));
     }
     if (st == CA_OK) st = upload_tables(tables, &d.block);
@@ -502,7 +496,7 @@ int build_static_image(ca_layout* L) {
 const char* kernel_name(const ca_layout* L, ca::Ways ways, bool dense, bool on_copies = false) {
   if (on_copies) {  // 128-token tiles
     if (ways != ca::kWaysNone) return ways == ca::kWays4x4 ? "closed-ways-4x4" : ways == ca::kWays8x4 ? "closed-ways-8x4" : "closed-ways-8x2";
-    return L->packed_faces ? "closed-packed-faces" : "closed-one-tile";
+    return "closed-one-tile";
   }
   if (ways != ca::kWaysNone) return ways == ca::kWays4x4 ? "ways-4x4" : ways == ca::kWays8x4 ? "ways-8x4" : "ways-8x2";
   if (L->prob.dtype != CA_BF16) return "f32";
