@@ -815,7 +815,7 @@ int compact_attn_forward_with_workspace(const void* q, const void* k, const void
   const bool dense = call == CA_CALL_DENSE, natural = call == CA_CALL_NATURAL;
   if (L) {
     const ca_problem& p = L->prob;
-    const int64_t need = ca::call_workspace_bytes(*L, dense);
+    const int64_t need = natural && p.dtype != CA_BF16 ? 0 : ca::call_workspace_bytes(*L, dense);  // (refused below)
     if (need == 0) {
       workspace = nullptr;
     } else {

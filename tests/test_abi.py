@@ -597,3 +597,14 @@ def test_dense_calls_that_are_not_priced_stay_as_they_are():
         return ca.compact_attn_layout_kernel(lay, dense=True)
     assert kernel(16) == "one-tile"
     assert kernel(4096) == "paired"   # 8 million rows of 64 tokens, 4 million of 128
+
+
+def test_natural_order_fp32_is_refused_for_what_it_is():
+    """With or without a workspace: unsupported, also for layouts whose tile-order calls can make use of one."""
+    lay = ca.compact_attn_build_layout(8, 64, 64, (1, 8, 8), 0, 1, 8, 128, "f32", [[(99, (99, 99), (-1, -1))]] * 8)
+    assert ca.compact_attn_layout_split(lay)[0] > 0
+    lib, nbytes = ca.load_library(), 8 * lay.n_tokens_padded * 128 * 4
+    q, k, v, out = (ctypes.c_void_p((1 << 40) + i * nbytes) for i in range(4))   # refused before anything is read
+    assert lib.compact_attn_forward_natural(q, k, v, lay.handle, out, None) == binding.CA_ERR_UNSUPPORTED
+    assert lib.compact_attn_forward_with_workspace(q, k, v, lay.handle, out, 1, None, 0, None) == binding.CA_ERR_UNSUPPORTED
+    assert "bf16" in ca.compact_attn_last_error()
