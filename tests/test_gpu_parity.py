@@ -453,7 +453,8 @@ def test_imported_random_mask_and_union(shape):
 @pytest.mark.parametrize("tile,D,dtype", [((1, 4, 4), 32, "f32"), ((1, 8, 8), 64, "f32"), ((2, 8, 8), 64, "bf16")])
 @pytest.mark.parametrize("heads", [127, 128, 129, 255, 1023, 1024])
 def test_launches_of_few_rounds(heads, tile, D, dtype):
-    """Launches around 512 and 4096 rows, where the order of their workgroups changes: every row of every head."""
+    """Launches around 512 and 4096 rows, where the order of the fp32 kernels' workgroups changes: every row of every head.  The bf16 ones
+    run the one-tile kernel, whose order does not, all but those of 129 heads; ways-4x4 has a test of its own."""
     _say("few rounds", heads, tile, D, dtype)
     wl = make_workload("rounds", tile[0], 2 * tile[1], 2 * tile[2] - 1, tile, 0, heads, D, dtype, [[]] * heads)
     lay = build_layout(ca, wl)
@@ -462,6 +463,40 @@ def test_launches_of_few_rounds(heads, tile, D, dtype):
     s = q[0].double().cpu() @ k[0].double().cpu().transpose(1, 2) * D ** -0.5
     err = (out[0].double().cpu() - torch.softmax(s, dim=2) @ v[0].double().cpu()).abs().max().item()
     assert err <= (1e-4 if dtype == "f32" else 2e-2)      # the bounds of the other forward tests
+
+
+@pytest.mark.parametrize("rows,D,tile,grid,heads", [
+    (508, 128, (2, 8, 8), (7, 4, 4), 127),
+    (512, 128, (4, 4, 8), (4, 5, 9), 128),
+    (513, 64, (2, 8, 8), (6, 8, 1), 171),
+    (4095, 64, (2, 8, 8), (1, 4, 20), 1365),
+    (4096, 128, (4, 4, 8), (14, 1, 8), 1024),
+    (4100, 128, (4, 4, 8), (5, 5, 1), 1025),
+])
+def test_launches_of_few_rounds_of_the_four_wave_kernel(rows, D, tile, grid, heads):
+    """ways-4x4 on both sides of 512 and 4096 workgroups, sparse, where rows differ in length and are taken from the order table, and dense:
+    every row of every head."""
+    _say("few rounds of ways-4x4", rows, D, tile, grid, heads)
+    cycle = [_GLOBAL, [(0, (0, 1), ABSENT)], [(1, (1, 0), ABSENT)], _GLOBAL]
+    wl = make_workload("rounds", *grid, tile, 0, heads, D, "bf16", [cycle[h % 4] for h in range(heads)])
+    lay = build_layout(ca, wl)
+    assert lay.n_tiles * heads == rows
+    q, k, v = make_qkv(wl, DEV)
+    tile_of = torch.from_numpy(np.asarray(geometry_of(wl).token_tile_and_slot()[0]))
+    keep = torch.zeros(4, lay.n_tiles, lay.n_tiles, dtype=torch.bool)
+    for h in range(4):                                        # the table itself is compared with the oracle elsewhere
+        row_ptr, col_idx = ca.compact_attn_layout_csr(lay, h)
+        for r in range(lay.n_tiles):
+            keep[h, r, torch.from_numpy(np.asarray(col_idx[row_ptr[r]:row_ptr[r + 1]]).astype(np.int64))] = True
+    seen = keep[:, tile_of][:, :, tile_of].to(DEV)
+    s = (q[0].double() @ k[0].double().transpose(1, 2).contiguous()) * D ** -0.5
+    x = [ca.compact_attn_permute(t, lay) for t in (q, k, v)]
+    for dense in (False, True):
+        assert ca.compact_attn_layout_kernel(lay, dense=dense) == "ways-4x4" and ca.compact_attn_layout_split(lay, dense=dense) == (0, None)
+        out = ca.compact_attn_permute((ca.compact_attn_dense if dense else ca.compact_attn_forward)(*x, lay), lay, inverse=True)
+        masked = s if dense else s.masked_fill(~seen[torch.arange(heads, device=DEV) % 4], -math.inf)
+        err = (out[0].double() - torch.softmax(masked, dim=2) @ v[0].double()).abs().max().item()
+        assert err <= 2e-2, dense                             # the bound of the other forward tests
 
 
 # ---------------------------------------------------------------- attention mass per tile pair
@@ -1705,6 +1740,32 @@ def test_fp32_in_three_planes_infinities(kernel, D, grid, tile, text_tiles, copi
     assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.isinf(want).any()
     finite = ~torch.isnan(want)
     assert finite.any() and torch.allclose(got[finite], want[finite], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("kernel,dense_kernel,D,grid,tile,copies", [
+    ("2x4", "2x4", 128, (5, 13, 21), (1, 8, 8), 1),
+    ("2x4", "2x2", 128, (3, 17, 29), (2, 8, 8), 1),
+    ("2x2", "2x2", 128, (9, 30, 25), (3, 3, 4), 1),
+    ("2x4", "2x4", 64, (5, 13, 21), (1, 8, 8), 1),
+    ("1x4", "1x4", 32, (3, 17, 29), (1, 6, 10), 1),
+    ("2x2", "2x2", 32, (5, 13, 21), (3, 3, 4), 2),
+    ("2x4", "1x4", 32, (9, 30, 25), (1, 6, 10), 2),
+])
+def test_fp32_in_three_planes_with_two_batch_entries_and_dense(kernel, dense_kernel, D, grid, tile, copies):
+    """Two batch entries of different values, on the sparse and the dense walk: against the oracle."""
+    _say("fp32 planes, batch", kernel, dense_kernel, D, grid, tile)
+    wl, lay = _plane_problem(kernel, D, grid, tile, 1, copies, batch=2)
+    assert ca.compact_attn_layout_split(lay, dense=True)[1] == "f32-planes-" + dense_kernel
+    g = geometry_of(wl)
+    q, k, v = make_qkv(wl, DEV, q_gain=2.0)
+    assert not torch.equal(k[0], k[1])
+    x = [ca.compact_attn_permute(t, lay) for t in (q, k, v)]
+    got, dense = (ca.compact_attn_permute(fn(*x, lay), lay, inverse=True) for fn in (ca.compact_attn_forward, ca.compact_attn_dense))
+    for b in range(2):
+        for h in range(4):
+            one = [to_f64(t[b, h])[None] for t in (q, k, v)]
+            compare(to_f64(got[b, h])[None], OA.masked_attention(g, [wl.heads[h]], *one), *tolerances("f32"), what=kernel)
+            compare(to_f64(dense[b, h])[None], OA.dense_attention(*one), *tolerances("f32"), what=dense_kernel)
 
 
 def _without_workspace(q, k, v, lay, call="forward"):
