@@ -1,5 +1,6 @@
 """Binding of libcompact_attn.so: argument marshalling only, with ctypes; the calls that a program makes
-at every layer go through the extension _calls where their arguments are the usual ones.
+at every layer go through the extension _calls where their arguments are the usual ones (see csrc/calls.cpp;
+a call with `out` or `stream`, or under a torch function mode such as torch.set_default_device, is not).
 
 Every function has the name of the C entry point it calls (see
 include/compact_attn.h).  Tensors are torch tensors used purely as device
@@ -549,5 +550,6 @@ def compact_attn_search_head(layout, mass, group_max_dt, tau, lam, pattern="dual
 
 
 def compact_attn_dense(q, k, v, layout, out=None, stream=None):
-    """Same kernel with every query tile keeping all tiles."""
+    """compact_attn_forward with every query tile keeping all tiles.  May run on copies of the tokens alone, or on tiles of other sizes:
+    results then differ from those of compact_attn_forward with full windows by the rounding of bf16 weights."""
     return _attention("compact_attn_dense", CA_CALL_DENSE, q, k, v, layout, out, stream)

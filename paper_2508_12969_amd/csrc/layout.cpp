@@ -764,7 +764,8 @@ Ways choose_ways(const ca_layout& L, bool dense, int64_t max_words, SplitPlan* p
 // The constants are a fit over 276 launches of under 0.1 TFLOP (1-40 heads, head dims 32-128, tiles of 60-128 tokens, masks from 5 %
 // to dense), per kernel and head dim, a step being 128 keys; residual 5-16 %.  On these the choice is 1.36 times faster than
 // attn_f32.hip (geometric mean; 1.41 is the best choice in hindsight), and four of them, calls of one head, are slower, by up to 8 %.
-// Without the 13 % ten are slower, by up to 20 %.
+// Without the 13 % ten are slower, by up to 20 %.  They were taken with launches dealt in chunks of kXcdChunk, as launch_time has
+// them; the kernels' own order (xcd_chunk) and the rounding of the parts came later, and made launches of 512 to 4095 workgroups up to 1.25 times as fast.
 Ways choose_planes(const ca_layout& L, bool dense, int64_t max_words) {
   const ca_problem& p = L.prob;
   if (p.dtype != CA_F32 || L.B <= 32 || L.B > 128 || (p.head_dim != 32 && p.head_dim != 64 && p.head_dim != 128) || L.class_mask.size() > 8) return kWaysNone;
@@ -854,7 +855,8 @@ namespace {
 // A padded grid multiplies its padding in queries and keys (13 x 30 x 52 tokens in 1 x 8 x 8 tiles: 32 % more products), and the
 // kernel for 128-token tiles beats those for 64 also where nothing is padded.  Measured with the copies: 16 heads x 20K in 64-token
 // tiles 4.09 / 3.10 ms (copies 0.11); 18 heads x 44K of a grid filled to 0.79 23.5 / 15.5 ms; 8 heads x 8K without padding 259 /
-// 247 us.  50 launches of 11 us to 24 ms take 1.18 times less as a whole (1.20 is the best choice in hindsight), one 3 % more.
+// 247 us.  Over 50 launches of 11 us to 24 ms, each way measured on its own and the time of the copies added to one, what is chosen is 1.18
+// times as fast (geometric mean; 1.20 is the best choice in hindsight), one launch 3 % slower.
 void close_dense(ca_layout& L, double dense_us) {
   const ca_problem& p = L.prob;
   const bool padded = L.class_mask.size() > 1;
